@@ -168,7 +168,8 @@ struct RolloutWs {
   Meta meta;
   Acts acts;
   Acts last;  // [B, .] activations of the final prefill layer's last-position rows
-  int *finished, *cur_tok;
+  int* finished;
+  void* parts;  // sampler scratch
   void* hl;
   float* logits;
   char* kv;
@@ -180,7 +181,7 @@ RolloutWs carve_rollout(Carver& c, const rlhf_model_config& cfg, int B, int Lq, 
   w.meta = carve_meta(c, B, Tmax);
   w.acts = carve_acts(c, cfg, Tmax, esz);
   w.finished = c.take<int>(B);
-  w.cur_tok = c.take<int>(B);
+  w.parts = c.take_bytes(sampler_scratch_bytes(B, cfg.vocab));
   w.hl = c.take_bytes((size_t)B * cfg.d_model * esz);
   w.logits = c.take<float>((size_t)B * cfg.vocab);
   w.acts.splitk_bytes = (size_t)16 * B * std::max(3 * cfg.d_model, cfg.d_ff) * sizeof(float);
@@ -1373,7 +1374,7 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
   sa.B = B; sa.V = c.vocab; sa.Lq = Lq; sa.N = N;
   sa.seed = seed; sa.seq_base = seq_id_base; sa.temperature = temperature;
   sa.eos_id = c.eos_id; sa.pad_id = c.pad_id;
-  sa.len = m.len; sa.finished = ws.finished; sa.cur_tok = ws.cur_tok;
+  sa.len = m.len; sa.finished = ws.finished; sa.parts = ws.parts;
   sa.out_tokens = out_tokens; sa.out_logprobs = out_logprobs; sa.out_lengths = out_lengths; sa.out_mask = out_mask;
 
   GemmArgs lm;
@@ -1390,17 +1391,17 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
                                        ws.hl, nullptr, 0.f, nullptr, s));
   LAUNCH("gemm_lm_head_decode", launch_gemm(dt, lm, s));
   sa.step = 0;
-  LAUNCH("sampler", launch_sampler(sa, s));
+  LAUNCH("sampler", launch_sampler(sa, dt, h->w.embed_in, d, N > 1 ? ws.acts.x : nullptr, s));
   HIP_OK(hipEventRecord(h->ph[1], s));
 
-  // decode: pass t feeds the token sampled at step t (position len + t) and samples step t + 1
+  // decode: pass t feeds the token sampled at step t (position len + t; the sampler left its embedding in x) and
+  // samples step t + 1
   p.mode = 1;
   p.rows_max = B;
   p.rows_dev = nullptr;
   p.pos = m.len;
   p.rowid = nullptr;
   for (int t = 0; t + 1 < N; ++t) {
-    LAUNCH("embed_rows", launch_embed_rows(dt, ws.cur_tok, B, h->w.embed_in, d, c.vocab, ws.acts.x, s));
     p.pos_add = t;
     p.ctx_add = t + 1;
     rc = run_layers(h, ws.acts, p, s);
@@ -1409,7 +1410,7 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
                                        ws.hl, nullptr, 0.f, nullptr, s));
     LAUNCH("gemm_lm_head_decode", launch_gemm(dt, lm, s));
     sa.step = t + 1;
-    LAUNCH("sampler", launch_sampler(sa, s));
+    LAUNCH("sampler", launch_sampler(sa, dt, h->w.embed_in, d, t + 2 < N ? ws.acts.x : nullptr, s));
   }
   HIP_OK(hipEventRecord(h->ph[2], s));
   h->ph_valid = true;

@@ -195,11 +195,8 @@ hipError_t launch_row_spans(const uint8_t* mask, int B, int L, int kv_extra, int
 hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, const int* start, const int* len,
                              const int* cu, const void* embed, int d, int vocab, int* pos, int* rowid, int* tok,
                              float* x, hipStream_t s);
-// Decode step: x[b, :] = embed[cur_tok[b], :] for b < B.
 hipError_t launch_gather_rows(const void* in, const int* src, int src_add, int rows, size_t row_bytes, void* out,
                               hipStream_t s);
-hipError_t launch_embed_rows(int dtype, const int32_t* tok, int B, const void* embed, int d, int vocab, float* x,
-                             hipStream_t s);
 
 // LayerNorm of fp32 rows; two affine outputs from one set of statistics (g2 may be null -> one).
 hipError_t launch_layernorm(int dtype, const float* x, int rows_max, const int* rows_dev, int d, float eps,
@@ -264,13 +261,15 @@ struct SampleArgs {
   int eos_id, pad_id;
   const int* len;       // true query lengths (0 = all-pad row)
   int* finished;        // [B] state, initialised at step 0
-  int32_t* cur_tok;     // [B] token fed to the next pass
   int32_t* out_tokens;  // [B, Lq+N]
   float* out_logprobs;  // [B, N]
   int32_t* out_lengths; // [B]
   uint8_t* out_mask;    // [B, Lq+N] or null
+  void* parts;          // scratch: sampler_scratch_bytes(B, V)
 };
-hipError_t launch_sampler(const SampleArgs& a, hipStream_t s);
+size_t sampler_scratch_bytes(int B, int V);
+// x (null after the last step): row b receives the embedding of the token sampled for row b, the next pass's input.
+hipError_t launch_sampler(const SampleArgs& a, int dtype, const void* embed, int d, float* x, hipStream_t s);
 hipError_t launch_copy_queries(const int32_t* queries, const uint8_t* pad_mask, int B, int Lq, int N, int pad_id,
                                int32_t* out_tokens, uint8_t* out_mask, hipStream_t s);
 

@@ -91,24 +91,6 @@ hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, con
   return hipGetLastError();
 }
 
-template <typename T>
-__global__ void embed_rows_kernel(const int32_t* __restrict__ tok, const T* __restrict__ embed, int d, int vocab,
-                                  float* __restrict__ x) {
-  const int b = blockIdx.x;
-  const T* e = embed + (size_t)min(max(tok[b], 0), vocab - 1) * d;  // an id outside the table never leaves it
-  float* xr = x + (size_t)b * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = to_f32(e[c]);
-}
-
-hipError_t launch_embed_rows(int dtype, const int32_t* tok, int B, const void* embed, int d, int vocab, float* x,
-                             hipStream_t s) {
-  if (dtype == 0)
-    hipLaunchKernelGGL(embed_rows_kernel<float>, dim3(B), dim3(256), 0, s, tok, (const float*)embed, d, vocab, x);
-  else
-    hipLaunchKernelGGL(embed_rows_kernel<bf16_t>, dim3(B), dim3(256), 0, s, tok, (const bf16_t*)embed, d, vocab, x);
-  return hipGetLastError();
-}
-
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 // out row r = in row src[r] + src_add, rows of `chunks` 16-byte pieces (any element type).
@@ -848,8 +830,10 @@ __device__ __forceinline__ uint64_t noise_step_key(uint64_t seed, uint64_t seq, 
   return fmix64(kr + RLHF_GOLDEN * (uint64_t)(step + 1));
 }
 
-__device__ __forceinline__ float gumbel_from_key(uint64_t step_key, uint32_t v) {
-  const uint32_t k = (uint32_t)(fmix64(step_key + RLHF_GOLDEN * (uint64_t)(v + 1)) >> 32);
+__device__ __forceinline__ uint32_t noise_bits(uint64_t step_key, uint32_t v) {
+  return (uint32_t)(fmix64(step_key + RLHF_GOLDEN * (uint64_t)(v + 1)) >> 32);
+}
+__device__ __forceinline__ float gumbel_from_bits(uint32_t k) {
   float E;  // E = -ln u, evaluated so that u close to 1 keeps its relative accuracy
   if (k < 0x80000000u) {
     E = -logf((float)k * 2.3283064365386963e-10f + 1.1641532182693481e-10f);
@@ -859,90 +843,148 @@ __device__ __forceinline__ float gumbel_from_key(uint64_t step_key, uint32_t v) 
   }
   return -logf(E);
 }
+// An upper bound of gumbel_from_bits(k) from one hardware logarithm: for u < 1/2, E > ln 2; otherwise E >= 1 - u.
+// 1e-3 covers the error of the logarithm (1 ulp of a value below 33) and of the bounded function itself.
+__device__ __forceinline__ float gumbel_bound(uint32_t k) {
+  if (k < 0x80000000u) return 0.36652f + 1e-3f;
+  return fmaf(__builtin_amdgcn_logf(((float)(0u - k) - 0.5f) * 2.3283064365386963e-10f), -0.69314718f, 1e-3f);
+}
 
-// One block per row.  Single pass over the logits: running (max, sum exp) for the log-sum-exp and
-// running best perturbed score; ties resolve to the lowest token id at every merge.
-__global__ void __launch_bounds__(1024) sampler_kernel(SampleArgs a) {
-  __shared__ float sm[16], ss[16], sb[16];
-  __shared__ int si[16];
-  const int b = blockIdx.x;
-  const float* row = a.logits + (size_t)b * a.V;
-  const uint64_t key = noise_step_key(a.seed, a.seq_base + (uint64_t)b, (uint32_t)a.step);
-  float m = -INFINITY, s = 0.f, best = -INFINITY;
-  int bi = 0x7FFFFFFF;
-  for (int v = threadIdx.x; v < a.V; v += 1024) {
-    const float z = row[v] / a.temperature;
-    if (z > m) {
-      s = s * expf(m - z) + 1.0f;
-      m = z;
-    } else {
-      s += expf(z - m);
-    }
-    const float sc = z + gumbel_from_key(key, (uint32_t)v);
-    if (sc > best) {  // v increases within a thread, so '>' keeps the lowest id among equals
-      best = sc;
-      bi = v;
-    }
-  }
-  // wave merge
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(s, o, 64), b2 = __shfl_xor(best, o, 64);
-    const int i2 = __shfl_xor(bi, o, 64);
+// Log-sum-exp and best perturbed score of a set of vocabulary entries; merging is associative up to rounding, ties
+// go to the lowest token id.
+struct SamplePart {
+  float m, s;        // max z and sum of exp(z - m)
+  float best, zbest; // best z + noise, and the z it belongs to
+  int bi;
+  __device__ __forceinline__ void merge(float m2, float s2, float b2, float z2, int i2) {
     const float mn = fmaxf(m, m2);
     s = (m == -INFINITY ? 0.f : s * expf(m - mn)) + (m2 == -INFINITY ? 0.f : s2 * expf(m2 - mn));
     m = mn;
     if (b2 > best || (b2 == best && i2 < bi)) {
       best = b2;
+      zbest = z2;
       bi = i2;
     }
   }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    sm[w] = m;
-    ss[w] = s;
-    sb[w] = best;
-    si[w] = bi;
+  __device__ __forceinline__ void merge_wave() {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+      merge(__shfl_xor(m, o, 64), __shfl_xor(s, o, 64), __shfl_xor(best, o, 64), __shfl_xor(zbest, o, 64),
+            __shfl_xor(bi, o, 64));
   }
+};
+
+// First stage: block (j, b) takes entries [j * per, (j + 1) * per) of row b's logits in one pass.  The work is
+// vector arithmetic, not the logits' bytes: a row is cut into as many blocks as it takes to cover the chip (with one
+// block per row a single row took 72 us, a dependent chain of 49 entries per thread), and the exact noise (a
+// logarithm of a logarithm, some 150 instructions) is only formed for entries whose upper bound reaches the best
+// score the wave has seen: H(n) of n batches instead of all of them.  Both stages at a vocabulary of 50,304: 256 rows
+// 53 us (one block per row, and a kernel for the next pass's embedding: 85), what is left being the hash's 64-bit
+// products; one row 18 us (80).
+__global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per) {
+  __shared__ SamplePart sp[4];
+  const int b = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, a.V);
+  const float* row = a.logits + (size_t)b * a.V;
+  const uint64_t key = noise_step_key(a.seed, a.seq_base + (uint64_t)b, (uint32_t)a.step);
+  SamplePart p = {-INFINITY, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
+  float wbest = -INFINITY;  // best score of the wave so far
+  for (int base = lo; base < hi; base += 1024) {  // all lanes stay in the loop: they exchange their best scores
+    const int v0 = base + threadIdx.x;
+    float z[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = v0 + 256 * u < hi ? row[v0 + 256 * u] / a.temperature : -INFINITY;
+    const float m4 = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+    if (m4 > p.m) {
+      p.s *= expf(p.m - m4);  // 0 before the first entry
+      p.m = m4;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int v = v0 + 256 * u;
+      bool better = false;
+      if (v < hi) {
+        p.s += expf(z[u] - p.m);
+        const uint32_t k = noise_bits(key, (uint32_t)v);
+        if (!(z[u] + gumbel_bound(k) < wbest)) {
+          const float sc = z[u] + gumbel_from_bits(k);
+          better = sc > p.best;  // v increases within a thread, so '>' keeps the lowest id among equals
+          if (better) {
+            p.best = sc;
+            p.zbest = z[u];
+            p.bi = v;
+          }
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(better) != 0) wbest = wave_max(p.best);
+    }
+  }
+  p.merge_wave();
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) sp[w] = p;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int j = 1; j < 16; ++j) {
-      const float mn = fmaxf(m, sm[j]);
-      s = (m == -INFINITY ? 0.f : s * expf(m - mn)) + (sm[j] == -INFINITY ? 0.f : ss[j] * expf(sm[j] - mn));
-      m = mn;
-      if (sb[j] > best || (sb[j] == best && si[j] < bi)) {
-        best = sb[j];
-        bi = si[j];
-      }
-    }
-    // A row without a single comparable score (every logit NaN) leaves bi at its start value: stop the row
-    // with EOS and a zero log-prob rather than index past the row and feed an id outside the table onwards.
-    const bool none = bi < 0 || bi >= a.V;
-    if (none) bi = a.eos_id;
-    const float ztok = row[bi] / a.temperature;
-    const float lp = none ? 0.f : ztok - (m + logf(s));
-    int fin = (a.step == 0) ? (a.len[b] == 0 ? 1 : 0) : a.finished[b];
-    if (a.step == 0) a.out_lengths[b] = (a.len[b] == 0) ? 0 : a.N;
-    const size_t to = (size_t)b * (a.Lq + a.N) + a.Lq + a.step;
-    if (a.out_mask) a.out_mask[to] = fin ? 0 : 1;
-    if (fin) {
-      a.out_tokens[to] = a.pad_id;
-      a.out_logprobs[(size_t)b * a.N + a.step] = 0.f;
-    } else {
-      a.out_tokens[to] = bi;
-      a.out_logprobs[(size_t)b * a.N + a.step] = lp;
-      if (bi == a.eos_id) {
-        fin = 1;
-        a.out_lengths[b] = a.step + 1;
-      }
-    }
-    a.finished[b] = fin;
-    a.cur_tok[b] = bi;  // fed back either way; what follows EOS never reaches a kept output
+    for (int k = 1; k < 4; ++k) p.merge(sp[k].m, sp[k].s, sp[k].best, sp[k].zbest, sp[k].bi);
+    ((SamplePart*)a.parts)[(size_t)b * gridDim.x + blockIdx.x] = p;
   }
 }
 
-hipError_t launch_sampler(const SampleArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(sampler_kernel, dim3(a.B), dim3(1024), 0, s, a);
+// Second stage, one block per row: the parts in a fixed order, the stop mask, the outputs, and (while another pass
+// follows) the embedding row of the token that pass is fed.
+template <typename T>
+__global__ void __launch_bounds__(256)
+    sampler_final_kernel(SampleArgs a, int nparts, const T* __restrict__ embed, int d, float* __restrict__ x) {
+  __shared__ int s_tok;
+  const int b = blockIdx.x;
+  if (threadIdx.x < 64) {
+    SamplePart p = {-INFINITY, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
+    const SamplePart* parts = (const SamplePart*)a.parts + (size_t)b * nparts;
+    for (int j = threadIdx.x; j < nparts; j += 64) p.merge(parts[j].m, parts[j].s, parts[j].best, parts[j].zbest, parts[j].bi);
+    p.merge_wave();
+    if (threadIdx.x == 0) {
+      // A row without a single comparable score (every logit NaN) leaves bi at its start value: stop the row
+      // with EOS and a zero log-prob rather than index past the row and feed an id outside the table onwards.
+      const bool none = p.bi < 0 || p.bi >= a.V;
+      const int bi = none ? a.eos_id : p.bi;
+      const float lp = none ? 0.f : p.zbest - (p.m + logf(p.s));
+      int fin = (a.step == 0) ? (a.len[b] == 0 ? 1 : 0) : a.finished[b];
+      if (a.step == 0) a.out_lengths[b] = (a.len[b] == 0) ? 0 : a.N;
+      const size_t to = (size_t)b * (a.Lq + a.N) + a.Lq + a.step;
+      if (a.out_mask) a.out_mask[to] = fin ? 0 : 1;
+      if (fin) {
+        a.out_tokens[to] = a.pad_id;
+        a.out_logprobs[(size_t)b * a.N + a.step] = 0.f;
+      } else {
+        a.out_tokens[to] = bi;
+        a.out_logprobs[(size_t)b * a.N + a.step] = lp;
+        if (bi == a.eos_id) {
+          fin = 1;
+          a.out_lengths[b] = a.step + 1;
+        }
+      }
+      a.finished[b] = fin;
+      s_tok = bi;  // fed back either way; what follows EOS never reaches a kept output
+    }
+  }
+  if (!x) return;
+  __syncthreads();
+  const T* e = embed + (size_t)min(max(s_tok, 0), a.V - 1) * d;
+  for (int c = threadIdx.x; c < d; c += 256) x[(size_t)b * d + c] = to_f32(e[c]);
+}
+
+// Blocks per row of the first stage: about 2048 blocks in all (eight per CU), at most one per 1024 entries (four
+// entries per thread, whose chains run side by side).
+static int sampler_parts(int B, int V) {
+  return std::max(1, std::min((V + 1023) / 1024, (2048 + B - 1) / B));
+}
+size_t sampler_scratch_bytes(int B, int V) { return (size_t)B * sampler_parts(B, V) * sizeof(SamplePart); }
+
+hipError_t launch_sampler(const SampleArgs& a, int dtype, const void* embed, int d, float* x, hipStream_t s) {
+  const int want = sampler_parts(a.B, a.V), per = (a.V + want - 1) / want, n = (a.V + per - 1) / per;
+  hipLaunchKernelGGL(sampler_part_kernel, dim3(n, a.B), dim3(256), 0, s, a, per);
+  if (dtype == 0)
+    hipLaunchKernelGGL(sampler_final_kernel<float>, dim3(a.B), dim3(256), 0, s, a, n, (const float*)embed, d, x);
+  else
+    hipLaunchKernelGGL(sampler_final_kernel<bf16_t>, dim3(a.B), dim3(256), 0, s, a, n, (const bf16_t*)embed, d, x);
   return hipGetLastError();
 }
 
