@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librlhf_rollout.so")
-SOURCES = ["api.hip", "gemm.hip", "gemm_skinny.hip", "attention.hip", "elementwise.hip", "ppo_signals.hip", "optimizer.hip", "head_backward.hip", "attention_backward.hip"]
+SOURCES = ["api.hip", "gemm.hip", "gemm_skinny.hip", "few_rows.hip", "decode.hip", "attention.hip", "elementwise.hip", "ppo_signals.hip", "optimizer.hip", "head_backward.hip", "attention_backward.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wno-unused-result",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -45,8 +45,8 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     # stand-alone kernel drivers (hardware-counter runs): each links the library's own object
-    for drv, obj in (("gemm_driver", "gemm.o gemm_skinny.o"), ("attn_driver", "attention.o"),
-                     ("dec_driver", "gemm.o gemm_skinny.o"), ("ceilings_driver", "")):
+    for drv, obj in (("gemm_driver", "gemm.o gemm_skinny.o few_rows.o"), ("attn_driver", "attention.o"),
+                     ("dec_driver", "gemm.o gemm_skinny.o few_rows.o"), ("ceilings_driver", "")):
         drv_obj = os.path.join(objdir, drv + ".o")
         r = subprocess.run([hipcc, *FLAGS, "-c", os.path.join(CSRC, drv + ".hip"), "-o", drv_obj],
                            capture_output=True, text=True)

@@ -164,10 +164,26 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
   return a;
 }
 
+// Activations of a decode pass of few sequences (run_decode_few), as packed operands (common.h).
+struct FewActs {
+  void *a, *m, *att;  // LN1 and LN2 outputs [rows, d]; attention output | FFN hidden [rows, d + d_ff]
+  void* hl;           // final LayerNorm
+};
+FewActs carve_few(Carver& c, const rlhf_model_config& cfg, int B, size_t esz) {
+  const size_t rows = (size_t)(B + 15) / 16 * 16, d = cfg.d_model;
+  FewActs f;
+  f.a = c.take_bytes(rows * d * esz);
+  f.m = c.take_bytes(rows * d * esz);
+  f.att = c.take_bytes(rows * (d + (size_t)cfg.d_ff) * esz);
+  f.hl = c.take_bytes(rows * d * esz);
+  return f;
+}
+
 struct RolloutWs {
   Meta meta;
   Acts acts;
   Acts last;  // [B, .] activations of the final prefill layer's last-position rows
+  FewActs few;  // activations of a decode pass of few sequences
   int* finished;
   void* parts;  // sampler scratch
   void* hl;
@@ -190,6 +206,7 @@ RolloutWs carve_rollout(Carver& c, const rlhf_model_config& cfg, int B, int Lq, 
   w.last = carve_acts(c, cfg, (size_t)B, esz);
   w.last.splitk_bytes = w.acts.splitk_bytes;
   w.last.splitk = w.acts.splitk;  // decode has not started: its partial-sum scratch is free
+  if (B <= kFewRows) w.few = carve_few(c, cfg, B, esz);
   w.kv_slots = (size_t)B * (Lq + N - 1);
   w.kv = (char*)c.take_bytes((size_t)cfg.n_layers * 2 * w.kv_slots * cfg.d_model * esz);
   return w;
@@ -556,6 +573,84 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   if (p.keep)
     HIP_OK(hipMemcpyAsync(p.keep + (size_t)c.n_layers * p.keep_stride, A.x, p.keep_rows * d * sizeof(float),
                           hipMemcpyDeviceToDevice, s));
+  return RLHF_OK;
+}
+
+// Decode pass of few sequences (up to kFewRows): four launches per layer, all on one stream.
+//   LayerNorm (adding the previous layer's partial sums) -> QKV and FC1 as one launch -> attention, with the rotary
+//   turn and the K / V store as its prologue -> out-projection and FC2 as one product over K = d + d_ff, left as slabs.
+// At these sizes a layer is a chain of launches, each near its own latency: the seven to nine launches on two streams
+// that larger batches use (above) took 104 us per layer for one sequence at the 2.8B width and 92 us for 64 at the
+// 160M shape, of which the two stream joins alone are about 12; this pass takes 50 and 35 us.
+struct FewDecode {
+  FewRowsArgs in, outp;  // QKV | FC1, and the two halves of the residual update
+};
+FewDecode few_decode_args(const rlhf_handle* h, const Acts& A, const FewActs& P, int B, int l) {
+  const rlhf_model_config& c = h->cfg;
+  const int d = c.d_model, F = c.d_ff, dt = c.dtype;
+  FewDecode f;
+  f.in.M_max = f.outp.M_max = B;
+  FewRowsProd& pq = f.in.p[0];
+  fr_seg(dt, pq.seg[0], P.a, h->w_qkv[l], d, -d, 0);
+  pq.bias = h->b_qkv[l]; pq.out = A.qkv; pq.N = pq.ldo = 3 * d; pq.epilogue = EPI_BIAS;
+  FewRowsProd& p1 = f.in.p[1];
+  fr_seg(dt, p1.seg[0], P.m, h->w_fc1[l], d, -d, 0);
+  p1.bias = h->b_fc1[l]; p1.N = F; p1.epilogue = EPI_BIAS_GELU;
+  p1.out = P.att; p1.packed_K = d + F; p1.packed_k0 = d;
+  FewRowsProd& po = f.outp.p[0];
+  if (h->ld_o2) {  // W_o | W_fc2 side by side
+    fr_seg(dt, po.seg[0], P.att, h->w_o[l], d + F, -(d + F), 0);
+  } else {
+    fr_seg(dt, po.seg[0], P.att, h->w_o[l], d, -(d + F), 0);
+    fr_seg(dt, po.seg[1], (char*)P.att + (size_t)16 * d * h->esz, h->w_fc2[l], F, -(d + F), 0);
+  }
+  po.out = A.splitk; po.N = po.ldo = d; po.epilogue = EPI_F32;
+  po.slab = (size_t)B * d;
+  po.ksplit = few_rows_splits(d, po.seg[0].steps + po.seg[1].steps);
+  return f;
+}
+bool decode_few_takes(const rlhf_handle* h, int B) {
+  const rlhf_model_config& c = h->cfg;
+  if (B > kFewRows || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
+      !attn_decode_rope_supported(c.head_dim, c.rotary_dims) || (c.dtype == 1 && !h->ld_o2))
+    return false;
+  GemmArgs g;
+  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = B; g.M_dev = nullptr; g.epilogue = EPI_F32;
+  const int shapes[4][2] = {{3 * c.d_model, c.d_model}, {c.d_ff, c.d_model}, {c.d_model, c.d_model}, {c.d_model, c.d_ff}};
+  for (auto& nk : shapes) {
+    g.N = g.ldo = nk[0]; g.K = nk[1];
+    g.lda = g.ldw = c.d_model + c.d_ff;  // the widest stride any of them has
+    if (!few_rows_takes(c.dtype, g)) return false;
+  }
+  return true;
+}
+// The layers, the final LayerNorm and the LM head (into logits).
+int run_decode_few(rlhf_handle* h, const Acts& A, const FewActs& P, const PassArgs& p, float* logits, hipStream_t s) {
+  const rlhf_model_config& c = h->cfg;
+  const int d = c.d_model, dt = c.dtype, B = p.rows_max;
+  const size_t plane = p.kv_slots * (size_t)d * h->esz;
+  int ks = 0;
+  for (int l = 0; l < c.n_layers; ++l) {
+    FewDecode f = few_decode_args(h, A, P, B, l);
+    char* kc = p.kv + (size_t)l * 2 * plane;
+    LAUNCH("layernorm_decode", launch_ln_decode(dt, A.x, B, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l], P.a, h->ln2_g[l],
+                                                h->ln2_b[l], P.m, (const float*)A.splitk, l ? ks : 0, f.outp.p[0].slab,
+                                                l ? h->b_o[l - 1] : nullptr, l ? h->b_fc2[l - 1] : nullptr, l > 0, s));
+    LAUNCH("gemm_decode_qkv_fc1", launch_few_rows(dt, f.in, 2, s));
+    LAUNCH("attn_decode", launch_attn_decode_rope(dt, A.qkv, kc, kc + plane, (long)p.kv_extra, B, p.len, p.pos_add,
+                                                  p.ctx_max, p.kvoff, c.n_heads, c.head_dim, c.rotary_dims, h->rope_cos,
+                                                  h->rope_sin, P.att, d + c.d_ff, s));
+    LAUNCH("gemm_decode_out_fc2", launch_few_rows(dt, f.outp, 1, s));
+    ks = f.outp.p[0].ksplit;
+  }
+  const int l = c.n_layers - 1;
+  LAUNCH("final_ln", launch_ln_decode(dt, A.x, B, d, c.ln_eps, h->w.lnf_g, h->w.lnf_b, P.hl, nullptr, nullptr, nullptr,
+                                      (const float*)A.splitk, ks, (size_t)B * d, h->b_o[l], h->b_fc2[l], false, s));
+  FewRowsArgs lm;
+  fr_seg(dt, lm.p[0].seg[0], P.hl, h->embed_out_mm, d, -d, 0);
+  lm.p[0].out = logits; lm.p[0].N = lm.p[0].ldo = c.vocab; lm.p[0].epilogue = EPI_F32;
+  lm.M_max = B;
+  LAUNCH("gemm_lm_head_decode", launch_few_rows(dt, lm, 1, s));
   return RLHF_OK;
 }
 
@@ -1401,14 +1496,20 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
   p.rows_dev = nullptr;
   p.pos = m.len;
   p.rowid = nullptr;
+  const bool few = decode_few_takes(h, B);
   for (int t = 0; t + 1 < N; ++t) {
     p.pos_add = t;
     p.ctx_add = t + 1;
-    rc = run_layers(h, ws.acts, p, s);
-    if (rc) return rc;
-    LAUNCH("final_ln", launch_final_ln(dt, ws.acts.x, nullptr, 0, B, nullptr, d, c.ln_eps, h->w.lnf_g, h->w.lnf_b,
-                                       ws.hl, nullptr, 0.f, nullptr, s));
-    LAUNCH("gemm_lm_head_decode", launch_gemm(dt, lm, s));
+    if (few) {
+      rc = run_decode_few(h, ws.acts, ws.few, p, ws.logits, s);
+      if (rc) return rc;
+    } else {
+      rc = run_layers(h, ws.acts, p, s);
+      if (rc) return rc;
+      LAUNCH("final_ln", launch_final_ln(dt, ws.acts.x, nullptr, 0, B, nullptr, d, c.ln_eps, h->w.lnf_g, h->w.lnf_b,
+                                         ws.hl, nullptr, 0.f, nullptr, s));
+      LAUNCH("gemm_lm_head_decode", launch_gemm(dt, lm, s));
+    }
     sa.step = t + 1;
     LAUNCH("sampler", launch_sampler(sa, dt, h->w.embed_in, d, t + 2 < N ? ws.acts.x : nullptr, s));
   }

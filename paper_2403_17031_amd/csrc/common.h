@@ -65,6 +65,21 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+
+// GELU for fp16 outputs: x * Phi(x) with Phi(x) ~ 1 / (1 + exp(-x * (c1 + c3 x^2 + c5 x^4))), the
+// coefficients fitted to the erf form over [-9, 9]: absolute error below 2.6e-5 everywhere (the
+// fp16 result itself is rounded to 2^-11 relative), one exp and one reciprocal per element.  x^2 is
+// capped at 64: beyond |x| = 8 the polynomial would bend back, and the sigmoid is saturated there.
+// The constants carry the factor -log2(e) of the base-2 exponential.
+__device__ __forceinline__ float gelu_f16out(float x) {
+  const float s = fminf(x * x, 64.0f);
+  float p = fmaf(1.01426504e-3f, s, -1.06775735e-1f);
+  p = fmaf(p, s, -2.30112140f);
+  const float e = __builtin_amdgcn_exp2f(x * p);  // exp(-u); inf for very negative x gives 1/inf = 0
+  return x * __frcp_rn(1.0f + e);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Launchers (host).  dtype: 0 = ModeF32, 1 = ModeBF16.  All enqueue on `s` and return the
 // launch status.  "n_rows_dev", where present, points to the device-resident row count; the grid
@@ -179,6 +194,45 @@ struct GemmArgs {
 bool gemm_skinny_takes(int dtype, const GemmArgs& a);
 int gemm_skinny_splitk(const GemmArgs& a);
 void launch_gemm_skinny(const GemmArgs& a, int ks, hipStream_t s);
+// Products of few rows (few_rows.hip): one launch runs one or two of them over the same M rows.
+constexpr int kFewRows = 64;  // most rows in bf16 mode
+// Packed activations: what a lane of the matrix instruction reads (16 bytes of a row) next to what its neighbour reads:
+// [rows / 16][K in 16-byte chunks][16 rows][16 bytes], so that a wave's load of 16 rows is contiguous.  Element index:
+template <typename T>
+__device__ __forceinline__ size_t packed_index(int m, int k, int K) {
+  constexpr int E = 16 / (int)sizeof(T);
+  return ((size_t)(m >> 4) * (K / E) + k / E) * (16 * E) + (m & 15) * E + k % E;
+}
+struct FewRowsSeg {           // K = steps * 128 bytes of every row of A and W
+  const void* A = nullptr;
+  const void* W = nullptr;
+  int steps = 0, ldw = 0;
+  // byte strides of A: between 16-row tiles and rows of a tile, between a lane group's two chunks of a step, between
+  // lane groups, between steps
+  uint32_t a_tile = 0, a_row = 0, a_half = 0, a_q = 0, a_step = 0;
+};
+struct FewRowsProd {
+  FewRowsSeg seg[2];          // K runs over seg[0], then (fp32 mode) over seg[1]
+  const void* bias = nullptr;
+  void* out = nullptr;
+  int N = 0, ldo = 0, epilogue = 0;
+  int packed_K = 0, packed_k0 = 0;  // packed_K > 0 (EPI_BIAS, EPI_BIAS_GELU): out is a packed operand of packed_K
+                                    // columns, this product its columns from packed_k0 on
+  int ksplit = 1;             // EPI_F32: K cut over this many blocks, block z writing slab z (`slab` floats each)
+  size_t slab = 0;
+};
+struct FewRowsArgs {
+  FewRowsProd p[2];
+  int blocks0 = 0;            // set by launch_few_rows
+  int M_max = 0, M_sub = 0;
+  const int* M_dev = nullptr;
+};
+bool few_rows_takes(int dtype, const GemmArgs& a);
+int few_rows_splits(int N, int steps);  // the ksplit of a product left as slabs (a power of two up to 8)
+// lda 0: K; lda < 0: A is packed with -lda columns in all (A points at its first column of this segment).
+void fr_seg(int dtype, FewRowsSeg& g, const void* A, const void* W, int K, int lda, int ldw);
+hipError_t launch_few_rows(int dtype, FewRowsArgs& args, int n_prods, hipStream_t s);
+hipError_t launch_few_rows_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // True when launch_gemm would route these arguments to the kernel that honours bias2.
 bool gemm_takes_bias2(int dtype, const GemmArgs& a);
 // > 1 when launch_gemm would take the split-K path for these arguments.
@@ -251,6 +305,22 @@ hipError_t launch_attn_prefill(int dtype, const void* q, const void* kc, const v
 hipError_t launch_attn_decode(int dtype, const void* q, const void* kc, const void* vc, long kv_extra,
                               int B, const int* len, int ctx_add, int ctx_max, const int* kvoff, int H, int hd,
                               void* out, hipStream_t s);
+
+// The decode pass of few sequences (decode.hip).
+// x <- x + (sum of ks <= 8 slabs) + bias_a + bias_b (ks = 0: x as it is), then LayerNorm with one or two affine outputs
+// (out2 null: one); x is written back if write_x.  d a multiple of 4 up to 4096, ks a power of two; the outputs are
+// packed operands (packed_index).
+bool ln_decode_supported(int d);
+hipError_t launch_ln_decode(int dtype, float* x, int rows, int d, float eps, const void* g1, const void* b1, void* out1,
+                            const void* g2, const void* b2, void* out2, const float* part, int ks, size_t slab,
+                            const void* bias_a, const void* bias_b, bool write_x, hipStream_t s);
+// Decode attention from the QKV product's rows [B, 3*H*hd]: rotary turn of q and k at position len[b] + step, K / V
+// store at that row of the cache, attention over rows 0 .. len[b] + step into the first
+// H*hd columns of the packed operand `out` of out_cols columns.
+bool attn_decode_rope_supported(int hd, int r);
+hipError_t launch_attn_decode_rope(int dtype, const void* qkv, void* kc, void* vc, long kv_extra, int B, const int* len,
+                                   int step, int ctx_max, const int* kvoff, int H, int hd, int r, const float* cos_t,
+                                   const float* sin_t, void* out, int out_cols, hipStream_t s);
 
 // Sampler: one step for every row from fp32 logits [B, V].
 struct SampleArgs {

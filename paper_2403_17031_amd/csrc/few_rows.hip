@@ -1,0 +1,315 @@
+// Products of few rows, C[M,N] = A[M,K] * W[N,K]^T for M up to 64 (a decode pass of a small batch), and all products
+// of the fp32 check mode.
+//
+// Such a product is its weights' bytes and nothing else: at M = 64 the matrix cores need a tenth of the time the
+// weights take to arrive.  What the kernel is built around is bytes in flight and few launches:
+//   * A block of eight waves owns 16 or 32 output columns for all K of its split; the waves divide K, each holding
+//     the weights of its next PF steps (128 bytes of every weight row per step) in registers.  At K = 2560 a wave has
+//     five steps, so nearly the whole weight tile of a block is requested before the first matrix instruction waits.
+//   * Both operands go global -> registers: 16 weight rows x 128 bytes per step, lane (l16, q) taking the 32 bytes at
+//     32q of row l16.  No LDS and no barrier until the waves' partial tiles are added at the end.  Sixteen consecutive
+//     lanes on sixteen rows cost the vector memory path four times what a contiguous kilobyte does (measured from L2:
+//     9.7 against 33 TB/s chip-wide).  The weights, which HBM delivers at 6, can afford that; A, read once per column
+//     block, cannot: its producers in a decode pass write it packed (packed_index), and a wave's load is contiguous.
+//   * The sum over K stays in the block (bias, GELU and the fp16 rounding are its epilogue) unless a product has too
+//     few column tiles to cover the chip: then K is cut over blocks into fp32 slabs that the consumer adds in order.
+//   * Two products that are ready together (QKV and FC1 of a parallel-residual layer) share one launch.
+// Width 2560, cold weights: QKV + FC1 24 us for up to 16 rows (3.9 TB/s), 29 for 30, 38 for 64; LM head 48 us (5.3 TB/s)
+// for one row, 82 for 64.  The weight-streaming kernel of gemm_skinny.hip, which this one replaces below 65 rows, took
+// 17.6 us for a QKV product alone and left slabs to add; the plain fp32 tile kernel took 50 us for each product of the
+// 70M shape at two rows (now 6).
+#include <algorithm>
+
+#include "common.h"
+
+namespace rlhf {
+
+typedef __attribute__((ext_vector_type(8))) _Float16 fr_f16x8_t;
+typedef __attribute__((ext_vector_type(4))) _Float16 fr_f16x4_t;
+typedef __attribute__((ext_vector_type(4))) float fr_f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t fr_u32x4_t;
+
+
+template <typename T>
+struct FrTypes;
+template <>
+struct FrTypes<half_t> {
+  typedef bf16_t P;
+};
+template <>
+struct FrTypes<float> {
+  typedef float P;
+};
+
+// 16 bytes of 16 weight rows (first operand) and of 16 rows of A: accumulator element e of lane (l16, q) is
+// (n = 4q + e, m = l16).
+__device__ __forceinline__ fr_f32x4_t fr_mfma(half_t, fr_u32x4_t w, fr_u32x4_t a, fr_f32x4_t acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(fr_f16x8_t, w), __builtin_bit_cast(fr_f16x8_t, a), acc,
+                                                0, 0, 0);
+}
+__device__ __forceinline__ fr_f32x4_t fr_mfma(float, fr_u32x4_t w, fr_u32x4_t a, fr_f32x4_t acc) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[j]), __uint_as_float(a[j]), acc, 0, 0, 0);
+  return acc;
+}
+
+// WV: waves per block (they divide K); MT x CT: 16x16 accumulator tiles along M and N per block; PF: steps held in
+// registers; OCC: waves per SIMD the registers are sized for; TWO: K runs over a second pair of operands after the
+// first.
+template <typename T, int WV, int MT, int CT, int PF, int OCC, bool TWO>
+__global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args) {
+  typedef typename FrTypes<T>::P P;
+  __shared__ fr_f32x4_t red[WV * MT * CT * 64];
+  const int M = args.M_dev ? min(args.M_max, *args.M_dev - args.M_sub) : args.M_max;
+  const int m0 = blockIdx.y * (16 * MT);
+  if (m0 >= M) return;
+  const bool second = (int)blockIdx.x >= args.blocks0;
+  const int bid = second ? blockIdx.x - args.blocks0 : blockIdx.x;
+  FewRowsProd p = args.p[0];
+  if (!TWO && second) p = args.p[1];  // (a launch of two products has one segment each)
+  const int tile = bid / p.ksplit, z = bid - tile * p.ksplit;
+  const int n0 = tile * (16 * CT);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q = lane >> 4;
+
+  const int steps0 = p.seg[0].steps, steps = steps0 + (TWO ? p.seg[1].steps : 0);
+  const int per_block = (steps + p.ksplit - 1) / p.ksplit;
+  const int b0 = z * per_block, b1 = min(steps, b0 + per_block);
+  const int per_wave = (b1 - b0 + WV - 1) / WV;
+  const int s0 = b0 + wave * per_wave, s1 = min(b1, s0 + per_wave);
+
+  uint32_t woff[TWO ? 2 : 1][CT], aoff[TWO ? 2 : 1][MT];
+#pragma unroll
+  for (int g = 0; g < (TWO ? 2 : 1); ++g) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+      woff[g][c] = (uint32_t)min(n0 + 16 * c + l16, p.N - 1) * (uint32_t)(p.seg[g].ldw * (int)sizeof(T)) + 32 * q;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m = min(m0 + 16 * i + l16, M - 1);
+      aoff[g][i] = (uint32_t)(m >> 4) * p.seg[g].a_tile + (m & 15) * p.seg[g].a_row + q * p.seg[g].a_q;
+    }
+  }
+  fr_u32x4_t w[PF][CT][2], a[PF][MT][2];
+  auto load = [&](int buf, int s) {
+    const bool g = TWO && s >= steps0;
+    const size_t k = (size_t)(s - (g ? steps0 : 0));
+    const char* wb = (const char*)(g ? p.seg[1].W : p.seg[0].W) + k * 128;
+    const char* ab = (const char*)(g ? p.seg[1].A : p.seg[0].A) + k * p.seg[0].a_step;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const char* r = wb + (TWO && g ? woff[TWO ? 1 : 0][c] : woff[0][c]);
+      w[buf][c][0] = *(const fr_u32x4_t*)r;
+      w[buf][c][1] = *(const fr_u32x4_t*)(r + 16);
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const char* r = ab + (TWO && g ? aoff[TWO ? 1 : 0][i] : aoff[0][i]);
+      a[buf][i][0] = *(const fr_u32x4_t*)r;
+      a[buf][i][1] = *(const fr_u32x4_t*)(r + p.seg[0].a_half);
+    }
+  };
+  fr_f32x4_t acc[CT][MT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) acc[c][i] = (fr_f32x4_t){0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int buf) {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[c][i] = fr_mfma(T(), w[buf][c][hh], a[buf][i][hh], acc[c][i]);
+  };
+  if (s0 < s1) {
+#pragma unroll
+    for (int b = 0; b < PF; ++b) load(b, min(s0 + b, s1 - 1));
+    int s = s0;
+    for (; s + 2 * PF <= s1; s += PF) {
+#pragma unroll
+      for (int b = 0; b < PF; ++b) {
+        compute(b);
+        load(b, s + PF + b);
+      }
+    }
+    // fewer than 2 * PF steps are left, the first PF of them already requested
+#pragma unroll
+    for (int b = 0; b < PF; ++b) {
+      if (s + b < s1) compute(b);
+      if (s + PF + b < s1) load(b, s + PF + b);
+    }
+#pragma unroll
+    for (int b = 0; b < PF; ++b)
+      if (s + PF + b < s1) compute(b);
+  }
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) red[((wave * CT + c) * MT + i) * 64 + lane] = acc[c][i];
+  __syncthreads();
+  for (int item = tid; item < CT * MT * 64; item += 64 * WV) {
+    fr_f32x4_t v = red[item];
+#pragma unroll
+    for (int k = 1; k < WV; ++k) v += red[k * CT * MT * 64 + item];
+    const int l = item & 63, ti = item >> 6;
+    const int c = ti / MT, i = ti - c * MT;
+    const int m = m0 + 16 * i + (l & 15), n = n0 + 16 * c + 4 * (l >> 4);
+    if (m >= M || n >= p.N) continue;
+    const size_t o = (size_t)m * p.ldo + n;
+    const bool vec = n + 4 <= p.N && (p.packed_K || (p.ldo & 3) == 0);
+    if (p.epilogue == EPI_F32) {
+      float* out = (float*)p.out + z * p.slab + o;
+      if (vec) *(fr_f32x4_t*)out = v;
+      else
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (n + u < p.N) out[u] = v[u];
+      continue;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (p.bias && n + u < p.N) v[u] += to_f32(((const P*)p.bias)[n + u]);
+    if (p.epilogue == EPI_BIAS_RESADD) {
+      float* out = (float*)p.out + o;
+      if (vec) *(fr_f32x4_t*)out += v;
+      else
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (n + u < p.N) out[u] += v[u];
+      continue;
+    }
+    if (p.epilogue == EPI_BIAS_GELU) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = sizeof(T) == 2 ? gelu_f16out(v[u]) : gelu_erf(v[u]);
+    }
+    T* out = (T*)p.out + (p.packed_K ? packed_index<T>(m, p.packed_k0 + n, p.packed_K) : o);
+    T t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = from_f32<T>(v[u]);
+    if (vec) __builtin_memcpy(__builtin_assume_aligned(out, 4 * sizeof(T)), t, sizeof(t));
+    else
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (n + u < p.N) out[u] = t[u];
+  }
+}
+
+static int fr_step(int dtype) { return dtype == 0 ? 32 : 64; }  // K elements per step (128 bytes)
+
+bool few_rows_takes(int dtype, const GemmArgs& a) {
+  const size_t esz = dtype == 0 ? 4 : 2, lda = a.lda ? a.lda : a.K, ldw = a.ldw ? a.ldw : a.K;
+  return a.M_max > 0 && a.M_max <= (dtype == 0 ? 1 << 20 : kFewRows) && a.K > 0 && a.K % fr_step(dtype) == 0 && !a.bias2 &&
+         !a.k_major && a.epilogue != EPI_LSE && a.epilogue != EPI_QKV && (lda * esz) % 16 == 0 && (ldw * esz) % 16 == 0 &&
+         (size_t)a.M_max * lda * esz < (1ull << 32) && (size_t)a.N * ldw * esz < (1ull << 32) &&
+         lda * esz < (1ull << 31) && ldw * esz < (1ull << 31);
+}
+
+// Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  Per row count one with 64 columns
+// and one with 32 (two for up to 16 rows: eight waves where K is long enough for them).
+#define RLHF_FR_FORMS(X)                                                                                          \
+  X(0, 4, 1, 4, 3, 3) X(1, 8, 1, 2, 4, 4) X(2, 4, 1, 2, 4, 4) X(3, 4, 2, 4, 2, 3) X(4, 4, 2, 2, 3, 3)            \
+  X(5, 4, 3, 4, 2, 2) X(6, 4, 3, 2, 3, 2) X(7, 4, 4, 4, 2, 2) X(8, 4, 4, 2, 3, 2)
+#define RLHF_FR_COLS(ID, WV, MT, CT, PF, OCC) 16 * CT,
+static const int kFormCols[] = {RLHF_FR_FORMS(RLHF_FR_COLS)};
+#undef RLHF_FR_COLS
+
+static int fr_form(int M, bool wide, int steps) {
+  if (M <= 16) return wide ? 0 : (steps >= 32 ? 1 : 2);
+  return M <= 32 ? (wide ? 3 : 4) : (M <= 48 ? (wide ? 5 : 6) : (wide ? 7 : 8));
+}
+
+// How a product is cut: 64 or 32 columns per block, and (max_split > 1) K over up to that many blocks.  What decides
+// is how evenly the blocks cover 256 CUs; 64 columns read A half as often and win until they cover the chip 10 % less
+// evenly, and always where K is long (rows of 8 KB and more: 46 against 62 us for QKV and FC1 at width 4096).
+// Measured, M = 8: QKV + FC1 at width 2560 28 us with 64 columns, 24 with 32; width 2048 14 and 16; width 768 6.4 and
+// 5.5; out-projection + FC2 at 2560 16.8 (160 blocks) and 15.6 (640 blocks).
+struct FrCut {
+  bool wide;
+  int ks;
+};
+static FrCut fr_cut(int n_cols_a, int n_cols_b, int steps, int max_split) {
+  FrCut best = {true, 1};
+  double best_e = 0;
+  for (int wide = 1; wide >= 0; --wide) {
+    const int c = wide ? 64 : 32;
+    const int tiles = (n_cols_a + c - 1) / c + (n_cols_b + c - 1) / c;
+    for (int ks = 1; ks <= max_split && (ks == 1 || steps / ks >= 7); ks *= 2) {
+      const int blocks = tiles * ks;
+      double e = (double)blocks / (256.0 * ((blocks + 255) / 256));
+      if (wide && blocks >= 160 && steps / ks >= 48) e *= 2;
+      if (e > best_e * 1.1) best_e = e, best = {wide != 0, ks};
+    }
+  }
+  return best;
+}
+int few_rows_splits(int N, int steps) { return fr_cut(N, 0, steps, 8).ks; }
+
+template <typename T, bool TWO>
+static void fr_launch(const FewRowsArgs& args, int form, int blocks, hipStream_t s) {
+  const int M = args.M_max;
+#define RLHF_FR(ID, WV, MT, CT, PF, OCC)                                                                        \
+  case ID:                                                                                                      \
+    hipLaunchKernelGGL((few_rows_kernel<T, WV, MT, CT, PF, OCC, TWO>),                                          \
+                       dim3(blocks, (M + 16 * MT - 1) / (16 * MT)), dim3(64 * WV), 0, s, args);                 \
+    break;
+  switch (form) { RLHF_FR_FORMS(RLHF_FR) }
+#undef RLHF_FR
+}
+
+hipError_t launch_few_rows(int dtype, FewRowsArgs& args, int n_prods, hipStream_t s) {
+  int blocks = 0, steps = 0;
+  bool two = false;
+  for (int i = 0; i < n_prods; ++i) steps = std::max(steps, args.p[i].seg[0].steps + args.p[i].seg[1].steps);
+  const bool split = n_prods == 1 && args.p[0].epilogue == EPI_F32 && args.p[0].ksplit > 1;
+  const FrCut cut = fr_cut(args.p[0].N, n_prods > 1 ? args.p[1].N : 0, steps, split ? 8 : 1);
+  if (split && cut.ks != args.p[0].ksplit) return hipErrorInvalidValue;  // few_rows_splits gives the count
+  const int form = fr_form(args.M_max, cut.wide, steps / cut.ks), c = kFormCols[form];
+  for (int i = 0; i < n_prods; ++i) {
+    FewRowsProd& p = args.p[i];
+    if (p.epilogue != EPI_F32) p.ksplit = 1;
+    blocks += ((p.N + c - 1) / c) * p.ksplit;
+    two = two || p.seg[1].steps > 0;
+    if (i == 0) args.blocks0 = blocks;
+  }
+  if (dtype == 0) {
+    if (two) fr_launch<float, true>(args, form, blocks, s);
+    else fr_launch<float, false>(args, form, blocks, s);
+  } else {
+    if (two) return hipErrorInvalidValue;  // fp16 matrices that are added up lie side by side
+    fr_launch<half_t, false>(args, form, blocks, s);
+  }
+  return hipGetLastError();
+}
+
+void fr_seg(int dtype, FewRowsSeg& g, const void* A, const void* W, int K, int lda, int ldw) {
+  g.A = A;
+  g.W = W;
+  g.steps = K / fr_step(dtype);
+  g.ldw = ldw ? ldw : K;
+  const uint32_t esz = dtype == 0 ? 4 : 2;
+  if (lda < 0) {
+    g.a_tile = 16 * (uint32_t)-lda * esz; g.a_row = 16; g.a_half = 256; g.a_q = 512; g.a_step = 2048;
+  } else {
+    g.a_row = (uint32_t)(lda ? lda : K) * esz; g.a_tile = 16 * g.a_row; g.a_half = 16; g.a_q = 32; g.a_step = 128;
+  }
+}
+
+hipError_t launch_few_rows_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
+  FewRowsArgs args;
+  FewRowsProd& p = args.p[0];
+  fr_seg(dtype, p.seg[0], a.A, a.W, a.K, a.lda, a.ldw);
+  p.bias = a.bias;
+  p.out = a.out;
+  p.N = a.N;
+  p.ldo = a.ldo;
+  p.epilogue = a.epilogue;
+  args.M_max = a.M_max;
+  args.M_dev = a.M_dev;
+  args.M_sub = a.M_sub;
+  return launch_few_rows(dtype, args, 1, s);
+}
+
+}  // namespace rlhf

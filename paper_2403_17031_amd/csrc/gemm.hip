@@ -23,21 +23,6 @@ typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-
-// GELU for fp16 outputs: x * Phi(x) with Phi(x) ~ 1 / (1 + exp(-x * (c1 + c3 x^2 + c5 x^4))), the
-// coefficients fitted to the erf form over [-9, 9]: absolute error below 2.6e-5 everywhere (the
-// fp16 result itself is rounded to 2^-11 relative), one exp and one reciprocal per element.  x^2 is
-// capped at 64: beyond |x| = 8 the polynomial would bend back, and the sigmoid is saturated there.
-// The constants carry the factor -log2(e) of the base-2 exponential.
-__device__ __forceinline__ float gelu_f16out(float x) {
-  const float s = fminf(x * x, 64.0f);
-  float p = fmaf(1.01426504e-3f, s, -1.06775735e-1f);
-  p = fmaf(p, s, -2.30112140f);
-  const float e = __builtin_amdgcn_exp2f(x * p);  // exp(-u); inf for very negative x gives 1/inf = 0
-  return x * __frcp_rn(1.0f + e);
-}
-
 template <int EPI, typename T>
 __device__ __forceinline__ void epilogue_store(void* out, size_t idx, float acc, float bias) {
   if (EPI == EPI_BIAS) {
@@ -802,6 +787,7 @@ __global__ void __launch_bounds__(256)
 // N tiles and by splitting K, so that every CU holds several short k-loops in flight; partial sums
 // go through the caller's fp32 scratch.
 int gemm_splitk_factor(int dtype, const GemmArgs& a) {
+  if (few_rows_takes(dtype, a)) return 1;  // sums over K inside a block
   if (RLHF_GEMM_SKINNY && gemm_skinny_takes(dtype, a)) return gemm_skinny_splitk(a);
   if (dtype != 1 || a.M_max > 512 || !a.splitk_ws || (a.ldo & 3) != 0) return 1;
   const int tiles = ((a.M_max + 127) / 128) * ((a.N + 63) / 64);
@@ -864,7 +850,9 @@ int gemm_lse_parts(int n_cols) { return (kDmaWaves == 8 ? 4 : 2) * ((n_cols + 25
 
 template <int EPI>
 static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {
-  if (dtype == 0) {
+  if (few_rows_takes(dtype, a)) {
+    (void)launch_few_rows_gemm(dtype, a, s);
+  } else if (dtype == 0) {
     dim3 grid((a.N + 63) / 64, (a.M_max + 63) / 64);
     hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, (const float*)a.A, (const float*)a.W,
                        (const float*)a.bias, a.out, a.M_max, a.M_dev, a.M_sub, a.N, a.K, a.ldo);
@@ -915,7 +903,7 @@ static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   if (a.M_max <= 0) return hipSuccess;
   if (dtype == 1 && (a.K % 8) != 0) return hipErrorInvalidValue;
-  if (dtype != 1 && (a.lda || a.ldw || a.bias2)) return hipErrorInvalidValue;
+  if (dtype != 1 && (a.bias2 || ((a.lda || a.ldw) && !few_rows_takes(dtype, a)))) return hipErrorInvalidValue;
   if (a.bias2 && !gemm_takes_bias2(dtype, a)) return hipErrorInvalidValue;
   if (a.k_major && !gemm_takes_k_major(dtype, a)) return hipErrorInvalidValue;
   switch (a.epilogue) {
