@@ -163,22 +163,30 @@ __global__ void __launch_bounds__(64 * WV)
     }
   };
   const int j_first = wave * (U * G);
+  // ---- the new row: load, turn, store.  Its loads are issued ahead of the cache's: loads retire in order, so nothing
+  //      below waits for the first group of K and V before it is needed.
+  dc_u32x4_t nrow = {0, 0, 0, 0};
+  if (tid < 3 * CPR) {
+    const int sec = tid / CPR, ch = tid - sec * CPR;
+    nrow = *(const dc_u32x4_t*)(qkv + (size_t)b * 3 * d + (size_t)sec * d + (size_t)h * HD + ch * EPC);
+  }
+  const int turn = tid < 2 * half ? tid : -1, tsec = turn >= half ? 1 : 0, ti = turn - tsec * half;  // 2 * half <= HD <= 256
+  float co = 0.f, si = 0.f;
+  if (turn >= 0) {
+    co = cos_t[(size_t)ctx * half + ti];
+    si = sin_t[(size_t)ctx * half + ti];
+  }
   if (j_first < ctx) load_rows(j_first);
-
-  // ---- the new row: load, turn, store
   if (!POW2)
     for (int c = tid; c < (POW2 ? 0 : WV * U * G * PDS); c += 64 * WV) s_pd[c] = 0.f;
   if (tid < 3 * CPR) {
     const int sec = tid / CPR, ch = tid - sec * CPR;
-    *(dc_u32x4_t*)(&s_row[sec][ch * EPC]) =
-        *(const dc_u32x4_t*)(qkv + (size_t)b * 3 * d + (size_t)sec * d + (size_t)h * HD + ch * EPC);
+    *(dc_u32x4_t*)(&s_row[sec][ch * EPC]) = nrow;
   }
   __syncthreads();
-  for (int c = tid; c < 2 * half; c += 64 * WV) {
-    const int sec = c >= half ? 1 : 0, i = c - sec * half;
-    T& lo = s_row[sec][ADJ ? 2 * i : i];
-    T& hi = s_row[sec][ADJ ? 2 * i + 1 : i + half];
-    const float co = cos_t[(size_t)ctx * half + i], si = sin_t[(size_t)ctx * half + i];
+  if (turn >= 0) {
+    T& lo = s_row[tsec][ADJ ? 2 * ti : ti];
+    T& hi = s_row[tsec][ADJ ? 2 * ti + 1 : ti + half];
     const float a = to_f32(lo), e = to_f32(hi);
     lo = from_f32<T>(a * co - e * si);
     hi = from_f32<T>(e * co + a * si);
@@ -277,7 +285,7 @@ __global__ void __launch_bounds__(64 * WV)
       l_run += p;
       add_v(p, vr[u]);
     }
-    if (j0 + WV * U * G < ctx) load_rows(j0 + WV * U * G);
+    if (j0 + WV * U * G < ctx) load_rows(j0 + WV * U * G);  // (a second group in flight measured the same)
   }
   // ---- merge: waves bring their sums to the common maximum, then the waves' rows are added
   {

@@ -830,9 +830,8 @@ __device__ __forceinline__ uint64_t noise_step_key(uint64_t seed, uint64_t seq, 
   return fmix64(kr + RLHF_GOLDEN * (uint64_t)(step + 1));
 }
 
-__device__ __forceinline__ uint32_t noise_bits(uint64_t step_key, uint32_t v) {
-  return (uint32_t)(fmix64(step_key + RLHF_GOLDEN * (uint64_t)(v + 1)) >> 32);
-}
+// the noise of token v at a step: in = step_key + RLHF_GOLDEN * (v + 1)
+__device__ __forceinline__ uint32_t noise_bits(uint64_t in) { return (uint32_t)(fmix64(in) >> 32); }
 __device__ __forceinline__ float gumbel_from_bits(uint32_t k) {
   float E;  // E = -ln u, evaluated so that u close to 1 keeps its relative accuracy
   if (k < 0x80000000u) {
@@ -866,11 +865,19 @@ struct SamplePart {
       bi = i2;
     }
   }
+  // all lanes of the wave into each of them
   __device__ __forceinline__ void merge_wave() {
+    const float mn = wave_max(m);
+    s = wave_sum(m == -INFINITY ? 0.f : s * expf(m - mn));
+    m = mn;
+    const float b = wave_max(best);
+    int i = best == b ? bi : 0x7FFFFFFF;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-      merge(__shfl_xor(m, o, 64), __shfl_xor(s, o, 64), __shfl_xor(best, o, 64), __shfl_xor(zbest, o, 64),
-            __shfl_xor(bi, o, 64));
+    for (int o = 32; o > 0; o >>= 1) i = min(i, __shfl_xor(i, o, 64));
+    const uint64_t owner = __builtin_amdgcn_ballot_w64(best == b && bi == i);
+    zbest = __shfl(zbest, owner ? __builtin_ctzll(owner) : 0, 64);
+    best = b;
+    bi = i;
   }
 };
 
@@ -879,7 +886,7 @@ struct SamplePart {
 // block per row a single row took 72 us, a dependent chain of 49 entries per thread), and the exact noise (a
 // logarithm of a logarithm, some 150 instructions) is only formed for entries whose upper bound reaches the best
 // score the wave has seen: H(n) of n batches instead of all of them.  Both stages at a vocabulary of 50,304: 256 rows
-// 53 us (one block per row, and a kernel for the next pass's embedding: 85), what is left being the hash's 64-bit
+// 50 us (one block per row, and a kernel for the next pass's embedding: 85), what is left being the hash's 64-bit
 // products; one row 18 us (80).
 __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per) {
   __shared__ SamplePart sp[4];
@@ -888,6 +895,7 @@ __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per
   const uint64_t key = noise_step_key(a.seed, a.seq_base + (uint64_t)b, (uint32_t)a.step);
   SamplePart p = {-INFINITY, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
   float wbest = -INFINITY;  // best score of the wave so far
+  uint64_t kin = key + RLHF_GOLDEN * (uint64_t)(lo + threadIdx.x + 1);  // hash input of this thread's next entry
   for (int base = lo; base < hi; base += 1024) {  // all lanes stay in the loop: they exchange their best scores
     const int v0 = base + threadIdx.x;
     float z[4];
@@ -904,7 +912,7 @@ __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per
       bool better = false;
       if (v < hi) {
         p.s += expf(z[u] - p.m);
-        const uint32_t k = noise_bits(key, (uint32_t)v);
+        const uint32_t k = noise_bits(kin);
         if (!(z[u] + gumbel_bound(k) < wbest)) {
           const float sc = z[u] + gumbel_from_bits(k);
           better = sc > p.best;  // v increases within a thread, so '>' keeps the lowest id among equals
@@ -915,6 +923,7 @@ __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per
           }
         }
       }
+      kin += RLHF_GOLDEN * 256u;
       if (__builtin_amdgcn_ballot_w64(better) != 0) wbest = wave_max(p.best);
     }
   }

@@ -239,7 +239,7 @@ static FrCut fr_cut(int n_cols_a, int n_cols_b, int steps, int max_split) {
     for (int ks = 1; ks <= max_split && (ks == 1 || steps / ks >= 7); ks *= 2) {
       const int blocks = tiles * ks;
       double e = (double)blocks / (256.0 * ((blocks + 255) / 256));
-      if (wide && blocks >= 160 && steps / ks >= 48) e *= 2;
+      if (wide && blocks >= 224 && steps / ks >= 48) e *= 2;
       if (e > best_e * 1.1) best_e = e, best = {wide != 0, ks};
     }
   }
