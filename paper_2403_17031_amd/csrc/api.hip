@@ -164,6 +164,19 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
   return a;
 }
 
+// Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256 while
+// the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such tile, its
+// launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of 64-256 tokens, 53
+// sampled; this pass against the other, ms): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9,
+// 192 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 80 29.6 / 31.9, 128 36.3 / 39.7, 192 50.3 / 51.2, 256 63.4 / 60.8;
+// 2.8B width (79 M) 80 41.4 / 40.9, 128 51.2 / 51.9, 192 70.1 / 66.6; 6.9B width (201 M) 80 41.5 / 37.4.  Break-even is
+// about 150 M; the line is at 2^27.
+bool few_decode_size(const rlhf_model_config& c, int B) {
+  if (B <= kFewRows) return true;
+  const size_t per_layer = (size_t)c.d_model * (4 * (size_t)c.d_model + 2 * (size_t)c.d_ff);
+  return B <= 256 && (size_t)((B + 63) / 64) * per_layer <= (size_t)1 << 27;
+}
+
 // Activations of a decode pass of few sequences (run_decode_few), as packed operands (common.h).
 struct FewActs {
   void *a, *m, *att;  // LN1 and LN2 outputs [rows, d]; attention output | FFN hidden [rows, d + d_ff]
@@ -206,7 +219,7 @@ RolloutWs carve_rollout(Carver& c, const rlhf_model_config& cfg, int B, int Lq, 
   w.last = carve_acts(c, cfg, (size_t)B, esz);
   w.last.splitk_bytes = w.acts.splitk_bytes;
   w.last.splitk = w.acts.splitk;  // decode has not started: its partial-sum scratch is free
-  if (B <= kFewRows) w.few = carve_few(c, cfg, B, esz);
+  if (few_decode_size(cfg, B)) w.few = carve_few(c, cfg, B, esz);
   w.kv_slots = (size_t)B * (Lq + N - 1);
   w.kv = (char*)c.take_bytes((size_t)cfg.n_layers * 2 * w.kv_slots * cfg.d_model * esz);
   return w;
@@ -576,7 +589,7 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   return RLHF_OK;
 }
 
-// Decode pass of few sequences (up to kFewRows): four launches per layer, all on one stream.
+// Decode pass of few sequences (few_decode_size): four launches per layer, all on one stream.
 //   LayerNorm (adding the previous layer's partial sums) -> QKV and FC1 as one launch -> attention, with the rotary
 //   turn and the K / V store as its prologue -> out-projection and FC2 as one product over K = d + d_ff, left as slabs.
 // At these sizes a layer is a chain of launches, each near its own latency: the seven to nine launches on two streams
@@ -611,11 +624,11 @@ FewDecode few_decode_args(const rlhf_handle* h, const Acts& A, const FewActs& P,
 }
 bool decode_few_takes(const rlhf_handle* h, int B) {
   const rlhf_model_config& c = h->cfg;
-  if (B > kFewRows || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
+  if (!few_decode_size(c, B) || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
       !attn_decode_rope_supported(c.head_dim, c.rotary_dims) || (c.dtype == 1 && !h->ld_o2))
     return false;
   GemmArgs g;
-  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = B; g.M_dev = nullptr; g.epilogue = EPI_F32;
+  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = std::min(B, kFewRows); g.M_dev = nullptr; g.epilogue = EPI_F32;
   const int shapes[4][2] = {{3 * c.d_model, c.d_model}, {c.d_ff, c.d_model}, {c.d_model, c.d_model}, {c.d_model, c.d_ff}};
   for (auto& nk : shapes) {
     g.N = g.ldo = nk[0]; g.K = nk[1];

@@ -195,7 +195,7 @@ bool gemm_skinny_takes(int dtype, const GemmArgs& a);
 int gemm_skinny_splitk(const GemmArgs& a);
 void launch_gemm_skinny(const GemmArgs& a, int ks, hipStream_t s);
 // Products of few rows (few_rows.hip): one launch runs one or two of them over the same M rows.
-constexpr int kFewRows = 64;  // most rows in bf16 mode
+constexpr int kFewRows = 64;  // most rows of a product by itself in bf16 mode, and the rows of one tile
 // Packed activations: what a lane of the matrix instruction reads (16 bytes of a row) next to what its neighbour reads:
 // [rows / 16][K in 16-byte chunks][16 rows][16 bytes], so that a wave's load of 16 rows is contiguous.  Element index:
 template <typename T>

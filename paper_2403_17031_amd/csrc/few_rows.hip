@@ -1,5 +1,5 @@
-// Products of few rows, C[M,N] = A[M,K] * W[N,K]^T for M up to 64 (a decode pass of a small batch), and all products
-// of the fp32 check mode.
+// Products of few rows, C[M,N] = A[M,K] * W[N,K]^T for M up to 64 (a decode pass of a small batch; of up to 256
+// sequences where the model is narrow, in tiles of 64 rows), and all products of the fp32 check mode.
 //
 // Such a product is its weights' bytes and nothing else: at M = 64 the matrix cores need a tenth of the time the
 // weights take to arrive.  What the kernel is built around is bytes in flight and few launches:

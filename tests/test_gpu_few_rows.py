@@ -1,5 +1,5 @@
 """Decode passes of few sequences: sampled tokens and log-probs against the oracle for batches at the edges of the row
-tiles (16, 32, 48, 64 and one past), every head size of the single-query attention kernel, contexts shorter and longer
+tiles (16, 32, 48, 64, 128, 256 and one past), every head size of the single-query attention kernel, contexts shorter and longer
 than what one block takes in one go, both modes, and column counts that are no multiple of a block's columns."""
 import numpy as np
 import pytest
@@ -22,7 +22,8 @@ SHAPES = {
 @pytest.mark.parametrize("shape,B,lo,hi", [
     ("hd64", 1, 1, 1), ("hd80", 1, 300, 300), ("hd16", 15, 1, 40), ("hd256", 16, 5, 90), ("hd80", 17, 1, 70),
     ("hd128", 32, 3, 33), ("hd64", 33, 1, 130), ("hd80", 48, 60, 61), ("hd16", 49, 1, 9), ("hd64", 64, 1, 20),
-    ("hd128", 64, 1, 8), ("hd64", 65, 1, 8)])
+    ("hd128", 64, 1, 8), ("hd64", 65, 1, 8), ("hd80", 128, 1, 40), ("hd256", 129, 1, 9), ("hd16", 193, 1, 70),
+    ("hd80", 256, 1, 8), ("hd64", 257, 1, 8)])
 def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
     import torch
     if not torch.cuda.is_available():
