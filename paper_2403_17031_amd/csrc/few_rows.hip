@@ -80,12 +80,17 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
   const int per_wave = (b1 - b0 + WV - 1) / WV;
   const int s0 = b0 + wave * per_wave, s1 = min(b1, s0 + per_wave);
 
+  // Weight rows: the block's first one as a 64-bit address, a lane's own as a 32-bit offset from it (an output embedding
+  // may be larger than 4 GiB, a block's 64 rows are not).
+  const char* wbase[TWO ? 2 : 1];
   uint32_t woff[TWO ? 2 : 1][CT], aoff[TWO ? 2 : 1][MT];
 #pragma unroll
   for (int g = 0; g < (TWO ? 2 : 1); ++g) {
+    const size_t row = (size_t)p.seg[g].ldw * sizeof(T);
+    wbase[g] = (const char*)p.seg[g].W + n0 * row;
 #pragma unroll
     for (int c = 0; c < CT; ++c)
-      woff[g][c] = (uint32_t)min(n0 + 16 * c + l16, p.N - 1) * (uint32_t)(p.seg[g].ldw * (int)sizeof(T)) + 32 * q;
+      woff[g][c] = (uint32_t)min(16 * c + l16, p.N - 1 - n0) * (uint32_t)row + 32 * q;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const int m = min(m0 + 16 * i + l16, M - 1);
@@ -96,7 +101,7 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
   auto load = [&](int buf, int s) {
     const bool g = TWO && s >= steps0;
     const size_t k = (size_t)(s - (g ? steps0 : 0));
-    const char* wb = (const char*)(g ? p.seg[1].W : p.seg[0].W) + k * 128;
+    const char* wb = (TWO && g ? wbase[TWO ? 1 : 0] : wbase[0]) + k * 128;
     const char* ab = (const char*)(g ? p.seg[1].A : p.seg[0].A) + k * p.seg[0].a_step;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
@@ -203,7 +208,7 @@ bool few_rows_takes(int dtype, const GemmArgs& a) {
   const size_t esz = dtype == 0 ? 4 : 2, lda = a.lda ? a.lda : a.K, ldw = a.ldw ? a.ldw : a.K;
   return a.M_max > 0 && a.M_max <= (dtype == 0 ? 1 << 20 : kFewRows) && a.K > 0 && a.K % fr_step(dtype) == 0 && !a.bias2 &&
          !a.k_major && a.epilogue != EPI_LSE && a.epilogue != EPI_QKV && (lda * esz) % 16 == 0 && (ldw * esz) % 16 == 0 &&
-         (size_t)a.M_max * lda * esz < (1ull << 32) && (size_t)a.N * ldw * esz < (1ull << 32) &&
+         (size_t)a.M_max * lda * esz < (1ull << 32) && (size_t)std::min(a.N, 64) * ldw * esz < (1ull << 32) &&
          lda * esz < (1ull << 31) && ldw * esz < (1ull << 31);
 }
 

@@ -45,3 +45,45 @@ def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
     for rep in O.verify_rollout(O.OracleModel(w, cfg), toks.cpu().numpy(), mask, 11, 0.7, N, rows=rows):
         assert rep["deficit"] <= (0.0 if dtype == "fp32" else NEAR_TIE), rep
         assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL[dtype], rep
+
+
+def test_output_embedding_of_more_than_4_gib():
+    """A vocabulary whose output embedding is larger than 4 GiB: the tokens at both ends of the table are told apart in
+    the decode passes.  Only 256 rows at either end are not zero; a row offset cut to 32 bits would land on row
+    v - 262144 for v >= 262144."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    from oracle import neox_oracle as O
+    d, V, ends = 4096, 262144 + 256, 256
+    cfg = ModelConfig(1, d, 32, 128, 32, 64, vocab=V, dtype="fp32", pad_id=V)
+    w = make_weights(cfg.with_(vocab=512), 5, variant="test")
+    for name in ("embed_in", "embed_out"):
+        small, w[name] = w[name], np.zeros((V, d), np.float32)  # (zero pages: only the ends are backed by memory)
+        w[name][:ends], w[name][-ends:] = small[:ends], small[ends:]
+    w["embed_out"][:ends] *= 8  # sampled tokens come from the ends: logits of N(0, 10)
+    w["embed_out"][-ends:] *= 8
+    g = np.random.default_rng(0)
+    B, Lq, N = 2, 4, 6
+    queries = g.integers(1, ends, size=(B, Lq)).astype(np.int32)
+    mask = np.ones((B, Lq), np.uint8)
+    pol = P.Policy(cfg, w)
+    toks, lps, _ = (x.cpu().numpy() for x in pol.rollout_generate(queries, mask, 3, 0.7, N))
+    pol.close()
+    # the same model without the zero rows, whose logit is 0 and whose noise is at most 22.9
+    keep = np.r_[0:ends, V - ends:V]
+    m = O.OracleModel({**w, "embed_in": w["embed_in"][keep], "embed_out": w["embed_out"][keep]}, cfg.with_(vocab=2 * ends))
+    for b in range(B):
+        seq = np.concatenate([queries[b], toks[b, Lq:]])
+        small = np.where(seq >= ends, seq - (V - 2 * ends), seq)
+        assert ((seq < ends) | (seq >= V - ends)).all(), seq
+        x, _ = O.forward_sequence(m, small, np.arange(seq.size))
+        logits, _ = O.heads(m, x[Lq - 1:-1])
+        for t in range(N):
+            full = np.zeros(V)
+            full[keep] = logits[t]
+            score = O.sample_token(full, 0.7, O.gumbel_from_bits(O.noise_bits(3, b, t, V)))[2]
+            assert int(np.argmax(score)) == toks[b, Lq + t], (b, t)
+            assert abs(O.log_softmax_at(full, 0.7, int(toks[b, Lq + t])) - lps[b, t]) <= TOL["fp32"], (b, t)
+    assert (toks[:, Lq + 1:] >= V - ends).any()  # decode passes did sample beyond the 32-bit range
