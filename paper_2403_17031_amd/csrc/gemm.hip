@@ -850,9 +850,7 @@ int gemm_lse_parts(int n_cols) { return (kDmaWaves == 8 ? 4 : 2) * ((n_cols + 25
 
 template <int EPI>
 static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {
-  if (few_rows_takes(dtype, a)) {
-    (void)launch_few_rows_gemm(dtype, a, s);
-  } else if (dtype == 0) {
+  if (dtype == 0) {
     dim3 grid((a.N + 63) / 64, (a.M_max + 63) / 64);
     hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, (const float*)a.A, (const float*)a.W,
                        (const float*)a.bias, a.out, a.M_max, a.M_dev, a.M_sub, a.N, a.K, a.ldo);
@@ -906,6 +904,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   if (dtype != 1 && (a.bias2 || ((a.lda || a.ldw) && !few_rows_takes(dtype, a)))) return hipErrorInvalidValue;
   if (a.bias2 && !gemm_takes_bias2(dtype, a)) return hipErrorInvalidValue;
   if (a.k_major && !gemm_takes_k_major(dtype, a)) return hipErrorInvalidValue;
+  if (few_rows_takes(dtype, a)) return launch_few_rows_gemm(dtype, a, s);
   switch (a.epilogue) {
     case EPI_BIAS: launch_epi<EPI_BIAS>(dtype, a, s); break;
     case EPI_BIAS_GELU: launch_epi<EPI_BIAS_GELU>(dtype, a, s); break;

@@ -1,0 +1,54 @@
+// Host-side checks of the library's product launchers, built by the tests against the library itself.
+//   products errors   the launch calls of the runtime are replaced by ones that always fail: every route through
+//                     launch_gemm reports it
+#include <cstdio>
+#include <cstring>
+
+#include "common.h"
+
+using namespace rlhf;
+
+// The runtime's launch calls, for this program and the library in it: nothing is launched, every launch fails, and the
+// error stays until hipGetLastError takes it, as the runtime's own does.
+static hipError_t last_error = hipSuccess;
+static int launches = 0;
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  ++launches;
+  return last_error = hipErrorLaunchFailure;
+}
+extern "C" hipError_t hipGetLastError() {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
+
+static GemmArgs product(int M, int N, int K, int epilogue) {
+  GemmArgs g;
+  g.A = g.W = (const void*)4096;  // never dereferenced: nothing is launched
+  g.bias = nullptr;
+  g.out = (void*)4096;
+  g.M_max = M; g.M_dev = nullptr; g.N = N; g.K = K; g.ldo = N; g.epilogue = epilogue;
+  return g;
+}
+
+static int errors() {
+  int bad = 0;
+  const int epilogues[] = {EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESADD, EPI_F32};
+  const int rows[] = {1, 64, 65, 600};
+  for (int dtype = 0; dtype < 2; ++dtype)
+    for (int epi : epilogues)
+      for (int M : rows) {
+        const hipError_t e = launch_gemm(dtype, product(M, 256, 256, epi), nullptr);
+        printf("dtype %d epilogue %d rows %d: %d launches, status %d\n", dtype, epi, M, launches, (int)e);
+        bad += e != hipErrorLaunchFailure || launches == 0;
+        launches = 0;
+      }
+  return bad ? 1 : 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
+  return 2;
+}
