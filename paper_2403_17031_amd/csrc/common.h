@@ -67,7 +67,7 @@ __device__ __forceinline__ float wave_max(float v) {
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
-// GELU for fp16 outputs: x * Phi(x) with Phi(x) ~ 1 / (1 + exp(-x * (c1 + c3 x^2 + c5 x^4))), the
+// GELU for the fp16 outputs of products of many rows: x * Phi(x) with Phi(x) ~ 1 / (1 + exp(-x * (c1 + c3 x^2 + c5 x^4))), the
 // coefficients fitted to the erf form over [-9, 9]: absolute error below 2.6e-5 everywhere (the
 // fp16 result itself is rounded to 2^-11 relative), one exp and one reciprocal per element.  x^2 is
 // capped at 64: beyond |x| = 8 the polynomial would bend back, and the sigmoid is saturated there.

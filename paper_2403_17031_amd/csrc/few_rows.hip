@@ -186,9 +186,9 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
           if (n + u < p.N) out[u] += v[u];
       continue;
     }
-    if (p.epilogue == EPI_BIAS_GELU) {
+    if (p.epilogue == EPI_BIAS_GELU) {  // the erf form for fp16 too: gelu_f16out is many fp16 steps off below -2
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = sizeof(T) == 2 ? gelu_f16out(v[u]) : gelu_erf(v[u]);
+      for (int u = 0; u < 4; ++u) v[u] = gelu_erf(v[u]);
     }
     T* out = (T*)p.out + (p.packed_K ? packed_index<T>(m, p.packed_k0 + n, p.packed_K) : o);
     T t[4];
