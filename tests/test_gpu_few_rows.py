@@ -84,6 +84,39 @@ def test_gelu_of_negative_inputs(B):
     assert np.sqrt(np.mean(np.square(err))) <= 3 * 4e-4 * np.mean(spread)
 
 
+@pytest.mark.parametrize("hd", [16, 64, 256])  # 1 / sqrt(hd) is exact: scores are, too
+def test_fp32_softmax_weights(hd):
+    """The fp32 decode attention's softmax weights, one by one: cached row j has the exact score -x_j (50 to 80 below the
+    new row's) and a one in column j of V, so column j of the result is exp(-x_j) / (1 + sum).  Bound: two exponentials of
+    1 ulp each (a wave's rescaling is one more) and five roundings, 2 * 2^-23 + 5 * 2^-24 = 5.4e-7.  exp(x) as the base-2
+    instruction on a rounded x * log2(e) is up to 4.4e-6 off there."""
+    import ctypes as C
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    attn = P.load_library()["_ZN4rlhf23launch_attn_decode_ropeEiPKvPvS2_liPKiiiS4_iiiPKfS6_S2_iP12ihipStream_t"]
+    vp, i32 = C.c_void_p, C.c_int
+    attn.argtypes = [i32, vp, vp, vp, C.c_long, i32, vp, i32, i32, vp, i32, i32, i32, vp, vp, vp, i32, vp]
+    n, extra = hd, 4
+    g = np.random.default_rng(hd)
+    score = -np.round(16 * g.uniform(50, 80, n)) / 16
+    dev = lambda a, t=torch.float32: torch.as_tensor(a, dtype=t, device="cuda:0").contiguous()  # noqa: E731
+    k, v = np.zeros((n + extra, hd)), np.zeros((n + extra, hd))
+    k[:n, 0], v[:n] = score, np.eye(n)
+    new = np.zeros((3, hd))  # q, k, v of the new row: score 0, value 0
+    new[0, 0] = np.sqrt(hd)
+    kc, vc, qkv = dev(k), dev(v), dev(new)
+    out = torch.zeros(16, hd, device="cuda:0")  # packed: 16-byte chunks of 16 rows
+    length, off = dev([n], torch.int32), dev([0], torch.int32)
+    rc = attn(0, qkv.data_ptr(), kc.data_ptr(), vc.data_ptr(), extra, 1, length.data_ptr(), 0, n + 1, off.data_ptr(), 1, hd,
+              0, None, None, out.data_ptr(), hd, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    got = out.view(hd // 4, 16, 4)[:, 0].reshape(hd).cpu().numpy().astype(np.float64)
+    want = np.exp(score) / (1 + np.exp(score).sum())
+    assert np.abs(got / want - 1).max() <= 5.4e-7
+
+
 def test_output_embedding_of_more_than_4_gib():
     """A vocabulary whose output embedding is larger than 4 GiB: the tokens at both ends of the table are told apart in
     the decode passes.  Only 256 rows at either end are not zero; a row offset cut to 32 bits would land on row
