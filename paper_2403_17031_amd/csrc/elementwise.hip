@@ -1,6 +1,7 @@
 // Row bookkeeping, embedding gather, LayerNorm (+ value head), partial rotary + KV store, the
 // Gumbel-max sampler, log-sum-exp + target gather, and output scatter.  All bandwidth-bound.
 #include <algorithm>
+#include <cfloat>
 
 #include "common.h"
 
@@ -850,14 +851,16 @@ __device__ __forceinline__ float gumbel_bound(uint32_t k) {
 }
 
 // Log-sum-exp and best perturbed score of a set of vocabulary entries; merging is associative up to rounding, ties
-// go to the lowest token id.
+// go to the lowest token id.  m starts at the lowest finite value, so that m - m2 is never inf - inf: a NaN logit makes
+// the sum NaN and stays one through every merge (the log-prob of a row says so however the row is cut), a logit of -inf
+// adds 0.
 struct SamplePart {
   float m, s;        // max z and sum of exp(z - m)
   float best, zbest; // best z + noise, and the z it belongs to
   int bi;
   __device__ __forceinline__ void merge(float m2, float s2, float b2, float z2, int i2) {
     const float mn = fmaxf(m, m2);
-    s = (m == -INFINITY ? 0.f : s * expf(m - mn)) + (m2 == -INFINITY ? 0.f : s2 * expf(m2 - mn));
+    s = s * expf(m - mn) + s2 * expf(m2 - mn);
     m = mn;
     if (b2 > best || (b2 == best && i2 < bi)) {
       best = b2;
@@ -868,7 +871,7 @@ struct SamplePart {
   // all lanes of the wave into each of them
   __device__ __forceinline__ void merge_wave() {
     const float mn = wave_max(m);
-    s = wave_sum(m == -INFINITY ? 0.f : s * expf(m - mn));
+    s = wave_sum(s * expf(m - mn));
     m = mn;
     const float b = wave_max(best);
     int i = best == b ? bi : 0x7FFFFFFF;
@@ -893,7 +896,7 @@ __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per
   const int b = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, a.V);
   const float* row = a.logits + (size_t)b * a.V;
   const uint64_t key = noise_step_key(a.seed, a.seq_base + (uint64_t)b, (uint32_t)a.step);
-  SamplePart p = {-INFINITY, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
+  SamplePart p = {-FLT_MAX, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
   float wbest = -INFINITY;  // best score of the wave so far
   uint64_t kin = key + RLHF_GOLDEN * (uint64_t)(lo + threadIdx.x + 1);  // hash input of this thread's next entry
   for (int base = lo; base < hi; base += 1024) {  // all lanes stay in the loop: they exchange their best scores
@@ -945,7 +948,7 @@ __global__ void __launch_bounds__(256)
   __shared__ int s_tok;
   const int b = blockIdx.x;
   if (threadIdx.x < 64) {
-    SamplePart p = {-INFINITY, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
+    SamplePart p = {-FLT_MAX, 0.f, -INFINITY, 0.f, 0x7FFFFFFF};
     const SamplePart* parts = (const SamplePart*)a.parts + (size_t)b * nparts;
     for (int j = threadIdx.x; j < nparts; j += 64) p.merge(parts[j].m, parts[j].s, parts[j].best, parts[j].zbest, parts[j].bi);
     p.merge_wave();
