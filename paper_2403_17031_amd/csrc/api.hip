@@ -335,6 +335,34 @@ struct PassArgs {
   int u_keep_layers = 0;
 };
 
+// Whether the few-rows kernel takes the four products of a layer over this many rows (of its tiles' rows at least).
+bool few_products_take(const rlhf_model_config& c, int rows) {
+  GemmArgs g;
+  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = std::min(rows, kFewRows); g.M_dev = nullptr; g.epilogue = EPI_F32;
+  const int shapes[4][2] = {{3 * c.d_model, c.d_model}, {c.d_ff, c.d_model}, {c.d_model, c.d_model}, {c.d_model, c.d_ff}};
+  for (auto& nk : shapes) {
+    g.N = g.ldo = nk[0]; g.K = nk[1];
+    g.lda = g.ldw = c.d_model + c.d_ff;  // the widest stride any of them has
+    if (!few_rows_takes(c.dtype, g)) return false;
+  }
+  return true;
+}
+
+// Whether the products of a run_layers decode pass (bf16; head sizes or widths that run_decode_few does not take) are the
+// few-rows kernel's: one launch each, but A row-major, K not split and no second stream, against split K with the
+// reductions folded into their consumers and the MLP beside attention.  Few rows of narrow layers: there launches are what
+// a pass consists of.  Measured with head sizes 32 and 96, 4 d hidden, at most 128 / 512 tokens of context (ms for 32
+// passes of two layers, few rows against split K): width 512, 64 rows 6.1 / 9.3 against 6.6 / 8.7; 768, 32 rows 5.1 / 7.8
+// against 6.6 / 8.2; 1024, 32 rows 5.9 / 9.8 against 6.8 / 9.6, 64 rows 8.1 / 15.3 against 8.0 / 14.1; 1536, 16 rows
+// 8.3 / 15.1 against 8.7 / 14.2; 2048, 4 rows 7.6 / 8.8 against 8.2 / 8.5, 64 rows 15.3 / 22.0 against 12.4 / 17.9; 3072, one
+// row 11.5 / 14.1 against 10.8 / 12.0.  From width 4096 on the unsplit out-projection covers half the chip by itself, and
+// very few rows win again: 4096, 4 rows 14.2 / 15.8 against 15.6 / 16.5, 32 rows 20.4 / 28.4 against 19.8 / 26.3; 5120, one
+// row 18.1 against 19.9, 16 rows 21.6 against 21.3 (32 tokens).
+bool few_rows_layer(const rlhf_model_config& c, int rows) {
+  const bool narrow = c.d_model <= 2048 && (size_t)rows * c.d_model * c.d_model <= (size_t)1 << 25;
+  return c.dtype == 1 && rows <= kFewRows && (narrow || (c.d_model >= 4096 && rows <= 4)) && few_products_take(c, rows);
+}
+
 int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) {
   const rlhf_model_config& c = h->cfg;
   if (c.n_layers == 0) {  // nothing to run (and no layer 0 to take shapes from below)
@@ -348,7 +376,8 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   GemmArgs base;
   base.M_max = p.rows_max;
   base.M_dev = p.rows_dev;
-  if (p.mode == 1) {
+  const bool split = p.mode == 1 && !few_rows_layer(c, p.rows_max);
+  if (split) {
     base.splitk_ws = A.splitk;
     base.splitk_ws_bytes = A.splitk_bytes;
   }
@@ -454,8 +483,10 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
       GemmArgs z;
       z.M_max = p.B;
       z.M_dev = nullptr;
-      z.splitk_ws = Z.splitk;
-      z.splitk_ws_bytes = Z.splitk_bytes;
+      if (p.B > kFewRows || !few_products_take(c, p.B)) {  // (few rows: one launch each, once per rollout)
+        z.splitk_ws = Z.splitk;
+        z.splitk_ws_bytes = Z.splitk_bytes;
+      }
       auto few = [&](const void* in, const void* w, const void* bias, void* out, int N, int K, int epi) {
         GemmArgs g = z;
         g.A = in; g.W = w; g.bias = bias; g.out = out; g.N = N; g.K = K; g.ldo = N; g.epilogue = epi;
@@ -521,7 +552,7 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
       g1.out = (char*)A.att + (size_t)d * h->esz;
       g1.ldo = d + c.d_ff;
     }
-    if (p.mode == 1) {  // the MLP branch has partial-sum scratch of its own
+    if (split) {  // the MLP branch has partial-sum scratch of its own
       g1.splitk_ws = A.splitk2;
       g2.splitk_ws = A.splitk2;
     }
@@ -627,15 +658,7 @@ bool decode_few_takes(const rlhf_handle* h, int B) {
   if (!few_decode_size(c, B) || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
       !attn_decode_rope_supported(c.head_dim, c.rotary_dims) || (c.dtype == 1 && !h->ld_o2))
     return false;
-  GemmArgs g;
-  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = std::min(B, kFewRows); g.M_dev = nullptr; g.epilogue = EPI_F32;
-  const int shapes[4][2] = {{3 * c.d_model, c.d_model}, {c.d_ff, c.d_model}, {c.d_model, c.d_model}, {c.d_model, c.d_ff}};
-  for (auto& nk : shapes) {
-    g.N = g.ldo = nk[0]; g.K = nk[1];
-    g.lda = g.ldw = c.d_model + c.d_ff;  // the widest stride any of them has
-    if (!few_rows_takes(c.dtype, g)) return false;
-  }
-  return true;
+  return few_products_take(c, B);
 }
 // The layers, the final LayerNorm and the LM head (into logits).
 int run_decode_few(rlhf_handle* h, const Acts& A, const FewActs& P, const PassArgs& p, float* logits, hipStream_t s) {

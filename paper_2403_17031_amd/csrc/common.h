@@ -171,12 +171,13 @@ struct GemmArgs {
   int M_sub = 0;      // with M_dev: M = min(M_max, *M_dev - M_sub)  (row chunk starting at M_sub)
   int N, K, ldo;
   int epilogue;
-  void* splitk_ws = nullptr;   // fp32 scratch for split-K partial sums (decode-sized M), or null
+  void* splitk_ws = nullptr;   // fp32 scratch for split-K partial sums (decode-sized M), or null (fp16, up to 64 rows:
+                               // with it the split-K kernels take the product, without it the few-rows kernel)
   size_t splitk_ws_bytes = 0;
   int phase = 0;               // split-K only: 0 = GEMM + reduce, 1 = partial sums only, 2 = reduce only
   const struct LseArgs* lse = nullptr;  // EPI_LSE only
   const struct QkvArgs* qkv = nullptr;  // EPI_QKV only
-  int lda = 0, ldw = 0;        // row strides of A and W in elements (0: K); fp16 kernels only
+  int lda = 0, ldw = 0;        // row strides of A and W in elements (0: K); fp16 kernels and the few-rows kernel
   const void* bias2 = nullptr; // second bias added like the first; large-M fp16 kernel only
   int max_split = 0;           // few-rows kernel: cap on the K split (0: as many as cover the chip)
   bool k_major = false;        // operands given K-major: A is [K, M_max], W is [K, N], row-major, lda / ldw their row

@@ -1,5 +1,5 @@
-// Product C[M,N] = A[M,K] * W[N,K]^T for the decode passes of large batches (M = batch, 65 to 512 rows; fewer rows:
-// few_rows.hip).
+// Product C[M,N] = A[M,K] * W[N,K]^T for the decode passes that run_layers takes (M = batch, up to 512 rows; batches that
+// run_decode_few takes, and single products of up to 64 rows without split-K scratch, are few_rows.hip's).
 //
 // Such a product streams every weight once and multiplies it with all M rows: 2*M flop per weight byte
 // pair, i.e. right at the ridge between HBM and the matrix cores for M = 256.  What the kernel is built
@@ -116,18 +116,19 @@ __global__ void __launch_bounds__(256, 1)
   {                                                                            \
     const uint32_t ad_ = fad[SB] + (uint32_t)((STG) * STAGE * 2);              \
     SK_RD(BUF, 0, ad_); SK_RD(BUF, 1, ad_);                                    \
-    SK_RD(BUF, 2, ad_); SK_RD(BUF, 3, ad_);                                    \
+    if (MT > 2) { SK_RD(BUF, 2 % MT, ad_); SK_RD(BUF, 3 % MT, ad_); }          \
     if (MT > 4) { SK_RD(BUF, 4 % MT, ad_); SK_RD(BUF, 5 % MT, ad_); SK_RD(BUF, 6 % MT, ad_); SK_RD(BUF, 7 % MT, ad_); } \
   }
   // wait until at most N fragment reads are outstanding; the buffer's registers pass through the statement so
   // that the matrix instructions using them cannot be moved in front of it
 #define SK_LGKM(N, BUF)                                                                        \
   {                                                                                            \
-    if (MT == 4)                                                                               \
-      asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(fa[BUF][0]), "+v"(fa[BUF][1]), "+v"(fa[BUF][2]), "+v"(fa[BUF][3])::"memory"); \
+    if (MT == 2) asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(fa[BUF][0]), "+v"(fa[BUF][1])::"memory"); \
+    else if (MT == 4)                                                                          \
+      asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(fa[BUF][0]), "+v"(fa[BUF][1]), "+v"(fa[BUF][2 % MT]), "+v"(fa[BUF][3 % MT])::"memory"); \
     else                                                                                       \
       asm volatile("s_waitcnt lgkmcnt(" #N ")"                                                 \
-                   : "+v"(fa[BUF][0]), "+v"(fa[BUF][1]), "+v"(fa[BUF][2]), "+v"(fa[BUF][3]), "+v"(fa[BUF][4 % MT]), \
+                   : "+v"(fa[BUF][0]), "+v"(fa[BUF][1]), "+v"(fa[BUF][2 % MT]), "+v"(fa[BUF][3 % MT]), "+v"(fa[BUF][4 % MT]), \
                      "+v"(fa[BUF][5 % MT]), "+v"(fa[BUF][6 % MT]), "+v"(fa[BUF][7 % MT])::"memory"); \
   }
   auto mfmas = [&](int buf, const sk_u32x4_t& wv) {
@@ -152,7 +153,7 @@ __global__ void __launch_bounds__(256, 1)
     __builtin_amdgcn_sched_barrier(0);                                                         \
   }
 #define SK_FENCE() __builtin_amdgcn_sched_barrier(0)
-#define SK_LGKM_MT(BUF) { if (MT == 8) SK_LGKM(8, BUF) else SK_LGKM(4, BUF) }
+#define SK_LGKM_MT(BUF) { if (MT == 8) SK_LGKM(8, BUF) else if (MT == 4) SK_LGKM(4, BUF) else SK_LGKM(2, BUF) }
   // One k-step on register set / stage S.  The MT fragments of a sub-step are read as one batch, two batches in
   // flight: while the matrix instructions of sub-steps 2 and 3 run, the first two batches of the NEXT step are
   // already being read -- which is why the wait-and-barrier sits in the middle of the step and not at its end
@@ -256,7 +257,7 @@ bool gemm_skinny_takes(int dtype, const GemmArgs& a) {
          (size_t)a.M_max * lda < (1ull << 31);
 }
 
-static int sk_rows_per_block(int M) { return M <= 128 ? 128 : 256; }
+static int sk_rows_per_block(int M) { return M <= 64 ? 64 : (M <= 128 ? 128 : 256); }
 
 // K split: enough blocks to cover the chip (or `max_split`, if the caller caps it: a product that runs in the
 // shadow of another kernel is better off with fewer, longer blocks and fewer partial sums), at least four
@@ -285,7 +286,8 @@ static void sk_launch(const GemmArgs& a, void* out, int ks, hipStream_t s) {
 template <int EPI>
 static void sk_launch_rows(const GemmArgs& a, void* out, int ks, hipStream_t s) {
   const int rows = sk_rows_per_block(a.M_max);
-  if (rows == 128) sk_launch<4, EPI>(a, out, ks, s);
+  if (rows == 64) sk_launch<2, EPI>(a, out, ks, s);
+  else if (rows == 128) sk_launch<4, EPI>(a, out, ks, s);
   else sk_launch<8, EPI>(a, out, ks, s);
 }
 

@@ -1,6 +1,7 @@
 // Host-side checks of the library's product launchers, built by the tests against the library itself.
 //   products errors   the launch calls of the runtime are replaced by ones that always fail: every route through
 //                     launch_gemm reports it
+//   products split    a decode product of few rows that is given split-K scratch is cut over K until it covers the chip
 #include <cstdio>
 #include <cstring>
 
@@ -48,7 +49,24 @@ static int errors() {
   return bad ? 1 : 0;
 }
 
+static int split() {
+  int bad = 0;
+  const int shapes[][2] = {{3072, 3072}, {3072, 12288}, {2048, 8192}, {5120, 20480}};  // out-projection and FC2
+  for (auto& nk : shapes)
+    for (int M : {1, 16, 33, 64}) {
+      GemmArgs g = product(M, nk[0], nk[1], EPI_BIAS_RESADD);
+      g.splitk_ws = (void*)4096;
+      g.splitk_ws_bytes = (size_t)16 * M * 3 * nk[1] * sizeof(float);
+      const int ks = gemm_splitk_factor(1, g);
+      g.splitk_ws = nullptr;
+      printf("rows %d, %d x %d: split %d\n", M, nk[0], nk[1], ks);
+      bad += ks < 2 || !few_rows_takes(1, g);
+    }
+  return bad ? 1 : 0;
+}
+
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
+  if (argc > 1 && !strcmp(argv[1], "split")) return split();
   return 2;
 }

@@ -15,6 +15,9 @@ NEAR_TIE = 1e-2
 SHAPES = {
     "hd16": (128, 8, 16, 4, 192, 211), "hd64": (128, 2, 64, 16, 512, 1003), "hd80": (320, 4, 80, 20, 448, 517),
     "hd128": (256, 2, 128, 32, 320, 300), "hd256": (256, 1, 256, 64, 1024, 259),
+    # head sizes without a decode kernel of their own: the general pass, with few-rows products or split ones
+    "hd32": (256, 8, 32, 8, 512, 300), "hd96": (768, 8, 96, 24, 512, 300), "hd32-1024": (1024, 32, 32, 8, 1024, 300),
+    "hd32-2112": (2112, 66, 32, 8, 256, 300), "hd32-4096": (4096, 128, 32, 8, 128, 300),
 }
 
 
@@ -23,7 +26,9 @@ SHAPES = {
     ("hd64", 1, 1, 1), ("hd80", 1, 300, 300), ("hd16", 15, 1, 40), ("hd256", 16, 5, 90), ("hd80", 17, 1, 70),
     ("hd128", 32, 3, 33), ("hd64", 33, 1, 130), ("hd80", 48, 60, 61), ("hd16", 49, 1, 9), ("hd64", 64, 1, 20),
     ("hd128", 64, 1, 8), ("hd64", 65, 1, 8), ("hd80", 128, 1, 40), ("hd256", 129, 1, 9), ("hd16", 193, 1, 70),
-    ("hd80", 256, 1, 8), ("hd64", 257, 1, 8)])
+    ("hd80", 256, 1, 8), ("hd64", 257, 1, 8), ("hd32", 1, 1, 5), ("hd32", 64, 1, 9), ("hd96", 56, 3, 20), ("hd96", 57, 1, 9),
+    ("hd32-1024", 32, 1, 9), ("hd32-1024", 33, 1, 9), ("hd32-1024", 64, 5, 40), ("hd32-2112", 3, 1, 9),
+    ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9)])
 def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
     import torch
     if not torch.cuda.is_available():

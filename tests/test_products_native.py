@@ -24,3 +24,8 @@ def products(tmp_path_factory):
 def test_a_product_that_cannot_launch_reports_it(products):
     r = subprocess.run([products, "errors"], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_a_decode_product_with_scratch_is_split(products):
+    r = subprocess.run([products, "split"], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
