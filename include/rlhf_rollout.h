@@ -63,7 +63,8 @@ typedef struct {
 
 /* Weights: DEVICE pointers, read-only, caller-owned, must outlive the handle.  Matrices are
  * row-major [out_features, in_features] (y = x W^T + b).  The per-layer members are HOST arrays of
- * n_layers device pointers (the arrays themselves are only read inside rlhf_create). */
+ * n_layers device pointers (the arrays themselves are only read inside rlhf_create).  fp32 arrays may start at
+ * any float; 16-byte aligned ones take faster kernels. */
 typedef struct {
   const void *embed_in;        /* [vocab, d_model] */
   const void *const *ln1_g, *const *ln1_b, *const *ln2_g, *const *ln2_b; /* [d_model] each */

@@ -81,6 +81,8 @@ struct rlhf_handle {
   // stride), so that prefill / scoring can run them as a single product over K = d + d_ff
   int ld_o2 = 0;
   size_t esz = 2;
+  // The arrays that run_decode_few's kernels read four parameters (or 16 bytes of a matrix) at a time are aligned for it.
+  bool vec_params = false;
   // once an update has run, the value head's bias lives on the device (the optimizer updates it there)
   const float* value_b_dev = nullptr;
   // profiling
@@ -655,7 +657,7 @@ FewDecode few_decode_args(const rlhf_handle* h, const Acts& A, const FewActs& P,
 }
 bool decode_few_takes(const rlhf_handle* h, int B) {
   const rlhf_model_config& c = h->cfg;
-  if (!few_decode_size(c, B) || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
+  if (!few_decode_size(c, B) || !h->vec_params || c.n_layers == 0 || !ln_decode_supported(c.d_model) ||
       !attn_decode_rope_supported(c.head_dim, c.rotary_dims) || (c.dtype == 1 && !h->ld_o2))
     return false;
   return few_products_take(c, B);
@@ -905,6 +907,15 @@ int rlhf_create(const rlhf_model_config* cfg, const rlhf_weights* w, void* weigh
                                        &h->w_o,   &h->b_o,   &h->w_fc1, &h->b_fc1, &h->w_fc2, &h->b_fc2};
   for (int i = 0; i < 12; ++i) dst[i]->assign(per_layer[i], per_layer[i] + c.n_layers);
   h->src_w_qkv = h->w_qkv; h->src_b_qkv = h->b_qkv; h->src_w_o = h->w_o; h->src_w_fc1 = h->w_fc1; h->src_w_fc2 = h->w_fc2;
+  uintptr_t vectors = (uintptr_t)w->lnf_g | (uintptr_t)w->lnf_b, matrices = 0;
+  for (auto p : {w->ln1_g, w->ln1_b, w->ln2_g, w->ln2_b, w->b_o, w->b_fc2})
+    for (int l = 0; l < c.n_layers; ++l) vectors |= (uintptr_t)p[l];
+  if (c.dtype == RLHF_DTYPE_FP32) {  // (bf16 mode reads its matrices from the image)
+    matrices = (uintptr_t)w->embed_out;
+    for (auto p : {w->w_qkv, w->w_o, w->w_fc1, w->w_fc2})
+      for (int l = 0; l < c.n_layers; ++l) matrices |= (uintptr_t)p[l];
+  }
+  h->vec_params = (vectors & (4 * h->esz - 1)) == 0 && (matrices & 15) == 0;
   // rotary tables, evaluated in double on the host: angle(p, i) = p * base^(-2i/r)
   const int half = c.rotary_dims / 2;
   if (half > 0) {

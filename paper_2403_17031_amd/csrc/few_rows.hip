@@ -204,9 +204,13 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
 
 static int fr_step(int dtype) { return dtype == 0 ? 32 : 64; }  // K elements per step (128 bytes)
 
+// Both operands are read, and four columns of a row written, with one instruction: addresses that are no multiple of its
+// size (an fp32 caller's own arrays may have any) stay with the other kernels, which move single floats.
 // (A bf16 product that comes with split-K scratch is not taken: see few_rows_layer in api.hip.)
 bool few_rows_takes(int dtype, const GemmArgs& a) {
   const size_t esz = dtype == 0 ? 4 : 2, lda = a.lda ? a.lda : a.K, ldw = a.ldw ? a.ldw : a.K;
+  const uintptr_t out_mask = dtype == 1 && (a.epilogue == EPI_BIAS || a.epilogue == EPI_BIAS_GELU) ? 7 : 15;
+  if ((((uintptr_t)a.A | (uintptr_t)a.W) & 15) != 0 || ((uintptr_t)a.out & out_mask) != 0) return false;
   return (dtype == 0 || !a.splitk_ws) && a.M_max > 0 && a.M_max <= (dtype == 0 ? 1 << 20 : kFewRows) && a.K > 0 && a.K % fr_step(dtype) == 0 && !a.bias2 &&
          !a.k_major && a.epilogue >= EPI_BIAS && a.epilogue <= EPI_F32 && (lda * esz) % 16 == 0 && (ldw * esz) % 16 == 0 &&
          (size_t)a.M_max * lda * esz < (1ull << 32) && (size_t)std::min(a.N, 64) * ldw * esz < (1ull << 32) &&

@@ -1,6 +1,7 @@
 // Host-side checks of the library's product launchers, built by the tests against the library itself.
 //   products errors   the launch calls of the runtime are replaced by ones that always fail: every route through
 //                     launch_gemm reports it
+//   products aligned  the few-rows kernel, which moves 16 bytes at a time, is not given addresses that are no multiple
 //   products split    a decode product of few rows that is given split-K scratch is cut over K until it covers the chip
 #include <cstdio>
 #include <cstring>
@@ -49,6 +50,29 @@ static int errors() {
   return bad ? 1 : 0;
 }
 
+static int aligned() {
+  int bad = 0;
+  const int epilogues[] = {EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESADD, EPI_F32};
+  for (int dtype = 0; dtype < 2; ++dtype)
+    for (int epi : epilogues)
+      for (int which = 0; which < 4; ++which)
+        for (int off = dtype ? 2 : 4; off < 16; off *= 2) {
+          GemmArgs g = product(8, 256, 256, epi);
+          const void* moved = (const char*)4096 + off;
+          if (which == 0) g.A = moved;
+          if (which == 1) g.W = moved;
+          if (which == 2) g.out = (void*)moved;
+          if (which == 3) g.bias = moved;  // read by single values
+          const bool half_out = dtype == 1 && (epi == EPI_BIAS || epi == EPI_BIAS_GELU);
+          const bool want = which == 3 || (which == 2 && half_out && off == 8);
+          if (few_rows_takes(dtype, g) != want) {
+            printf("dtype %d epilogue %d operand %d offset %d\n", dtype, epi, which, off);
+            ++bad;
+          }
+        }
+  return bad ? 1 : 0;
+}
+
 static int split() {
   int bad = 0;
   const int shapes[][2] = {{3072, 3072}, {3072, 12288}, {2048, 8192}, {5120, 20480}};  // out-projection and FC2
@@ -67,6 +91,7 @@ static int split() {
 
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
+  if (argc > 1 && !strcmp(argv[1], "aligned")) return aligned();
   if (argc > 1 && !strcmp(argv[1], "split")) return split();
   return 2;
 }

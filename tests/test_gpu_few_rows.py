@@ -52,6 +52,38 @@ def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
         assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL[dtype], rep
 
 
+def test_weights_at_any_float_address(monkeypatch):
+    """An fp32 model whose arrays start four bytes past a 16-byte boundary: decode takes the general pass, whose kernels
+    read them float by float, and the results stand."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    from oracle import neox_oracle as O
+    d, H, hd, r, F, V = SHAPES["hd64"]
+    cfg = ModelConfig(2, d, H, hd, r, F, vocab=V, dtype="fp32", pad_id=V)
+    w = make_weights(cfg, 77, variant="test")
+    to = torch.Tensor.to
+
+    def shifted(t, *args, **kw):
+        t = to(t, *args, **kw)
+        return torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape) if t.is_cuda else t
+
+    g = np.random.default_rng(5)
+    B, Lq, N = 3, 9, 5
+    queries, mask = g.integers(1, V, size=(B, Lq)).astype(np.int32), np.ones((B, Lq), np.uint8)
+    with monkeypatch.context() as m:
+        m.setattr(torch.Tensor, "to", shifted)
+        pol = P.Policy(cfg, w)
+    assert all(t.data_ptr() % 16 == 4 for t in pol._dev.values())
+    for p, few in ((pol, False), (P.Policy(cfg, w), True)):
+        p.profile_enable()
+        toks, lps, _ = (x.cpu().numpy() for x in p.rollout_generate(queries, mask, 11, 0.7, N))
+        assert ("gemm_decode_qkv_fc1" in p.profile_read()) == few
+        for rep in O.verify_rollout(O.OracleModel(w, cfg), toks, mask, 11, 0.7, N, rows=list(range(B))):
+            assert rep["deficit"] <= 0.0 and abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL["fp32"], rep
+
+
 @pytest.mark.parametrize("B", [1, 17, 64])
 def test_gelu_of_negative_inputs(B):
     """FC1 outputs in [-4, -3], where GELU is x * Phi(x) with Phi down to 3e-5: an absolute error that fp16 would hide

@@ -29,3 +29,8 @@ def test_a_product_that_cannot_launch_reports_it(products):
 def test_a_decode_product_with_scratch_is_split(products):
     r = subprocess.run([products, "split"], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_unaligned_operands_stay_off_the_few_rows_kernel(products):
+    r = subprocess.run([products, "aligned"], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
