@@ -2,8 +2,12 @@
 //   products errors   the launch calls of the runtime are replaced by ones that always fail: every route through
 //                     launch_gemm reports it
 //   products aligned  the few-rows kernel, which moves 16 bytes at a time, is not given addresses that are no multiple
+//   products forms d F V rows   the kernels that the product launches of a decode pass take (bf16 mode)
 //   products split    a decode product of few rows that is given split-K scratch is cut over K until it covers the chip
+#include <dlfcn.h>
+
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "common.h"
@@ -14,10 +18,12 @@ using namespace rlhf;
 // error stays until hipGetLastError takes it, as the runtime's own does.
 static hipError_t last_error = hipSuccess;
 static int launches = 0;
+static const void* last_kernel = nullptr;
 extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 extern "C" hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
-extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+extern "C" hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
   ++launches;
+  last_kernel = kernel;
   return last_error = hipErrorLaunchFailure;
 }
 extern "C" hipError_t hipGetLastError() {
@@ -73,6 +79,28 @@ static int aligned() {
   return bad ? 1 : 0;
 }
 
+static int forms(int d, int F, int V, int rows) {
+  const void* p = (const void*)4096;
+  FewRowsArgs in, out, head;
+  in.M_max = out.M_max = head.M_max = rows;
+  fr_seg(1, in.p[0].seg[0], p, p, d, -d, 0);
+  in.p[0].N = in.p[0].ldo = 3 * d; in.p[0].epilogue = EPI_BIAS;
+  fr_seg(1, in.p[1].seg[0], p, p, d, -d, 0);
+  in.p[1].N = F; in.p[1].epilogue = EPI_BIAS_GELU; in.p[1].packed_K = d + F; in.p[1].packed_k0 = d;
+  fr_seg(1, out.p[0].seg[0], p, p, d + F, -(d + F), 0);
+  out.p[0].N = out.p[0].ldo = d; out.p[0].epilogue = EPI_F32; out.p[0].slab = (size_t)rows * d;
+  out.p[0].ksplit = few_rows_splits(d, out.p[0].seg[0].steps);
+  fr_seg(1, head.p[0].seg[0], p, p, d, -d, 0);
+  head.p[0].N = head.p[0].ldo = V; head.p[0].epilogue = EPI_F32;
+  for (FewRowsArgs* a : {&in, &out, &head}) {
+    if (launch_few_rows(1, *a, a == &in ? 2 : 1, nullptr) != hipErrorLaunchFailure) return 1;
+    Dl_info info;
+    if (!dladdr(last_kernel, &info) || !info.dli_sname) return 1;
+    printf("%s split %d steps %d\n", info.dli_sname, a->p[0].ksplit, a->p[0].seg[0].steps);
+  }
+  return 0;
+}
+
 static int split() {
   int bad = 0;
   const int shapes[][2] = {{3072, 3072}, {3072, 12288}, {2048, 8192}, {5120, 20480}};  // out-projection and FC2
@@ -92,6 +120,7 @@ static int split() {
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
   if (argc > 1 && !strcmp(argv[1], "aligned")) return aligned();
+  if (argc > 5 && !strcmp(argv[1], "forms")) return forms(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]));
   if (argc > 1 && !strcmp(argv[1], "split")) return split();
   return 2;
 }

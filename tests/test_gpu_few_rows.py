@@ -20,15 +20,23 @@ SHAPES = {
     "hd32-2112": (2112, 66, 32, 8, 256, 300), "hd32-4096": (4096, 128, 32, 8, 128, 300),
 }
 
-
-@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
-@pytest.mark.parametrize("shape,B,lo,hi", [
+DECODES = [  # shape, sequences, shortest and longest query
     ("hd64", 1, 1, 1), ("hd80", 1, 300, 300), ("hd16", 15, 1, 40), ("hd256", 16, 5, 90), ("hd80", 17, 1, 70),
     ("hd128", 32, 3, 33), ("hd64", 33, 1, 130), ("hd80", 48, 60, 61), ("hd16", 49, 1, 9), ("hd64", 64, 1, 20),
     ("hd128", 64, 1, 8), ("hd64", 65, 1, 8), ("hd80", 128, 1, 40), ("hd256", 129, 1, 9), ("hd16", 193, 1, 70),
     ("hd80", 256, 1, 8), ("hd64", 257, 1, 8), ("hd32", 1, 1, 5), ("hd32", 64, 1, 9), ("hd96", 56, 3, 20), ("hd96", 57, 1, 9),
     ("hd32-1024", 32, 1, 9), ("hd32-1024", 33, 1, 9), ("hd32-1024", 64, 5, 40), ("hd32-2112", 3, 1, 9),
-    ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9)])
+    ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9)
+]
+# One layer of the wide models, whose products take the other forms of the kernel (64 columns per block, K loops long
+# enough to be pipelined): sequences at the edges of the row tiles
+WIDTHS = {"1b": (2048, 8, 256, 64, 8192), "2.8b": (2560, 32, 80, 20, 10240), "6.9b": (4096, 32, 128, 32, 16384)}
+WIDE = [("1b", 1), ("1b", 17), ("1b", 48), ("1b", 64), ("2.8b", 16), ("2.8b", 32), ("2.8b", 48), ("2.8b", 64), ("6.9b", 5),
+        ("6.9b", 31), ("6.9b", 37), ("6.9b", 64)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("shape,B,lo,hi", DECODES)
 def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
     import torch
     if not torch.cuda.is_available():
@@ -50,6 +58,42 @@ def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
     for rep in O.verify_rollout(O.OracleModel(w, cfg), toks.cpu().numpy(), mask, 11, 0.7, N, rows=rows):
         assert rep["deficit"] <= (0.0 if dtype == "fp32" else NEAR_TIE), rep
         assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL[dtype], rep
+
+
+@pytest.fixture(scope="module")
+def wide_model():
+    kept = {}
+
+    def get(width):
+        if width not in kept:
+            kept.clear()  # one at a time: a layer at width 4096 is 1.6 GB in float64
+            d, H, hd, r, F = WIDTHS[width]
+            cfg = ModelConfig(1, d, H, hd, r, F, vocab=515, dtype="bf16", pad_id=515)
+            w = make_weights(cfg, 78, variant="test")
+            from oracle import neox_oracle as O
+            kept[width] = (cfg, w, O.OracleModel(w, cfg))
+        return kept[width]
+    return get
+
+
+@pytest.mark.parametrize("width,B", WIDE)
+def test_decode_at_the_width_of_a_wide_model(wide_model, width, B):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    from oracle import neox_oracle as O
+    cfg, w, oracle = wide_model(width)
+    g = np.random.default_rng(B)
+    hi, N = 12, 4
+    lens = g.integers(1, hi + 1, size=B)
+    lens[-1] = hi
+    mask = (np.arange(hi)[None, :] >= (hi - lens)[:, None]).astype(np.uint8)
+    queries = np.where(mask == 1, g.integers(1, 515, size=(B, hi)), 515).astype(np.int32)
+    toks, lps, _ = (x.cpu().numpy() for x in P.Policy(cfg, w).rollout_generate(queries, mask, 12, 0.7, N))
+    for rep in O.verify_rollout(oracle, toks, mask, 12, 0.7, N, rows=sorted({0, B // 2, B - 1})):
+        assert rep["deficit"] <= NEAR_TIE, rep
+        assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL["bf16"], rep
 
 
 def test_weights_at_any_float_address(monkeypatch):
