@@ -172,7 +172,9 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
 // sampled; this pass against the other, ms): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9,
 // 192 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 80 29.6 / 31.9, 128 36.3 / 39.7, 192 50.3 / 51.2, 256 63.4 / 60.8;
 // 2.8B width (79 M) 80 41.4 / 40.9, 128 51.2 / 51.9, 192 70.1 / 66.6; 6.9B width (201 M) 80 41.5 / 37.4.  Break-even is
-// about 150 M; the line is at 2^27.
+// about 150 M; the line is at 2^27, and at 256 sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width,
+// two layers): 1 15.3 / 28.6, 17 18.7 / 30.3, 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the
+// gap (1900 tokens, 20 sampled: 160M 256 sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
 bool few_decode_size(const rlhf_model_config& c, int B) {
   if (B <= kFewRows) return true;
   const size_t per_layer = (size_t)c.d_model * (4 * (size_t)c.d_model + 2 * (size_t)c.d_ff);

@@ -4,6 +4,8 @@
 // matrix (warm: it stays in the caches) and rotating over more than 1 GB of weight copies (cold: every launch
 // streams its weights from HBM, as a decode pass does).  Like the other drivers it exists because hardware
 // counters (rocprofv3 --pmc) can be collected on a small native process where they cannot on the Python benchmark.
+// Up to 256 rows the three product launches of a few-rows decode pass follow, cold, as that pass makes them (packed A,
+// QKV and FC1 in one launch, out-projection and FC2 as one product left as slabs, LM head), and again with row-major A.
 //   usage: dec_driver [M=256] [d_model=2560] [reps=96] [max_split=0] [timed_phase=0] [pad_a=0] [pad_w=0]
 //   (pad_a / pad_w: elements added to the row strides of A / W, to see what the address-to-channel mapping costs)
 //   (timed_phase 1 times the partial products alone, as the decode loop runs them: their reductions are folded
@@ -32,6 +34,76 @@ static float h2f(uint16_t u) { _Float16 h; memcpy(&h, &u, 2); return (float)h; }
 static uint16_t f2bf(float f) { unsigned u; memcpy(&u, &f, 4); u += 0x7FFF + ((u >> 16) & 1); return (uint16_t)(u >> 16); }
 static float bf2f(uint16_t h) { unsigned u = ((unsigned)h) << 16; float f; memcpy(&f, &u, 4); return f; }
 
+// The few-rows launches.  W: R copies of wmax elements, of which QKV | FC1 | (W_o | W_fc2) of a layer, or the LM head, are
+// the first.  Returns the number of wrong outputs.
+static int few_rows_part(int M, int d, int F, int V, int reps, int R, size_t wmax, const std::vector<uint16_t>& hW,
+                         const uint16_t* dW, const std::vector<uint16_t>& hb, const uint16_t* db, float* dO, hipEvent_t e0,
+                         hipEvent_t e1) {
+  const size_t rows = (size_t)(M + 15) / 16 * 16;
+  std::vector<uint16_t> hA(rows * (d + F));  // read as [rows, d] or [rows, d + F], packed or row-major
+  for (auto& x : hA) x = f2h((rand() % 2001 - 1000) / 1000.0f);
+  uint16_t *dA, *dF;
+  CK(hipMalloc(&dA, hA.size() * 2)); CK(hipMalloc(&dF, hA.size() * 2));
+  CK(hipMemcpy(dA, hA.data(), hA.size() * 2, hipMemcpyHostToDevice));
+  auto at = [](int m, int k, int K) { return ((size_t)(m >> 4) * (K / 8) + k / 8) * 128 + (m & 15) * 8 + k % 8; };
+  const size_t o_fc1 = (size_t)3 * d * d, o_out = o_fc1 + (size_t)F * d;
+  int bad = 0;
+  for (int which = 0; which < 3; ++which)
+    for (int packed = 1; packed >= 0; --packed) {
+      const int K = which == 1 ? d + F : d, N = which == 1 ? d : (which == 2 ? V : 3 * d);
+      FewRowsArgs a;
+      a.M_max = M;
+      auto point = [&](const uint16_t* w) {
+        fr_seg(1, a.p[0].seg[0], dA, which == 1 ? w + o_out : w, K, packed ? -K : 0, 0);
+        if (which == 0) fr_seg(1, a.p[1].seg[0], dA, w + o_fc1, d, packed ? -d : 0, 0);
+      };
+      point(dW);
+      a.p[0].out = dO; a.p[0].N = a.p[0].ldo = N; a.p[0].epilogue = which ? EPI_F32 : EPI_BIAS;
+      if (which == 0) {
+        a.p[0].bias = a.p[1].bias = db;
+        a.p[1].out = dF; a.p[1].N = F; a.p[1].epilogue = EPI_BIAS_GELU; a.p[1].packed_K = d + F; a.p[1].packed_k0 = d;
+      }
+      if (which == 1) { a.p[0].slab = (size_t)M * d; a.p[0].ksplit = few_rows_splits(d, a.p[0].seg[0].steps); }
+      const int prods = which ? 1 : 2, ks = a.p[0].ksplit;
+      CK(launch_few_rows(1, a, prods, 0)); CK(hipDeviceSynchronize());
+      std::vector<uint16_t> o16((size_t)M * N), f16(hA.size());
+      std::vector<float> o32((size_t)ks * M * N);
+      if (which) CK(hipMemcpy(o32.data(), dO, o32.size() * 4, hipMemcpyDeviceToHost));
+      else {
+        CK(hipMemcpy(o16.data(), dO, o16.size() * 2, hipMemcpyDeviceToHost));
+        CK(hipMemcpy(f16.data(), dF, f16.size() * 2, hipMemcpyDeviceToHost));
+      }
+      for (int t = 0; t < 600; ++t) {
+        const bool fc1 = which == 0 && t % 2;
+        const int r = rand() % M, c = rand() % (fc1 ? F : N);
+        const uint16_t* w = hW.data() + (which == 1 ? o_out : (fc1 ? o_fc1 : 0)) + (size_t)c * K;
+        double acc = 0, got = 0;
+        for (int k = 0; k < K; ++k) acc += (double)h2f(hA[packed ? at(r, k, K) : (size_t)r * K + k]) * h2f(w[k]);
+        if (which == 0) acc += bf2f(hb[c]);
+        if (fc1) acc = 0.5 * acc * (1 + erf(acc / sqrt(2.0)));
+        if (which) for (int z = 0; z < ks; ++z) got += o32[((size_t)z * M + r) * N + c];
+        else got = h2f(fc1 ? f16[at(r, d + c, d + F)] : o16[(size_t)r * N + c]);
+        if (fabs(got - acc) > (which ? 4e-3 : 8e-3 * fmax(1.0, fabs(acc)))) {
+          printf("MISMATCH few rows, launch %d, packed %d: r=%d c=%d got %f want %f\n", which, packed, r, c, got, acc);
+          ++bad;
+          break;
+        }
+      }
+      for (int i = 0; i < 8; ++i) { point(dW + (size_t)(i % R) * wmax); CK(launch_few_rows(1, a, prods, 0)); }
+      CK(hipEventRecord(e0, 0));
+      for (int i = 0; i < reps; ++i) { point(dW + (size_t)(i % R) * wmax); CK(launch_few_rows(1, a, prods, 0)); }
+      CK(hipEventRecord(e1, 0)); CK(hipEventSynchronize(e1));
+      float ms; CK(hipEventElapsedTime(&ms, e0, e1)); ms /= reps;
+      const double wb = 2.0 * (which == 0 ? (double)(3 * d + F) * d : (double)N * K);
+      printf("few rows %-9s M=%d K=%d split %d, %s A: cold %.1f us (%.2f TB/s of weights)\n",
+             which == 0 ? "qkv+fc1" : (which == 1 ? "out+fc2" : "lm_head"), M, K, ks, packed ? "packed" : "row-major", ms * 1e3,
+             wb / ms / 1e9);
+      fflush(stdout);
+    }
+  CK(hipFree(dA)); CK(hipFree(dF));
+  return bad;
+}
+
 int main(int argc, char** argv) {
   const int M = argc > 1 ? atoi(argv[1]) : 256;
   const int d = argc > 2 ? atoi(argv[2]) : 2560, F = 4 * d, V = 50304;
@@ -53,7 +125,7 @@ int main(int argc, char** argv) {
   uint16_t *dA, *dW, *db; void *dO, *dsk;
   const size_t skb = (size_t)16 * 512 * F * 4;
   CK(hipMalloc(&dA, hA.size() * 2)); CK(hipMalloc(&dW, wmax * 2 * R)); CK(hipMalloc(&db, hb.size() * 2));
-  CK(hipMalloc(&dO, (size_t)M * std::max(F, V) * 4)); CK(hipMalloc(&dsk, skb));
+  CK(hipMalloc(&dO, (size_t)M * std::max(std::max(F, V), 8 * d) * 4)); CK(hipMalloc(&dsk, skb));
   CK(hipMemcpy(dA, hA.data(), hA.size() * 2, hipMemcpyHostToDevice));
   for (int r = 0; r < R; ++r) CK(hipMemcpy(dW + (size_t)r * wmax, hW.data(), wmax * 2, hipMemcpyHostToDevice));
   CK(hipMemcpy(db, hb.data(), hb.size() * 2, hipMemcpyHostToDevice));
@@ -102,5 +174,7 @@ int main(int argc, char** argv) {
            s.name, M, s.N, s.K, ks, ms_w * 1e3, ms_c * 1e3, wb / ms_c / 1e9, fl / ms_c / 1e9, maxerr);
     fflush(stdout);
   }
+  if (M <= 256 && (size_t)4 * d * d + (size_t)2 * d * F <= wmax)
+    bad += few_rows_part(M, d, F, V, reps, R, wmax, hW, dW, hb, db, (float*)dO, e0, e1);
   return bad ? 2 : 0;
 }

@@ -888,9 +888,9 @@ struct SamplePart {
 // vector arithmetic, not the logits' bytes: a row is cut into as many blocks as it takes to cover the chip (with one
 // block per row a single row took 72 us, a dependent chain of 49 entries per thread), and the exact noise (a
 // logarithm of a logarithm, some 150 instructions) is only formed for entries whose upper bound reaches the best
-// score the wave has seen: H(n) of n batches instead of all of them.  Both stages at a vocabulary of 50,304: 256 rows
-// 50 us (one block per row, and a kernel for the next pass's embedding: 85), what is left being the hash's 64-bit
-// products; one row 18 us (80).
+// score the wave has seen: H(n) of n batches instead of all of them.  First and second stage at a vocabulary of
+// 50,304: 256 rows 39 + 9 us, 64 rows 18 + 5, one row 7 + 7 (one block per row, and a kernel for the next pass's
+// embedding: 72 to 77 us and 5 to 8); what is left at many rows is the hash's 64-bit products.
 __global__ void __launch_bounds__(256) sampler_part_kernel(SampleArgs a, int per) {
   __shared__ SamplePart sp[4];
   const int b = blockIdx.y, lo = blockIdx.x * per, hi = min(lo + per, a.V);

@@ -1,23 +1,24 @@
-// Products of few rows, C[M,N] = A[M,K] * W[N,K]^T for M up to 64 (a decode pass of a small batch; of up to 256
-// sequences where the model is narrow, in tiles of 64 rows), and all products of the fp32 check mode.
+// Products of few rows, C[M,N] = A[M,K] * W[N,K]^T: the decode passes of run_decode_few (up to 64 sequences; up to 256
+// where the model is narrow, in tiles of 64 rows), other products of up to 64 rows that come without split-K scratch, and
+// products of any number of rows in the fp32 check mode (K a multiple of 32, aligned operands).
 //
 // Such a product is its weights' bytes and nothing else: at M = 64 the matrix cores need a tenth of the time the
 // weights take to arrive.  What the kernel is built around is bytes in flight and few launches:
-//   * A block of eight waves owns 16 or 32 output columns for all K of its split; the waves divide K, each holding
-//     the weights of its next PF steps (128 bytes of every weight row per step) in registers.  At K = 2560 a wave has
-//     five steps, so nearly the whole weight tile of a block is requested before the first matrix instruction waits.
+//   * A block of four waves (eight in one form) owns 32 or 64 output columns for all K of its split; the waves divide K,
+//     each holding the weights of its next PF steps (128 bytes of every weight row per step; PF is two to four) in
+//     registers.  At K = 2560 a wave has ten steps, five in the form of eight waves, four of them in flight.
 //   * Both operands go global -> registers: 16 weight rows x 128 bytes per step, lane (l16, q) taking the 32 bytes at
-//     32q of row l16.  No LDS and no barrier until the waves' partial tiles are added at the end.  Sixteen consecutive
-//     lanes on sixteen rows cost the vector memory path four times what a contiguous kilobyte does (measured from L2:
-//     9.7 against 33 TB/s chip-wide).  The weights, which HBM delivers at 6, can afford that; A, read once per column
-//     block, cannot: its producers in a decode pass write it packed (packed_index), and a wave's load is contiguous.
+//     32q of row l16.  No LDS and no barrier until the waves' partial tiles are added at the end.  Such a load touches
+//     sixteen rows.  The weights, which HBM delivers, can afford that; A, read from L2 once per column block, cannot: its
+//     producers in a decode pass write it packed (packed_index), and a wave's load is contiguous.  QKV + FC1 at width
+//     2560 with packed / row-major A: 8 rows 24 / 26 us, 30 rows 30 / 39, 64 rows 40 / 57.
 //   * The sum over K stays in the block (bias, GELU and the fp16 rounding are its epilogue) unless a product has too
 //     few column tiles to cover the chip: then K is cut over blocks into fp32 slabs that the consumer adds in order.
 //   * Two products that are ready together (QKV and FC1 of a parallel-residual layer) share one launch.
-// Width 2560, cold weights: QKV + FC1 24 us for up to 16 rows (3.9 TB/s), 29 for 30, 38 for 64; LM head 48 us (5.3 TB/s)
-// for one row, 82 for 64.  The weight-streaming kernel of gemm_skinny.hip, which this one replaces below 65 rows, took
-// 17.6 us for a QKV product alone and left slabs to add; the plain fp32 tile kernel took 50 us for each product of the
-// 70M shape at two rows (now 6).
+// Width 2560, cold weights (dec_driver): QKV + FC1 24 us for one row (3.8 TB/s), 26 for 16, 30 for 30, 40 for 64;
+// out-projection + FC2 15 to 25; LM head 49 us for one row (5.2 TB/s), 85 for 64.  The weight-streaming kernel of
+// gemm_skinny.hip took 17.6 us for a QKV product alone and left slabs to add; the plain fp32 tile kernel 50 us for each
+// product of the 70M shape at two rows (now 4 to 9).
 #include <algorithm>
 
 #include "common.h"
@@ -25,10 +26,8 @@
 namespace rlhf {
 
 typedef __attribute__((ext_vector_type(8))) _Float16 fr_f16x8_t;
-typedef __attribute__((ext_vector_type(4))) _Float16 fr_f16x4_t;
 typedef __attribute__((ext_vector_type(4))) float fr_f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t fr_u32x4_t;
-
 
 template <typename T>
 struct FrTypes;
@@ -218,7 +217,7 @@ bool few_rows_takes(int dtype, const GemmArgs& a) {
 }
 
 // Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  Per row count one with 64 columns
-// and one with 32 (two for up to 16 rows: eight waves where K is long enough for them).
+// and one with 32 (two for up to 16 rows: eight waves from 32 steps per block on).
 #define RLHF_FR_FORMS(X)                                                                                          \
   X(0, 4, 1, 4, 3, 3) X(1, 8, 1, 2, 4, 4) X(2, 4, 1, 2, 4, 4) X(3, 4, 2, 4, 2, 3) X(4, 4, 2, 2, 3, 3)            \
   X(5, 4, 3, 4, 2, 2) X(6, 4, 3, 2, 3, 2) X(7, 4, 4, 4, 2, 2) X(8, 4, 4, 2, 3, 2)
@@ -233,9 +232,20 @@ static int fr_form(int M, bool wide, int steps) {
 
 // How a product is cut: 64 or 32 columns per block, and (max_split > 1) K over up to that many blocks.  What decides
 // is how evenly the blocks cover 256 CUs; 64 columns read A half as often and win until they cover the chip 10 % less
-// evenly, and always where K is long (rows of 8 KB and more: 46 against 62 us for QKV and FC1 at width 4096).
-// Measured, M = 8: QKV + FC1 at width 2560 28 us with 64 columns, 24 with 32; width 2048 14 and 16; width 768 6.4 and
-// 5.5; out-projection + FC2 at 2560 16.8 (160 blocks) and 15.6 (640 blocks).
+// evenly, and whatever they cover where blocks of 48 and more steps (6 KB of every weight row) are at least 224.
+// Measured with either column count forced (dec_driver, cold; us with 64 / 32 columns; * the one taken):
+//   QKV + FC1       width  768:  8 rows  6.3 /  5.4*   64 rows 10.6 /  7.2*
+//                         2048:  8 rows 13.8*/ 14.9    64 rows 20.6*/ 22.0
+//                         2560:  8 rows 28.4 / 24.1*   64 rows 40.6 / 39.5*
+//                         3072:  8 rows 34.0*/ 29.8    64 rows 46.7*/ 45.8
+//                         4096:  8 rows 46.4*/ 60.5    64 rows 62.3*/ 73.1
+//   out-proj + FC2        2560:  8 rows 16.8 / 15.2*   64 rows 24.7 / 24.5*
+//                         3072:  8 rows 20.3 / 23.5*   64 rows 29.6 / 30.3*
+//                         4096:  8 rows 31.0*/ 42.6    64 rows 41.5*/ 49.7
+//   LM head               2560:  8 rows 56.3 / 51.6*   64 rows 78.2 / 84.5*
+//                         3072:  8 rows 66.9*/ 60.4    64 rows 88.9*/ 97.4
+// (Width 3072, at 48 steps, is where the second condition changes sides: it costs 12 % at few rows and gains as much in
+// the LM head at 64.)
 struct FrCut {
   bool wide;
   int ks;
