@@ -60,6 +60,24 @@ def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
         assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL[dtype], rep
 
 
+@pytest.mark.parametrize("shape,B,few", [
+    ("hd64", 1, True), ("hd64", 256, True), ("hd64", 257, False), ("hd32", 4, False),  # a size, a head size without a kernel
+    ("d1536", 64, True), ("d1536", 192, True), ("d1536", 193, False),  # weights of a layer times row tiles up to 2^27
+    ("d4160", 1, False)])  # a width the decode LayerNorm does not take
+def test_which_decode_pass(shape, B, few):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    more = {"d1536": (1536, 24, 64, 16, 11456, 64), "d4160": (4160, 65, 64, 16, 64, 64)}
+    d, H, hd, r, F, V = SHAPES.get(shape) or more[shape]
+    cfg = ModelConfig(1, d, H, hd, r, F, vocab=V, dtype="bf16", pad_id=V)
+    p = P.Policy(cfg, make_weights(cfg, 77, variant="test"))
+    p.profile_enable()
+    p.rollout_generate(np.ones((B, 2), np.int32), np.ones((B, 2), np.uint8), 11, 0.7, 2)
+    assert ("gemm_decode_qkv_fc1" in p.profile_read()) == few
+
+
 @pytest.fixture(scope="module")
 def wide_model():
     kept = {}
