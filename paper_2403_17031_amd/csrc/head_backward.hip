@@ -440,7 +440,7 @@ __device__ __forceinline__ float phi_cdf_fast(float x) {
   const float s = fminf(x * x, 64.0f);
   float p = fmaf(1.01426504e-3f, s, -1.06775735e-1f);
   p = fmaf(p, s, -2.30112140f);
-  return __frcp_rn(1.0f + __builtin_amdgcn_exp2f(x * p));
+  return recip_rn_sigmoid(x * p);
 }
 __global__ void __launch_bounds__(256)
     gelu_f16x8_kernel(const half_t* __restrict__ u, half_t* __restrict__ f, size_t n8) {
