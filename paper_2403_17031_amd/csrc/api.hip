@@ -1195,12 +1195,21 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
   const void* u = sh.kept_u ? sh.kept_u : ws.u;
   if (!sh.kept_u)
     LAUNCH("gemm_mlp_fwd", launch_gemm(dt, gemm(ws.m, h->w_fc1[l], h->b_fc1[l], ws.u, T, F, d, EPI_BIAS), s));
-  LAUNCH("gelu", launch_gelu(dt, u, ws.f, (size_t)T * F, s));
-  // ---- FC2: db2 = sum_t G, dW2 = G^T f, df = G W2
+  // ---- FC2: db2 = sum_t G, df = G W2, dW2 = G^T f
   const void* go = sh.go16 ? sh.go16 : ws.go;
   if (!sh.go16) {
     LAUNCH("colsum", launch_colsum(0, d_out, T, d, ws.part, ws.splits, d_b_fc2, s));
     LAUNCH("convert", launch_convert_from_f32(dt, d_out, ws.go, (size_t)T * d, s));
+  }
+  LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, h->w_fc2[l], ld_w2, ws.w2T, (size_t)d, d, F, d, s));
+  LAUNCH("gemm_mlp_dx", launch_gemm(dt, gemm(go, ws.w2T, nullptr, ws.df, T, F, d, EPI_BIAS), s));
+  // ---- GELU: f = gelu(u), du = df * gelu'(u) (in place), db1 = sum_t du
+  if (gelu_backward_colsum_supported(dt, u, ws.df, ws.f, F)) {
+    LAUNCH("gelu", launch_gelu_backward_colsum(u, ws.df, ws.f, T, F, ws.part, ws.splits, d_b_fc1, s));
+  } else {
+    LAUNCH("gelu", launch_gelu(dt, u, ws.f, (size_t)T * F, s));
+    LAUNCH("gelu", launch_gelu_backward(dt, u, ws.df, (size_t)T * F, s));
+    LAUNCH("colsum", launch_colsum(dt, ws.df, T, F, ws.part, ws.splits, d_b_fc1, s));
   }
   auto dw_gemm = [&](const void* A, const void* W, void* out, int M, int N) {  // K = the rows: sliced
     GemmArgs g = gemm(A, W, nullptr, out, M, N, Tp, EPI_F32);
@@ -1231,15 +1240,7 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
     LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, ws.f, (size_t)F, ws.fT, (size_t)Tp, T, F, Tp, s));
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_gemm(ws.goT, ws.fT, d_w_fc2, d, F), s));
   }
-  LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, h->w_fc2[l], ld_w2, ws.w2T, (size_t)d, d, F, d, s));
-  LAUNCH("gemm_mlp_dx", launch_gemm(dt, gemm(go, ws.w2T, nullptr, ws.df, T, F, d, EPI_BIAS), s));
-  // ---- GELU, then FC1: du = df * gelu'(u) (in place), db1 = sum_t du, dW1 = du^T m, dm = du W1
-  if (gelu_backward_colsum_supported(dt, u, ws.df, F)) {
-    LAUNCH("gelu", launch_gelu_backward_colsum(u, ws.df, T, F, ws.part, ws.splits, d_b_fc1, s));
-  } else {
-    LAUNCH("gelu", launch_gelu_backward(dt, u, ws.df, (size_t)T * F, s));
-    LAUNCH("colsum", launch_colsum(dt, ws.df, T, F, ws.part, ws.splits, d_b_fc1, s));
-  }
+  // ---- FC1: dW1 = du^T m, dm = du W1
   if (kmaj) {
     LAUNCH("mlp_bwd_zero", zero_tail(ws.df, F));
     LAUNCH("mlp_bwd_zero", zero_tail(ws.m, d));

@@ -337,38 +337,61 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-__global__ void __launch_bounds__(256)
+// Sums part [waves][2][d] over the waves (a multiple of 4): four interleaved chains per column, added at the end -- a fixed
+// order.  A block owns 32 columns (one 128-byte line of a row): its 1024 threads bring 256 rows at a time through LDS, two
+// chunks ahead of the 128 threads that add up one chain of one column each.  With one thread per column, six blocks
+// waited for 512 loads one after the other: 160 us at width 768 (2048 waves), now 9.
+constexpr int kSumChunk = 256;
+__global__ void __launch_bounds__(1024)
     ln_backward_rows_final_kernel(const float* __restrict__ part, int waves, int d, float* __restrict__ d_g,
                                   float* __restrict__ d_b) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= 2 * d) return;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;  // four interleaved chains, added at the end: a fixed order
-  int w = 0;
-  for (; w + 4 <= waves; w += 4) {
-    s0 += part[(size_t)w * 2 * d + c];
-    s1 += part[(size_t)(w + 1) * 2 * d + c];
-    s2 += part[(size_t)(w + 2) * 2 * d + c];
-    s3 += part[(size_t)(w + 3) * 2 * d + c];
+  __shared__ float buf[2][kSumChunk][32];
+  __shared__ float chain[4][32];
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int c = blockIdx.x * 32 + tx, cl = min(c, 2 * d - 1);
+  float v[kSumChunk / 32], s = 0.f;
+  auto fetch = [&](int w0) {
+#pragma unroll
+    for (int i = 0; i < kSumChunk / 32; ++i) {
+      const int w = w0 + ty + 32 * i;
+      v[i] = w < waves ? part[(size_t)w * 2 * d + cl] : 0.f;
+    }
+  };
+  fetch(0);
+  for (int w0 = 0, k = 0; w0 < waves; w0 += kSumChunk, k ^= 1) {
+#pragma unroll
+    for (int i = 0; i < kSumChunk / 32; ++i) buf[k][ty + 32 * i][tx] = v[i];
+    if (w0 + kSumChunk < waves) fetch(w0 + kSumChunk);
+    __syncthreads();
+    if (ty < 4) {
+      const int n = min(kSumChunk, waves - w0);
+#pragma unroll 8
+      for (int w = ty; w < n; w += 4) s += buf[k][w][tx];
+    }
   }
-  for (; w < waves; ++w) s0 += part[(size_t)w * 2 * d + c];
-  const float r = (s0 + s1) + (s2 + s3);
-  if (c < d) d_g[c] = r;
-  else d_b[c - d] = r;
+  if (ty < 4) chain[ty][tx] = s;
+  __syncthreads();
+  if (ty == 0 && c < 2 * d) {
+    const float r = (chain[0][tx] + chain[1][tx]) + (chain[2][tx] + chain[3][tx]);
+    if (c < d) d_g[c] = r;
+    else d_b[c - d] = r;
+  }
 }
 
-// Column sums over a range of rows: block (column block, row split) leaves, for each of its 256
+// Column sums over a range of rows: block (column block, row split) leaves, for each of its 64
 // columns, sum dy * xh, sum dy and sum gv * h over its rows (h = the final LayerNorm's output in the
 // activation type A, as the forward pass produces it).  part: [splits][3][d].
 template <typename W, typename A>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64)
     head_colsum_kernel(const float* __restrict__ x, const float* __restrict__ dhl, const float* __restrict__ gv,
                        float scale, const W* __restrict__ value_w, const W* __restrict__ g, const W* __restrict__ b,
                        const float* __restrict__ stats, int T, int d, int rows_per_split, float* __restrict__ part) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+  const int c = blockIdx.x * 64 + threadIdx.x;
   const int t0 = blockIdx.y * rows_per_split, t1 = min(T, t0 + rows_per_split);
   if (c >= d) return;
   const float gc = to_f32(g[c]), bc = to_f32(b[c]), wv = value_w ? to_f32(value_w[c]) : 0.f;
   float sg = 0.f, sb = 0.f, sw = 0.f;
+#pragma unroll 8
   for (int t = t0; t < t1; ++t) {
     const float gvt = value_w ? gv[t] * scale : 0.f;
     const float dy = dhl[(size_t)t * d + c] + gvt * wv;
@@ -473,41 +496,65 @@ __global__ void __launch_bounds__(256)
     ((f16x8_t*)df)[i] = g;
   }
 }
-// df *= gelu'(u) on a [R, C] fp16 matrix and, in the same pass, the column sums of the result (of the rounded values,
-// as a separate pass over the stored matrix would see them): part [splits][C], rows added in increasing order.
+// The column-sum passes below: a block owns 64 columns of a row split.  Its 256 threads move a chunk of rows with 16-byte
+// accesses, four rows of each operand in flight per thread, and leave the values to be summed in LDS; one wave then adds
+// them, a lane per column, in increasing row order, while the others are at the next chunk (two buffers, one barrier per
+// chunk).  One row of part per split.
+// (A thread that walks its columns alone, load after load, left 87 to 174 blocks of one load per lane: 258 us for the GELU
+// pass over 22 k x 3072, 54 and 50 us for the two others at width 768.)
+//
+template <typename T>
+__device__ __forceinline__ float add_rows(float s, const T (*buf)[64], int n) {  // first wave: s + column's n rows, in order
+#pragma unroll 16
+  for (int r = 0; r < n; ++r) s += to_f32(buf[r][threadIdx.x]);
+  return s;
+}
+// df *= gelu'(u) on a [R, C] fp16 matrix, the column sums of the result (of the rounded values, as a separate pass over
+// the stored matrix would see them) and f = gelu(u), which the weight gradient reads.  Bound by its four passes over
+// [R, C] fp16.
 __global__ void __launch_bounds__(256)
-    gelu_backward_colsum_kernel(const half_t* __restrict__ u, half_t* __restrict__ df, int R, int C, int rows_per_split,
-                                float* __restrict__ part) {
-  const int c0 = (blockIdx.x * 256 + threadIdx.x) * 8;
-  if (c0 >= C) return;
+    gelu_backward_colsum_kernel(const half_t* __restrict__ u, half_t* __restrict__ df, half_t* __restrict__ f, int R,
+                                int C, int rows_per_split, float* __restrict__ part) {
+  constexpr int RC = 64;
+  __shared__ half_t buf[2][RC][64];
+  const int tq = threadIdx.x & 7, tr = threadIdx.x >> 3;
+  const int c0 = blockIdx.x * 64 + 8 * tq;
+  const bool ok = c0 < C;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
-  float s[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) s[i] = 0.f;
-  for (int r = r0; r < r1; r += 2) {
+  float s = 0.f;
+  for (int rc = r0, k = 0; rc < r1; rc += RC, k ^= 1) {
     f16x8_t v[2], g[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const size_t o = (size_t)min(r + k, r1 - 1) * C + c0;
-      v[k] = *(const f16x8_t*)(u + o);
-      g[k] = *(const f16x8_t*)(df + o);
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      if (r + k < r1) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = (float)v[k][e];
-          const float phi = 0.3989422804014327f * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);
-          g[k][e] = from_f32<half_t>((float)g[k][e] * (phi_cdf_fast(x) + x * phi));
-          s[e] += (float)g[k][e];
-        }
-        *(f16x8_t*)(df + (size_t)(r + k) * C + c0) = g[k];
+    for (int i = 0; i < 2; ++i) {
+      if (ok && rc + tr + 32 * i < r1) {
+        const size_t o = (size_t)(rc + tr + 32 * i) * C + c0;
+        v[i] = *(const f16x8_t*)(u + o);
+        g[i] = *(const f16x8_t*)(df + o);
       }
     }
-  }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) part[(size_t)blockIdx.y * C + c0 + i] = s[i];
+    for (int i = 0; i < 2; ++i) {
+      if (ok && rc + tr + 32 * i < r1) {
+        const size_t o = (size_t)(rc + tr + 32 * i) * C + c0;
+        f16x8_t fo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = (float)v[i][e];
+          const float Phi = phi_cdf_fast(x);
+          const float phi = 0.3989422804014327f * __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x);
+          fo[e] = from_f32<half_t>(x * Phi);
+          g[i][e] = from_f32<half_t>((float)g[i][e] * (Phi + x * phi));
+        }
+        *(f16x8_t*)(f + o) = fo;
+        *(f16x8_t*)(df + o) = g[i];
+        *(f16x8_t*)&buf[k][tr + 32 * i][8 * tq] = g[i];
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) s = add_rows(s, buf[k], min(RC, r1 - rc));
+  }
+  const int c = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && c < C) part[(size_t)blockIdx.y * C + c] = s;
 }
 template <typename T>
 __global__ void __launch_bounds__(256) convert_kernel(const float* __restrict__ src, T* __restrict__ dst, size_t n) {
@@ -527,64 +574,65 @@ __global__ void __launch_bounds__(256)
   for (int r = r0; r < r1; ++r) s += to_f32(a[(size_t)r * C + c]);
   part[(size_t)blockIdx.y * C + c] = s;
 }
-// The same with 16-byte accesses: a thread owns 16 bytes' worth of neighbouring columns (4 floats or 8 halfs) and
-// keeps four rows' loads in flight; rows are still added in increasing order.
+// The same with 16-byte accesses (C a multiple of 4 floats or 8 halfs).
 template <typename T>
 __global__ void __launch_bounds__(256)
     colsum_part_vec_kernel(const T* __restrict__ a, int R, int C, int rows_per_split, float* __restrict__ part) {
-  constexpr int V = 16 / sizeof(T);
-  const int c0 = (blockIdx.x * 256 + threadIdx.x) * V;
-  if (c0 >= C) return;
+  constexpr int V = 16 / sizeof(T), LPR = 64 / V, RPP = 256 / LPR, RC = 4 * RPP;  // lanes per row, rows per pass and chunk
+  __shared__ __attribute__((aligned(16))) T buf[2][RC][64];
+  const int tq = threadIdx.x % LPR, tr = threadIdx.x / LPR;
+  const int c0 = blockIdx.x * 64 + V * tq;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
-  float s[V];
-#pragma unroll
-  for (int i = 0; i < V; ++i) s[i] = 0.f;
-  const u32x4_t zero = {0u, 0u, 0u, 0u};
-  for (int r = r0; r < r1; r += 4) {
+  float s = 0.f;
+  for (int rc = r0, k = 0; rc < r1; rc += RC, k ^= 1) {
     u32x4_t v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = r + k < r1 ? *(const u32x4_t*)(a + (size_t)(r + k) * C + c0) : zero;
+    for (int i = 0; i < 4; ++i)
+      if (c0 < C && rc + tr + RPP * i < r1) v[i] = *(const u32x4_t*)(a + (size_t)(rc + tr + RPP * i) * C + c0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const T* e = (const T*)&v[k];
-#pragma unroll
-      for (int i = 0; i < V; ++i) s[i] += to_f32(e[i]);
-    }
+    for (int i = 0; i < 4; ++i) *(u32x4_t*)&buf[k][tr + RPP * i][V * tq] = v[i];
+    __syncthreads();
+    if (threadIdx.x < 64) s = add_rows(s, buf[k], min(RC, r1 - rc));
   }
-#pragma unroll
-  for (int i = 0; i < V; ++i) part[(size_t)blockIdx.y * C + c0 + i] = s[i];
+  const int c = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && c < C) part[(size_t)blockIdx.y * C + c] = s;
 }
 // Column sums of a float [R, C] matrix as above and, in the same pass, its fp16 copy.
 __global__ void __launch_bounds__(256)
     convert_colsum_part_kernel(const float* __restrict__ a, int R, int C, int rows_per_split, float* __restrict__ part,
                                half_t* __restrict__ out) {
-  const int c0 = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (c0 >= C) return;
+  constexpr int RC = 64;
+  __shared__ __attribute__((aligned(16))) float buf[2][RC][64];
+  const int tq = threadIdx.x & 15, tr = threadIdx.x >> 4;
+  const int c0 = blockIdx.x * 64 + 4 * tq;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
-  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
-  for (int r = r0; r < r1; r += 4) {
+  float s = 0.f;
+  for (int rc = r0, k = 0; rc < r1; rc += RC, k ^= 1) {
     f32x4_t v[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      v[k] = r + k < r1 ? *(const f32x4_t*)(a + (size_t)(r + k) * C + c0) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4; ++i)
+      if (c0 < C && rc + tr + 16 * i < r1) v[i] = *(const f32x4_t*)(a + (size_t)(rc + tr + 16 * i) * C + c0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      s += v[k];
-      if (r + k < r1) {
-        const f16x4_t hv = {from_f32<half_t>(v[k][0]), from_f32<half_t>(v[k][1]), from_f32<half_t>(v[k][2]),
-                            from_f32<half_t>(v[k][3])};
-        *(f16x4_t*)(out + (size_t)(r + k) * C + c0) = hv;
+    for (int i = 0; i < 4; ++i) {
+      if (c0 < C && rc + tr + 16 * i < r1) {
+        const f16x4_t hv = {from_f32<half_t>(v[i][0]), from_f32<half_t>(v[i][1]), from_f32<half_t>(v[i][2]),
+                            from_f32<half_t>(v[i][3])};
+        *(f16x4_t*)(out + (size_t)(rc + tr + 16 * i) * C + c0) = hv;
+        *(f32x4_t*)&buf[k][tr + 16 * i][4 * tq] = v[i];
       }
     }
+    __syncthreads();
+    if (threadIdx.x < 64) s = add_rows(s, buf[k], min(RC, r1 - rc));
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) part[(size_t)blockIdx.y * C + c0 + i] = s[i];
+  const int c = blockIdx.x * 64 + threadIdx.x;
+  if (threadIdx.x < 64 && c < C) part[(size_t)blockIdx.y * C + c] = s;
 }
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64)
     colsum_final_kernel(const float* __restrict__ part, int splits, int C, float* __restrict__ out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+  const int c = blockIdx.x * 64 + threadIdx.x;
   if (c >= C) return;
   float s = 0.f;
+#pragma unroll 32
   for (int z = 0; z < splits; ++z) s += part[(size_t)z * C + c];
   out[c] = s;
 }
@@ -695,16 +743,16 @@ hipError_t launch_gelu_backward(int dtype, const void* u, void* df, size_t n, hi
     hipLaunchKernelGGL(gelu_backward_kernel<half_t>, dim3(blocks), dim3(256), 0, s, (const half_t*)u, (half_t*)df, n);
   return hipGetLastError();
 }
-bool gelu_backward_colsum_supported(int dtype, const void* u, const void* df, int C) {
-  return dtype == 1 && (C & 7) == 0 && (((uintptr_t)u | (uintptr_t)df) & 15) == 0;
+bool gelu_backward_colsum_supported(int dtype, const void* u, const void* df, const void* f, int C) {
+  return dtype == 1 && (C & 7) == 0 && (((uintptr_t)u | (uintptr_t)df | (uintptr_t)f) & 15) == 0;
 }
-hipError_t launch_gelu_backward_colsum(const void* u, void* df, int R, int C, float* part, int splits, float* sums,
-                                       hipStream_t s) {
+hipError_t launch_gelu_backward_colsum(const void* u, void* df, void* f, int R, int C, float* part, int splits,
+                                       float* sums, hipStream_t s) {
   if (R <= 0 || C <= 0) return hipSuccess;
   const int rps = (R + splits - 1) / splits;
-  hipLaunchKernelGGL(gelu_backward_colsum_kernel, dim3((C / 8 + 255) / 256, splits), dim3(256), 0, s, (const half_t*)u,
-                     (half_t*)df, R, C, rps, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 255) / 256), dim3(256), 0, s, part, splits, C, sums);
+  hipLaunchKernelGGL(gelu_backward_colsum_kernel, dim3((C + 63) / 64, splits), dim3(256), 0, s, (const half_t*)u,
+                     (half_t*)df, (half_t*)f, R, C, rps, part);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 63) / 64), dim3(64), 0, s, part, splits, C, sums);
   return hipGetLastError();
 }
 hipError_t launch_convert_from_f32(int dtype, const float* src, void* dst, size_t n, hipStream_t s) {
@@ -719,9 +767,9 @@ hipError_t launch_convert_colsum(const float* a, int R, int C, float* part, int 
   if (C <= 0 || R <= 0) return hipSuccess;
   if ((C & 3) != 0 || (((uintptr_t)a | (uintptr_t)out_f16) & 15) != 0) return hipErrorInvalidValue;
   const int rps = (R + splits - 1) / splits;
-  hipLaunchKernelGGL(convert_colsum_part_kernel, dim3((C / 4 + 255) / 256, splits), dim3(256), 0, s, a, R, C, rps, part,
+  hipLaunchKernelGGL(convert_colsum_part_kernel, dim3((C + 63) / 64, splits), dim3(256), 0, s, a, R, C, rps, part,
                      (half_t*)out_f16);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 255) / 256), dim3(256), 0, s, part, splits, C, sums);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 63) / 64), dim3(64), 0, s, part, splits, C, sums);
   return hipGetLastError();
 }
 // elem: 0 = float matrix, 1 = fp16 matrix.  part: [splits][C] floats of scratch.
@@ -731,7 +779,7 @@ hipError_t launch_colsum(int elem, const void* a, int R, int C, float* part, int
   dim3 grid((C + 255) / 256, splits);
   const int V = elem == 0 ? 4 : 8;
   if (C % V == 0 && ((uintptr_t)a & 15) == 0) {
-    dim3 vgrid((C / V + 255) / 256, splits);
+    dim3 vgrid((C + 63) / 64, splits);
     if (elem == 0)
       hipLaunchKernelGGL(colsum_part_vec_kernel<float>, vgrid, dim3(256), 0, s, (const float*)a, R, C, rps, part);
     else
@@ -739,7 +787,7 @@ hipError_t launch_colsum(int elem, const void* a, int R, int C, float* part, int
   } else if (elem == 0)
     hipLaunchKernelGGL(colsum_part_kernel<float>, grid, dim3(256), 0, s, (const float*)a, R, C, rps, part);
   else hipLaunchKernelGGL(colsum_part_kernel<half_t>, grid, dim3(256), 0, s, (const half_t*)a, R, C, rps, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 255) / 256), dim3(256), 0, s, part, splits, C, out);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((C + 63) / 64), dim3(64), 0, s, part, splits, C, out);
   return hipGetLastError();
 }
 
@@ -808,7 +856,7 @@ hipError_t launch_ln_backward_rows(const float* x, const float* dy, const void* 
     default: return hipErrorInvalidValue;
   }
 #undef RLHF_LNB
-  hipLaunchKernelGGL(ln_backward_rows_final_kernel, dim3((2 * d + 255) / 256), dim3(256), 0, s, part, waves, d, d_g, d_b);
+  hipLaunchKernelGGL(ln_backward_rows_final_kernel, dim3((2 * d + 31) / 32), dim3(1024), 0, s, part, waves, d, d_g, d_b);
   return hipGetLastError();
 }
 
@@ -818,16 +866,16 @@ hipError_t launch_head_ln_backward(int dtype, const float* x, const float* dhl, 
                                    float* d_wv, float* d_bv, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   const int rps = (T + splits - 1) / splits;
-  dim3 cgrid((d + 255) / 256, splits);
+  dim3 cgrid((d + 63) / 64, splits);
   if (dtype == 0) {
     hipLaunchKernelGGL(ln_backward_kernel<float>, dim3(T), dim3(256), 0, s, x, dhl, gv, scale, (const float*)value_w,
                        (const float*)g, d, eps, dx, stats);
-    hipLaunchKernelGGL((head_colsum_kernel<float, float>), cgrid, dim3(256), 0, s, x, dhl, gv, scale,
+    hipLaunchKernelGGL((head_colsum_kernel<float, float>), cgrid, dim3(64), 0, s, x, dhl, gv, scale,
                        (const float*)value_w, (const float*)g, (const float*)b, stats, T, d, rps, part);
   } else {
     hipLaunchKernelGGL(ln_backward_kernel<bf16_t>, dim3(T), dim3(256), 0, s, x, dhl, gv, scale,
                        (const bf16_t*)value_w, (const bf16_t*)g, d, eps, dx, stats);
-    hipLaunchKernelGGL((head_colsum_kernel<bf16_t, half_t>), cgrid, dim3(256), 0, s, x, dhl, gv, scale,
+    hipLaunchKernelGGL((head_colsum_kernel<bf16_t, half_t>), cgrid, dim3(64), 0, s, x, dhl, gv, scale,
                        (const bf16_t*)value_w, (const bf16_t*)g, (const bf16_t*)b, stats, T, d, rps, part);
   }
   hipLaunchKernelGGL(head_colsum_final_kernel, dim3((d + 255) / 256), dim3(256), 0, s, part, splits, d, gv, scale, T,
