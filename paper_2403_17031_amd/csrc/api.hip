@@ -1896,7 +1896,9 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
     if (!share) LAUNCH("add3", launch_add3(dx, dx_a, dx_m, dx_n, n, s));
     std::swap(dx, dx_n);
   }
-  LAUNCH("embed_backward", launch_embed_backward(packed_tokens, dx, T, c.d_model, c.vocab, g->embed_in, s));
+  // the branches' workspace is free again; the output heads' share of it alone holds 128 rows of the vocabulary and more
+  if (sub_bytes < embed_backward_scratch_bytes(c.vocab)) return fail(RLHF_ENOMEM, "workspace too small for the embedding gradient");
+  LAUNCH("embed_backward", launch_embed_backward(packed_tokens, dx, T, c.d_model, c.vocab, sub, g->embed_in, s));
   return RLHF_OK;
 }
 

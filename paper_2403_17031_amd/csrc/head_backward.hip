@@ -638,39 +638,75 @@ __global__ void __launch_bounds__(64)
 }
 
 // Gradient of the input embedding: out[v][:] = sum over packed rows t with tok[t] == v of dx[t][:], rows added
-// in increasing t (a fixed order: no atomics).  One block per vocabulary entry scans the token list 256 rows at a
-// time; a thread keeps up to 32 columns (d <= 8192) in registers.
+// in increasing t (a fixed order).  Two passes.  The first leaves, for every vocabulary entry, how often it occurs and its
+// first kBucket rows to arrive (in any order; integer counts only).  The second runs one block per entry: it sorts the
+// bucket, or, for an entry that occurs more often, collects the rows in order by scanning the token list.
+// Bound by writing out ([V, d] floats, mostly zeros).  One pass in which every block scanned all tokens spent its time on
+// that scan: 1335 us for 22 k tokens, 50,304 entries and width 768, where the writes take 26.
+constexpr int kBucket = 16;
+__global__ void __launch_bounds__(256)
+    embed_bucket_kernel(const int* __restrict__ tok, int T, int V, int* __restrict__ count, int* __restrict__ bucket) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= T) return;
+  const int v = tok[t];
+  if (v < 0 || v >= V) return;
+  const int slot = atomicAdd(count + v, 1);
+  if (slot < kBucket) bucket[(size_t)v * kBucket + slot] = t;
+}
+template <int E>  // floats per access: 4, or 1 where d is no multiple of 4
 __global__ void __launch_bounds__(256)
     embed_backward_kernel(const int* __restrict__ tok, const float* __restrict__ dx, int T, int d,
-                          float* __restrict__ out) {
+                          const int* __restrict__ count, const int* __restrict__ bucket, float* __restrict__ out) {
+  typedef __attribute__((ext_vector_type(E))) float vec_t;
+  constexpr int NC = 8192 / 256 / E;  // column groups per thread (d <= 8192)
   __shared__ int hits[256];
+  __shared__ int wave_n[4];
   const int v = blockIdx.x, tid = threadIdx.x;
-  float acc[32];
+  const int n = count[v], nc = d / E;
+  vec_t* o = (vec_t*)(out + (size_t)v * d);
+  if (n <= kBucket) {
+    if (tid < n) {
+      const int t = bucket[(size_t)v * kBucket + tid];
+      int rank = 0;
+      for (int i = 0; i < n; ++i) rank += bucket[(size_t)v * kBucket + i] < t;
+      hits[rank] = t;
+    }
+    __syncthreads();
+    for (int c = tid; c < nc; c += 256) {
+      vec_t a = 0.f;
+      for (int i = 0; i < n; ++i) a += ((const vec_t*)(dx + (size_t)hits[i] * d))[c];
+      o[c] = a;
+    }
+    return;
+  }
+  vec_t acc[NC];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) acc[i] = 0.f;
+  for (int u = 0; u < NC; ++u) acc[u] = 0.f;
   for (int t0 = 0; t0 < T; t0 += 256) {
     const int t = t0 + tid;
-    const int match = (t < T && tok[t] == v) ? 1 : 0;
-    if (__syncthreads_or(match)) {
-      hits[tid] = match;
-      __syncthreads();
-      for (int i = 0; i < 256; ++i) {
-        if (!hits[i]) continue;
-        const float* row = dx + (size_t)(t0 + i) * d;
+    const bool match = t < T && tok[t] == v;
+    const uint64_t m = __ballot(match);
+    if ((tid & 63) == 0) wave_n[tid >> 6] = __popcll(m);
+    __syncthreads();
+    int at = __popcll(m & (((uint64_t)1 << (tid & 63)) - 1)), k = 0;
 #pragma unroll
-        for (int u = 0; u < 32; ++u) {
-          const int c = tid + 256 * u;
-          if (c < d) acc[u] += row[c];
-        }
-      }
-      __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+      if (w < (tid >> 6)) at += wave_n[w];
+      k += wave_n[w];
     }
+    if (match) hits[at] = t;
+    __syncthreads();
+    for (int i = 0; i < k; ++i) {
+      const vec_t* row = (const vec_t*)(dx + (size_t)hits[i] * d);
+#pragma unroll
+      for (int u = 0; u < NC; ++u)
+        if (tid + 256 * u < nc) acc[u] += row[tid + 256 * u];
+    }
+    __syncthreads();
   }
 #pragma unroll
-  for (int u = 0; u < 32; ++u) {
-    const int c = tid + 256 * u;
-    if (c < d) out[(size_t)v * d + c] = acc[u];
-  }
+  for (int u = 0; u < NC; ++u)
+    if (tid + 256 * u < nc) o[tid + 256 * u] = acc[u];
 }
 
 __global__ void __launch_bounds__(256)
@@ -683,10 +719,19 @@ __global__ void __launch_bounds__(256)
 
 }  // namespace
 
-hipError_t launch_embed_backward(const int* tok, const float* dx, int T, int d, int V, float* out, hipStream_t s) {
+size_t embed_backward_scratch_bytes(int V) { return (size_t)V * (1 + kBucket) * sizeof(int); }
+hipError_t launch_embed_backward(const int* tok, const float* dx, int T, int d, int V, void* scratch, float* out,
+                                 hipStream_t s) {
   if (V <= 0) return hipSuccess;
   if (d > 8192) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_backward_kernel, dim3(V), dim3(256), 0, s, tok, dx, T, d, out);
+  int *count = (int*)scratch, *bucket = count + V;
+  hipError_t e = launch_fill_zero(count, (size_t)V * sizeof(int), s);
+  if (e != hipSuccess) return e;
+  if (T > 0) hipLaunchKernelGGL(embed_bucket_kernel, dim3((T + 255) / 256), dim3(256), 0, s, tok, T, V, count, bucket);
+  if ((d & 3) == 0 && (((uintptr_t)dx | (uintptr_t)out) & 15) == 0)
+    hipLaunchKernelGGL(embed_backward_kernel<4>, dim3(V), dim3(256), 0, s, tok, dx, T, d, count, bucket, out);
+  else
+    hipLaunchKernelGGL(embed_backward_kernel<1>, dim3(V), dim3(256), 0, s, tok, dx, T, d, count, bucket, out);
   return hipGetLastError();
 }
 hipError_t launch_add3(const float* a, const float* b, const float* c, float* out, size_t n, hipStream_t s) {
