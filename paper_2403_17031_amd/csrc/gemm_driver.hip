@@ -45,7 +45,7 @@ int main(int argc, char** argv) {
   if (M <= 512 || d % 128 != 0) { printf("M must exceed 512 and d_model be a multiple of 128\n"); return 1; }
   struct Shape { const char* name; int N, K, epi; bool bias2; } shapes[] = {
       {"qkv", 3 * d, d, EPI_QKV, false}, {"fc1", F, d, EPI_BIAS_GELU, false}, {"out+fc2", d, d + F, EPI_BIAS_RESADD, true}};
-  const size_t maxA = (size_t)M * (d + F), maxW = (size_t)F * d * 3, maxO = (size_t)M * F;
+  const size_t maxA = (size_t)M * (d + F), maxW = (size_t)F * d * 3, maxO = (size_t)std::max(M, d) * F;  // (the weight-gradient product writes d x F)
   std::vector<uint16_t> hA(maxA), hW(maxW), hb(F), hb2(F);
   srand(1);
   for (auto& x : hA) x = f2h((rand() % 2001 - 1000) / 1000.0f);
