@@ -56,6 +56,7 @@ struct Carver {  // bump allocator over the workspace; base == nullptr only meas
 
 struct Meta {
   int *start, *len, *cu, *kvoff, *total, *pos, *rowid, *tok;
+  KvSlot* slots;
 };
 struct Acts {
   float* x;
@@ -150,6 +151,7 @@ Meta carve_meta(Carver& c, int B, size_t Tmax) {
   m.pos = c.take<int>(Tmax);
   m.rowid = c.take<int>(Tmax);
   m.tok = c.take<int>(Tmax);
+  m.slots = c.take<KvSlot>(Tmax);
   return m;
 }
 
@@ -302,6 +304,7 @@ struct PassArgs {
   const int* pos;
   int pos_add;
   const int* rowid;
+  const KvSlot* slots = nullptr;  // mode 0: the packed rows' places in the cache that kvoff and kv_extra describe
   const int* kvoff;
   const int* len;
   const int* cu;
@@ -462,9 +465,9 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
     } else if (p.mode == 0 && gemm_takes_qkv(dt, g, c.n_heads, c.head_dim, c.rotary_dims)) {
       // prefill / scoring: the rotary turn and the K/V store are the epilogue of the QKV product
       QkvArgs qa;
-      qa.pos = p.pos; qa.rowid = p.rowid; qa.kvoff = p.kvoff; qa.len = p.len;
+      qa.pos = p.pos; qa.slots = p.slots;
       qa.cos_t = h->rope_cos; qa.sin_t = h->rope_sin;
-      qa.q = q_l; qa.kc = kc; qa.vc = vc; qa.kv_extra = (long)p.kv_extra;
+      qa.q = q_l; qa.kc = kc; qa.vc = vc;
       qa.pos_add = p.pos_add; qa.H = c.n_heads; qa.hd = c.head_dim; qa.r = c.rotary_dims;
       g.epilogue = EPI_QKV;
       g.qkv = &qa;
@@ -1490,7 +1493,7 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
   LAUNCH("copy_queries", launch_copy_queries(queries, pad_mask, B, Lq, N, c.pad_id, out_tokens, out_mask, s));
   LAUNCH("row_spans", launch_row_spans(pad_mask, B, Lq, N - 1, m.start, m.len, m.cu, m.kvoff, m.total, s));
   LAUNCH("pack_embed", launch_pack_embed(dt, queries, B, Lq, m.start, m.len, m.cu, h->w.embed_in, d, c.vocab,
-                                         m.pos, m.rowid, m.tok, ws.acts.x, s));
+                                         m.pos, m.rowid, m.tok, ws.acts.x, m.kvoff, c.n_heads, N - 1, m.slots, s));
   PassArgs p;
   p.mode = 0;
   p.rows_max = B * Lq;
@@ -1498,6 +1501,7 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
   p.pos = m.pos;
   p.pos_add = 0;
   p.rowid = m.rowid;
+  p.slots = m.slots;
   p.kvoff = m.kvoff;
   p.len = m.len;
   p.cu = m.cu;
@@ -1578,7 +1582,7 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
   const Meta& m = ws.meta;
   LAUNCH("row_spans", launch_row_spans(mask, B, L, 0, m.start, m.len, m.cu, m.kvoff, m.total, s));
   LAUNCH("pack_embed", launch_pack_embed(c.dtype, tokens, B, L, m.start, m.len, m.cu, h->w.embed_in, c.d_model,
-                                         c.vocab, m.pos, m.rowid, m.tok, ws.acts.x, s));
+                                         c.vocab, m.pos, m.rowid, m.tok, ws.acts.x, m.cu, c.n_heads, 0, m.slots, s));
   PassArgs p;
   p.mode = 0;
   p.rows_max = B * L;
@@ -1586,6 +1590,7 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
   p.pos = m.pos;
   p.pos_add = 0;
   p.rowid = m.rowid;
+  p.slots = m.slots;
   p.kvoff = m.cu;  // the single-layer K/V scratch is indexed like the packed rows
   p.len = m.len;
   p.cu = m.cu;

@@ -150,18 +150,19 @@ hipError_t launch_gather_rows_strided(const void* in, size_t in_stride, const in
 // rounds to fp16 and stores q to q[row, d] and the K / V heads to the cache slot of (sequence, head,
 // position): what the product followed by the stand-alone rotary kernel leaves, without the
 // [rows, 3*d] intermediate.  Large-M fp16 kernel only.
+// Cache slots of a packed row: head h's K (and V) row is slot x + h * y (slots of head_dim elements).
+struct __align__(8) KvSlot {
+  uint32_t x, y;
+};
 struct QkvArgs {
   const int* pos;      // [rows] position of a packed row (+ pos_add); rows are indexed from the start of the
                        // packed batch: a launch over a row chunk (GemmArgs::M_sub) adds its offset
-  const int* rowid;    // [rows] sequence of a packed row, or null (row = sequence)
-  const int* kvoff;    // [sequences] first cache slot of a sequence (in units of H slots)
-  const int* len;      // [sequences] real length; a head's slab holds len + kv_extra slots
+  const KvSlot* slots; // [rows] where a packed row's K and V go
   const float* cos_t;  // [positions][r/2]
   const float* sin_t;
   void* q;             // [rows, d] fp16
   void* kc;            // K cache, V cache (fp16)
   void* vc;
-  long kv_extra;
   int pos_add, H, hd, r;
 };
 struct GemmArgs;
@@ -255,10 +256,11 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 hipError_t launch_row_spans(const uint8_t* mask, int B, int L, int kv_extra, int* start, int* len, int* cu,
                             int* kvoff, int* total, hipStream_t s);
 // Packed row t = cu[b] + i for i < len[b]: pos[t] = i, rowid[t] = b, tok[t] = tokens[b, start[b]+i],
-// x[t, :] = embed[tok[t], :].
+// x[t, :] = embed[tok[t], :]; slots[t] = the row's place in a K/V cache whose sequence b starts at slot kvoff[b] * H and
+// holds len[b] + kv_extra rows per head.
 hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, const int* start, const int* len,
                              const int* cu, const void* embed, int d, int vocab, int* pos, int* rowid, int* tok,
-                             float* x, hipStream_t s);
+                             float* x, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s);
 hipError_t launch_gather_rows(const void* in, const int* src, int src_add, int rows, size_t row_bytes, void* out,
                               hipStream_t s);
 

@@ -63,7 +63,8 @@ template <typename T>
 __global__ void pack_embed_kernel(const int32_t* __restrict__ tokens, int L, const int* __restrict__ start,
                                   const int* __restrict__ len, const int* __restrict__ cu,
                                   const T* __restrict__ embed, int d, int vocab, int* __restrict__ pos,
-                                  int* __restrict__ rowid, int* __restrict__ tok, float* __restrict__ x) {
+                                  int* __restrict__ rowid, int* __restrict__ tok, float* __restrict__ x,
+                                  const int* __restrict__ kvoff, int H, int kv_extra, KvSlot* __restrict__ slots) {
   const int i = blockIdx.x, b = blockIdx.y;
   if (i >= len[b]) return;
   const int t = cu[b] + i;
@@ -73,6 +74,7 @@ __global__ void pack_embed_kernel(const int32_t* __restrict__ tokens, int L, con
     pos[t] = i;
     rowid[t] = b;
     tok[t] = id;
+    slots[t] = KvSlot{(uint32_t)kvoff[b] * (uint32_t)H + (uint32_t)i, (uint32_t)(len[b] + kv_extra)};
   }
   const T* e = embed + (size_t)id * d;
   float* xr = x + (size_t)t * d;
@@ -81,14 +83,14 @@ __global__ void pack_embed_kernel(const int32_t* __restrict__ tokens, int L, con
 
 hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, const int* start, const int* len,
                              const int* cu, const void* embed, int d, int vocab, int* pos, int* rowid, int* tok,
-                             float* x, hipStream_t s) {
+                             float* x, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s) {
   dim3 grid(L, B), block(256);
   if (dtype == 0)
     hipLaunchKernelGGL(pack_embed_kernel<float>, grid, block, 0, s, tokens, L, start, len, cu,
-                       (const float*)embed, d, vocab, pos, rowid, tok, x);
+                       (const float*)embed, d, vocab, pos, rowid, tok, x, kvoff, H, kv_extra, slots);
   else
     hipLaunchKernelGGL(pack_embed_kernel<bf16_t>, grid, block, 0, s, tokens, L, start, len, cu,
-                       (const bf16_t*)embed, d, vocab, pos, rowid, tok, x);
+                       (const bf16_t*)embed, d, vocab, pos, rowid, tok, x, kvoff, H, kv_extra, slots);
   return hipGetLastError();
 }
 

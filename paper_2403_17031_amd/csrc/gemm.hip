@@ -278,9 +278,10 @@ __global__ void __launch_bounds__(256)
 }
 
 // =================================================================================================
-// Large-M kernel: 256x256 block tile, one block per CU, 8 waves of 128x64 (two per SIMD; a 4-wave
-// form, 128x128 per wave, is kept as a template option).  Tiles go global -> LDS directly (global_load_lds, 16 bytes per lane: a wave
-// instruction fills 1 KB; no staging registers, no ds_write) into TWO 64 KB stages of K depth 64.
+// Large-M kernel: 256x256 block tile, one block per CU, 8 waves of 128x64 (two per SIMD: what one wave
+// cannot overlap the SIMD's other wave fills; measured 8-10 % faster than 4 waves of 128x128).  Tiles go global -> LDS
+// directly (global_load_lds, 16 bytes per lane: a wave instruction fills 1 KB; no staging registers, no ds_write) into
+// TWO 64 KB stages of K depth 64.
 // The depth is what matters: a tile row is then one full 128-byte line per stage.  With half
 // lines (K depth 32, more and smaller stages) every line was requested twice from L2, one half per
 // k-step, and the matrix cores waited on that request stream; fetching whole lines removed the
@@ -290,212 +291,78 @@ __global__ void __launch_bounds__(256)
 // keep the order), so each issues in the shadow of a matrix instruction.  Each lane picks its
 // global chunk so that the linear LDS image is the XOR-swizzled layout the fragment reads expect
 // (conflict-free ds_read_b128).
+//
+// The launch is persistent: one block per CU walks its share of the tiles, and the last two stages of a tile issue the
+// loads of the next tile's first two, so that its start-up (index arithmetic, two cold loads) runs under the epilogue,
+// which has 32 KB of LDS of its own.  A round is 256 neighbouring tiles, 32 in a row on each XCD (they share panels in its
+// L2).  (One block per tile and an eighth of all tiles per XCD put 33 tiles on 32 CUs whenever the count was a little above
+// a multiple of 256, or 35 in the K-sliced form: a whole extra round.)  What is left over after the whole rounds is cut
+// into 128x128 tiles, four per tile, if that fills at most two half-length rounds; the sums of an output element are
+// formed in the same order either way.  gemm_driver, us, one block per tile / this: 22,200 rows of width 768 QKV 118 / 97,
+// FC1 180 / 132, out-projection + FC2 190 / 150, K-major 159 / 110; 3,456 rows 33 / 25, 35 / 30, 78 / 40; 83,373 rows of width
+// 2560 3381 / 3280, 4511 / 4240, 5203 / 5065; 21,504 of 4096 2041 / 1970, 2709 / 2572, 3410 / 3186 (FC1's with a fifth less
+// GELU arithmetic, and about 2 % of each between runs).
 // =================================================================================================
 #define RLHF_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define RLHF_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
-constexpr int kDmaWaves = 8;                // waves per block of the large-M kernel (4 or 8)
+constexpr int kCUs = 256;                   // CUs of the chip = blocks of a launch (a multiple of its 8 XCDs)
 constexpr int DK = 64;                      // K depth of one stage: 128 bytes per tile row
-constexpr int DSTAGE = (256 + 256) * DK;    // halfs per stage (64 KB)
+constexpr int DOP = 256 * DK;               // halfs per stage and operand (32 KB)
+constexpr int EPW = 2048;                   // halfs of epilogue LDS per wave (4 KB)
 
-// KMAJ: both operands are given K-major -- A as [K, M] and W as [K, N], row-major, lda / ldw their row strides
-// (the weight-gradient products of a backward pass: out = A^T W over the batch's rows, no transposed copies).  A stage
-// then holds 64 k-rows of 512 bytes per operand, and a matrix-instruction operand slice (8 consecutive k of one
-// column) comes from two transposing LDS reads (ds_read_b64_tr_b16: within a group of 16 lanes, lane i receives the
-// (i mod 4)-th element of the 8-byte items addressed by lanes i/4, i/4+4, i/4+8, i/4+12; with lane r pointing at row
-// k + r/4, columns 4(r mod 4).. of the tile, lane i gets column i of rows k .. k+3).  16-byte chunk c of k-row k sits at
-// chunk c ^ 2(k mod 4) of the row, so that the four rows one group reads fall into four different 32-byte bank groups.
-template <int EPI, int WAVES, bool KMAJ = false>
-__global__ void __launch_bounds__(64 * WAVES, 1)
-    gemm_f16_dma_kernel(const half_t* __restrict__ A, const half_t* __restrict__ W, const bf16_t* __restrict__ bias,
-                        void* __restrict__ out, int M_max, const int* __restrict__ M_dev, int M_sub, int N, int K,
-                        int ldo, int nb_m, int nb_n, int lda, int ldw, const bf16_t* __restrict__ bias2,
-                        LseArgs lse, QkvArgs qk, int k_slice, size_t slab) {
-  // WAVES = 4: one wave per SIMD, each 128 x 128 of the tile (256 accumulator registers).
-  // WAVES = 8: two waves per SIMD, each 128 x 64 (128 accumulator registers): what one wave cannot
-  // overlap (waits, epilogue arithmetic against stores) the SIMD's other wave fills.
-  constexpr int TM = 256, TN = 256, MT = 4, NT = WAVES == 8 ? 2 : 4;
-  constexpr int WN = 32 * NT;         // columns per wave
-  constexpr int NWN = TN / WN;        // waves along N
-  constexpr int NLD = 64 / WAVES;     // tile loads per wave per stage
-  constexpr int NMF = MT * NT;        // matrix instructions per wave per sub-step
-  __shared__ __attribute__((aligned(16))) uint16_t lds0[DSTAGE];
-  __shared__ __attribute__((aligned(16))) uint16_t lds1[DSTAGE];
-  const int M = M_dev ? min(M_max, *M_dev - M_sub) : M_max;
-  nb_m = min(nb_m, (M + TM - 1) / TM);
-  const int total = nb_m * nb_n;
-  const int per_xcd = (total + 7) >> 3;
-  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
-  const int lt = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (lt >= total) return;
-  const int group_sz = GROUP_M * nb_n;
-  const int grp = lt / group_sz, rem = lt - grp * group_sz;
-  const int gm = min(GROUP_M, nb_m - grp * GROUP_M);
-  const int tm = grp * GROUP_M + rem % gm, tn = rem / gm;
-  const int m0 = tm * TM, n0 = tn * TN;
+struct DmaArgs {
+  const half_t *A, *W;
+  const bf16_t *bias, *bias2;
+  void* out;
+  const int* M_dev;
+  int M_max, M_sub, N, K, ldo, lda, ldw;
+  int slices, k_slice;  // K cut into `slices` ranges of k_slice; slice z writes its fp32 result to slab z of out
+  size_t slab;
+};
 
-  // K split over blockIdx.y (weight-gradient products: few tiles, a very long K): slice z covers
-  // [z * k_slice, min(K, (z + 1) * k_slice)) and writes its fp32 result to slab z of `out`
-  if (k_slice > 0) {
-    const int kb = blockIdx.y * k_slice;
-    A += KMAJ ? (size_t)kb * lda : (size_t)kb;
-    W += KMAJ ? (size_t)kb * ldw : (size_t)kb;
-    K = min(k_slice, K - kb);
-    out = (float*)out + (size_t)blockIdx.y * slab;
-  }
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps LDS bases in SGPRs
-  const int wm = (wave / NWN) * 128, wn = (wave % NWN) * WN;
-
-  // ---- direct loads: a stage row is 128 B (8 chunks); wave-load j (= NLD*wave + i, i < NLD) fills
-  //      rows 8j .. 8j+7 (rows < 256: A, else W); lane l lands at row 8j + l/8, physical chunk l%8,
-  //      and therefore fetches logical chunk (l%8) ^ ((row>>1)&7)
-  uint32_t goff[NLD];
-  const int gld = wave < WAVES / 2 ? lda : ldw;  // row stride of the operand this wave loads
-#pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    if (KMAJ) {
-      // wave-load j covers k-rows 2j', 2j'+1 (j' = j mod 32) of its operand; lane l lands at k-row 2j' + l/32,
-      // physical chunk l%32, and fetches logical chunk (l%32) ^ 2(k-row mod 4); columns past the operand's width
-      // re-read its last chunk (those output columns are never stored)
-      const int krow = 2 * ((NLD * wave + i) & 31) + (lane >> 5);
-      const int c = (lane & 31) ^ (2 * (krow & 3));
-      const int colb = wave < WAVES / 2 ? min(m0 + c * 8, M - 8) : min(n0 + c * 8, N - 8);
-      goff[i] = (uint32_t)(krow * gld + colb);
-    } else {
-      const int row = 8 * (NLD * wave + i) + (lane >> 3);
-      const int c = (lane & 7) ^ ((row >> 1) & 7);
-      goff[i] = (uint32_t)((row < TM ? min(m0 + row, M - 1) * lda : min(n0 + row - TM, N - 1) * ldw) + c * 8);
-    }
-  }
-  const half_t* gbase = wave < WAVES / 2 ? A : W;  // the first half of the waves loads A rows, the second W rows
-  auto load_one = [&](uint16_t* stage, int k0, int i) {
-    __builtin_amdgcn_global_load_lds(RLHF_GLOBAL_PTR(gbase + goff[i] + (KMAJ ? (size_t)k0 * gld : (size_t)k0)),
-                                     RLHF_LDS_PTR(stage + (8 * (NLD * wave + i)) * DK), 16, 0, 0);
-  };
-
-  const int l32 = lane & 31, hf = lane >> 5;
-  const int key = (l32 >> 1) & 7;
-  const int a_off = (wm + l32) * DK, w_off = (TM + wn + l32) * DK;
-  // sub-step s (16 of the 64 k of a stage) reads logical chunks 2s and 2s+1: one per half-wave
-  // KMAJ: sub-step s reads k-rows 16s + 8hf .. +7 (256 halfs per row); the column part of a lane's address, with
-  // the row swizzle, is fixed per fragment
-  const int ch0 = KMAJ ? (0 + 8 * hf) * 256 : ((0 + hf) ^ key) << 3, ch1 = KMAJ ? (16 + 8 * hf) * 256 : ((2 + hf) ^ key) << 3,
-            ch2 = KMAJ ? (32 + 8 * hf) * 256 : ((4 + hf) ^ key) << 3, ch3 = KMAJ ? (48 + 8 * hf) * 256 : ((6 + hf) ^ key) << 3;
-  int koff[MT + NT];
-  if (KMAJ) {
-    const int r = lane & 15, gsel = (lane >> 4) & 1;
-#pragma unroll
-    for (int q = 0; q < MT + NT; ++q) {
-      const int colb = (q < MT ? wm + 32 * q : wn + 32 * (q - MT)) + 16 * gsel;  // first column of the group's 16
-      const int chunk = ((colb >> 3) + ((r & 3) >> 1)) ^ (2 * ((r >> 2) & 3));
-      koff[q] = (q < MT ? 0 : 64 * 256) + (r >> 2) * 256 + chunk * 8 + (r & 1) * 4;
-    }
-  }
-
-  f32x16_t acc[NT][MT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
-
-  // fragment buffers, used alternately by the four sub-steps of a stage.  Weights are the first
-  // matrix operand: accumulator element e of a lane is then (n = 8*(e/4) + 4*(lane/32) + e%4,
-  // m = lane%32), i.e. 4 consecutive output columns per lane
-  f16x8_t fa0[MT], fw0[NT], fa1[MT], fw1[NT];
-  auto frag_one = [&](const uint16_t* ls, int ch, int q, f16x8_t* fa, f16x8_t* fw) {
-    if (KMAJ) {
-      typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-      typedef __attribute__((ext_vector_type(8))) short s16x8_t;
-      typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
-      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(ls + koff[q] + ch));
-      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(ls + koff[q] + ch + 4 * 256));
-      const s16x8_t b = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      const f16x8_t v = __builtin_bit_cast(f16x8_t, b);
-      if (q < MT) fa[q] = v;
-      else fw[q - MT] = v;
-    } else if (q < MT) {
-      fa[q] = *(const f16x8_t*)(ls + a_off + q * 32 * DK + ch);
-    } else {
-      fw[q - MT] = *(const f16x8_t*)(ls + w_off + (q - MT) * 32 * DK + ch);
-    }
-  };
-  // NMF matrix instructions on (FA, FW); after the n-th, fragment read n (n < MT + NT) of the next
-  // sub-step from (LS, CH) into (GA, GW) and, if LOAD, tile load n of the stage at K offset KL
-#define RLHF_SUB(FA, FW, LS, CH, GA, GW, LOAD, LSTAGE, KL)                                        \
-  _Pragma("unroll") for (int n = 0; n < NMF; ++n) {                                               \
-    const int mi = ((n >> 2) & 1) ? 3 - (n & 3) : (n & 3); /* serpentine: one operand changes at a time */ \
-    acc[n >> 2][mi] = __builtin_amdgcn_mfma_f32_32x32x16_f16(FW[n >> 2], FA[mi],                  \
-                                                             acc[n >> 2][mi], 0, 0, 0);           \
-    __builtin_amdgcn_sched_barrier(0);                                                            \
-    if (n < MT + NT) frag_one(LS, CH, n, GA, GW);                                                 \
-    if (LOAD && n < NLD) load_one(LSTAGE, KL, n);                                                 \
-    __builtin_amdgcn_sched_barrier(0);                                                            \
-  }
-  // vmcnt(0) lgkmcnt(0) + barrier: every wave's tile loads have landed and every wave has finished
-  // reading the current stage
-#define RLHF_WAIT_BARRIER()                      \
-  __builtin_amdgcn_sched_barrier(0);             \
-  asm volatile("" ::: "memory");                 \
-  __builtin_amdgcn_s_waitcnt(0x0070);            \
-  __builtin_amdgcn_s_barrier();                  \
-  asm volatile("" ::: "memory");                 \
+// The epilogue of one wave: its 32 * MT rows x 64 columns from (row0, col0) on, accumulators in acc.  In the accumulator
+// layout a lane owns 4 consecutive columns of ONE row (n = 32*j + 8*g + 4*hf + u, m = 32*i + l32), so a direct store
+// would touch 32 rows with 8-16 bytes each -- partial-line writes that the memory system handles an order of magnitude
+// slower than full lines.  The wave therefore transposes 32 rows at a time through its own 4 KB of LDS (ep; XOR-swizzled
+// by row) and stores 16 bytes per lane, 8 lanes per 128-byte row segment.  Waves need not wait for each other.
+// bv: the bias of the lane's columns (bf16 pairs), loaded ahead; prow: the positions of its rows (EPI_QKV).
+#define RLHF_WAVE_LDS_FENCE()                  \
+  __builtin_amdgcn_sched_barrier(0);           \
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); \
+  __builtin_amdgcn_wave_barrier();             \
   __builtin_amdgcn_sched_barrier(0);
-  // One stage (K depth 64).  The first three sub-steps read their successors' fragments from CUR.
-  // After the barrier CUR is free and OTHER holds the next stage: the last sub-step reads the next
-  // stage's first fragments from OTHER and issues the loads of the stage after that into CUR, so a
-  // load has a whole stage of matrix work to land.
-#define RLHF_STAGE(CUR, OTHER, KT)                                                                \
-  {                                                                                               \
-    const int kload = min((KT) + 2, nk - 1) * DK;                                                 \
-    RLHF_SUB(fa0, fw0, CUR, ch1, fa1, fw1, false, CUR, 0)                                         \
-    RLHF_SUB(fa1, fw1, CUR, ch2, fa0, fw0, false, CUR, 0)                                         \
-    RLHF_SUB(fa0, fw0, CUR, ch3, fa1, fw1, false, CUR, 0)                                         \
-    RLHF_WAIT_BARRIER()                                                                           \
-    RLHF_SUB(fa1, fw1, OTHER, ch0, fa0, fw0, true, CUR, kload)                                    \
-  }
-
-  // K is a multiple of 2*DK here (the launcher routes other shapes to the staged kernel), so the
-  // loop is branch-free: past the end the final tile is re-issued into a stage nobody reads.
-  const int nk = K / DK;
-#pragma unroll
-  for (int i = 0; i < NLD; ++i) load_one(lds0, 0, i);
-#pragma unroll
-  for (int i = 0; i < NLD; ++i) load_one(lds1, min(1, nk - 1) * DK, i);
-  RLHF_WAIT_BARRIER()
-#pragma unroll
-  for (int q = 0; q < MT + NT; ++q) frag_one(lds0, ch0, q, fa0, fw0);
-  for (int kt = 0; kt < nk; kt += 2) {
-    RLHF_STAGE(lds0, lds1, kt)
-    RLHF_STAGE(lds1, lds0, kt + 1)
-  }
-#undef RLHF_STAGE
-#undef RLHF_SUB
-#undef RLHF_WAIT_BARRIER
-  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the surplus loads have landed too
-  __syncthreads();
-
-  if (EPI == EPI_LSE) {
-    // ---- scoring LM head: the logits stay in the accumulators.  A lane holds, for each of its 4
-    //      rows (32*i + lane%32), half of the wave's WN columns (the other half is in lane ^ 32):
-    //      running max and sum of exp over them, combined across the two half-waves, plus the
-    //      target token's z if its column is among this lane's.
-    const int part = NWN * tn + (wave % NWN);
+template <int EPI, int MT>
+__device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& lse, const QkvArgs& qk, void* out,
+                                             const f32x16_t (&acc)[2][MT], int row0, int col0, int M, uint16_t* ep,
+                                             int lane, const u32x2_t (&bv)[2][4], const u32x2_t (&bv2)[2][4],
+                                             const int (&prow)[MT]) {
+  constexpr int NT = 2;
+  // (opaque, so that what is derived from it is formed here, per tile, and not kept in registers through the main loop)
+  asm volatile("" : "+v"(lane));
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int N = g.N, ldo = g.ldo;
+  if constexpr (EPI == EPI_LSE) {
+    // ---- scoring LM head: the logits stay in the accumulators.  A lane holds, for each of its rows (32*i + l32), half
+    //      of the wave's 64 columns (the other half is in lane ^ 32): running max and sum of exp over them, combined
+    //      across the two half-waves, plus the target token's z if its column is among this lane's.
+    const int part = col0 >> 6;
     const int T = *lse.T_dev;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const int tr = M_sub + m0 + wm + 32 * i + l32;  // packed row
-      const bool row_ok = m0 + wm + 32 * i + l32 < M;
+      const int tr = g.M_sub + row0 + 32 * i + l32;  // packed row
+      const bool row_ok = row0 + 32 * i + l32 < M;
       int tcol = -1;  // target column relative to this wave's first column, or out of range
       if (lse.tgt) {
         const int tg = row_ok && tr < T ? lse.tgt[tr] : -1;
-        if (tg >= 0) tcol = tg - (n0 + wn);
+        if (tg >= 0) tcol = tg - col0;
       } else if (row_ok && tr + 1 < T && lse.pos[tr + 1] == lse.pos[tr] + 1) {
-        tcol = lse.tok[tr + 1] - (n0 + wn);
+        tcol = lse.tok[tr + 1] - col0;
       }
+      // the target's logit is this lane's if its column falls into one of the lane's groups of four
+      const bool has_t = tcol >= 0 && tcol < 64 && ((tcol >> 2) & 1) == hf;
+      int lim = N - col0;  // columns of this wave that exist (kept opaque: 32 masks would otherwise be held in registers)
+      asm volatile("" : "+s"(lim));
       float m = -INFINITY, zt = 0.f;
-      bool has_t = false;
       float z[NT][16];
 #pragma unroll
       for (int j = 0; j < NT; ++j)
@@ -503,8 +370,8 @@ __global__ void __launch_bounds__(64 * WAVES, 1)
         for (int e = 0; e < 16; ++e) {
           const int col = 32 * j + 8 * (e >> 2) + 4 * hf + (e & 3);
           float v = acc[j][i][e] * lse.inv_temperature;
-          if (n0 + wn + col >= N) v = -INFINITY;
-          if (col == tcol) { zt = v; has_t = true; }
+          if (col >= lim) v = -INFINITY;
+          zt = col == tcol ? v : zt;
           z[j][e] = v;
           m = fmaxf(m, v);
         }
@@ -525,220 +392,507 @@ __global__ void __launch_bounds__(64 * WAVES, 1)
         if (has_t) lse.ztgt[tr] = zt;
       }
     }
-    return;
-  }
-  // ---- epilogue.  In the accumulator layout a lane owns 4 consecutive columns of ONE row, so a
-  //      direct store touches 32 rows with 8-16 bytes each -- partial-line writes that the memory
-  //      system handles an order of magnitude slower than full lines.  Each wave therefore
-  //      transposes its 128x128 tile through one of the four (now idle) 32 KB LDS stages and stores
-  //      16 bytes per lane, 16 lanes per 256-byte row segment.  The LDS image is XOR-swizzled by
-  //      row (chunk ^ (row & 15)); accumulator tiles are addressed through compile-time indices
-  //      (a loop the compiler declines to unroll would spill all 256 accumulators to scratch).
-  // The staging regions are private to a wave, so the waves need not wait for each other: a wave's
-  // own LDS writes are complete, and visible to all its lanes, once its LDS counter has drained.
-#define RLHF_WAVE_LDS_FENCE()                  \
-  __builtin_amdgcn_sched_barrier(0);           \
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); \
-  __builtin_amdgcn_wave_barrier();             \
-  __builtin_amdgcn_sched_barrier(0);
-  constexpr int EPW = 128 * WN;  // halfs of LDS per wave: its tile as fp16, or half of it as fp32
-  uint16_t* ep = wave * EPW < DSTAGE ? lds0 + wave * EPW : lds1 + (wave * EPW - DSTAGE);
-  constexpr int CH = WN / 8;     // 16-byte chunks per fp16 row of the wave's tile = lanes per row on the way out
-  constexpr int RPI = 64 / CH;   // rows per store instruction
-  const int rd_row = lane / CH, rd_c = lane % CH;
-  // bias of this lane's 64 columns: 16 eight-byte loads issued together (N is a multiple of 8 here
-  // and every column group starts at a multiple of 4, so a group is inside or outside as a whole)
-  f32x4_t bias_v[NT][4];
+  } else {
+    f32x4_t bias_v[NT][4];
 #pragma unroll
-  for (int j = 0; j < NT; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int nb = n0 + wn + 32 * j + 8 * g + 4 * hf;
-      u32x2_t raw = {0, 0};
-      if (EPI != EPI_F32 && bias && nb < N) raw = *(const u32x2_t*)(bias + nb);
-      bias_v[j][g][0] = __uint_as_float(raw[0] << 16);
-      bias_v[j][g][1] = __uint_as_float(raw[0] & 0xFFFF0000u);
-      bias_v[j][g][2] = __uint_as_float(raw[1] << 16);
-      bias_v[j][g][3] = __uint_as_float(raw[1] & 0xFFFF0000u);
-      if (EPI != EPI_F32 && bias2 && nb < N) {
-        raw = *(const u32x2_t*)(bias2 + nb);
-        bias_v[j][g][0] += __uint_as_float(raw[0] << 16);
-        bias_v[j][g][1] += __uint_as_float(raw[0] & 0xFFFF0000u);
-        bias_v[j][g][2] += __uint_as_float(raw[1] << 16);
-        bias_v[j][g][3] += __uint_as_float(raw[1] & 0xFFFF0000u);
+      for (int q = 0; q < 4; ++q) {
+        bias_v[j][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (EPI != EPI_F32) {
+          const u32x2_t raw = bv[j][q];
+          bias_v[j][q] = f32x4_t{__uint_as_float(raw[0] << 16), __uint_as_float(raw[0] & 0xFFFF0000u),
+                                 __uint_as_float(raw[1] << 16), __uint_as_float(raw[1] & 0xFFFF0000u)};
+        }
+        if (EPI == EPI_BIAS_RESADD) {
+          const u32x2_t raw = bv2[j][q];
+          bias_v[j][q][0] += __uint_as_float(raw[0] << 16);
+          bias_v[j][q][1] += __uint_as_float(raw[0] & 0xFFFF0000u);
+          bias_v[j][q][2] += __uint_as_float(raw[1] << 16);
+          bias_v[j][q][3] += __uint_as_float(raw[1] & 0xFFFF0000u);
+        }
+      }
+    const int rd_row = lane >> 3, rd_c = lane & 7;  // on the way out: row within a group of 8, 16-byte chunk of the row
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_QKV) {
+      // EPI_QKV: for each of the lane's eight 4-column groups the index of its first rotary angle (-1: the group is not
+      // rotary).  A group is two whole pairs.
+      const int qd = qk.H * qk.hd;
+      int ang[NT][4];
+      if (EPI == EPI_QKV) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int c = col0 + 32 * j + 8 * q + 4 * hf;
+            const int sec = c >= 2 * qd ? 2 : (c >= qd ? 1 : 0);
+            const int e = (c - sec * qd) % qk.hd;
+            ang[j][q] = (sec < 2 && e < qk.r && c < N) ? (e >> 1) : -1;
+          }
+      }
+      const int gcol = col0 + rd_c * 8;
+      const int ld = EPI == EPI_QKV ? qd : ldo;  // row stride of what is stored as rows
+      char* const ob = EPI == EPI_QKV ? (char*)((half_t*)qk.q + (size_t)(g.M_sub + row0) * ld + col0)
+                                      : (char*)((half_t*)out + (size_t)row0 * ld + col0);
+      const uint32_t lo = 2u * (uint32_t)(rd_row * ld + rd_c * 8);
+      // this lane's 16-byte chunk lies in one head of one section (head_dim is a multiple of 8)
+      const int sec = EPI == EPI_QKV ? (gcol >= 2 * qd ? 2 : (gcol >= qd ? 1 : 0)) : 0;
+      const int hh = EPI == EPI_QKV ? (gcol - sec * qd) / qk.hd : 0, e0 = gcol - sec * qd - hh * qk.hd;
+      half_t* const cache = (half_t*)(sec == 1 ? qk.kc : qk.vc);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        KvSlot slot[4];
+        if (EPI == EPI_QKV && sec > 0) {
+#pragma unroll
+          for (int it = 0; it < 4; ++it) slot[it] = qk.slots[g.M_sub + min(row0 + 32 * i + 8 * it + rd_row, M - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            f16x4_t h;
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = acc[j][i][4 * q + u] + bias_v[j][q][u];
+            if (EPI == EPI_QKV) {
+              if (ang[j][q] >= 0) {
+                // the stand-alone kernel turns values already rounded to fp16: keep that order of roundings
+                const f32x2_t co = *(const f32x2_t*)(qk.cos_t + prow[i] + ang[j][q]);
+                const f32x2_t si = *(const f32x2_t*)(qk.sin_t + prow[i] + ang[j][q]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                  const float lo = (float)from_f32<half_t>(v[2 * u]), hi = (float)from_f32<half_t>(v[2 * u + 1]);
+                  v[2 * u] = lo * co[u] - hi * si[u];
+                  v[2 * u + 1] = hi * co[u] + lo * si[u];
+                }
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) h[u] = from_f32<half_t>(EPI == EPI_BIAS_GELU ? gelu_f16out(v[u]) : v[u]);
+            *(f16x4_t*)(ep + l32 * 64 + (((4 * j + q) ^ (l32 & 7)) << 3) + 4 * hf) = h;
+          }
+        RLHF_WAVE_LDS_FENCE();
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int row = 8 * it + rd_row, grow = row0 + 32 * i + row;
+          const u32x4_t v = *(const u32x4_t*)(ep + row * 64 + ((rd_c ^ (row & 7)) << 3));
+          if (grow < M && gcol < N) {
+            if (EPI == EPI_QKV && sec != 0)
+              *(u32x4_t*)(cache + ((size_t)slot[it].x + (size_t)hh * slot[it].y) * qk.hd + e0) = v;
+            else
+              *(u32x4_t*)(ob + (size_t)(32 * i + 8 * it) * ld * 2 + lo) = v;
+          }
+        }
+        RLHF_WAVE_LDS_FENCE();
+      }
+    } else {
+      // fp32 results: 32 rows x 32 columns per pass; the residual rows are requested two passes ahead (more do not fit the
+      // registers beside the accumulators)
+      float* const epf = (float*)ep;
+      char* const ob = (char*)((float*)out + (size_t)row0 * ldo + col0);
+      const uint32_t lo = 4u * (uint32_t)(rd_row * ldo + rd_c * 4);
+      f32x4_t xv[3][4];
+      auto fetch = [&](int p) {
+        const int i = p / NT, j = p % NT;
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+          if (row0 + 32 * i + 8 * it + rd_row < M && col0 + 32 * j + 4 * rd_c < N)
+            xv[p % 3][it] = *(const f32x4_t*)(ob + ((size_t)(32 * i + 8 * it) * ldo + 32 * j) * 4 + lo);
+      };
+      if (EPI == EPI_BIAS_RESADD) {
+        fetch(0);
+        fetch(1);
+      }
+#pragma unroll
+      for (int p = 0; p < MT * NT; ++p) {
+        const int i = p / NT, j = p % NT;
+        if (EPI == EPI_BIAS_RESADD && p + 2 < MT * NT) fetch(p + 2);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16_t& a = acc[j][i];
+          const f32x4_t v = {a[4 * q] + bias_v[j][q][0], a[4 * q + 1] + bias_v[j][q][1],
+                             a[4 * q + 2] + bias_v[j][q][2], a[4 * q + 3] + bias_v[j][q][3]};
+          *(f32x4_t*)(epf + l32 * 32 + (((2 * q + hf) ^ (l32 & 7)) << 2)) = v;
+        }
+        RLHF_WAVE_LDS_FENCE();
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int row = 8 * it + rd_row;
+          f32x4_t v = *(const f32x4_t*)(epf + row * 32 + ((rd_c ^ (row & 7)) << 2));
+          if (row0 + 32 * i + row < M && col0 + 32 * j + 4 * rd_c < N) {
+            if (EPI == EPI_BIAS_RESADD) v += xv[p % 3][it];
+            *(f32x4_t*)(ob + ((size_t)(32 * i + 8 * it) * ldo + 32 * j) * 4 + lo) = v;
+          }
+        }
+        RLHF_WAVE_LDS_FENCE();
       }
     }
-  if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_QKV) {
-    // EPI_QKV: position of this lane's four rows, and for each of its eight 4-column groups the
-    // index of its first rotary angle (-1: the group is not rotary).  A group is two whole pairs.
-    const int qd = qk.H * qk.hd, qhalf = qk.r >> 1;
-    int prow[MT], ang[NT][4];
-    if (EPI == EPI_QKV) {
+  }
+}
+
+// Bias of a lane's columns from col0 on: eight 8-byte loads (N is a multiple of 8 here and every column group starts at a
+// multiple of 4, so a group is inside or outside as a whole).
+__device__ __forceinline__ void dma_load_bias(const bf16_t* bias, int col0, int N, int hf, u32x2_t (&bv)[2][4]) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i) prow[i] = (qk.pos[M_sub + min(m0 + wm + 32 * i + l32, M - 1)] + qk.pos_add) * qhalf;
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int nb = col0 + 32 * j + 8 * q + 4 * hf;
+      bv[j][q] = u32x2_t{0, 0};
+      if (bias && nb < N) bv[j][q] = *(const u32x2_t*)(bias + nb);
+    }
+}
+
+// KMAJ: both operands are given K-major -- A as [K, M] and W as [K, N], row-major, lda / ldw their row strides
+// (the weight-gradient products of a backward pass: out = A^T W over the batch's rows, no transposed copies).  A stage
+// then holds 64 k-rows of 512 bytes per operand, and a matrix-instruction operand slice (8 consecutive k of one
+// column) comes from two transposing LDS reads (ds_read_b64_tr_b16: within a group of 16 lanes, lane i receives the
+// (i mod 4)-th element of the 8-byte items addressed by lanes i/4, i/4+4, i/4+8, i/4+12; with lane r pointing at row
+// k + r/4, columns 4(r mod 4).. of the tile, lane i gets column i of rows k .. k+3).  16-byte chunk c of k-row k sits at
+// chunk c ^ 2(k mod 4) of the row, so that the four rows one group reads fall into four different 32-byte bank groups.
+template <int EPI, bool KMAJ>
+__global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs lse, QkvArgs qk) {
+  constexpr int TM = 256, TN = 256, MT = 4, NT = 2;
+  constexpr int NLD = 4;        // tile loads per wave, stage and operand
+  constexpr int NMF = MT * NT;  // matrix instructions per wave per sub-step
+  // stage s of the big tile: A rows in la<s>, W rows in lw<s> (separate variables, so that a read of one does not wait for
+  // the loads into another); the 128x128 tiles use the four as a ring of stages
+  __shared__ __attribute__((aligned(16))) uint16_t la0[DOP];
+  __shared__ __attribute__((aligned(16))) uint16_t lw0[DOP];
+  __shared__ __attribute__((aligned(16))) uint16_t la1[DOP];
+  __shared__ __attribute__((aligned(16))) uint16_t lw1[DOP];
+  __shared__ __attribute__((aligned(16))) uint16_t lep[8 * EPW];
+  const int M = g.M_dev ? min(g.M_max, *g.M_dev - g.M_sub) : g.M_max;
+  const int N = g.N;
+  const int nb_m = (M + TM - 1) / TM, nb_n = (N + TN - 1) / TN;
+  const int tiles = max(nb_m, 0) * nb_n, items = tiles * g.slices;
+  const int G = gridDim.x, P = G >> 3;
+  const int xcd = blockIdx.x & 7, slot_x = blockIdx.x >> 3;
+  const int full = items / G, rem = items - full * G;
+  const bool cut = !KMAJ && g.slices == 1 && 2 * rem <= G;  // the rest as 128x128 tiles
+  // whole tiles of this block: `full` rounds, and one more if the rest is not cut and reaches it
+  const int per_x = (rem + 7) >> 3;
+  const int rest = full * G + xcd * per_x + slot_x;
+  const int mine = full + (!cut && slot_x < per_x && rest < items ? 1 : 0);
+  auto item_at = [&](int it) { return it < full ? it * G + xcd * P + slot_x : rest; };
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps LDS bases in SGPRs
+  const int l32 = lane & 31, hf = lane >> 5;
+  const int key = (l32 >> 1) & 7;
+  uint16_t* const ep = lep + wave * EPW;
+
+  // tile t of the current row count: consecutive tiles walk GROUP_M m-tiles for each n-tile
+  auto tile_pos = [&](int lt, int& m0, int& n0) {
+    const int group_sz = GROUP_M * nb_n;
+    const int grp = lt / group_sz, r = lt - grp * group_sz;
+    const int gm = min(GROUP_M, nb_m - grp * GROUP_M);
+    m0 = (grp * GROUP_M + r % gm) * TM;
+    n0 = (r / gm) * TN;
+  };
+
+  {
+    const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
+    // the tile's first rows (wave-uniform), and this lane's chunks as byte offsets from there: A rows, then W rows
+    const char *gA = nullptr, *gW = nullptr;
+    uint32_t goff[2 * NLD];
+    int m0 = 0, n0 = 0, nk = 0;
+    void* out = g.out;
+    // ---- direct loads: a stage row is 128 B (8 chunks); wave-load j (= NLD*wave + i) of an operand fills its rows
+    //      8j .. 8j+7; lane l lands at row 8j + l/8, physical chunk l%8, and therefore fetches logical chunk
+    //      (l%8) ^ ((row>>1)&7).  KMAJ: wave-load j covers k-rows 2j, 2j+1; lane l lands at k-row 2j + l/32, physical
+    //      chunk l%32, and fetches logical chunk (l%32) ^ 2(k-row mod 4); columns past the operand's width re-read its
+    //      last chunk (those output columns are never stored).
+    auto set_item = [&](int item, int& m, int& n, int& kk, void*& o) {
+      int lane = tid & 63;  // (opaque: see dma_epilogue)
+      asm volatile("" : "+v"(lane));
+      const int z = KMAJ || g.slices > 1 ? item / tiles : 0;
+      tile_pos(item - z * tiles, m, n);
+      const int kb = z * g.k_slice;
+      kk = (g.k_slice > 0 ? min(g.k_slice, g.K - kb) : g.K) / DK;
+      gA = (const char*)(g.A + (KMAJ ? (size_t)kb * g.lda + m : (size_t)m * g.lda + kb));
+      gW = (const char*)(g.W + (KMAJ ? (size_t)kb * g.ldw + n : (size_t)n * g.ldw + kb));
+      o = g.slices > 1 ? (void*)((float*)g.out + (size_t)z * g.slab) : g.out;
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        if (KMAJ) {
+          const int krow = 2 * (NLD * wave + i) + (lane >> 5);
+          const int c = ((lane & 31) ^ (2 * (krow & 3))) * 8;
+          goff[i] = 2u * (uint32_t)(krow * g.lda + min(c, M - 8 - m));
+          goff[NLD + i] = 2u * (uint32_t)(krow * g.ldw + min(c, N - 8 - n));
+        } else {
+          const int row = 8 * (NLD * wave + i) + (lane >> 3);
+          const int c = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+          goff[i] = 2u * (uint32_t)(min(row, M - 1 - m) * g.lda + c);
+          goff[NLD + i] = 2u * (uint32_t)(min(row, N - 1 - n) * g.ldw + c);
+        }
+      }
+    };
+    // (the uniform part of the address is kept opaque per stage: scalar base + 32-bit lane offset, no 64-bit vector adds)
+    auto k_base = [&](int k0, const char*& pa, const char*& pw) {
+      pa = gA + 2 * (KMAJ ? (size_t)k0 * g.lda : (size_t)k0);
+      pw = gW + 2 * (KMAJ ? (size_t)k0 * g.ldw : (size_t)k0);
+      asm volatile("" : "+s"(pa), "+s"(pw));
+    };
+    auto load_one = [&](uint16_t* la, uint16_t* lw, const char* pa, const char* pw, int i) {
+      uint32_t o = goff[i];
+      asm volatile("" : "+v"(o));
+      if (i < NLD)
+        __builtin_amdgcn_global_load_lds(RLHF_GLOBAL_PTR(pa + o), RLHF_LDS_PTR(la + 8 * (NLD * wave + i) * DK), 16, 0, 0);
+      else
+        __builtin_amdgcn_global_load_lds(RLHF_GLOBAL_PTR(pw + o), RLHF_LDS_PTR(lw + 8 * (NLD * wave + i - NLD) * DK),
+                                         16, 0, 0);
+    };
+
+    const int a_off = (wm + l32) * DK, w_off = (wn + l32) * DK;
+    // sub-step s (16 of the 64 k of a stage) reads logical chunks 2s and 2s+1: one per half-wave
+    // KMAJ: sub-step s reads k-rows 16s + 8hf .. +7 (256 halfs per row); the column part of a lane's address, with
+    // the row swizzle, is fixed per fragment
+    const int ch0 = KMAJ ? (0 + 8 * hf) * 256 : ((0 + hf) ^ key) << 3, ch1 = KMAJ ? (16 + 8 * hf) * 256 : ((2 + hf) ^ key) << 3,
+              ch2 = KMAJ ? (32 + 8 * hf) * 256 : ((4 + hf) ^ key) << 3, ch3 = KMAJ ? (48 + 8 * hf) * 256 : ((6 + hf) ^ key) << 3;
+    int koff[MT + NT];
+    if (KMAJ) {
+      const int r = lane & 15, gsel = (lane >> 4) & 1;
+#pragma unroll
+      for (int q = 0; q < MT + NT; ++q) {
+        const int colb = (q < MT ? wm + 32 * q : wn + 32 * (q - MT)) + 16 * gsel;  // first column of the group's 16
+        const int chunk = ((colb >> 3) + ((r & 3) >> 1)) ^ (2 * ((r >> 2) & 3));
+        koff[q] = (r >> 2) * 256 + chunk * 8 + (r & 1) * 4;
+      }
+    }
+
+    f32x16_t acc[NT][MT];
+    // fragment buffers, used alternately by the four sub-steps of a stage.  Weights are the first
+    // matrix operand: accumulator element e of a lane is then (n = 8*(e/4) + 4*(lane/32) + e%4,
+    // m = lane%32), i.e. 4 consecutive output columns per lane
+    f16x8_t fa0[MT], fw0[NT], fa1[MT], fw1[NT];
+    auto frag_one = [&](const uint16_t* la, const uint16_t* lw, int ch, int q, f16x8_t* fa, f16x8_t* fw) {
+      const uint16_t* ls = q < MT ? la : lw;
+      f16x8_t v;
+      if (KMAJ) {
+        typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+        typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+        typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(ls + koff[q] + ch));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(ls + koff[q] + ch + 4 * 256));
+        const s16x8_t b = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        v = __builtin_bit_cast(f16x8_t, b);
+      } else {
+        v = *(const f16x8_t*)(ls + (q < MT ? a_off + q * 32 * DK : w_off + (q - MT) * 32 * DK) + ch);
+      }
+      if (q < MT) fa[q] = v;
+      else fw[q - MT] = v;
+    };
+  // NMF matrix instructions on (FA, FW); after the n-th, fragment read n (n < MT + NT) of the next
+  // sub-step from (LA, LW, CH) into (GA, GW) and, if LOAD, tile load n of the stage at (pa, pw)
+#define RLHF_SUB(FA, FW, LA, LW, CH, GA, GW, LOAD, SA, SW)                                         \
+  _Pragma("unroll") for (int n = 0; n < NMF; ++n) {                                               \
+    const int mi = ((n >> 2) & 1) ? 3 - (n & 3) : (n & 3); /* serpentine: one operand changes at a time */ \
+    acc[n >> 2][mi] = __builtin_amdgcn_mfma_f32_32x32x16_f16(FW[n >> 2], FA[mi],                  \
+                                                             acc[n >> 2][mi], 0, 0, 0);           \
+    __builtin_amdgcn_sched_barrier(0);                                                            \
+    if (n < MT + NT) frag_one(LA, LW, CH, n, GA, GW);                                             \
+    if (LOAD && n < 2 * NLD) load_one(SA, SW, pa, pw, n);                                         \
+    __builtin_amdgcn_sched_barrier(0);                                                            \
+  }
+  // vmcnt(0) lgkmcnt(0) + barrier: every wave's tile loads have landed and every wave has finished
+  // reading the current stage
+#define RLHF_WAIT_BARRIER()                      \
+  __builtin_amdgcn_sched_barrier(0);             \
+  asm volatile("" ::: "memory");                 \
+  __builtin_amdgcn_s_waitcnt(0x0070);            \
+  __builtin_amdgcn_s_barrier();                  \
+  asm volatile("" ::: "memory");                 \
+  __builtin_amdgcn_sched_barrier(0);
+  // One stage (K depth 64).  The first three sub-steps read their successors' fragments from the stage itself (CA, CW).
+  // After the barrier it is free and (OA, OW) holds the next stage: the last sub-step reads the next
+  // stage's first fragments from there and issues the loads at K offset KL into (CA, CW), so a
+  // load has a whole stage of matrix work to land.
+#define RLHF_STAGE(CA, CW, OA, OW, KL)                                                            \
+  {                                                                                               \
+    const char *pa, *pw;                                                                          \
+    k_base(KL, pa, pw);                                                                           \
+    RLHF_SUB(fa0, fw0, CA, CW, ch1, fa1, fw1, false, CA, CW)                                      \
+    RLHF_SUB(fa1, fw1, CA, CW, ch2, fa0, fw0, false, CA, CW)                                      \
+    RLHF_SUB(fa0, fw0, CA, CW, ch3, fa1, fw1, false, CA, CW)                                      \
+    RLHF_WAIT_BARRIER()                                                                           \
+    RLHF_SUB(fa1, fw1, OA, OW, ch0, fa0, fw0, true, CA, CW)                                       \
+  }
+    if (mine > 0) {
+      set_item(item_at(0), m0, n0, nk, out);
+      const char *pa, *pw;
+      k_base(0, pa, pw);
+#pragma unroll
+      for (int i = 0; i < 2 * NLD; ++i) load_one(la0, lw0, pa, pw, i);
+      k_base(DK, pa, pw);
+#pragma unroll
+      for (int i = 0; i < 2 * NLD; ++i) load_one(la1, lw1, pa, pw, i);
+      RLHF_WAIT_BARRIER()
+    }
+    for (int it = 0; it < mine; ++it) {
+      // here stage 0 of this tile is in LDS for every wave, and its stage 1 has been requested
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int c = n0 + wn + 32 * j + 8 * g + 4 * hf;
-          const int sec = c >= 2 * qd ? 2 : (c >= qd ? 1 : 0);
-          const int e = (c - sec * qd) % qk.hd;
-          ang[j][g] = (sec < 2 && e < qk.r && c < N) ? (e >> 1) : -1;
-        }
-    }
-    auto put = [&](auto jc, auto ic) {
-      constexpr int j = decltype(jc)::value, i = decltype(ic)::value;
-      const int row = 32 * i + l32;
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f16x4_t h;
-        if (EPI == EPI_QKV) {
-          float v[4];
+          for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = acc[j][i][4 * g + u] + bias_v[j][g][u];
-          if (ang[j][g] >= 0) {
-            // the stand-alone kernel turns values already rounded to fp16: keep that order of roundings
-            const f32x2_t co = *(const f32x2_t*)(qk.cos_t + prow[i] + ang[j][g]);
-            const f32x2_t si = *(const f32x2_t*)(qk.sin_t + prow[i] + ang[j][g]);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              const float lo = (float)from_f32<half_t>(v[2 * u]), hi = (float)from_f32<half_t>(v[2 * u + 1]);
-              v[2 * u] = lo * co[u] - hi * si[u];
-              v[2 * u + 1] = hi * co[u] + lo * si[u];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) h[u] = from_f32<half_t>(v[u]);
-        } else {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float v = acc[j][i][4 * g + u] + bias_v[j][g][u];
-            h[u] = from_f32<half_t>(EPI == EPI_BIAS_GELU ? gelu_f16out(v) : v);
-          }
-        }
-        *(f16x4_t*)(ep + row * WN + (((4 * j + g) ^ (row & (CH - 1))) << 3) + 4 * hf) = h;
+      for (int q = 0; q < MT + NT; ++q) frag_one(la0, lw0, ch0, q, fa0, fw0);
+      // K is a multiple of 2*DK here (the launcher routes other shapes to the staged kernel)
+      for (int kt = 0; kt + 2 < nk; kt += 2) {
+        RLHF_STAGE(la0, lw0, la1, lw1, (kt + 2) * DK)
+        RLHF_STAGE(la1, lw1, la0, lw0, (kt + 3) * DK)
       }
-    };
-#define RLHF_ROW(J)                                                                        \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 0>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 1>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 2>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 3>{});
-    RLHF_ROW(0) RLHF_ROW(1)
-    if constexpr (NT > 2) { RLHF_ROW(NT - 2) RLHF_ROW(NT - 1) }
-#undef RLHF_ROW
-    RLHF_WAVE_LDS_FENCE();
-    const int gcol = n0 + wn + rd_c * 8;
-    if (EPI == EPI_QKV) {
-      // this lane's 16-byte chunk lies in one head of one section (head_dim is a multiple of 8)
-      const int sec = gcol >= 2 * qd ? 2 : (gcol >= qd ? 1 : 0);
-      const int hh = (gcol - sec * qd) / qk.hd, e = gcol - sec * qd - hh * qk.hd;
-      half_t* cache = (half_t*)(sec == 1 ? qk.kc : qk.vc);
-#pragma unroll 8
-      for (int it = 0; it < 128 / RPI; ++it) {
-        const int row = it * RPI + rd_row;
-        const int grow = m0 + wm + row;
-        const u32x4_t v = *(const u32x4_t*)(ep + row * WN + ((rd_c ^ (row & (CH - 1))) << 3));
-        if (grow < M && gcol < N) {
-          const int t = M_sub + grow;  // packed row: the row chunk of this launch starts at M_sub
-          if (sec == 0) {
-            *(u32x4_t*)((half_t*)qk.q + (size_t)t * qd + gcol) = v;
-          } else {
-            const int b = qk.rowid ? qk.rowid[t] : t;
-            const long slot = (long)qk.kvoff[b] * qk.H + (qk.pos[t] + qk.pos_add) + (long)hh * (qk.len[b] + qk.kv_extra);
-            *(u32x4_t*)(cache + (size_t)slot * qk.hd + e) = v;
+      // The last two stages request the first two of the block's next tile; after its last tile they re-issue a stage
+      // that nobody reads.
+      const int cm0 = m0, cn0 = n0;
+      void* const cout = out;
+      int kl0 = (nk - 1) * DK, kl1 = kl0;
+      if (it + 1 < mine) {
+        set_item(item_at(it + 1), m0, n0, nk, out);
+        kl0 = 0;
+        kl1 = DK;
+      }
+      u32x2_t bv[2][4], bv2[2][4];
+      int prow[MT];
+      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_QKV) dma_load_bias(g.bias, cn0 + wn, N, hf, bv);
+      if (EPI == EPI_QKV) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          prow[i] = (qk.pos[g.M_sub + min(cm0 + wm + 32 * i + l32, M - 1)] + qk.pos_add) * (qk.r >> 1);
+      }
+      RLHF_STAGE(la0, lw0, la1, lw1, kl0)
+      RLHF_STAGE(la1, lw1, la0, lw0, kl1)
+      if (EPI == EPI_BIAS_RESADD) {  // (two biases do not fit the registers beside the main loop's)
+        dma_load_bias(g.bias, cn0 + wn, N, hf, bv);
+        dma_load_bias(g.bias2, cn0 + wn, N, hf, bv2);
+      }
+      dma_epilogue<EPI, MT>(g, lse, qk, cout, acc, cm0 + wm, cn0 + wn, M, ep, lane, bv, bv2, prow);
+    }
+#undef RLHF_STAGE
+#undef RLHF_SUB
+  }
+
+  // ---- the rest: 128x128 tiles, 8 waves (4 x 2) of 32x64, two 64 KB stages of K depth 128 (k 0..63 of the A rows, then
+  //      of the W rows, in one array and k 64..127 in the other)
+  if (KMAJ || !cut || rem == 0) return;
+  if constexpr (!KMAJ) {
+    const int n_sub = 4 * rem, per_sx = (n_sub + 7) >> 3;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+    const int nk = g.K / (2 * DK);
+    for (int j = slot_x; j < per_sx; j += P) {
+      const int st = xcd * per_sx + j;
+      if (st >= n_sub) break;
+      int m0, n0;
+      tile_pos(full * G + (st >> 2), m0, n0);
+      m0 += 128 * ((st >> 1) & 1);
+      n0 += 128 * (st & 1);
+      if (m0 >= M || (EPI != EPI_LSE && n0 >= N)) continue;  // (EPI_LSE: columns past N leave empty parts)
+      const int nw = min(n0, N - 1);  // (first W row to read)
+      uint32_t goff[4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = 8 * (2 * wave + i) + (lane >> 3);
+        const int c = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+        goff[i] = 2u * (uint32_t)(min(row, M - 1 - m0) * g.lda + c);
+        goff[2 + i] = 2u * (uint32_t)((min(n0 + row, N - 1) - nw) * g.ldw + c);
+      }
+      const char* const gA = (const char*)(g.A + (size_t)m0 * g.lda);
+      const char* const gW = (const char*)(g.W + (size_t)nw * g.ldw);
+      auto load_stage = [&](uint16_t* s0, uint16_t* s1, int kt) {
+        const size_t k0 = (size_t)min(kt, nk - 1) * (2 * DK);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const char *pa = gA + 2 * (k0 + h * DK), *pw = gW + 2 * (k0 + h * DK);
+          asm volatile("" : "+s"(pa), "+s"(pw));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            uint32_t o = goff[i];
+            asm volatile("" : "+v"(o));
+            __builtin_amdgcn_global_load_lds(RLHF_GLOBAL_PTR((i < 2 ? pa : pw) + o),
+                                             RLHF_LDS_PTR((h ? s1 : s0) + ((i >> 1) * 128 + 8 * (2 * wave + (i & 1))) * DK),
+                                             16, 0, 0);
           }
-        }
-      }
-      return;
-    }
-#pragma unroll 8
-    for (int it = 0; it < 128 / RPI; ++it) {
-      const int row = it * RPI + rd_row;
-      const int grow = m0 + wm + row;
-      const u32x4_t v = *(const u32x4_t*)(ep + row * WN + ((rd_c ^ (row & (CH - 1))) << 3));
-      if (grow < M && gcol < N) *(u32x4_t*)((half_t*)out + (size_t)grow * ldo + gcol) = v;
-    }
-  } else {
-    float* epf = (float*)ep;   // 128 rows x PC floats per pass
-    constexpr int PC = WN / 2;  // columns per pass; a row is PC/4 = CH 16-byte chunks, as in the fp16 case
-    constexpr int JP = NT / 2;  // accumulator tiles along N per pass
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int gcol = n0 + wn + PC * hh + rd_c * 4;
-      // residual rows of this pass: all loads are issued before the transpose, so their latency
-      // hides behind the LDS traffic
-      f32x4_t xv[128 / RPI];
-      if (EPI == EPI_BIAS_RESADD) {
-#pragma unroll
-        for (int it = 0; it < 128 / RPI; ++it) {
-          const int grow = m0 + wm + it * RPI + rd_row;
-          if (grow < M && gcol < N) xv[it] = *(const f32x4_t*)((const float*)out + (size_t)grow * ldo + gcol);
-        }
-      }
-      auto put = [&](auto jc, auto ic) {
-        constexpr int j = decltype(jc)::value, i = decltype(ic)::value;
-        const int row = 32 * i + l32;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4_t v = {acc[j][i][4 * g] + bias_v[j][g][0], acc[j][i][4 * g + 1] + bias_v[j][g][1],
-                             acc[j][i][4 * g + 2] + bias_v[j][g][2], acc[j][i][4 * g + 3] + bias_v[j][g][3]};
-          const int c = 8 * (j % JP) + 2 * g + hf;
-          *(f32x4_t*)(epf + row * PC + ((c ^ (row & (CH - 1))) << 2)) = v;
         }
       };
-#define RLHF_ROW(J)                                                                        \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 0>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 1>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 2>{});                 \
-  put(std::integral_constant<int, J>{}, std::integral_constant<int, 3>{});
-      if constexpr (NT > 2) {
-        if (hh == 0) { RLHF_ROW(0) RLHF_ROW(1) } else { RLHF_ROW(NT - 2) RLHF_ROW(NT - 1) }
-      } else {
-        if (hh == 0) { RLHF_ROW(0) } else { RLHF_ROW(1) }
-      }
-#undef RLHF_ROW
-      RLHF_WAVE_LDS_FENCE();
+      f32x16_t acc[2][1];
 #pragma unroll
-      for (int it = 0; it < 128 / RPI; ++it) {
-        const int row = it * RPI + rd_row;
-        const int grow = m0 + wm + row;
-        f32x4_t v = *(const f32x4_t*)(epf + row * PC + ((rd_c ^ (row & (CH - 1))) << 2));
-        if (grow < M && gcol < N) {
-          if (EPI == EPI_BIAS_RESADD) v += xv[it];
-          *(f32x4_t*)((float*)out + (size_t)grow * ldo + gcol) = v;
+      for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[jj][0][e] = 0.f;
+      // one stage: once its loads have landed for every wave (and every wave has left the stage before), the next stage is
+      // requested into the one just left
+      auto stage = [&](const uint16_t* c0, const uint16_t* c1, uint16_t* n0, uint16_t* n1, int kt) {
+        RLHF_WAIT_BARRIER()
+        load_stage(n0, n1, kt + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint16_t* cur = h ? c1 : c0;
+          f16x8_t fa[4], fw[4][2];
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) {
+            const int ch = ((2 * ks + hf) ^ key) << 3;
+            fa[ks] = *(const f16x8_t*)(cur + (wm + l32) * DK + ch);
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) fw[ks][jj] = *(const f16x8_t*)(cur + (128 + wn + 32 * jj + l32) * DK + ch);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              acc[jj][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[ks][jj], fa[ks], acc[jj][0], 0, 0, 0);
         }
+      };
+      RLHF_WAIT_BARRIER()  // every wave is done with the stages
+      load_stage(la0, lw0, 0);
+      for (int kt = 0; kt < nk; kt += 2) {
+        stage(la0, lw0, la1, lw1, kt);
+        if (kt + 1 >= nk) break;
+        stage(la1, lw1, la0, lw0, kt + 1);
       }
-      RLHF_WAVE_LDS_FENCE();
+      u32x2_t bv[2][4], bv2[2][4];
+      int prow[1];
+      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESADD || EPI == EPI_QKV)
+        dma_load_bias(g.bias, n0 + wn, N, hf, bv);
+      if (EPI == EPI_BIAS_RESADD) dma_load_bias(g.bias2, n0 + wn, N, hf, bv2);
+      if (EPI == EPI_QKV) prow[0] = (qk.pos[g.M_sub + min(m0 + wm + l32, M - 1)] + qk.pos_add) * (qk.r >> 1);
+      dma_epilogue<EPI, 1>(g, lse, qk, g.out, acc, m0 + wm, n0 + wn, M, ep, lane, bv, bv2, prow);
     }
   }
-#undef RLHF_WAVE_LDS_FENCE
+#undef RLHF_WAIT_BARRIER
 }
+#undef RLHF_WAVE_LDS_FENCE
 
 template <int EPI>
 static void launch_f16_dma(const GemmArgs& a, hipStream_t s, int k_slices = 1, int k_slice = 0) {
-  const int nb_m = (a.M_max + 255) / 256, nb_n = (a.N + 255) / 256;
-  const int per_xcd = (nb_m * nb_n + 7) / 8;
-  // Eight waves measure 8-10 % faster than four on the layer shapes.
-  constexpr int WV = kDmaWaves;
   const bool split = k_slices > 1;
-  const dim3 grid(per_xcd * 8, split ? k_slices : 1), block(64 * WV);
-  void* out = split ? a.splitk_ws : a.out;
-  const int ldo = split ? a.N : a.ldo, ks = split ? k_slice : 0;
-  const size_t slab = split ? (size_t)a.M_max * a.N : (size_t)0;
+  DmaArgs g;
+  g.A = (const half_t*)a.A;
+  g.W = (const half_t*)a.W;
+  g.bias = (const bf16_t*)a.bias;
+  g.bias2 = (const bf16_t*)a.bias2;
+  g.out = split ? a.splitk_ws : a.out;
+  g.M_dev = a.M_dev;
+  g.M_max = a.M_max; g.M_sub = a.M_sub; g.N = a.N; g.K = a.K;
+  g.ldo = split ? a.N : a.ldo;
+  g.slices = split ? k_slices : 1;
+  g.k_slice = split ? k_slice : 0;
+  g.slab = split ? (size_t)a.M_max * a.N : (size_t)0;
+  const dim3 grid(kCUs), block(512);
   if constexpr (EPI == EPI_F32) {
     if (a.k_major) {
-      hipLaunchKernelGGL((gemm_f16_dma_kernel<EPI_F32, WV, true>), grid, block, 0, s, (const half_t*)a.A,
-                         (const half_t*)a.W, (const bf16_t*)nullptr, out, a.M_max, (const int*)nullptr, 0, a.N, a.K, ldo,
-                         nb_m, nb_n, a.lda ? a.lda : a.M_max, a.ldw ? a.ldw : a.N, (const bf16_t*)nullptr, LseArgs{},
-                         QkvArgs{}, ks, slab);
+      g.lda = a.lda ? a.lda : a.M_max;
+      g.ldw = a.ldw ? a.ldw : a.N;
+      hipLaunchKernelGGL((gemm_f16_dma_kernel<EPI_F32, true>), grid, block, 0, s, g, LseArgs{}, QkvArgs{});
       return;
     }
   }
-  hipLaunchKernelGGL((gemm_f16_dma_kernel<EPI, WV>), grid, block, 0, s, (const half_t*)a.A, (const half_t*)a.W,
-                     (const bf16_t*)a.bias, out, a.M_max, a.M_dev, a.M_sub, a.N, a.K, ldo, nb_m, nb_n,
-                     a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K, (const bf16_t*)a.bias2, a.lse ? *a.lse : LseArgs{},
-                     a.qkv ? *a.qkv : QkvArgs{}, ks, slab);
+  g.lda = a.lda ? a.lda : a.K;
+  g.ldw = a.ldw ? a.ldw : a.K;
+  hipLaunchKernelGGL((gemm_f16_dma_kernel<EPI, false>), grid, block, 0, s, g, a.lse ? *a.lse : LseArgs{},
+                     a.qkv ? *a.qkv : QkvArgs{});
 }
 
 #ifndef RLHF_GEMM_DMA
@@ -846,7 +1000,7 @@ bool gemm_takes_qkv(int dtype, const GemmArgs& a, int H, int hd, int r) {
 }
 // Parts (column groups with their own max / sum-exp) the log-sum-exp epilogue leaves per row: one per wave
 // column of every 256-column tile.
-int gemm_lse_parts(int n_cols) { return (kDmaWaves == 8 ? 4 : 2) * ((n_cols + 255) / 256); }
+int gemm_lse_parts(int n_cols) { return 4 * ((n_cols + 255) / 256); }
 
 template <int EPI>
 static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {

@@ -75,9 +75,14 @@ int main(int argc, char** argv) {
   CK(hipMemcpy(dpos, hpos.data(), hpos.size() * 4, hipMemcpyHostToDevice)); CK(hipMemcpy(drow, hrow.data(), hrow.size() * 4, hipMemcpyHostToDevice));
   CK(hipMemcpy(dkv, hkv.data(), hkv.size() * 4, hipMemcpyHostToDevice)); CK(hipMemcpy(dlen, hlen.data(), hlen.size() * 4, hipMemcpyHostToDevice));
   CK(hipMemcpy(dcs, hcs.data(), hcs.size() * 4, hipMemcpyHostToDevice)); CK(hipMemcpy(dsn, hsn.data(), hsn.size() * 4, hipMemcpyHostToDevice));
+  std::vector<KvSlot> hslot(M + 1000, KvSlot{0, 0});
+  for (int t = 0; t < M; ++t) hslot[t] = KvSlot{(uint32_t)(hkv[hrow[t]] * H + hpos[t]), (uint32_t)hlen[hrow[t]]};
+  KvSlot* dslot;
+  CK(hipMalloc(&dslot, hslot.size() * sizeof(KvSlot)));
+  CK(hipMemcpy(dslot, hslot.data(), hslot.size() * sizeof(KvSlot), hipMemcpyHostToDevice));
   QkvArgs qa;
-  qa.pos = dpos; qa.rowid = drow; qa.kvoff = dkv; qa.len = dlen; qa.cos_t = dcs; qa.sin_t = dsn; qa.q = dq; qa.kc = dkc; qa.vc = dvc;
-  qa.kv_extra = 0; qa.pos_add = 0; qa.H = H; qa.hd = hd; qa.r = r;
+  qa.pos = dpos; qa.slots = dslot; qa.cos_t = dcs; qa.sin_t = dsn; qa.q = dq; qa.kc = dkc; qa.vc = dvc;
+  qa.pos_add = 0; qa.H = H; qa.hd = hd; qa.r = r;
   int bad = 0;
   for (auto& s : shapes) {
     GemmArgs g;

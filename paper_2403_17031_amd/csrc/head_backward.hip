@@ -340,7 +340,7 @@ __global__ void __launch_bounds__(256)
 // Sums part [waves][2][d] over the waves (a multiple of 4): four interleaved chains per column, added at the end -- a fixed
 // order.  A block owns 32 columns (one 128-byte line of a row): its 1024 threads bring 256 rows at a time through LDS, two
 // chunks ahead of the 128 threads that add up one chain of one column each.  With one thread per column, six blocks
-// waited for 512 loads one after the other: 160 us at width 768 (2048 waves), now 9.
+// waited for 512 loads one after the other: 160 us at width 768 (2048 waves), now 11.
 constexpr int kSumChunk = 256;
 __global__ void __launch_bounds__(1024)
     ln_backward_rows_final_kernel(const float* __restrict__ part, int waves, int d, float* __restrict__ d_g,

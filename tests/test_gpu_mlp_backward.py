@@ -73,6 +73,13 @@ def test_bf16_mode(gpu, T, d, F):
     _check(gpu, _cfg(d, F, "bf16"), T, seed=T, layer=0, scale=8.0)
 
 
+@pytest.mark.parametrize("T", [600, 5000, 8200, 8703])
+def test_rounds_of_the_large_product(gpu, T):
+    """FC1's product has ceil(T / 256) x 8 tiles of 256 x 256 for 256 blocks: only quarter tiles (24), one unfilled round of
+    whole tiles (160), a whole round and quarter tiles (264, 272), the last of them without rows."""
+    _check(gpu, _cfg(256, 2048, "bf16"), T, seed=T, layer=0, scale=8.0)
+
+
 def test_linear_in_the_upstream_gradient_and_deterministic(gpu):
     cfg = _cfg(128, 512, "fp32")
     w = make_weights(cfg, 44, variant="test")
