@@ -8,6 +8,17 @@
 
 namespace rlhf {
 
+// Sum over the N lanes (a power of two) of a lane's group, in all of them: exchanges with lane ^ N/2, ..., ^ 1.
+template <int N>
+__device__ __forceinline__ float row_fold(float v) {
+  if constexpr (N > 1) {
+    v += lane_xor<N / 2>(v);
+    return row_fold<N / 2>(v);
+  }
+  return v;
+}
+
+
 // =================================================================================================
 // Generic tile kernel (any storage type, any head_dim <= 256): 32 queries x 32 keys per step,
 // fp32 throughout, online softmax.  Used for fp32 check mode and as the fallback.
@@ -272,7 +283,7 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
     for (int kf = 0; kf < 2; ++kf)
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[kf][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = half_max(mx);
     const float m_new = fmaxf(m_run, mx * scale_log2e);  // finite: key 0 is visible to every query
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // arguments <= 0: the bare instruction will do
     m_run = m_new;
@@ -314,7 +325,7 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
       __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
     }
   }
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const float l_tot = half_sum(l_run);
   if (qi < n) {
     const float inv = 1.0f / l_tot;
     half_t* orow = out + ((size_t)cu[b] + qi) * out_ld + (size_t)h * HD;
@@ -499,9 +510,8 @@ __global__ void __launch_bounds__(256)
         __builtin_memcpy(&kk, &w, 4);
         pd = __builtin_amdgcn_fdot2(kk, qv[i], pd, false);
       }
-      if (POW2) {
-#pragma unroll
-        for (int o = CPR >> 1; o > 0; o >>= 1) pd += __shfl_xor(pd, o, 64);
+      if constexpr (POW2) {
+        pd = row_fold<CPR>(pd);
         if (part == 0 && j < ctx) sc[j] = pd * scale;
       } else {
         if (active && it < n_it) scratch[it * ACTIVE + lane] = pd;  // row j's CPR partials are contiguous

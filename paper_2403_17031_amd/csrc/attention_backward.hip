@@ -631,7 +631,7 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
     for (int kf = 0; kf < 2; ++kf)
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[kf][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = half_max(mx);
     const float m_new = fmaxf(m_run, mx * scale_log2e);  // finite: key 0 is visible to every query
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     m_run = m_new;
@@ -654,7 +654,7 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
     }
     BWD_OUT(Vt, pf, acc)
   }
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const float l_tot = half_sum(l_run);
   const float inv = 1.0f / l_tot;
   const float lse2 = m_run + __builtin_amdgcn_logf(l_tot);  // log2 of the row's sum of exponentials
   // O_i (optional output) and delta_i = dO_i . O_i: this lane holds 4-dim groups of its query's output
@@ -679,7 +679,7 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
         }
       }
   }
-  dl += __shfl_xor(dl, 32, 64);
+  dl = half_sum(dl);
   if (qi < n && half == 0) {
     lse[(size_t)(s0 + qi) * H + h] = lse2 * 0.6931471805599453f;  // natural logarithm, as the key-side kernels read it
     delta[(size_t)(s0 + qi) * H + h] = dl;

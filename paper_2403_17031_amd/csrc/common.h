@@ -54,15 +54,64 @@ __device__ __forceinline__ half_t from_f32<half_t>(float f) {  // round to neare
   return (half_t)fminf(fmaxf(f, -65504.0f), 65504.0f);
 }
 
+// Exchanges between the lanes of a wave as register moves (DPP within 16 lanes, permlane swaps between them; all lanes take
+// part).  __shfl_xor goes through the LDS pipe, a hundred cycles of latency a step, which is what a LayerNorm row or a
+// softmax waits for: a 64-lane sum of six of them is six dependent round trips.
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ int dpp_mov(int v, int old = 0) {
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, BANKS, false);
+}
+// lane i: the value of lane i ^ O
+template <int O>
+__device__ __forceinline__ int lane_xor(int v) {
+  static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "one bit");
+  if constexpr (O == 1) return dpp_mov<0xB1>(v);  // quad_perm 1,0,3,2
+  if constexpr (O == 2) return dpp_mov<0x4E>(v);  // quad_perm 2,3,0,1
+  if constexpr (O == 4) return dpp_mov<0x114, 0xA>(v, dpp_mov<0x104, 0x5>(v));  // shifts by 4 in a row of 16, per bank
+  if constexpr (O == 8) return dpp_mov<0x128>(v);  // rotation of a row by 8
+  const bool upper = (threadIdx.x & O) != 0;  // (blocks are whole waves)
+  if constexpr (O == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    return (int)(upper ? p[0] : p[1]);
+  }
+  const auto p = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return (int)(upper ? p[0] : p[1]);
+}
+template <int O>
+__device__ __forceinline__ float lane_xor(float v) {
+  return __int_as_float(lane_xor<O>(__float_as_int(v)));
+}
+// op over all lanes, in all lanes: the tree that exchanges with lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 in this order (op
+// commutative).  The swaps leave both partners' values in either lane, and after the steps before it a value repeats
+// every 8, 4 or 2 lanes, so that a rotation of a row is the same exchange.
+template <typename OP>
+__device__ __forceinline__ float wave_fold(float v, OP op) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+  v = op(v, __int_as_float(dpp_mov<0x128>(__float_as_int(v))));
+  v = op(v, __int_as_float(dpp_mov<0x124>(__float_as_int(v))));
+  v = op(v, __int_as_float(dpp_mov<0x122>(__float_as_int(v))));
+  return op(v, __int_as_float(dpp_mov<0x121>(__float_as_int(v))));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_fold(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_fold(v, [](float a, float b) { return fmaxf(a, b); });
+}
+// op with lane ^ 32, in both lanes
+template <typename OP>
+__device__ __forceinline__ float half_fold(float v, OP op) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ __forceinline__ float half_sum(float v) {
+  return half_fold(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float half_max(float v) {
+  return half_fold(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }

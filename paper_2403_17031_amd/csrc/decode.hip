@@ -43,8 +43,9 @@ __global__ void __launch_bounds__(1024)
                      AT* __restrict__ out1, const WT* __restrict__ g2, const WT* __restrict__ b2, AT* __restrict__ out2,
                      const float* __restrict__ part, size_t slab, const WT* __restrict__ bias_a,
                      const WT* __restrict__ bias_b, int write_x) {
-  __shared__ float sh[2][16];
+  __shared__ __attribute__((aligned(16))) float sh[2][16];
   const int r = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  if (lane < 32 && wave == 0 && (lane & 15) >= waves) sh[lane >> 4][lane & 15] = 0.f;
   const int c = 4 * threadIdx.x;
   const bool in = c < d;
   const int cc = in ? c : 0;
@@ -72,8 +73,13 @@ __global__ void __launch_bounds__(1024)
     s = wave_sum(s);
     if (lane == 0) buf[wave] = s;
     __syncthreads();
-    float tot = buf[0];
-    for (int w = 1; w < waves; ++w) tot += buf[w];
+    // (buf is zero past the block's waves, so that all sixteen are read at once)
+    dc_f32x4_t t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = *(const dc_f32x4_t*)(buf + 4 * i);
+    float tot = t[0][0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) tot += t[w >> 2][w & 3];
     return tot;
   };
   const float mean = block_sum(in ? (v[0] + v[1]) + (v[2] + v[3]) : 0.f, sh[0]) / (float)d;
@@ -220,11 +226,17 @@ __global__ void __launch_bounds__(64 * WV)
   float* pdw = s_pd + (POW2 ? 0 : wave * (U * G * PDS));
   auto row_sums = [&](float* pd, auto nu) {
     constexpr int NU = decltype(nu)::value;
-    if (POW2) {
+    if constexpr (POW2) {
 #pragma unroll
-      for (int o = 1; o < CPR; o <<= 1)
-#pragma unroll
-        for (int u = 0; u < NU; ++u) pd[u] += __shfl_xor(pd[u], o, 64);
+      for (int u = 0; u < NU; ++u) {
+        if (CPR > 1) pd[u] += lane_xor<1>(pd[u]);
+        if (CPR > 2) pd[u] += lane_xor<2>(pd[u]);
+        // (the value repeats every 4, 8 lanes by now: mirroring a half row, a row, is the exchange with lane ^ 4, ^ 8)
+        if (CPR > 4) pd[u] += __int_as_float(dpp_mov<0x141>(__float_as_int(pd[u])));
+        if (CPR > 8) pd[u] += __int_as_float(dpp_mov<0x140>(__float_as_int(pd[u])));
+        if (CPR > 16) pd[u] += lane_xor<16>(pd[u]);
+        if (CPR > 32) pd[u] += lane_xor<32>(pd[u]);
+      }
     } else {
       __builtin_amdgcn_wave_barrier();
       if (active) {

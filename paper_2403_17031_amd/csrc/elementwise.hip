@@ -877,8 +877,12 @@ struct SamplePart {
     m = mn;
     const float b = wave_max(best);
     int i = best == b ? bi : 0x7FFFFFFF;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) i = min(i, __shfl_xor(i, o, 64));
+    i = min(i, lane_xor<32>(i));
+    i = min(i, lane_xor<16>(i));
+    i = min(i, lane_xor<8>(i));
+    i = min(i, lane_xor<4>(i));
+    i = min(i, lane_xor<2>(i));
+    i = min(i, lane_xor<1>(i));
     const uint64_t owner = __builtin_amdgcn_ballot_w64(best == b && bi == i);
     zbest = __shfl(zbest, owner ? __builtin_ctzll(owner) : 0, 64);
     best = b;

@@ -375,7 +375,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
           z[j][e] = v;
           m = fmaxf(m, v);
         }
-      m = fmaxf(m, __shfl_xor(m, 32, 64));
+      m = half_max(m);
       float sum = 0.f;
       if (m > -INFINITY) {
 #pragma unroll
@@ -383,7 +383,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
 #pragma unroll
           for (int e = 0; e < 16; ++e) sum += __expf(z[j][e] - m);
       }
-      sum += __shfl_xor(sum, 32, 64);
+      sum = half_sum(sum);
       if (row_ok) {
         if (hf == 0) {
           lse.pmax[(size_t)part * lse.stride + tr] = m;
