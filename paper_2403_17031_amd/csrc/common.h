@@ -283,7 +283,6 @@ struct FewRowsProd {
 };
 struct FewRowsArgs {
   FewRowsProd p[2];
-  int blocks0 = 0;            // set by launch_few_rows
   int M_max = 0, M_sub = 0;
   const int* M_dev = nullptr;
 };

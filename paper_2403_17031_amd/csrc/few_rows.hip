@@ -29,16 +29,49 @@ typedef __attribute__((ext_vector_type(8))) _Float16 fr_f16x8_t;
 typedef __attribute__((ext_vector_type(4))) float fr_f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t fr_u32x4_t;
 
+#define FR_GLOBAL __attribute__((address_space(1)))  // (pointers that come as plain words would be generic ones)
+typedef const FR_GLOBAL char* fr_in_t;
+
 template <typename T>
 struct FrTypes;
 template <>
 struct FrTypes<half_t> {
   typedef bf16_t P;
+  typedef uint64_t B;  // four columns' bias as stored
 };
 template <>
 struct FrTypes<float> {
   typedef float P;
+  typedef fr_f32x4_t B;
 };
+
+// Bias of columns n .. n + 3 (0 past N), kept as stored until it is used; vec: the array is aligned for one load and N a
+// multiple of 4.
+__device__ __forceinline__ uint64_t load_bias(const FR_GLOBAL bf16_t* b, int n, int N, bool vec) {
+  if (vec) return n < N ? *(const FR_GLOBAL uint64_t*)(b + n) : 0;
+  uint64_t v = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (n + u < N) v |= (uint64_t)b[n + u].bits << (16 * u);
+  return v;
+}
+__device__ __forceinline__ fr_f32x4_t load_bias(const FR_GLOBAL float* b, int n, int N, bool vec) {
+  fr_f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+  if (vec) {
+    if (n < N) v = *(const FR_GLOBAL fr_f32x4_t*)(b + n);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (n + u < N) v[u] = b[n + u];
+  }
+  return v;
+}
+__device__ __forceinline__ fr_f32x4_t bias_f32(uint64_t r) {
+  const uint32_t lo = (uint32_t)r, hi = (uint32_t)(r >> 32);
+  return (fr_f32x4_t){__uint_as_float(lo << 16), __uint_as_float(lo & 0xFFFF0000u), __uint_as_float(hi << 16),
+                      __uint_as_float(hi & 0xFFFF0000u)};
+}
+__device__ __forceinline__ fr_f32x4_t bias_f32(fr_f32x4_t v) { return v; }
 
 // 16 bytes of 16 weight rows (first operand) and of 16 rows of A: accumulator element e of lane (l16, q) is
 // (n = 4q + e, m = l16).
@@ -53,66 +86,98 @@ __device__ __forceinline__ fr_f32x4_t fr_mfma(float, fr_u32x4_t w, fr_u32x4_t a,
   return acc;
 }
 
+// A product as the kernel reads it: 128 bytes, fetched by two scalar loads, with every division done by the host.  Coming
+// field by field, each group's address waiting for the one before, the arguments kept a block 1.5 to 2.7 us from its first
+// weight load, and a bias read after the sum kept it another 1 to 2 us from its end (clock readings inside the kernels of a
+// decode pass).  With both moved: 64 rows of width 768 QKV + FC1 7.1 -> 6.1 us, out-projection + FC2 5.8 -> 5.3; 37 of
+// 2048 18.2 -> 17.4, 11.6 -> 11.0; one of 2560 23.9 -> 22.5, 15.2 -> 14.9 (dec_driver, cold).
+struct __attribute__((aligned(64))) FrProd {
+  fr_in_t W, A, W1, A1;  // segment 0, segment 1
+  fr_in_t bias;
+  FR_GLOBAL char* out;
+  uint32_t ldw, ldw1;           // row strides of W, bytes
+  int steps0, steps, per_block, ks_shift;  // steps of segment 0, of both, of a block; log2 of the K split
+  uint32_t a_tile, a_row, a_half, a_q, a_step;
+  int N, ldo, epilogue, packed_K, packed_k0, bias_vec;  // bias_vec: four columns' bias with one load
+  uint32_t slab;
+};
+struct FrArgs {
+  FrProd p[2];
+  int blocks0, M_max, M_sub, pad;
+  const int* M_dev;
+};
+static_assert(sizeof(FrProd) == 128, "two loads of 16 dwords");
+
 // WV: waves per block (they divide K); MT x CT: 16x16 accumulator tiles along M and N per block; PF: steps held in
 // registers; OCC: waves per SIMD the registers are sized for; TWO: K runs over a second pair of operands after the
 // first.
 template <typename T, int WV, int MT, int CT, int PF, int OCC, bool TWO>
-__global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args) {
+__global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FrArgs args) {
   typedef typename FrTypes<T>::P P;
+  typedef __attribute__((ext_vector_type(16))) uint32_t u16x_t;
   __shared__ fr_f32x4_t red[WV * MT * CT * 64];
   const int M = args.M_dev ? min(args.M_max, *args.M_dev - args.M_sub) : args.M_max;
   const int m0 = blockIdx.y * (16 * MT);
   if (m0 >= M) return;
   const bool second = (int)blockIdx.x >= args.blocks0;
-  const int bid = second ? blockIdx.x - args.blocks0 : blockIdx.x;
-  FewRowsProd p = args.p[0];
-  if (!TWO && second) p = args.p[1];  // (a launch of two products has one segment each)
-  const int tile = bid / p.ksplit, z = bid - tile * p.ksplit;
+  FrProd p;
+  {
+    const u16x_t* src = (const u16x_t*)&args.p[second ? 1 : 0];
+    u16x_t both[2] = {src[0], src[1]};
+    __builtin_memcpy(&p, both, sizeof(p));
+  }
+  const int bid = blockIdx.x - (second ? args.blocks0 : 0);
+  const int tile = bid >> p.ks_shift, z = bid - (tile << p.ks_shift);
   const int n0 = tile * (16 * CT);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q = lane >> 4;
 
-  const int steps0 = p.seg[0].steps, steps = steps0 + (TWO ? p.seg[1].steps : 0);
-  const int per_block = (steps + p.ksplit - 1) / p.ksplit;
-  const int b0 = z * per_block, b1 = min(steps, b0 + per_block);
+  const int steps0 = p.steps0, steps = p.steps;
+  const int b0 = z * p.per_block, b1 = min(steps, b0 + p.per_block);
   const int per_wave = (b1 - b0 + WV - 1) / WV;
   const int s0 = b0 + wave * per_wave, s1 = min(b1, s0 + per_wave);
 
+  // The outputs of this thread: result tile ti = wave + it * WV of the block's CT x MT, its lane's four columns of one row.
+  // Their bias is requested ahead of everything else (TWO: products without one): after the sum it would be a cold load
+  // with nothing to hide it.
+  constexpr int IT = (CT * MT + WV - 1) / WV;
+  typename FrTypes<T>::B bias[IT] = {};
+#pragma unroll
+  for (int it = 0; it < IT && !TWO; ++it)
+    if (p.bias) bias[it] = load_bias((const FR_GLOBAL P*)p.bias, n0 + 16 * ((wave + it * WV) / MT) + 4 * q, p.N, p.bias_vec != 0);
+
   // Weight rows: the block's first one as a 64-bit address, a lane's own as a 32-bit offset from it (an output embedding
   // may be larger than 4 GiB, a block's 64 rows are not).
-  const char* wbase[TWO ? 2 : 1];
   uint32_t woff[TWO ? 2 : 1][CT], aoff[TWO ? 2 : 1][MT];
 #pragma unroll
   for (int g = 0; g < (TWO ? 2 : 1); ++g) {
-    const size_t row = (size_t)p.seg[g].ldw * sizeof(T);
-    wbase[g] = (const char*)p.seg[g].W + n0 * row;
+    const uint32_t row = g ? p.ldw1 : p.ldw;
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
-      woff[g][c] = (uint32_t)min(16 * c + l16, p.N - 1 - n0) * (uint32_t)row + 32 * q;
+    for (int c = 0; c < CT; ++c) woff[g][c] = (uint32_t)min(16 * c + l16, p.N - 1 - n0) * row + 32 * q;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const int m = min(m0 + 16 * i + l16, M - 1);
-      aoff[g][i] = (uint32_t)(m >> 4) * p.seg[g].a_tile + (m & 15) * p.seg[g].a_row + q * p.seg[g].a_q;
+      aoff[g][i] = (uint32_t)(m >> 4) * p.a_tile + (m & 15) * p.a_row + q * p.a_q;
     }
   }
+  const fr_in_t wbase[2] = {p.W + (size_t)n0 * p.ldw, TWO ? p.W1 + (size_t)n0 * p.ldw1 : p.W};
   fr_u32x4_t w[PF][CT][2], a[PF][MT][2];
   auto load = [&](int buf, int s) {
     const bool g = TWO && s >= steps0;
     const size_t k = (size_t)(s - (g ? steps0 : 0));
-    const char* wb = (TWO && g ? wbase[TWO ? 1 : 0] : wbase[0]) + k * 128;
-    const char* ab = (const char*)(g ? p.seg[1].A : p.seg[0].A) + k * p.seg[0].a_step;
+    const fr_in_t wb = wbase[TWO && g ? 1 : 0] + k * 128, ab = (TWO && g ? p.A1 : p.A) + k * p.a_step, ab2 = ab + p.a_half;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-      const char* r = wb + (TWO && g ? woff[TWO ? 1 : 0][c] : woff[0][c]);
-      w[buf][c][0] = *(const fr_u32x4_t*)r;
-      w[buf][c][1] = *(const fr_u32x4_t*)(r + 16);
+      const fr_in_t r = wb + (TWO && g ? woff[TWO ? 1 : 0][c] : woff[0][c]);
+      w[buf][c][0] = *(const FR_GLOBAL fr_u32x4_t*)r;
+      w[buf][c][1] = *(const FR_GLOBAL fr_u32x4_t*)(r + 16);
     }
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const char* r = ab + (TWO && g ? aoff[TWO ? 1 : 0][i] : aoff[0][i]);
-      a[buf][i][0] = *(const fr_u32x4_t*)r;
-      a[buf][i][1] = *(const fr_u32x4_t*)(r + p.seg[0].a_half);
+      const uint32_t o = TWO && g ? aoff[TWO ? 1 : 0][i] : aoff[0][i];
+      a[buf][i][0] = *(const FR_GLOBAL fr_u32x4_t*)(ab + o);
+      a[buf][i][1] = *(const FR_GLOBAL fr_u32x4_t*)(ab2 + o);
     }
   };
   fr_f32x4_t acc[CT][MT];
@@ -154,31 +219,32 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
 #pragma unroll
     for (int i = 0; i < MT; ++i) red[((wave * CT + c) * MT + i) * 64 + lane] = acc[c][i];
   __syncthreads();
-  for (int item = tid; item < CT * MT * 64; item += 64 * WV) {
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int ti = wave + it * WV;
+    if (ti >= CT * MT) break;
+    const int item = ti * 64 + lane;
     fr_f32x4_t v = red[item];
 #pragma unroll
     for (int k = 1; k < WV; ++k) v += red[k * CT * MT * 64 + item];
-    const int l = item & 63, ti = item >> 6;
     const int c = ti / MT, i = ti - c * MT;
-    const int m = m0 + 16 * i + (l & 15), n = n0 + 16 * c + 4 * (l >> 4);
+    const int m = m0 + 16 * i + l16, n = n0 + 16 * c + 4 * q;
     if (m >= M || n >= p.N) continue;
     const size_t o = (size_t)m * p.ldo + n;
     const bool vec = n + 4 <= p.N && (p.packed_K || (p.ldo & 3) == 0);
     if (p.epilogue == EPI_F32) {
-      float* out = (float*)p.out + z * p.slab + o;
-      if (vec) *(fr_f32x4_t*)out = v;
+      FR_GLOBAL float* out = (FR_GLOBAL float*)p.out + (size_t)z * p.slab + o;
+      if (vec) *(FR_GLOBAL fr_f32x4_t*)out = v;
       else
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (n + u < p.N) out[u] = v[u];
       continue;
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (p.bias && n + u < p.N) v[u] += to_f32(((const P*)p.bias)[n + u]);
+    if (p.bias) v += bias_f32(TWO ? load_bias((const FR_GLOBAL P*)p.bias, n, p.N, p.bias_vec != 0) : bias[it]);
     if (p.epilogue == EPI_BIAS_RESADD) {
-      float* out = (float*)p.out + o;
-      if (vec) *(fr_f32x4_t*)out += v;
+      FR_GLOBAL float* out = (FR_GLOBAL float*)p.out + o;
+      if (vec) *(FR_GLOBAL fr_f32x4_t*)out += v;
       else
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -189,11 +255,10 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FewRowsArgs args
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] = gelu_erf(v[u]);
     }
-    T* out = (T*)p.out + (p.packed_K ? packed_index<T>(m, p.packed_k0 + n, p.packed_K) : o);
-    T t[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = from_f32<T>(v[u]);
-    if (vec) __builtin_memcpy(__builtin_assume_aligned(out, 4 * sizeof(T)), t, sizeof(t));
+    FR_GLOBAL T* out = (FR_GLOBAL T*)p.out + (p.packed_K ? packed_index<T>(m, p.packed_k0 + n, p.packed_K) : o);
+    typedef __attribute__((ext_vector_type(4))) T t4_t;
+    const t4_t t = {from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
+    if (vec) *(FR_GLOBAL t4_t*)out = t;
     else
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -268,7 +333,7 @@ static FrCut fr_cut(int n_cols_a, int n_cols_b, int steps, int max_split) {
 int few_rows_splits(int N, int steps) { return fr_cut(N, 0, steps, 8).ks; }
 
 template <typename T, bool TWO>
-static void fr_launch(const FewRowsArgs& args, int form, int blocks, hipStream_t s) {
+static void fr_launch(const FrArgs& args, int form, int blocks, hipStream_t s) {
   const int M = args.M_max;
 #define RLHF_FR(ID, WV, MT, CT, PF, OCC)                                                                        \
   case ID:                                                                                                      \
@@ -287,19 +352,43 @@ hipError_t launch_few_rows(int dtype, FewRowsArgs& args, int n_prods, hipStream_
   const FrCut cut = fr_cut(args.p[0].N, n_prods > 1 ? args.p[1].N : 0, steps, split ? 8 : 1);
   if (split && cut.ks != args.p[0].ksplit) return hipErrorInvalidValue;  // few_rows_splits gives the count
   const int form = fr_form(args.M_max, cut.wide, steps / cut.ks), c = kFormCols[form];
+  const uint32_t esz = dtype == 0 ? 4 : 2;
+  FrArgs f = {};
   for (int i = 0; i < n_prods; ++i) {
     FewRowsProd& p = args.p[i];
     if (p.epilogue != EPI_F32) p.ksplit = 1;
     blocks += ((p.N + c - 1) / c) * p.ksplit;
     two = two || p.seg[1].steps > 0;
-    if (i == 0) args.blocks0 = blocks;
+    if (i == 0) f.blocks0 = blocks;
+    FrProd& d = f.p[i];
+    d.W = (fr_in_t)p.seg[0].W; d.A = (fr_in_t)p.seg[0].A;
+    d.W1 = (fr_in_t)p.seg[1].W; d.A1 = (fr_in_t)p.seg[1].A;
+    d.bias = (fr_in_t)(p.epilogue == EPI_F32 ? nullptr : p.bias);
+    d.out = (FR_GLOBAL char*)p.out;
+    d.ldw = (uint32_t)p.seg[0].ldw * esz; d.ldw1 = (uint32_t)p.seg[1].ldw * esz;
+    d.steps0 = p.seg[0].steps;
+    d.steps = p.seg[0].steps + p.seg[1].steps;
+    d.per_block = (d.steps + p.ksplit - 1) / p.ksplit;
+    while ((1 << d.ks_shift) < p.ksplit) ++d.ks_shift;  // (a power of two)
+    d.a_tile = p.seg[0].a_tile; d.a_row = p.seg[0].a_row; d.a_half = p.seg[0].a_half; d.a_q = p.seg[0].a_q;
+    d.a_step = p.seg[0].a_step;
+    if (p.seg[1].steps > 0 && (p.seg[1].a_tile != d.a_tile || p.seg[1].a_row != d.a_row || p.seg[1].a_half != d.a_half ||
+                               p.seg[1].a_q != d.a_q || p.seg[1].a_step != d.a_step))
+      return hipErrorInvalidValue;  // both segments of A lie in one operand
+    d.N = p.N; d.ldo = p.ldo; d.epilogue = p.epilogue; d.packed_K = p.packed_K; d.packed_k0 = p.packed_k0;
+    d.bias_vec = (p.N & 3) == 0 && ((uintptr_t)p.bias & (4 * esz - 1)) == 0;
+    if (p.slab >= ((size_t)1 << 32) || (1 << d.ks_shift) != p.ksplit) return hipErrorInvalidValue;
+    d.slab = (uint32_t)p.slab;
   }
+  f.M_max = args.M_max;
+  f.M_sub = args.M_sub;
+  f.M_dev = args.M_dev;
   if (dtype == 0) {
-    if (two) fr_launch<float, true>(args, form, blocks, s);
-    else fr_launch<float, false>(args, form, blocks, s);
+    if (two) fr_launch<float, true>(f, form, blocks, s);
+    else fr_launch<float, false>(f, form, blocks, s);
   } else {
     if (two) return hipErrorInvalidValue;  // fp16 matrices that are added up lie side by side
-    fr_launch<half_t, false>(args, form, blocks, s);
+    fr_launch<half_t, false>(f, form, blocks, s);
   }
   return hipGetLastError();
 }
