@@ -4,19 +4,19 @@
 //
 // Such a product is its weights' bytes and nothing else: at M = 64 the matrix cores need a tenth of the time the
 // weights take to arrive.  What the kernel is built around is bytes in flight and few launches:
-//   * A block of four waves (eight in one form) owns 32 or 64 output columns for all K of its split; the waves divide K,
-//     each holding the weights of its next PF steps (128 bytes of every weight row per step; PF is two to four) in
-//     registers.  At K = 2560 a wave has ten steps, five in the form of eight waves, four of them in flight.
+//   * A block of four waves owns 32 to 128 output columns for all K of its split; the waves divide K, each holding the
+//     weights of its next PF steps (128 bytes of every weight row per step; PF is two to four) in registers.  At K = 2560
+//     a wave has ten steps.
 //   * Both operands go global -> registers: 16 weight rows x 128 bytes per step, lane (l16, q) taking the 32 bytes at
 //     32q of row l16.  No LDS and no barrier until the waves' partial tiles are added at the end.  Such a load touches
 //     sixteen rows.  The weights, which HBM delivers, can afford that; A, read from L2 once per column block, cannot: its
 //     producers in a decode pass write it packed (packed_index), and a wave's load is contiguous.  QKV + FC1 at width
-//     2560 with packed / row-major A: 8 rows 24 / 26 us, 30 rows 30 / 39, 64 rows 40 / 57.
+//     2560 with packed / row-major A, in the forms of two column tiles: 8 rows 24 / 26 us, 30 rows 30 / 39, 64 rows 40 / 57.
 //   * The sum over K stays in the block (bias, GELU and the fp16 rounding are its epilogue) unless a product has too
 //     few column tiles to cover the chip: then K is cut over blocks into fp32 slabs that the consumer adds in order.
 //   * Two products that are ready together (QKV and FC1 of a parallel-residual layer) share one launch.
-// Width 2560, cold weights (dec_driver): QKV + FC1 24 us for one row (3.8 TB/s), 26 for 16, 30 for 30, 40 for 64;
-// out-projection + FC2 15 to 25; LM head 49 us for one row (5.2 TB/s), 85 for 64.  The weight-streaming kernel of
+// Width 2560, cold weights (dec_driver): QKV + FC1 21 us for one row (4.4 TB/s), 21 for 16, 24 for 30, 29 for 64;
+// out-projection + FC2 13 to 18; LM head 52 us for one row (5.0 TB/s), 73 for 64.  The weight-streaming kernel of
 // gemm_skinny.hip took 17.6 us for a QKV product alone and left slabs to add; the plain fp32 tile kernel 50 us for each
 // product of the 70M shape at two rows (now 4 to 9).
 #include <algorithm>
@@ -281,56 +281,69 @@ bool few_rows_takes(int dtype, const GemmArgs& a) {
          lda * esz < (1ull << 31) && ldw * esz < (1ull << 31);
 }
 
-// Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  Per row count one with 64 columns
-// and one with 32 (two for up to 16 rows: eight waves from 32 steps per block on).
+// Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  A row tile past M costs little, since all
+// of its lanes ask for row M - 1 (a form of three tiles against one of two at 30 rows: 2-4 %), so not every count of row
+// tiles has every count of column tiles.
 #define RLHF_FR_FORMS(X)                                                                                          \
-  X(0, 4, 1, 4, 3, 3) X(1, 8, 1, 2, 4, 4) X(2, 4, 1, 2, 4, 4) X(3, 4, 2, 4, 2, 3) X(4, 4, 2, 2, 3, 3)            \
-  X(5, 4, 3, 4, 2, 2) X(6, 4, 3, 2, 3, 2) X(7, 4, 4, 4, 2, 2) X(8, 4, 4, 2, 3, 2)
-#define RLHF_FR_COLS(ID, WV, MT, CT, PF, OCC) 16 * CT,
-static const int kFormCols[] = {RLHF_FR_FORMS(RLHF_FR_COLS)};
-#undef RLHF_FR_COLS
-
-static int fr_form(int M, bool wide, int steps) {
-  if (M <= 16) return wide ? 0 : (steps >= 32 ? 1 : 2);
-  return M <= 32 ? (wide ? 3 : 4) : (M <= 48 ? (wide ? 5 : 6) : (wide ? 7 : 8));
-}
-
-// How a product is cut: 64 or 32 columns per block, and (max_split > 1) K over up to that many blocks.  What decides
-// is how evenly the blocks cover 256 CUs; 64 columns read A half as often and win until they cover the chip 10 % less
-// evenly, and whatever they cover where blocks of 48 and more steps (6 KB of every weight row) are at least 224.
-// Measured with either column count forced (dec_driver, cold; us with 64 / 32 columns; * the one taken):
-//   QKV + FC1       width  768:  8 rows  6.3 /  5.4*   64 rows 10.6 /  7.2*
-//                         2048:  8 rows 13.8*/ 14.9    64 rows 20.6*/ 22.0
-//                         2560:  8 rows 28.4 / 24.1*   64 rows 40.6 / 39.5*
-//                         3072:  8 rows 34.0*/ 29.8    64 rows 46.7*/ 45.8
-//                         4096:  8 rows 46.4*/ 60.5    64 rows 62.3*/ 73.1
-//   out-proj + FC2        2560:  8 rows 16.8 / 15.2*   64 rows 24.7 / 24.5*
-//                         3072:  8 rows 20.3 / 23.5*   64 rows 29.6 / 30.3*
-//                         4096:  8 rows 31.0*/ 42.6    64 rows 41.5*/ 49.7
-//   LM head               2560:  8 rows 56.3 / 51.6*   64 rows 78.2 / 84.5*
-//                         3072:  8 rows 66.9*/ 60.4    64 rows 88.9*/ 97.4
-// (Width 3072, at 48 steps, is where the second condition changes sides: it costs 12 % at few rows and gains as much in
-// the LM head at 64.)
-struct FrCut {
-  bool wide;
-  int ks;
+  X(0, 4, 1, 2, 4, 4) X(1, 4, 1, 4, 3, 3) X(2, 4, 1, 5, 4, 2) X(3, 4, 2, 2, 3, 3) X(4, 4, 3, 5, 2, 2)            \
+  X(5, 4, 4, 2, 3, 2) X(6, 4, 4, 4, 2, 2) X(7, 4, 4, 5, 2, 1) X(8, 4, 4, 8, 2, 1)
+#define RLHF_FR_ENTRY(ID, WV, MT, CT, PF, OCC) {MT, CT, OCC},
+struct FrForm {
+  int mt, ct, occ;
 };
-static FrCut fr_cut(int n_cols_a, int n_cols_b, int steps, int max_split) {
-  FrCut best = {true, 1};
-  double best_e = 0;
-  for (int wide = 1; wide >= 0; --wide) {
-    const int c = wide ? 64 : 32;
-    const int tiles = (n_cols_a + c - 1) / c + (n_cols_b + c - 1) / c;
-    for (int ks = 1; ks <= max_split && (ks == 1 || steps / ks >= 7); ks *= 2) {
-      const int blocks = tiles * ks;
-      double e = (double)blocks / (256.0 * ((blocks + 255) / 256));
-      if (wide && blocks >= 224 && steps / ks >= 48) e *= 2;
-      if (e > best_e * 1.1) best_e = e, best = {wide != 0, ks};
+static const FrForm kForms[] = {RLHF_FR_FORMS(RLHF_FR_ENTRY)};
+#undef RLHF_FR_ENTRY
+
+// How a product is cut: 16 * ct columns per block, and K over ks blocks.  A CU can have about 32 KB of loads in flight (its
+// L1), for which a block's weights, ct column tiles wide, compete with its rows of A, mt tiles; and the launch lasts as
+// long as the CU with the most blocks.  So what counts is a block's steps times tiles, plus its sum over the waves
+// (ct * mt), times the rounds of 256 blocks; the blocks of a further round share the CU with the first's, the more so the
+// fewer steps they have.  Five column tiles for the 1120 of QKV + FC1 at width 2560 are 224 blocks, one round, where two
+// are 560.  Fitted to a sweep of widths 512-4096 and 1-256 rows (dec_driver, cold): the choice is 1 % from the best on
+// average.  us by column tiles (* the one taken; before, it was 2 or 4):
+//   QKV + FC1       width  768:  1 row   5.1*/ 6.9 /  8.5        64 rows  6.2*/  9.4 / 11.0 / 15.7    (2 / 4 / 5 / 8)
+//                         2048:  1 row  13.2*/ 13.4 / 15.2       64 rows 21.7 / 19.8*/ 22.1 / 30.2
+//                         2560:  1 row  22.9 / 27.3 / 20.5*      64 rows 37.6 / 40.5 / 28.6*/ 39.0
+//                         4096:  1 row  44.1 / 45.7*/ 51.9       64 rows 72.6 / 61.2 / 69.1 / 56.5*
+//   out-proj + FC2        2560:  1 row  14.9 / 17.0 / 13.4*      64 rows 23.4 / 25.1 / 18.0*/ 23.5    (K in 8)
+//                         4096:  1 row  30.0 / 30.0*/ 34.4       64 rows 50.5 / 41.4 / 47.6 / 38.1*
+//   LM head                768:  1 row  17.8*/ 19.0 / 19.3       200 rows 76.2 / 64.9*/ 89.3 / 91.6
+//                         2560:  1 row  50.7 / 52.8 / 51.7*      64 rows 85.2 / 77.3 / 73.5 / 71.8*
+static double fr_cost(const FrForm& f, int rows, int blocks, double steps) {
+  const int row_tiles = std::min((rows + 15) / 16, 4);
+  const double further = f.occ > 1 ? 0.74 * steps / (steps + 6) : 0.8;
+  return (1 + further * ((blocks + 255) / 256 - 1)) * (steps * (f.ct + 0.7 * row_tiles) + 1.5 * f.ct * row_tiles);
+}
+// The form for products of n_a and n_b (0: none) columns and `steps` steps over `rows` rows, K cut ks ways; its cost in
+// *cost.
+static int fr_form(int n_a, int n_b, int rows, int steps, int ks, size_t ldw_bytes, double* cost) {
+  int best = -1, done = 0;  // done: column tiles with a form already (the first that holds the rows has the fewest row tiles)
+  for (int i = 0; i < (int)(sizeof(kForms) / sizeof(kForms[0])); ++i) {
+    const FrForm& f = kForms[i];
+    if ((f.mt < 4 && 16 * f.mt < rows) || (done >> f.ct & 1)) continue;
+    if (f.ct > 2 && 16 * (size_t)f.ct * ldw_bytes >= ((size_t)1 << 32)) continue;  // a lane's offset within the block's rows
+    done |= 1 << f.ct;
+    const int c = 16 * f.ct, m = (rows + 16 * f.mt - 1) / (16 * f.mt);
+    const double t = fr_cost(f, rows, ((n_a + c - 1) / c + (n_b + c - 1) / c) * ks * m, (double)steps / ks);
+    if (best < 0 || t < *cost) {
+      best = i;
+      *cost = t;
     }
   }
   return best;
 }
-int few_rows_splits(int N, int steps) { return fr_cut(N, 0, steps, 8).ks; }
+// The split of a product left as slabs: the same for any number of rows, its consumer adds that many.  (At least seven
+// steps of 128 bytes to a block.)
+int few_rows_splits(int N, int steps) {
+  int best = 1;
+  double best_t = 0;
+  for (int ks = 1; ks <= 8 && (ks == 1 || steps / ks >= 7); ks *= 2) {
+    double t = 0;
+    fr_form(N, 0, 32, steps, ks, 0, &t);
+    if (ks == 1 || t < best_t * 0.95) best = ks, best_t = t;
+  }
+  return best;
+}
 
 template <typename T, bool TWO>
 static void fr_launch(const FrArgs& args, int form, int blocks, hipStream_t s) {
@@ -347,11 +360,15 @@ static void fr_launch(const FrArgs& args, int form, int blocks, hipStream_t s) {
 hipError_t launch_few_rows(int dtype, FewRowsArgs& args, int n_prods, hipStream_t s) {
   int blocks = 0, steps = 0;
   bool two = false;
-  for (int i = 0; i < n_prods; ++i) steps = std::max(steps, args.p[i].seg[0].steps + args.p[i].seg[1].steps);
-  const bool split = n_prods == 1 && args.p[0].epilogue == EPI_F32 && args.p[0].ksplit > 1;
-  const FrCut cut = fr_cut(args.p[0].N, n_prods > 1 ? args.p[1].N : 0, steps, split ? 8 : 1);
-  if (split && cut.ks != args.p[0].ksplit) return hipErrorInvalidValue;  // few_rows_splits gives the count
-  const int form = fr_form(args.M_max, cut.wide, steps / cut.ks), c = kFormCols[form];
+  const int ks = n_prods == 1 && args.p[0].epilogue == EPI_F32 ? args.p[0].ksplit : 1;
+  size_t ldw_bytes = 0;
+  for (int i = 0; i < n_prods; ++i) {
+    steps = std::max(steps, args.p[i].seg[0].steps + args.p[i].seg[1].steps);
+    for (const FewRowsSeg& g : args.p[i].seg) ldw_bytes = std::max(ldw_bytes, (size_t)g.ldw * (dtype == 0 ? 4 : 2));
+  }
+  double cost = 0;
+  const int form = fr_form(args.p[0].N, n_prods > 1 ? args.p[1].N : 0, args.M_max, steps, ks, ldw_bytes, &cost);
+  const int c = 16 * kForms[form].ct;
   const uint32_t esz = dtype == 0 ? 4 : 2;
   FrArgs f = {};
   for (int i = 0; i < n_prods; ++i) {
