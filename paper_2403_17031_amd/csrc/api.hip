@@ -842,26 +842,36 @@ int rlhf_attention_backward_noalloc(const void* q, const void* k, const void* v,
                                  base + kStaticScratchFloats, dq, dk, dv, stream);
 }
 
-int rlhf_adamw_step(float* param, const float* grad, float* exp_avg, float* exp_avg_sq, uint16_t* param_bf16,
-                    uint64_t n, int32_t step, double lr, double beta1, double beta2, double eps, double weight_decay,
-                    double grad_scale, void* stream) {
+// The step over `count` tensors; a tensor of no elements may have null pointers.
+static int adamw_tensors(const AdamwTensor* ts, int count, int32_t step, double lr, double beta1, double beta2, double eps,
+                         double weight_decay, double grad_scale, void* stream) {
   if (step < 1) return fail(RLHF_EINVAL, "step counts from 1");
   if (!(beta1 >= 0.0 && beta1 < 1.0) || !(beta2 >= 0.0 && beta2 < 1.0))
     return fail(RLHF_EINVAL, "beta1 and beta2 must be in [0, 1)");
   if (!(lr >= 0.0) || !(eps > 0.0) || !(weight_decay >= 0.0) || !std::isfinite(lr) || !std::isfinite(eps) ||
       !std::isfinite(weight_decay) || !std::isfinite(grad_scale))
     return fail(RLHF_EINVAL, "lr, weight_decay must be finite and >= 0, eps finite and > 0, grad_scale finite");
-  if (n == 0) return RLHF_OK;  // nothing to update; the pointers may then be null
-  if (!param || !grad || !exp_avg || !exp_avg_sq) return fail(RLHF_EINVAL, "null pointer argument");
-  if ((((uintptr_t)param | (uintptr_t)grad | (uintptr_t)exp_avg | (uintptr_t)exp_avg_sq) & 15) != 0 ||
-      ((uintptr_t)param_bf16 & 7) != 0)
-    return fail(RLHF_EINVAL, "fp32 arrays must be 16-byte aligned, the bf16 array 8-byte aligned");
+  for (int i = 0; i < count; ++i) {
+    const AdamwTensor& t = ts[i];
+    if (t.n == 0) continue;
+    if (!t.p || !t.g || !t.m || !t.v) return fail(RLHF_EINVAL, "null pointer argument");
+    if ((((uintptr_t)t.p | (uintptr_t)t.g | (uintptr_t)t.m | (uintptr_t)t.v) & 15) != 0 || ((uintptr_t)t.p_bf16 & 7) != 0)
+      return fail(RLHF_EINVAL, "fp32 arrays must be 16-byte aligned, the bf16 array 8-byte aligned");
+  }
   const double bias1 = 1.0 - std::pow(beta1, (double)step);
   const double bias2 = 1.0 - std::pow(beta2, (double)step);
-  HIP_OK(launch_adamw(param, grad, exp_avg, exp_avg_sq, param_bf16, (size_t)n, (float)(1.0 - lr * weight_decay),
-                      (float)beta1, (float)(1.0 - beta1), (float)beta2, (float)(1.0 - beta2), (float)(lr / bias1),
-                      (float)(1.0 / std::sqrt(bias2)), (float)eps, (float)grad_scale, (hipStream_t)stream));
+  const AdamwScalars c = {(float)(1.0 - lr * weight_decay), (float)beta1,        (float)(1.0 - beta1),
+                          (float)beta2,                     (float)(1.0 - beta2), (float)(lr / bias1),
+                          (float)(1.0 / std::sqrt(bias2)),  (float)eps,           (float)grad_scale};
+  HIP_OK(launch_adamw(ts, count, c, (hipStream_t)stream));
   return RLHF_OK;
+}
+
+int rlhf_adamw_step(float* param, const float* grad, float* exp_avg, float* exp_avg_sq, uint16_t* param_bf16,
+                    uint64_t n, int32_t step, double lr, double beta1, double beta2, double eps, double weight_decay,
+                    double grad_scale, void* stream) {
+  const AdamwTensor t = {param, grad, exp_avg, exp_avg_sq, param_bf16, (size_t)n};
+  return adamw_tensors(&t, 1, step, lr, beta1, beta2, eps, weight_decay, grad_scale, stream);
 }
 
 int rlhf_weight_image_bytes(const rlhf_model_config* cfg, size_t* out) {
@@ -2055,14 +2065,13 @@ int rlhf_ppo_update(rlhf_handle* h, const rlhf_ppo_update_config* cfg, const rlh
                                 ws.q_keep, ws.kv_keep, ws.u_keep, ws.u_stride, ws.u_layers);
       if (rc) return rc;
       // AdamW on every tensor; a bf16 model keeps fp32 masters and gets its storage arrays rewritten
-      const double inv_scale = 1.0 / (double)cfg->grad_scale;
-      for (const Tensor& t : ts) {
-        rc = rlhf_adamw_step(bf16 ? t.master : (float*)t.weight, t.grad, t.m, t.v, bf16 ? (uint16_t*)t.weight : nullptr,
-                             t.n, step, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, cfg->weight_decay, inv_scale, stream);
-        if (rc) return rc;
-      }
-      rc = rlhf_adamw_step(P.value_b, G.value_b, M1.value_b, M2.value_b, nullptr, 1, step, cfg->lr, cfg->beta1,
-                           cfg->beta2, cfg->eps, cfg->weight_decay, inv_scale, stream);
+      std::vector<AdamwTensor> adam;
+      adam.reserve(ts.size() + 1);
+      for (const Tensor& t : ts)
+        adam.push_back({bf16 ? t.master : (float*)t.weight, t.grad, t.m, t.v, bf16 ? (uint16_t*)t.weight : nullptr, t.n});
+      adam.push_back({P.value_b, G.value_b, M1.value_b, M2.value_b, nullptr, 1});
+      rc = adamw_tensors(adam.data(), (int)adam.size(), step, cfg->lr, cfg->beta1, cfg->beta2, cfg->eps, cfg->weight_decay,
+                         1.0 / (double)cfg->grad_scale, stream);
       if (rc) return rc;
       rc = rlhf_refresh_weights(h, stream);
       if (rc) return rc;

@@ -441,9 +441,21 @@ hipError_t launch_ppo_pack_grads(const int32_t* tokens, int B, int L, int Lq, in
                                  const int* cu, const float* d_lp, const float* d_v, int32_t* targets, float* gl,
                                  float* gv, hipStream_t s);
 // Optimizer step (optimizer.hip).
-hipError_t launch_adamw(float* p, const float* g, float* m, float* v, uint16_t* p_bf16, size_t n, float decay,
-                        float beta1, float omb1, float beta2, float omb2, float step_size, float inv_sqrt_bias2,
-                        float eps, float grad_scale, hipStream_t s);
+struct AdamwTensor {  // p, g, m, v fp32, 16-byte aligned; p_bf16 (8-byte aligned) may be null
+  float* p;
+  const float* g;
+  float *m, *v;
+  uint16_t* p_bf16;
+  size_t n;
+};
+// decay = 1 - lr * weight_decay; omb1 = 1 - beta1; omb2 = 1 - beta2; step_size = lr / (1 - beta1^t);
+// inv_sqrt_bias2 = 1 / sqrt(1 - beta2^t): formed once on the host in double (1 - 0.999 in fp32 would
+// already be off by 1.3e-5 relative).
+struct AdamwScalars {
+  float decay, beta1, omb1, beta2, omb2, step_size, inv_sqrt_bias2, eps, grad_scale;
+};
+constexpr int kAdamwTensors = 32;  // per launch: 1.8 KB of kernel arguments; a power of two
+hipError_t launch_adamw(const AdamwTensor* ts, int count, const AdamwScalars& c, hipStream_t s);
 
 // bf16 -> fp16 conversion of a weight matrix (exact within fp16's normal range).
 // ---- backward through the output heads (head_backward.hip); dtype 0: float operands, 1: fp16 ----
