@@ -1240,13 +1240,16 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
   };
   const bool kmaj = gemm_takes_k_major(dt, dw_kmajor(go, ws.f, d_w_fc2, d, F)) &&
                     gemm_takes_k_major(dt, dw_kmajor(ws.df, ws.m, d_w_fc1, F, d));
-  auto zero_tail = [&](void* buf, int width) {
-    return Tp > T ? launch_fill_zero((char*)buf + (size_t)T * width * h->esz, (size_t)(Tp - T) * width * h->esz, s)
-                  : hipSuccess;
-  };
   if (kmaj) {
-    if (!sh.go16) LAUNCH("mlp_bwd_zero", zero_tail(ws.go, d));
-    LAUNCH("mlp_bwd_zero", zero_tail(ws.f, F));
+    ZeroSpans tails;
+    auto tail = [&](void* buf, int width) {
+      tails.add((char*)buf + (size_t)T * width * h->esz, (size_t)(Tp - T) * width * h->esz);
+    };
+    if (!sh.go16) tail(ws.go, d);
+    tail(ws.f, F);
+    tail(ws.df, F);
+    tail(ws.m, d);
+    LAUNCH("mlp_bwd_zero", launch_fill_zero_spans(tails, s));
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_kmajor(go, ws.f, d_w_fc2, d, F), s));
   } else {
     LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, go, (size_t)d, ws.goT, (size_t)Tp, T, d, Tp, s));
@@ -1255,8 +1258,6 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
   }
   // ---- FC1: dW1 = du^T m, dm = du W1
   if (kmaj) {
-    LAUNCH("mlp_bwd_zero", zero_tail(ws.df, F));
-    LAUNCH("mlp_bwd_zero", zero_tail(ws.m, d));
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_kmajor(ws.df, ws.m, d_w_fc1, F, d), s));
   } else {
     LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, ws.df, (size_t)F, ws.fT, (size_t)Tp, T, F, Tp, s));
@@ -1430,13 +1431,16 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
   };
   const bool kmaj = gemm_takes_k_major(dt, dw_kmajor(go, ws.att, d_w_o, d, d)) &&
                     gemm_takes_k_major(dt, dw_kmajor(ws.dqkv, ws.a, d_w_qkv, 3 * d, d));
-  auto zero_tail = [&](void* buf, int width) {
-    return Tp > T ? launch_fill_zero((char*)buf + (size_t)T * width * esz, (size_t)(Tp - T) * width * esz, s)
-                  : hipSuccess;
-  };
   if (kmaj) {
-    if (!sh.go16) LAUNCH("attn_bwd_zero", zero_tail(ws.go, d));
-    LAUNCH("attn_bwd_zero", zero_tail(ws.att, d));
+    ZeroSpans tails;
+    auto tail = [&](void* buf, int width) {
+      tails.add((char*)buf + (size_t)T * width * esz, (size_t)(Tp - T) * width * esz);
+    };
+    if (!sh.go16) tail(ws.go, d);
+    tail(ws.att, d);
+    tail(ws.dqkv, 3 * d);
+    tail(ws.a, d);
+    LAUNCH("attn_bwd_zero", launch_fill_zero_spans(tails, s));
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(go, ws.att, d_w_o, d, d), s));
   } else {
     LAUNCH("attn_bwd_transpose", launch_transpose_pad(dt, go, (size_t)d, ws.goT, (size_t)Tp, T, d, Tp, s));
@@ -1448,8 +1452,6 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
                                              h->rope_cos, h->rope_sin, 1, s));
   LAUNCH("colsum", launch_colsum(dt, ws.dqkv, T, 3 * d, ws.part, ws.splits, reordered ? ws.dbq : d_b_qkv, s));
   if (kmaj) {
-    LAUNCH("attn_bwd_zero", zero_tail(ws.dqkv, 3 * d));
-    LAUNCH("attn_bwd_zero", zero_tail(ws.a, d));
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(ws.dqkv, ws.a, reordered ? ws.dwq : d_w_qkv, 3 * d, d), s));
   } else {
     LAUNCH("attn_bwd_transpose", launch_transpose_pad(dt, ws.dqkv, (size_t)3 * d, ws.dqkvT, (size_t)Tp, T, 3 * d, Tp, s));

@@ -463,6 +463,13 @@ hipError_t launch_adamw(const AdamwTensor* ts, int count, const AdamwScalars& c,
 hipError_t launch_transpose_pad(int dtype, const void* src, size_t ld_src, void* dst, size_t ld_dst, int R, int C,
                                 int R_pad, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);  // bytes: a multiple of 4
+struct ZeroSpans {  // bytes: multiples of 4
+  void* p[4];
+  size_t bytes[4];
+  int count = 0;
+  void add(void* at, size_t b) { p[count] = at, bytes[count++] = b; }
+};
+hipError_t launch_fill_zero_spans(const ZeroSpans& z, hipStream_t s);
 // dz[r][v] = gl[r] * scale * inv_temp * (onehot(targets[r])[v] - softmax(logits[r] * inv_temp)[v]) for r < rows with
 // a target; zero for rows without one, rows rows .. rows_pad-1 and columns V .. V_pad-1.
 hipError_t launch_softmax_grad(int dtype, const float* logits, int V, int V_pad, const int* targets, const float* gl,

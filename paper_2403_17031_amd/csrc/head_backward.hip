@@ -865,6 +865,22 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Up to four spans in one launch.  (A fill of some rows is a launch and the gap after it, 6 us, and nothing else: a layer of
+// a backward pass zeroes the rest of five operands.)
+__global__ void __launch_bounds__(256) fill_zero_spans_kernel(ZeroSpans z) {
+  uint32_t* const p = (uint32_t*)z.p[blockIdx.y];
+  const size_t n = z.bytes[blockIdx.y] / 4;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0;
+}
+hipError_t launch_fill_zero_spans(const ZeroSpans& z, hipStream_t s) {
+  size_t most = 0;
+  for (int i = 0; i < z.count; ++i) most = std::max(most, z.bytes[i]);
+  if (most == 0) return hipSuccess;
+  const int blocks = (int)std::min<size_t>((most / 4 + 255) / 256, 65536);
+  hipLaunchKernelGGL(fill_zero_spans_kernel, dim3(blocks, z.count), dim3(256), 0, s, z);
+  return hipGetLastError();
+}
+
 hipError_t launch_softmax_grad(int dtype, const float* logits, int V, int V_pad, const int* targets, const float* gl,
                                int rows, int rows_pad, float inv_temp, float scale, void* dz, hipStream_t s) {
   if (rows_pad <= 0) return hipSuccess;
