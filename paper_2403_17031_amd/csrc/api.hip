@@ -1077,9 +1077,8 @@ int rlhf_head_backward(rlhf_handle* h, const float* x_final, const int32_t* targ
   const int dt = c.dtype, d = c.d_model, V = c.vocab;
   const size_t esz = h->esz;
 
-  // W^T [d, V_pad] (zero columns past V), and d_embed_out = 0: the chunks add into it
+  // W^T [d, V_pad] (zero columns past V)
   LAUNCH("head_bwd_prep", launch_transpose_pad(dt, h->embed_out_mm, (size_t)d, ws.WT, (size_t)ws.V_pad, V, d, ws.V_pad, s));
-  LAUNCH("head_bwd_prep", launch_fill_zero(d_embed_out, (size_t)V * d * sizeof(float), s));
   for (int r0 = 0; r0 < T; r0 += ws.chunk) {
     const int rows = std::min(ws.chunk, T - r0);
     const int rows_pad = (rows + 127) & ~127;
@@ -1098,12 +1097,20 @@ int rlhf_head_backward(rlhf_handle* h, const float* x_final, const int32_t* targ
     gi.A = ws.dz; gi.W = ws.WT; gi.bias = nullptr; gi.out = ws.dhl + (size_t)r0 * d;
     gi.M_max = rows; gi.M_dev = nullptr; gi.N = d; gi.K = ws.V_pad; gi.ldo = d; gi.epilogue = EPI_F32;
     LAUNCH("gemm_head_dx", launch_gemm(dt, gi, s));
-    // dL/dW += dz^T h: rows of dz^T [V, rows_pad] against rows of h^T [d, rows_pad]
-    LAUNCH("head_bwd_transpose", launch_transpose_pad(dt, ws.dz, (size_t)ws.V_pad, ws.dzT, (size_t)rows_pad, rows_pad, V, rows_pad, s));
-    LAUNCH("head_bwd_transpose", launch_transpose_pad(dt, ws.hl, (size_t)d, ws.hlT, (size_t)rows_pad, rows_pad, d, rows_pad, s));
+    // dL/dW = dz^T h, of the first chunk straight from the row-major operands where the kernel takes the shape (3456 rows
+    // of 50304 x 768: without the two transposes, the fill and the read of the result 0.25 ms less).  Otherwise rows of
+    // dz^T [V, rows_pad] against rows of h^T [d, rows_pad], added to what is there: zeros at first.
     GemmArgs gw;
-    gw.A = ws.dzT; gw.W = ws.hlT; gw.bias = nullptr; gw.out = d_embed_out;
-    gw.M_max = V; gw.M_dev = nullptr; gw.N = d; gw.K = rows_pad; gw.ldo = d; gw.epilogue = EPI_BIAS_RESADD;
+    gw.A = ws.dz; gw.W = ws.hl; gw.bias = nullptr; gw.out = d_embed_out;
+    gw.M_max = V; gw.M_dev = nullptr; gw.N = d; gw.K = rows_pad; gw.ldo = d; gw.epilogue = EPI_F32;
+    gw.k_major = true; gw.lda = ws.V_pad;
+    if (r0 > 0 || !gemm_takes_k_major(dt, gw)) {
+      if (r0 == 0) LAUNCH("head_bwd_prep", launch_fill_zero(d_embed_out, (size_t)V * d * sizeof(float), s));
+      LAUNCH("head_bwd_transpose", launch_transpose_pad(dt, ws.dz, (size_t)ws.V_pad, ws.dzT, (size_t)rows_pad, rows_pad, V, rows_pad, s));
+      LAUNCH("head_bwd_transpose", launch_transpose_pad(dt, ws.hl, (size_t)d, ws.hlT, (size_t)rows_pad, rows_pad, d, rows_pad, s));
+      gw.A = ws.dzT; gw.W = ws.hlT; gw.epilogue = EPI_BIAS_RESADD;
+      gw.k_major = false; gw.lda = 0;
+    }
     LAUNCH("gemm_head_dw", launch_gemm(dt, gw, s));
   }
   LAUNCH("head_ln_backward", launch_head_ln_backward(dt, x_final, ws.dhl, d_values, grad_scale, h->w.value_w, h->w.lnf_g,
