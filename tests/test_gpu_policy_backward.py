@@ -87,3 +87,15 @@ def test_bf16_mode(gpu, layers, H, hd, r, F, B, L):
                       pad_id=519, eos_id=1)
     worst = _check(gpu, cfg, B=B, L=L, seed=layers + hd, scale=float(B * L) * 64.0)
     print("largest relative Frobenius errors:", sorted(worst.items(), key=lambda kv: -kv[1])[:4])
+
+
+@pytest.mark.parametrize("hd,V", [(16, 36), (4, 36), (16, 8)])
+def test_tokens_that_occur_often(gpu, hd, V):
+    """The input embedding's gradient adds the rows of a token in row order: of up to 16 occurrences from a list, of more by
+    a scan.  About 400 rows over 32 tokens (both), over 4 (about 100 each)."""
+    cfg = ModelConfig(n_layers=1, d_model=3 * hd, n_heads=3, head_dim=hd, rotary_dims=2, d_ff=32, vocab=V, dtype="fp32",
+                      pad_id=V - 1, eos_id=1)
+    tokens, mask, *_ = _batch(cfg, 6, 100, 7)
+    counts = np.bincount(tokens[mask != 0], minlength=V)[2:V - 2]
+    assert (counts > 16).any() and (V == 8 or (counts <= 16).any())
+    _check(gpu, cfg, B=6, L=100, seed=7, scale=1.0)

@@ -3,6 +3,8 @@ loss head (rlhf_ppo_loss), backward pass (rlhf_policy_backward), optimizer (rlhf
 fp32 check mode.  The gradients are held to 2e-4 of each tensor's largest magnitude, the updated weights to 5e-3 of
 the learning rate (AdamW's first step is lr * g / (|g| + eps): with eps = 1e-3 here a gradient error of 1e-6 moves a
 weight by at most 1e-3 lr), and the loss must go down."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -226,4 +228,29 @@ def test_update_loop_rejects_bad_arguments(gpu):
         pol.ppo_update(tokens, mask, Lq, z, adv, z, ret, kept, 0.0)                       # temperature
     with pytest.raises(gpu.RlhfError):
         pol.ppo_update(tokens, mask, Lq, z, adv, z, ret, kept, 0.7, epochs=0)
+    pol.close()
+
+
+@pytest.mark.parametrize("layers", [3, 6])
+def test_the_optimizer_step_over_all_tensors_is_the_step_of_each(gpu, layers):
+    """An update steps its tensors together, up to 32 a launch (3 layers: 42 tensors, 6: 78): master weights, moments and
+    storage copies are bit for bit those of adamw_step on each tensor with the gradients the update left."""
+    import torch
+    cfg, _, g, tokens, mask, kept, adv, ret, Lq, N = _loop_case("bf16")
+    cfg = replace(cfg, n_layers=layers)
+    pol = gpu.Policy(cfg, make_weights(cfg, 93, variant="test"))
+    st = pol.train_state()
+    before = {k: t.clone() for k, t in st["master"].items()}
+    lp0, v0 = pol.score_sequences(tokens, mask, 0.7)
+    pol.ppo_update(tokens, mask, Lq, lp0[:, Lq:].contiguous(), adv, v0[:, Lq - 1:Lq - 1 + N].contiguous(), ret, kept, 0.7,
+                   epochs=1, n_minibatches=1, lr=1e-3, grad_scale=1024.0)
+    assert len(before) > 32
+    for name, p in before.items():
+        grad, m, v = st["grads"][name], torch.zeros_like(p), torch.zeros_like(p)
+        bf = torch.empty_like(p, dtype=torch.bfloat16)
+        gpu.adamw_step(p, grad, m, v, 1, lr=1e-3, grad_scale=1.0 / 1024.0, param_bf16=bf)
+        assert bool((st["master"][name] == p).all()), name
+        assert bool((st["exp_avg"][name] == m).all()) and bool((st["exp_avg_sq"][name] == v).all()), name
+        if name != "value_b":
+            assert bool((pol._dev[name] == bf).all()), name
     pol.close()
