@@ -170,17 +170,18 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
 
 // Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256 while
 // the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such tile, its
-// launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of 64-256 tokens, 53
+// launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of 64-512 tokens, 53
 // sampled; this pass against the other, ms): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9,
-// 192 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 80 29.6 / 31.9, 128 36.3 / 39.7, 192 50.3 / 51.2, 256 63.4 / 60.8;
-// 2.8B width (79 M) 80 41.4 / 40.9, 128 51.2 / 51.9, 192 70.1 / 66.6; 6.9B width (201 M) 80 41.5 / 37.4.  Break-even is
-// about 150 M; the line is at 2^27, and at 256 sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width,
-// two layers): 1 15.3 / 28.6, 17 18.7 / 30.3, 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the
-// gap (1900 tokens, 20 sampled: 160M 256 sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
+// 192 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 130 78.6 / 81.4, 192 100.4 / 103.5, 256 127.9 / 127.0; 2.8B width (79 M)
+// 65 65.9 / 68.1, 96 80.5 / 84.6, 128 95.9 / 99.8, 160 121.0 / 118.9, 256 173.6 / 161.8; 6.9B width (201 M, two layers) 65
+// 46.2 / 42.9, 128 63.5 / 60.4.  It gains 3-5 % at 150 to 157 M and loses 1 % at 201 M; the line is at 168 M, and at 256
+// sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width, two layers): 1 15.3 / 28.6, 17 18.7 / 30.3,
+// 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the gap (1900 tokens, 20 sampled: 160M 256
+// sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
 bool few_decode_size(const rlhf_model_config& c, int B) {
   if (B <= kFewRows) return true;
   const size_t per_layer = (size_t)c.d_model * (4 * (size_t)c.d_model + 2 * (size_t)c.d_ff);
-  return B <= 256 && (size_t)((B + 63) / 64) * per_layer <= (size_t)1 << 27;
+  return B <= 256 && (size_t)((B + 63) / 64) * per_layer <= (size_t)5 << 25;
 }
 
 // Activations of a decode pass of few sequences (run_decode_few), as packed operands (common.h).

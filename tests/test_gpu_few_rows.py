@@ -78,6 +78,20 @@ def test_which_decode_pass(shape, B, few):
     assert ("gemm_decode_qkv_fc1" in p.profile_read()) == few
 
 
+@pytest.mark.parametrize("F,few", [(15104, True), (15168, False)])
+def test_the_line_between_the_decode_passes(F, few):
+    """129 sequences are three row tiles: weights of a layer times three, 167.5 and 168.1 M on either side of 5 * 2^25."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    cfg = ModelConfig(1, 1536, 24, 64, 16, F, vocab=64, dtype="bf16", pad_id=64)
+    p = P.Policy(cfg, make_weights(cfg, 77, variant="test"))
+    p.profile_enable()
+    p.rollout_generate(np.ones((129, 2), np.int32), np.ones((129, 2), np.uint8), 11, 0.7, 2)
+    assert ("gemm_decode_qkv_fc1" in p.profile_read()) == few
+
+
 @pytest.fixture(scope="module")
 def wide_model():
     kept = {}
