@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(64 * WV, OCC) few_rows_kernel(FrArgs args) {
     if (p.bias) bias[it] = load_bias((const FR_GLOBAL P*)p.bias, n0 + 16 * ((wave + it * WV) / MT) + 4 * q, p.N, p.bias_vec != 0);
 
   // Weight rows: the block's first one as a 64-bit address, a lane's own as a 32-bit offset from it (an output embedding
-  // may be larger than 4 GiB, a block's 64 rows are not).
+  // may be larger than 4 GiB, a block's rows are not: few_rows_takes for 64, fr_form for more).
   uint32_t woff[TWO ? 2 : 1][CT], aoff[TWO ? 2 : 1][MT];
 #pragma unroll
   for (int g = 0; g < (TWO ? 2 : 1); ++g) {

@@ -4,9 +4,10 @@
 //
 //  * bf16 mode (fp16 operands), many rows: v_mfma_f32_32x32x16_f16, 256x256 block tile, 8 waves
 //    (2x4) of 128x64, K step 64 (a tile row is one full 128-byte line), two 64 KB LDS stages
-//    filled directly from global memory, XOR-swizzled 16-byte chunks (conflict-free ds_read_b128),
-//    workgroup ids remapped so that the 32 tiles resident on one XCD share A and W panels in that
-//    XCD's L2.  Few rows (decode): 128x64 tiles staged through registers, split over K.
+//    filled directly from global memory, XOR-swizzled 16-byte chunks (conflict-free ds_read_b128).
+//    One block per CU takes tile after tile, in rounds in which the 32 tiles of an XCD are neighbours
+//    and share A and W panels in its L2; what is left for a last round is cut smaller.
+//    Few rows (decode): 128x64 tiles staged through registers, split over K.
 //  * fp32: plain FMA tile kernel (check mode only; not tuned).
 #include <algorithm>
 #include <type_traits>
