@@ -975,7 +975,7 @@ static bool takes_dma(const GemmArgs& a) {
 // stage pairs, the fp32 slabs fitting the caller's scratch) that minimises rounds of 256 tiles times slice length.
 static int dma_k_slices(const GemmArgs& a, int* k_slice) {
   *k_slice = 0;
-  if (!a.long_k || !a.splitk_ws || a.M_dev || a.bias || a.ldo != a.N ||
+  if (!a.long_k || !a.splitk_ws || a.M_dev || a.bias || a.bias2 || a.ldo != a.N ||
       (a.epilogue != EPI_F32 && a.epilogue != EPI_BIAS_RESADD))
     return 1;
   const int tiles = ((a.M_max + 255) / 256) * ((a.N + 255) / 256), pairs = a.K / (2 * DK);
@@ -990,7 +990,11 @@ static int dma_k_slices(const GemmArgs& a, int* k_slice) {
   *k_slice = best_q * 2 * DK;
   return best;
 }
-bool gemm_takes_bias2(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
+// The residual epilogue alone reads a second bias (the others request theirs ahead, under the main loop, where a second
+// one does not fit the registers).
+bool gemm_takes_bias2(int dtype, const GemmArgs& a) {
+  return dtype == 1 && a.epilogue == EPI_BIAS_RESADD && takes_dma(a);
+}
 bool gemm_takes_k_major(int dtype, const GemmArgs& a) { return dtype == 1 && a.k_major && takes_dma(a); }
 bool gemm_takes_lse(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
 // EPI_QKV: 16-byte chunks must not straddle heads, a lane's 4-column group must be whole pairs, and the

@@ -3,6 +3,7 @@
 //                     launch_gemm reports it
 //   products aligned  the few-rows kernel, which moves 16 bytes at a time, is not given addresses that are no multiple
 //   products forms d F V rows   the kernels that the product launches of a decode pass take (bf16 mode)
+//   products bias2    a second bias is taken by the one epilogue that reads it and refused elsewhere, never dropped
 //   products split    a decode product of few rows that is given split-K scratch is cut over K until it covers the chip
 #include <dlfcn.h>
 
@@ -117,10 +118,41 @@ static int split() {
   return bad ? 1 : 0;
 }
 
+static int bias2() {
+  int bad = 0;
+  const int epilogues[] = {EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESADD, EPI_F32, EPI_LSE, EPI_QKV};
+  LseArgs lse = {};
+  QkvArgs qkv = {};
+  qkv.H = 4; qkv.hd = 64; qkv.r = 16;
+  for (int epi : epilogues)
+    for (int M : {64, 600})
+      for (int sliced = 0; sliced < 2; ++sliced) {
+        GemmArgs g = product(M, 768, 4096, epi);
+        g.bias = sliced ? nullptr : (const void*)4096;
+        g.bias2 = (const void*)8192;
+        g.lse = &lse;
+        g.qkv = &qkv;
+        g.long_k = sliced != 0;
+        g.splitk_ws = sliced ? (void*)4096 : nullptr;
+        g.splitk_ws_bytes = (size_t)1 << 30;
+        const bool takes = epi == EPI_BIAS_RESADD && M > 512;
+        launches = 0;
+        const hipError_t e = launch_gemm(1, g, nullptr);
+        // (one launch: slices of K and their sum, which adds no bias, are two)
+        if (e != (takes ? hipErrorLaunchFailure : hipErrorInvalidValue) || launches != (takes ? 1 : 0) ||
+            gemm_takes_bias2(1, g) != takes) {
+          printf("epilogue %d rows %d sliced %d: status %d, %d launches\n", epi, M, sliced, (int)e, launches);
+          ++bad;
+        }
+      }
+  return bad ? 1 : 0;
+}
+
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
   if (argc > 1 && !strcmp(argv[1], "aligned")) return aligned();
   if (argc > 5 && !strcmp(argv[1], "forms")) return forms(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]));
   if (argc > 1 && !strcmp(argv[1], "split")) return split();
+  if (argc > 1 && !strcmp(argv[1], "bias2")) return bias2();
   return 2;
 }

@@ -37,6 +37,11 @@ def test_unaligned_operands_stay_off_the_few_rows_kernel(products):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_a_second_bias_is_added_or_refused(products):
+    r = subprocess.run([products, "bias2"], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 def test_decode_passes_on_the_gpu_cover_every_form_of_the_kernel(products):
     """The shapes that the GPU tests grade against the oracle reach every form of the few-rows kernel in bf16, each but
     the short-K one (form 2) with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
