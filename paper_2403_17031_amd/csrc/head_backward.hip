@@ -516,7 +516,8 @@ __global__ void __launch_bounds__(256)
     gelu_backward_colsum_kernel(const half_t* __restrict__ u, half_t* __restrict__ df, half_t* __restrict__ f, int R,
                                 int C, int rows_per_split, float* __restrict__ part) {
   constexpr int RC = 64;
-  __shared__ half_t buf[2][RC][64];
+  __shared__ __attribute__((aligned(16))) half_t buf[2][RC][64];
+  static_assert(__alignof__(buf) >= 16, "rows are stored 16 bytes at a time");
   const int tq = threadIdx.x & 7, tr = threadIdx.x >> 3;
   const int c0 = blockIdx.x * 64 + 8 * tq;
   const bool ok = c0 < C;
@@ -580,6 +581,7 @@ __global__ void __launch_bounds__(256)
     colsum_part_vec_kernel(const T* __restrict__ a, int R, int C, int rows_per_split, float* __restrict__ part) {
   constexpr int V = 16 / sizeof(T), LPR = 64 / V, RPP = 256 / LPR, RC = 4 * RPP;  // lanes per row, rows per pass and chunk
   __shared__ __attribute__((aligned(16))) T buf[2][RC][64];
+  static_assert(__alignof__(buf) >= 16, "rows are stored 16 bytes at a time");
   const int tq = threadIdx.x % LPR, tr = threadIdx.x / LPR;
   const int c0 = blockIdx.x * 64 + V * tq;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
@@ -603,6 +605,7 @@ __global__ void __launch_bounds__(256)
                                half_t* __restrict__ out) {
   constexpr int RC = 64;
   __shared__ __attribute__((aligned(16))) float buf[2][RC][64];
+  static_assert(__alignof__(buf) >= 16, "rows are stored 16 bytes at a time");
   const int tq = threadIdx.x & 15, tr = threadIdx.x >> 4;
   const int c0 = blockIdx.x * 64 + 4 * tq;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
