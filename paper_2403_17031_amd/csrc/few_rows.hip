@@ -281,12 +281,13 @@ bool few_rows_takes(int dtype, const GemmArgs& a) {
          lda * esz < (1ull << 31) && ldw * esz < (1ull << 31);
 }
 
-// Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  A row tile past M costs little, since all
-// of its lanes ask for row M - 1 (a form of three tiles against one of two at 30 rows: 2-4 %), so not every count of row
-// tiles has every count of column tiles.
+// Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  An idle row tile costs the bf16 mode 2-4 %
+// where it is one of three (its lanes all ask for row M - 1) and 5-18 % where it is one or two of four (registers, waves in
+// flight): 24 rows in forms of 2 / 4 row tiles, four column tiles each, width 2048 QKV + FC1 14.8 / 17.7 us, 4096 48.8 / 53.5.
 #define RLHF_FR_FORMS(X)                                                                                          \
-  X(0, 4, 1, 2, 4, 4) X(1, 4, 1, 4, 3, 3) X(2, 4, 1, 5, 4, 2) X(3, 4, 2, 2, 3, 3) X(4, 4, 3, 5, 2, 2)            \
-  X(5, 4, 4, 2, 3, 2) X(6, 4, 4, 4, 2, 2) X(7, 4, 4, 5, 2, 1) X(8, 4, 4, 8, 2, 1)
+  X(0, 4, 1, 2, 4, 4) X(1, 4, 1, 4, 3, 3) X(2, 4, 1, 5, 4, 2) X(3, 4, 2, 2, 3, 3) X(4, 4, 2, 4, 2, 3)            \
+  X(5, 4, 3, 2, 3, 2) X(6, 4, 3, 4, 2, 2) X(7, 4, 3, 5, 2, 2) X(8, 4, 4, 2, 3, 2) X(9, 4, 4, 4, 2, 2)            \
+  X(10, 4, 4, 5, 2, 1) X(11, 4, 4, 8, 2, 1)
 #define RLHF_FR_ENTRY(ID, WV, MT, CT, PF, OCC) {MT, CT, OCC},
 struct FrForm {
   int mt, ct, occ;
@@ -299,32 +300,40 @@ static const FrForm kForms[] = {RLHF_FR_FORMS(RLHF_FR_ENTRY)};
 // long as the CU with the most blocks.  So what counts is a block's steps times tiles, plus its sum over the waves
 // (ct * mt), times the rounds of 256 blocks; the blocks of a further round share the CU with the first's, the more so the
 // fewer steps they have.  Five column tiles for the 1120 of QKV + FC1 at width 2560 are 224 blocks, one round, where two
-// are 560.  Fitted to a sweep of widths 512-4096 and 1-256 rows (dec_driver, cold): the choice is 1 % from the best on
-// average.  us by column tiles (* the one taken; before, it was 2 or 4):
-//   QKV + FC1       width  768:  1 row   5.1*/ 6.9 /  8.5        64 rows  6.2*/  9.4 / 11.0 / 15.7    (2 / 4 / 5 / 8)
-//                         2048:  1 row  13.2*/ 13.4 / 15.2       64 rows 21.7 / 19.8*/ 22.1 / 30.2
-//                         2560:  1 row  22.9 / 27.3 / 20.5*      64 rows 37.6 / 40.5 / 28.6*/ 39.0
-//                         4096:  1 row  44.1 / 45.7*/ 51.9       64 rows 72.6 / 61.2 / 69.1 / 56.5*
-//   out-proj + FC2        2560:  1 row  14.9 / 17.0 / 13.4*      64 rows 23.4 / 25.1 / 18.0*/ 23.5    (K in 8)
-//                         4096:  1 row  30.0 / 30.0*/ 34.4       64 rows 50.5 / 41.4 / 47.6 / 38.1*
-//   LM head                768:  1 row  17.8*/ 19.0 / 19.3       200 rows 76.2 / 64.9*/ 89.3 / 91.6
-//                         2560:  1 row  50.7 / 52.8 / 51.7*      64 rows 85.2 / 77.3 / 73.5 / 71.8*
+// are 560.  Fitted to a sweep of widths 512-4096 and 1-256 rows (dec_driver, cold).  us by column tiles (* the one taken):
+//   QKV + FC1       width  768:  1 row   5.1*/ 6.2 /  8.4        32 rows  4.9*/  7.0 /  9.5    64 rows  6.2*/  9.2 / 10.7 / 15.4    (2 / 4 / 5 / 8)
+//                         2048:  1 row  13.4*/ 13.4 / 14.9       32 rows 16.7 / 15.4*/ 18.0    64 rows 21.8 / 20.1*/ 22.1 / 30.4
+//                         2560:  1 row  24.2 / 27.4 / 20.5*      32 rows 29.4 / 33.0 / 24.4*   64 rows 37.3 / 40.1 / 28.4*/ 38.6
+//                         4096:  1 row  45.6 / 45.7*/ 51.9       32 rows 56.7 / 51.4*/ 58.2    64 rows 72.4 / 60.6 / 68.2 / 55.5*
+//   out-proj + FC2        2048:  1 row   8.3*/  9.3 /  9.1       32 rows  9.5*/  9.9 / 11.3    64 rows 12.5 / 12.5*/ 13.7 / 18.7    (K in 8)
+//                         2560:  1 row  14.6 / 16.8 / 13.3*      32 rows 17.9 / 19.5 / 15.5*   64 rows 23.0 / 24.6 / 17.7*/ 23.2
+//                         4096:  1 row  31.5 / 30.0*/ 34.0       32 rows 39.1 / 34.4*/ 39.5    64 rows 50.5 / 41.4 / 47.2 / 38.2*
+//   LM head                768:  1 row  17.8*/ 17.3 / 19.1       32 rows 20.6 / 21.5 / 20.8*   64 rows 26.8 / 26.3*/ 30.7 / 29.6
+//                         2560:  1 row  53.2 / 53.4 / 51.5*                                  64 rows 83.9 / 76.9 / 73.3 / 71.2*
 static double fr_cost(const FrForm& f, int rows, int blocks, double steps) {
   const int row_tiles = std::min((rows + 15) / 16, 4);
   const double further = f.occ > 1 ? 0.74 * steps / (steps + 6) : 0.8;
   return (1 + further * ((blocks + 255) / 256 - 1)) * (steps * (f.ct + 0.7 * row_tiles) + 1.5 * f.ct * row_tiles);
 }
-// The form for products of n_a and n_b (0: none) columns and `steps` steps over `rows` rows, K cut ks ways; its cost in
-// *cost.
-static int fr_form(int n_a, int n_b, int rows, int steps, int ks, size_t ldw_bytes, double* cost) {
+// The form for products of n_a and n_b (0: none) columns and `steps` steps over `rows` rows, K cut ks ways; the least cost
+// in *cost.
+static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, size_t ldw_bytes, double* cost) {
+  const int tiles = std::min((rows + 15) / 16, 4);
+  auto blocks = [&](const FrForm& f) {
+    const int c = 16 * f.ct;
+    return ((n_a + c - 1) / c + (n_b + c - 1) / c) * ks * ((rows + 16 * f.mt - 1) / (16 * f.mt));
+  };
+  auto takes = [&](const FrForm& f) {
+    if (f.mt < tiles) return false;
+    if (f.ct > 2 && 16 * (size_t)f.ct * ldw_bytes >= ((size_t)1 << 32)) return false;  // a lane's offset within the block's rows
+    return true;
+  };
   int best = -1, done = 0;  // done: column tiles with a form already (the first that holds the rows has the fewest row tiles)
   for (int i = 0; i < (int)(sizeof(kForms) / sizeof(kForms[0])); ++i) {
     const FrForm& f = kForms[i];
-    if ((f.mt < 4 && 16 * f.mt < rows) || (done >> f.ct & 1)) continue;
-    if (f.ct > 2 && 16 * (size_t)f.ct * ldw_bytes >= ((size_t)1 << 32)) continue;  // a lane's offset within the block's rows
+    if (!takes(f) || (done >> f.ct & 1)) continue;
     done |= 1 << f.ct;
-    const int c = 16 * f.ct, m = (rows + 16 * f.mt - 1) / (16 * f.mt);
-    const double t = fr_cost(f, rows, ((n_a + c - 1) / c + (n_b + c - 1) / c) * ks * m, (double)steps / ks);
+    const double t = fr_cost(f, rows, blocks(f), (double)steps / ks);
     if (best < 0 || t < *cost) {
       best = i;
       *cost = t;
@@ -339,7 +348,7 @@ int few_rows_splits(int N, int steps) {
   double best_t = 0;
   for (int ks = 1; ks <= 8 && (ks == 1 || steps / ks >= 7); ks *= 2) {
     double t = 0;
-    fr_form(N, 0, 32, steps, ks, 0, &t);
+    fr_form(1, N, 0, 32, steps, ks, 0, &t);
     if (ks == 1 || t < best_t * 0.95) best = ks, best_t = t;
   }
   return best;
@@ -367,7 +376,7 @@ hipError_t launch_few_rows(int dtype, FewRowsArgs& args, int n_prods, hipStream_
     for (const FewRowsSeg& g : args.p[i].seg) ldw_bytes = std::max(ldw_bytes, (size_t)g.ldw * (dtype == 0 ? 4 : 2));
   }
   double cost = 0;
-  const int form = fr_form(args.p[0].N, n_prods > 1 ? args.p[1].N : 0, args.M_max, steps, ks, ldw_bytes, &cost);
+  const int form = fr_form(dtype, args.p[0].N, n_prods > 1 ? args.p[1].N : 0, args.M_max, steps, ks, ldw_bytes, &cost);
   const int c = 16 * kForms[form].ct;
   const uint32_t esz = dtype == 0 ? 4 : 2;
   FrArgs f = {};

@@ -2,7 +2,8 @@
 //   products errors   the launch calls of the runtime are replaced by ones that always fail: every route through
 //                     launch_gemm reports it
 //   products aligned  the few-rows kernel, which moves 16 bytes at a time, is not given addresses that are no multiple
-//   products forms d F V rows   the kernels that the product launches of a decode pass take (bf16 mode)
+//   products forms dtype d F V rows   the kernels that the product launches of a decode pass take
+//   products many d F V rows    the kernels that the products of a pass over many rows take in fp32 mode
 //   products bias2    a second bias is taken by the one epilogue that reads it and refused elsewhere, never dropped
 //   products split    a decode product of few rows that is given split-K scratch is cut over K until it covers the chip
 #include <dlfcn.h>
@@ -80,24 +81,44 @@ static int aligned() {
   return bad ? 1 : 0;
 }
 
-static int forms(int d, int F, int V, int rows) {
+static int kernel_of(hipError_t e, int split, int steps, int rows) {
+  Dl_info info;
+  if (e != hipErrorLaunchFailure || !dladdr(last_kernel, &info) || !info.dli_sname) return 1;
+  printf("%s split %d steps %d rows %d\n", info.dli_sname, split, steps, rows);
+  return 0;
+}
+
+static int forms(int dtype, int d, int F, int V, int rows) {
   const void* p = (const void*)4096;
   FewRowsArgs in, out, head;
   in.M_max = out.M_max = head.M_max = rows;
-  fr_seg(1, in.p[0].seg[0], p, p, d, -d, 0);
+  fr_seg(dtype, in.p[0].seg[0], p, p, d, -d, 0);
   in.p[0].N = in.p[0].ldo = 3 * d; in.p[0].epilogue = EPI_BIAS;
-  fr_seg(1, in.p[1].seg[0], p, p, d, -d, 0);
+  fr_seg(dtype, in.p[1].seg[0], p, p, d, -d, 0);
   in.p[1].N = F; in.p[1].epilogue = EPI_BIAS_GELU; in.p[1].packed_K = d + F; in.p[1].packed_k0 = d;
-  fr_seg(1, out.p[0].seg[0], p, p, d + F, -(d + F), 0);
+  if (dtype) {
+    fr_seg(dtype, out.p[0].seg[0], p, p, d + F, -(d + F), 0);
+  } else {  // the caller's two matrices
+    fr_seg(dtype, out.p[0].seg[0], p, p, d, -(d + F), d);
+    fr_seg(dtype, out.p[0].seg[1], p, p, F, -(d + F), F);
+  }
+  const int steps = out.p[0].seg[0].steps + out.p[0].seg[1].steps;
   out.p[0].N = out.p[0].ldo = d; out.p[0].epilogue = EPI_F32; out.p[0].slab = (size_t)rows * d;
-  out.p[0].ksplit = few_rows_splits(d, out.p[0].seg[0].steps);
-  fr_seg(1, head.p[0].seg[0], p, p, d, -d, 0);
+  out.p[0].ksplit = few_rows_splits(d, steps);
+  fr_seg(dtype, head.p[0].seg[0], p, p, d, -d, 0);
   head.p[0].N = head.p[0].ldo = V; head.p[0].epilogue = EPI_F32;
   for (FewRowsArgs* a : {&in, &out, &head}) {
-    if (launch_few_rows(1, *a, a == &in ? 2 : 1, nullptr) != hipErrorLaunchFailure) return 1;
-    Dl_info info;
-    if (!dladdr(last_kernel, &info) || !info.dli_sname) return 1;
-    printf("%s split %d steps %d\n", info.dli_sname, a->p[0].ksplit, a->p[0].seg[0].steps);
+    const hipError_t e = launch_few_rows(dtype, *a, a == &in ? 2 : 1, nullptr);
+    if (kernel_of(e, a->p[0].ksplit, a == &out ? steps : a->p[0].seg[0].steps, rows)) return 1;
+  }
+  return 0;
+}
+
+static int many(int d, int F, int V, int rows) {
+  const int shapes[][3] = {{3 * d, d, EPI_BIAS}, {d, d, EPI_BIAS_RESADD}, {F, d, EPI_BIAS_GELU}, {d, F, EPI_BIAS_RESADD}, {V, d, EPI_F32}};
+  for (auto& q : shapes) {
+    const GemmArgs g = product(rows, q[0], q[1], q[2]);
+    if (few_rows_takes(0, g) && kernel_of(launch_gemm(0, g, nullptr), 1, q[1] / 32, rows)) return 1;
   }
   return 0;
 }
@@ -151,7 +172,9 @@ static int bias2() {
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "errors")) return errors();
   if (argc > 1 && !strcmp(argv[1], "aligned")) return aligned();
-  if (argc > 5 && !strcmp(argv[1], "forms")) return forms(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]));
+  if (argc > 6 && !strcmp(argv[1], "forms"))
+    return forms(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
+  if (argc > 5 && !strcmp(argv[1], "many")) return many(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]));
   if (argc > 1 && !strcmp(argv[1], "split")) return split();
   if (argc > 1 && !strcmp(argv[1], "bias2")) return bias2();
   return 2;

@@ -44,24 +44,40 @@ def test_a_second_bias_is_added_or_refused(products):
 
 def test_decode_passes_on_the_gpu_cover_every_form_of_the_kernel(products):
     """The shapes that the GPU tests grade against the oracle reach every form of the few-rows kernel in bf16, each but
-    the short-K one (form 2) with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
+    the short-K one (4 waves, 1 x 2 tiles) with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
     of eight."""
     from test_gpu_few_rows import DECODES, SHAPES, WIDE, WIDTHS
     runs = [(SHAPES[s][0], SHAPES[s][4], SHAPES[s][5], B) for s, B, *_ in DECODES if SHAPES[s][2] in (16, 64, 80, 128, 256)]
     runs += [(WIDTHS[w][0], WIDTHS[w][4], 515, B) for w, B in WIDE]
     seen, pipelined, splits = set(), set(), set()
     for d, F, V, B in runs:
-        r = subprocess.run([products, "forms", *map(str, (d, F, V, min(B, 256)))], capture_output=True, text=True, timeout=100)
+        r = subprocess.run([products, "forms", "1", *map(str, (d, F, V, min(B, 256)))], capture_output=True, text=True, timeout=100)
         assert r.returncode == 0, r.stdout + r.stderr
         for line in r.stdout.splitlines():
-            name, _, split, _, steps = line.split()
+            name, _, split, _, steps, *_ = line.split()
             form = tuple(map(int, re.search(r"DF16_Li(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups()))
             seen.add(form)
             splits.add(int(split))
             if int(steps) // int(split) // form[0] >= 2 * form[3]:
                 pipelined.add(form)
     with open(os.path.join(ROOT, "paper_2403_17031_amd", "csrc", "few_rows.hip")) as f:
-        forms = {tuple(map(int, m)) for m in re.findall(r"X\(\d, (\d), (\d), (\d), (\d), (\d)\)", f.read())}
-    assert len(forms) == 9 and seen == forms
+        forms = {tuple(map(int, m)) for m in re.findall(r"X\(\d+, (\d), (\d), (\d), (\d), (\d)\)", f.read())}
+    assert len(forms) == 12 and seen == forms
     assert {f for f in forms if f[:3] != (4, 1, 2)} <= pipelined
     assert max(splits) == 8
+
+
+def _forms(products, dtype, d, rows, vocab=50304):
+    """(waves, row tiles, column tiles) that a decode pass of a model of width d takes for QKV + FC1, for out-projection +
+    FC2 and for the LM head."""
+    args = ["forms", *(str(x) for x in (dtype, d, 4 * d, vocab, rows))]
+    r = subprocess.run([products, *args], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return [tuple(map(int, re.search(r"I(?:DF16_|f)Li(\d)ELi(\d)ELi(\d)E", line).groups())) for line in r.stdout.splitlines()]
+
+
+@pytest.mark.parametrize("d", [512, 768, 1536, 2048, 4096])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 64])
+def test_no_idle_row_tiles_in_forms_of_two_and_four_column_tiles(products, d, rows):
+    for _, row_tiles, column_tiles in _forms(products, 1, d, rows):
+        assert column_tiles > 4 or row_tiles == (rows + 15) // 16
