@@ -302,10 +302,12 @@ static const FrForm kForms[] = {RLHF_FR_FORMS(RLHF_FR_ENTRY)};
 // fewer steps they have.  Five column tiles for the 1120 of QKV + FC1 at width 2560 are 224 blocks, one round, where two
 // are 560.  Fitted to a sweep of widths 512-4096 and 1-256 rows (dec_driver, cold).  us by column tiles (* the one taken):
 //   QKV + FC1       width  768:  1 row   5.1*/ 6.2 /  8.4        32 rows  4.9*/  7.0 /  9.5    64 rows  6.2*/  9.2 / 10.7 / 15.4    (2 / 4 / 5 / 8)
-//                         2048:  1 row  13.4*/ 13.4 / 14.9       32 rows 16.7 / 15.4*/ 18.0    64 rows 21.8 / 20.1*/ 22.1 / 30.4
+//                         1536:  1 row  10.0 / 9.5*/ 11.6        32 rows 12.0 / 11.4*/ 13.7    64 rows 15.1*/ 15.3 / 17.1 / 24.7
+//                         2048:  1 row  13.4 / 13.4*/ 14.9       32 rows 16.7 / 15.4*/ 18.0    64 rows 21.8 / 20.1*/ 22.1 / 30.4
 //                         2560:  1 row  24.2 / 27.4 / 20.5*      32 rows 29.4 / 33.0 / 24.4*   64 rows 37.3 / 40.1 / 28.4*/ 38.6
 //                         4096:  1 row  45.6 / 45.7*/ 51.9       32 rows 56.7 / 51.4*/ 58.2    64 rows 72.4 / 60.6 / 68.2 / 55.5*
-//   out-proj + FC2        2048:  1 row   8.3*/  9.3 /  9.1       32 rows  9.5*/  9.9 / 11.3    64 rows 12.5 / 12.5*/ 13.7 / 18.7    (K in 8)
+//   out-proj + FC2        1152:  1 row   6.5 /  5.4*/  7.3                                                                     (K in 8)
+//                         2048:  1 row   8.3*/  9.3 /  9.1       32 rows  9.5*/  9.9 / 11.3    64 rows 12.5 / 12.5*/ 13.7 / 18.7
 //                         2560:  1 row  14.6 / 16.8 / 13.3*      32 rows 17.9 / 19.5 / 15.5*   64 rows 23.0 / 24.6 / 17.7*/ 23.2
 //                         4096:  1 row  31.5 / 30.0*/ 34.0       32 rows 39.1 / 34.4*/ 39.5    64 rows 50.5 / 41.4 / 47.2 / 38.2*
 //   LM head                768:  1 row  17.8*/ 17.3 / 19.1       32 rows 20.6 / 21.5 / 20.8*   64 rows 26.8 / 26.3*/ 30.7 / 29.6
@@ -338,6 +340,21 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
       best = i;
       *cost = t;
     }
+  }
+  // A second round that is not full costs more than the average of further ones: a wider form that does with one round, on
+  // half of the CUs or more, is up to 20 % faster (1 to 16 rows, two / four column tiles, us: width 1152 out-projection + FC2
+  // 6.5 / 5.4, 1536 6.9 / 6.3 and QKV + FC1 10.0 / 9.5, 2304 16.7 / 15.0; 1920 out-projection + FC2 7.8 / 7.9), but not
+  // where two full rounds are against one full (2048 out-projection + FC2 8.3 / 9.3) or the rows are 49 and more.
+  if (rows <= 48 && blocks(kForms[best]) > 256 && blocks(kForms[best]) < 512) {
+    int one = -1;
+    double one_t = 0;
+    for (int i = 0; i < (int)(sizeof(kForms) / sizeof(kForms[0])); ++i) {
+      const FrForm& f = kForms[i];
+      if (f.mt != tiles || f.ct <= kForms[best].ct || !takes(f) || blocks(f) > 256 || blocks(f) < 128) continue;
+      const double t = fr_cost(f, rows, blocks(f), (double)steps / ks);
+      if (one < 0 || t < one_t) one = i, one_t = t;
+    }
+    if (one >= 0) best = one;
   }
   return best;
 }

@@ -81,3 +81,14 @@ def _forms(products, dtype, d, rows, vocab=50304):
 def test_no_idle_row_tiles_in_forms_of_two_and_four_column_tiles(products, d, rows):
     for _, row_tiles, column_tiles in _forms(products, 1, d, rows):
         assert column_tiles > 4 or row_tiles == (rows + 15) // 16
+
+
+@pytest.mark.parametrize("rows", [1, 16, 17, 48])
+def test_one_round_rather_than_a_second_that_is_not_full(products, rows):
+    """Two column tiles would be 288 to 448 blocks where four are 144 to 224; at 512 blocks both rounds are full."""
+    tiles = (rows + 15) // 16
+    assert _forms(products, 1, 1152, rows)[1] == (4, tiles, 4)
+    assert [f for f in _forms(products, 1, 1536, rows)[:2]] == [(4, tiles, 4)] * 2
+    assert _forms(products, 1, 2048, rows)[0] == (4, tiles, 4)
+    if rows <= 16:
+        assert _forms(products, 1, 2048, rows)[1] == (4, 1, 2)
