@@ -4,7 +4,7 @@
 //
 // Such a product is its weights' bytes and nothing else: at M = 64 the matrix cores need a tenth of the time the
 // weights take to arrive.  What the kernel is built around is bytes in flight and few launches:
-//   * A block of four waves owns 32 to 128 output columns for all K of its split; the waves divide K, each holding the
+//   * A block of four waves (eight in one form) owns 32 to 128 output columns for all K of its split; the waves divide K, each holding the
 //     weights of its next PF steps (128 bytes of every weight row per step; PF is two to four) in registers.  At K = 2560
 //     a wave has ten steps.
 //   * Both operands go global -> registers: 16 weight rows x 128 bytes per step, lane (l16, q) taking the 32 bytes at
@@ -16,7 +16,7 @@
 //     few column tiles to cover the chip: then K is cut over blocks into fp32 slabs that the consumer adds in order.
 //   * Two products that are ready together (QKV and FC1 of a parallel-residual layer) share one launch.
 // Width 2560, cold weights (dec_driver): QKV + FC1 21 us for one row (4.4 TB/s), 21 for 16, 24 for 30, 29 for 64;
-// out-projection + FC2 13 to 18; LM head 52 us for one row (5.0 TB/s), 73 for 64.  The weight-streaming kernel of
+// out-projection + FC2 13 to 18; LM head 49 us for one row (5.3 TB/s), 73 for 64.  The weight-streaming kernel of
 // gemm_skinny.hip took 17.6 us for a QKV product alone and left slabs to add; the plain fp32 tile kernel 50 us for each
 // product of the 70M shape at two rows (now 4 to 9).
 #include <algorithm>
@@ -284,16 +284,18 @@ bool few_rows_takes(int dtype, const GemmArgs& a) {
 // Forms of the kernel: waves, row tiles, column tiles, steps held, waves per SIMD.  An idle row tile costs the bf16 mode 2-4 %
 // where it is one of three (its lanes all ask for row M - 1) and 5-18 % where it is one or two of four (registers, waves in
 // flight): 24 rows in forms of 2 / 4 row tiles, four column tiles each, width 2048 QKV + FC1 14.8 / 17.7 us, 4096 48.8 / 53.5.
+// The last form divides K over eight waves (fr_form).
 #define RLHF_FR_FORMS(X)                                                                                          \
   X(0, 4, 1, 2, 4, 4) X(1, 4, 1, 4, 3, 3) X(2, 4, 1, 5, 4, 2) X(3, 4, 2, 2, 3, 3) X(4, 4, 2, 4, 2, 3)            \
   X(5, 4, 3, 2, 3, 2) X(6, 4, 3, 4, 2, 2) X(7, 4, 3, 5, 2, 2) X(8, 4, 4, 2, 3, 2) X(9, 4, 4, 4, 2, 2)            \
-  X(10, 4, 4, 5, 2, 1) X(11, 4, 4, 8, 2, 1)
+  X(10, 4, 4, 5, 2, 1) X(11, 4, 4, 8, 2, 1) X(12, 8, 1, 2, 4, 4)
 #define RLHF_FR_ENTRY(ID, WV, MT, CT, PF, OCC) {MT, CT, OCC},
 struct FrForm {
   int mt, ct, occ;
 };
 static const FrForm kForms[] = {RLHF_FR_FORMS(RLHF_FR_ENTRY)};
 #undef RLHF_FR_ENTRY
+constexpr int kEightWaves = 12;
 
 // How a product is cut: 16 * ct columns per block, and K over ks blocks.  A CU can have about 32 KB of loads in flight (its
 // L1), for which a block's weights, ct column tiles wide, compete with its rows of A, mt tiles; and the launch lasts as
@@ -311,7 +313,7 @@ static const FrForm kForms[] = {RLHF_FR_FORMS(RLHF_FR_ENTRY)};
 //                         2560:  1 row  14.6 / 16.8 / 13.3*      32 rows 17.9 / 19.5 / 15.5*   64 rows 23.0 / 24.6 / 17.7*/ 23.2
 //                         4096:  1 row  31.5 / 30.0*/ 34.0       32 rows 39.1 / 34.4*/ 39.5    64 rows 50.5 / 41.4 / 47.2 / 38.2*
 //   LM head                768:  1 row  17.8*/ 17.3 / 19.1       32 rows 20.6 / 21.5 / 20.8*   64 rows 26.8 / 26.3*/ 30.7 / 29.6
-//                         2560:  1 row  53.2 / 53.4 / 51.5*                                  64 rows 83.9 / 76.9 / 73.3 / 71.2*
+//                         2560:  1 row  53.2 / 53.4 / 51.5 (eight waves 48.5*)                 64 rows 83.9 / 76.9 / 73.3 / 71.2*
 static double fr_cost(const FrForm& f, int rows, int blocks, double steps) {
   const int row_tiles = std::min((rows + 15) / 16, 4);
   const double further = f.occ > 1 ? 0.74 * steps / (steps + 6) : 0.8;
@@ -331,7 +333,7 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
     return true;
   };
   int best = -1, done = 0;  // done: column tiles with a form already (the first that holds the rows has the fewest row tiles)
-  for (int i = 0; i < (int)(sizeof(kForms) / sizeof(kForms[0])); ++i) {
+  for (int i = 0; i < kEightWaves; ++i) {
     const FrForm& f = kForms[i];
     if (!takes(f) || (done >> f.ct & 1)) continue;
     done |= 1 << f.ct;
@@ -348,7 +350,7 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
   if (rows <= 48 && blocks(kForms[best]) > 256 && blocks(kForms[best]) < 512) {
     int one = -1;
     double one_t = 0;
-    for (int i = 0; i < (int)(sizeof(kForms) / sizeof(kForms[0])); ++i) {
+    for (int i = 0; i < kEightWaves; ++i) {
       const FrForm& f = kForms[i];
       if (f.mt != tiles || f.ct <= kForms[best].ct || !takes(f) || blocks(f) > 256 || blocks(f) < 128) continue;
       const double t = fr_cost(f, rows, blocks(f), (double)steps / ks);
@@ -356,6 +358,14 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
     }
     if (one >= 0) best = one;
   }
+  // An LM head of few rows is weights alone, and eight waves keep more of them in flight where each has four to seven steps
+  // and rows do not start at one multiple of 4 KB each, which all fall on the same memory channels.  One row, two or five
+  // column tiles / eight waves, us: width 2176 41.7 / 39.8, 2560 51.5 / 48.5, 3072 62.6 / 56.2, 3584 67.9 / 64.8; but 1536
+  // 29.5 / 32.2, 2048 37.7 / 40.3, 3840 73.0 / 74.7, 4096 75.0 / 96.4.  Sixteen rows: 5 column tiles win where the cost
+  // takes them (2560 54.3 / 55.9), eight waves against two column tiles (2048 45.4 / 44.2, 2432 54.3 / 51.5).
+  if (rows <= 16 && ks == 1 && blocks(kForms[kEightWaves]) > 1024 && steps >= 32 && steps < 58 &&
+      (rows > 8 ? kForms[best].ct == 2 : ldw_bytes % 4096 != 0))
+    best = kEightWaves;
   return best;
 }
 // The split of a product left as slabs: the same for any number of rows, its consumer adds that many.  (At least seven

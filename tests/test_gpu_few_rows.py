@@ -18,6 +18,8 @@ SHAPES = {
     # head sizes without a decode kernel of their own: the general pass, with few-rows products or split ones
     "hd32": (256, 8, 32, 8, 512, 300), "hd96": (768, 8, 96, 24, 512, 300), "hd32-1024": (1024, 32, 32, 8, 1024, 300),
     "hd32-2112": (2112, 66, 32, 8, 256, 300), "hd32-4096": (4096, 128, 32, 8, 128, 300),
+    # LM heads of more than 1024 blocks and 33 or 34 steps (bf16 / fp32): the form of eight waves
+    "head2112": (2112, 33, 64, 16, 128, 32800), "head1088": (1088, 17, 64, 16, 128, 32800),
 }
 
 DECODES = [  # shape, sequences, shortest and longest query
@@ -26,7 +28,8 @@ DECODES = [  # shape, sequences, shortest and longest query
     ("hd128", 64, 1, 8), ("hd64", 65, 1, 8), ("hd80", 128, 1, 40), ("hd256", 129, 1, 9), ("hd16", 193, 1, 70),
     ("hd80", 256, 1, 8), ("hd64", 257, 1, 8), ("hd32", 1, 1, 5), ("hd32", 64, 1, 9), ("hd96", 56, 3, 20), ("hd96", 57, 1, 9),
     ("hd32-1024", 32, 1, 9), ("hd32-1024", 33, 1, 9), ("hd32-1024", 64, 5, 40), ("hd32-2112", 3, 1, 9),
-    ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9)
+    ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9), ("head2112", 1, 1, 9), ("head2112", 8, 1, 9), ("head1088", 1, 1, 9),
+    ("head1088", 8, 1, 9)
 ]
 # One layer of the wide models, whose products take the other forms of the kernel (64 columns per block, K loops long
 # enough to be pipelined): sequences at the edges of the row tiles

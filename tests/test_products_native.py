@@ -44,7 +44,7 @@ def test_a_second_bias_is_added_or_refused(products):
 
 def test_decode_passes_on_the_gpu_cover_every_form_of_the_kernel(products):
     """The shapes that the GPU tests grade against the oracle reach every form of the few-rows kernel in bf16, each but
-    the short-K one (4 waves, 1 x 2 tiles) with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
+    the two of 1 x 2 tiles, which short K loops take, with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
     of eight."""
     from test_gpu_few_rows import DECODES, SHAPES, WIDE, WIDTHS
     runs = [(SHAPES[s][0], SHAPES[s][4], SHAPES[s][5], B) for s, B, *_ in DECODES if SHAPES[s][2] in (16, 64, 80, 128, 256)]
@@ -62,8 +62,8 @@ def test_decode_passes_on_the_gpu_cover_every_form_of_the_kernel(products):
                 pipelined.add(form)
     with open(os.path.join(ROOT, "paper_2403_17031_amd", "csrc", "few_rows.hip")) as f:
         forms = {tuple(map(int, m)) for m in re.findall(r"X\(\d+, (\d), (\d), (\d), (\d), (\d)\)", f.read())}
-    assert len(forms) == 12 and seen == forms
-    assert {f for f in forms if f[:3] != (4, 1, 2)} <= pipelined
+    assert len(forms) == 13 and seen == forms
+    assert {f for f in forms if f[1:3] != (1, 2)} <= pipelined
     assert max(splits) == 8
 
 
@@ -92,3 +92,9 @@ def test_one_round_rather_than_a_second_that_is_not_full(products, rows):
     assert _forms(products, 1, 2048, rows)[0] == (4, tiles, 4)
     if rows <= 16:
         assert _forms(products, 1, 2048, rows)[1] == (4, 1, 2)
+
+
+def test_eight_waves_for_the_lm_head_of_few_rows(products):
+    head = {(d, rows): _forms(products, 1, d, rows)[2] for d in (1536, 2048, 2432, 2560, 3072, 4096) for rows in (1, 8, 16, 17)}
+    eight = {k for k, form in head.items() if form == (8, 1, 2)}
+    assert eight == {(2432, 1), (2432, 8), (2560, 1), (2560, 8), (3072, 1), (3072, 8), (2048, 16), (2432, 16)}
