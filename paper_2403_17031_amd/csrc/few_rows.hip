@@ -330,7 +330,10 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
   auto takes = [&](const FrForm& f) {
     if (f.mt < tiles) return false;
     if (f.ct > 2 && 16 * (size_t)f.ct * ldw_bytes >= ((size_t)1 << 32)) return false;  // a lane's offset within the block's rows
-    return true;
+    // fp32: the matrix instructions of an idle row tile take as long as any other's, eight times as many as in bf16 (an LM head
+    // of 24 rows in forms of 2 x 2 / 3 x 5 tiles: width 512 30 / 45 us, 768 46 / 62); and 3 x 5 loses to 3 x 2 and 3 x 4 at all
+    // four widths measured (40 rows, 512: 45.9 / 41.0).
+    return dtype != 0 || (f.mt == tiles && !(f.mt == 3 && f.ct == 5));
   };
   int best = -1, done = 0;  // done: column tiles with a form already (the first that holds the rows has the fewest row tiles)
   for (int i = 0; i < kEightWaves; ++i) {

@@ -98,3 +98,10 @@ def test_eight_waves_for_the_lm_head_of_few_rows(products):
     head = {(d, rows): _forms(products, 1, d, rows)[2] for d in (1536, 2048, 2432, 2560, 3072, 4096) for rows in (1, 8, 16, 17)}
     eight = {k for k, form in head.items() if form == (8, 1, 2)}
     assert eight == {(2432, 1), (2432, 8), (2560, 1), (2560, 8), (3072, 1), (3072, 8), (2048, 16), (2432, 16)}
+
+
+@pytest.mark.parametrize("d", [512, 768, 1024, 2048])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 64, 100])
+def test_no_idle_row_tiles_in_fp32(products, d, rows):
+    for _, row_tiles, column_tiles in _forms(products, 0, d, rows):
+        assert row_tiles == min((rows + 15) // 16, 4) and (row_tiles, column_tiles) != (3, 5)
