@@ -31,11 +31,14 @@ DECODES = [  # shape, sequences, shortest and longest query
     ("hd32-4096", 4, 1, 9), ("hd32-4096", 5, 1, 9), ("head2112", 1, 1, 9), ("head2112", 8, 1, 9), ("head1088", 1, 1, 9),
     ("head1088", 8, 1, 9)
 ]
-# One layer of the wide models, whose products take the other forms of the kernel (64 columns per block, K loops long
-# enough to be pipelined): sequences at the edges of the row tiles
+# One layer of the wide models, whose products take the other forms of the kernel (64 to 128 columns per block, K loops
+# long enough to be pipelined): sequences at the edges of the row tiles, and several row tiles of the forms of 64 and 80
+# columns up to the line to the other decode pass
 WIDTHS = {"1b": (2048, 8, 256, 64, 8192), "2.8b": (2560, 32, 80, 20, 10240), "6.9b": (4096, 32, 128, 32, 16384)}
 WIDE = [("1b", 1), ("1b", 17), ("1b", 48), ("1b", 64), ("2.8b", 16), ("2.8b", 32), ("2.8b", 48), ("2.8b", 64), ("6.9b", 5),
-        ("6.9b", 31), ("6.9b", 37), ("6.9b", 64)]
+        ("6.9b", 31), ("6.9b", 37), ("6.9b", 64), ("2.8b", 65), ("2.8b", 128), ("1b", 129), ("1b", 192)]
+WIDE_FP32 = [("1b", 1), ("1b", 17), ("1b", 33), ("1b", 64), ("2.8b", 1), ("2.8b", 64), ("6.9b", 64)]
+MANY_FP32 = [("1b", 3, 50), ("1b", 4, 75)]  # rescoring: width, sequences, tokens of each
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
@@ -65,7 +68,7 @@ def test_decode_of_few_sequences(dtype, shape, B, lo, hi):
 
 @pytest.mark.parametrize("shape,B,few", [
     ("hd64", 1, True), ("hd64", 256, True), ("hd64", 257, False), ("hd32", 4, False),  # a size, a head size without a kernel
-    ("d1536", 64, True), ("d1536", 192, True), ("d1536", 193, False),  # weights of a layer times row tiles up to 2^27
+    ("d1536", 64, True), ("d1536", 192, True), ("d1536", 193, False),  # weights of a layer times row tiles up to 5 * 2^25
     ("d4160", 1, False)])  # a width the decode LayerNorm does not take
 def test_which_decode_pass(shape, B, few):
     import torch
@@ -99,26 +102,26 @@ def test_the_line_between_the_decode_passes(F, few):
 def wide_model():
     kept = {}
 
-    def get(width):
-        if width not in kept:
+    def get(width, dtype):
+        if (width, dtype) not in kept:
             kept.clear()  # one at a time: a layer at width 4096 is 1.6 GB in float64
             d, H, hd, r, F = WIDTHS[width]
-            cfg = ModelConfig(1, d, H, hd, r, F, vocab=515, dtype="bf16", pad_id=515)
+            cfg = ModelConfig(1, d, H, hd, r, F, vocab=515, dtype=dtype, pad_id=515)
             w = make_weights(cfg, 78, variant="test")
             from oracle import neox_oracle as O
-            kept[width] = (cfg, w, O.OracleModel(w, cfg))
-        return kept[width]
+            kept[width, dtype] = (cfg, w, O.OracleModel(w, cfg))
+        return kept[width, dtype]
     return get
 
 
-@pytest.mark.parametrize("width,B", WIDE)
-def test_decode_at_the_width_of_a_wide_model(wide_model, width, B):
+@pytest.mark.parametrize("dtype,width,B", [("bf16", *c) for c in sorted(WIDE)] + [("fp32", *c) for c in sorted(WIDE_FP32)])
+def test_decode_at_the_width_of_a_wide_model(wide_model, dtype, width, B):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2403_17031_amd as P
     from oracle import neox_oracle as O
-    cfg, w, oracle = wide_model(width)
+    cfg, w, oracle = wide_model(width, dtype)
     g = np.random.default_rng(B)
     hi, N = 12, 4
     lens = g.integers(1, hi + 1, size=B)
@@ -126,9 +129,27 @@ def test_decode_at_the_width_of_a_wide_model(wide_model, width, B):
     mask = (np.arange(hi)[None, :] >= (hi - lens)[:, None]).astype(np.uint8)
     queries = np.where(mask == 1, g.integers(1, 515, size=(B, hi)), 515).astype(np.int32)
     toks, lps, _ = (x.cpu().numpy() for x in P.Policy(cfg, w).rollout_generate(queries, mask, 12, 0.7, N))
-    for rep in O.verify_rollout(oracle, toks, mask, 12, 0.7, N, rows=sorted({0, B // 2, B - 1})):
-        assert rep["deficit"] <= NEAR_TIE, rep
-        assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL["bf16"], rep
+    for rep in O.verify_rollout(oracle, toks, mask, 12, 0.7, N, rows=sorted({0, B // 2, 64 if B > 64 else 0, B - 1})):
+        assert rep["deficit"] <= (0.0 if dtype == "fp32" else NEAR_TIE), rep
+        assert abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL[dtype], rep
+
+
+@pytest.mark.parametrize("width,B,L", MANY_FP32)
+def test_fp32_rescoring_of_many_rows(wide_model, width, B, L):
+    """The products of an fp32 pass over many rows are the few-rows kernel's too, its forms of up to 128 columns with
+    several row tiles."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_17031_amd as P
+    from oracle import neox_oracle as O
+    cfg, w, oracle = wide_model(width, "fp32")
+    g = np.random.default_rng(L)
+    tokens, mask = g.integers(1, 515, size=(B, L)).astype(np.int32), np.ones((B, L), np.uint8)
+    lp, val = (x.cpu().numpy() for x in P.Policy(cfg, w).score_sequences(tokens, mask, 0.7))
+    olp, oval = O.score_sequences(oracle, tokens, mask, 0.7)
+    assert np.abs(lp - olp).max() <= TOL["fp32"]
+    assert np.abs(val - oval).max() <= TOL["fp32"] * max(1.0, float(np.abs(oval).max()))
 
 
 def test_weights_at_any_float_address(monkeypatch):

@@ -42,28 +42,38 @@ def test_a_second_bias_is_added_or_refused(products):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
-def test_decode_passes_on_the_gpu_cover_every_form_of_the_kernel(products):
-    """The shapes that the GPU tests grade against the oracle reach every form of the few-rows kernel in bf16, each but
-    the two of 1 x 2 tiles, which short K loops take, with a K loop that is long enough to be pipelined (2 * PF steps per wave), and a K split
-    of eight."""
-    from test_gpu_few_rows import DECODES, SHAPES, WIDE, WIDTHS
-    runs = [(SHAPES[s][0], SHAPES[s][4], SHAPES[s][5], B) for s, B, *_ in DECODES if SHAPES[s][2] in (16, 64, 80, 128, 256)]
-    runs += [(WIDTHS[w][0], WIDTHS[w][4], 515, B) for w, B in WIDE]
-    seen, pipelined, splits = set(), set(), set()
-    for d, F, V, B in runs:
-        r = subprocess.run([products, "forms", "1", *map(str, (d, F, V, min(B, 256)))], capture_output=True, text=True, timeout=100)
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_runs_on_the_gpu_cover_every_form_of_the_kernel(products, dtype):
+    """The shapes that the GPU tests grade against the oracle reach every form of the few-rows kernel in either mode (3 x 5
+    tiles are bf16's alone), each but the two that are taken for short K loops (1 x 2 tiles) with one that is long
+    enough to be pipelined (2 * PF steps per wave) in bf16, those of 4 row tiles and up to 80 columns with several row tiles, and a K
+    split of eight."""
+    from test_gpu_few_rows import DECODES, MANY_FP32, SHAPES, WIDE, WIDE_FP32, WIDTHS
+    fp32 = dtype == "fp32"
+    runs = [("forms", SHAPES[s][0], SHAPES[s][4], SHAPES[s][5], min(B, 256)) for s, B, *_ in DECODES
+            if SHAPES[s][2] in (16, 64, 80, 128, 256)]
+    runs += [("forms", WIDTHS[w][0], WIDTHS[w][4], 515, B) for w, B in (WIDE_FP32 if fp32 else WIDE)]
+    runs += [("many", WIDTHS[w][0], WIDTHS[w][4], 515, B * L) for w, B, L in MANY_FP32 if fp32]
+    seen, pipelined, tiles, splits = set(), set(), set(), set()
+    for what, *sizes in runs:
+        args = [what, *(["0" if fp32 else "1"] if what == "forms" else []), *map(str, sizes)]
+        r = subprocess.run([products, *args], capture_output=True, text=True, timeout=100)
         assert r.returncode == 0, r.stdout + r.stderr
         for line in r.stdout.splitlines():
-            name, _, split, _, steps, *_ = line.split()
-            form = tuple(map(int, re.search(r"DF16_Li(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups()))
+            name, _, split, _, steps, _, rows = line.split()
+            form = tuple(map(int, re.search(r"I(?:DF16_|f)Li(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups()))
             seen.add(form)
             splits.add(int(split))
             if int(steps) // int(split) // form[0] >= 2 * form[3]:
                 pipelined.add(form)
+            if int(rows) > 64:
+                tiles.add(form[:3])
     with open(os.path.join(ROOT, "paper_2403_17031_amd", "csrc", "few_rows.hip")) as f:
         forms = {tuple(map(int, m)) for m in re.findall(r"X\(\d+, (\d), (\d), (\d), (\d), (\d)\)", f.read())}
-    assert len(forms) == 13 and seen == forms
-    assert {f for f in forms if f[1:3] != (1, 2)} <= pipelined
+    assert len(forms) == 13
+    assert seen == {f for f in forms if not fp32 or f[:3] != (4, 3, 5)}
+    assert fp32 or {f for f in forms if f[1:3] != (1, 2)} <= pipelined
+    assert {(4, 4, 2), (4, 4, 4), (4, 4, 5)} <= tiles and (not fp32 or (4, 4, 8) in tiles)
     assert max(splits) == 8
 
 
