@@ -118,10 +118,11 @@ __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + e
 
 // 1 / (1 + 2^t), the division correctly rounded.  The compiler's division is eleven instructions, half of the GELU below,
 // and in the FC1 product's epilogue nothing hides them; the hardware reciprocal (1 ulp) with one correction step by FMA is
-// three, and gives the same bits (compared for every float from 1 to 2^126).  t is capped at 126, which keeps the step
-// away from infinities: there the result is 2^-126 in the place of something smaller, zero in an fp16 product either way.
+// three, and gives the same bits (compared for every float from 1 to 2^126).  t is capped at 127.5, which keeps the step
+// away from infinities; beyond 126 the reciprocal is a denormal number, which the instruction flushes, so that the result is
+// the 0 that 1 / infinity is: with the smallest normal number instead, -3e38 (a bias, say) times it would be -3.5.
 __device__ __forceinline__ float recip_rn_sigmoid(float t) {
-  const float y = 1.0f + __builtin_amdgcn_exp2f(fminf(t, 126.0f));
+  const float y = 1.0f + __builtin_amdgcn_exp2f(fminf(t, 127.5f));
   const float r = __builtin_amdgcn_rcpf(y);
   return fmaf(fmaf(-y, r, 1.0f), r, r);
 }

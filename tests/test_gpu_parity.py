@@ -356,3 +356,24 @@ def test_rotary_layouts_with_many_rows(gpu, H, hd, r):
     queries, mask = _queries(cfg, B=24, Lq=48, lo=20, hi=48, seed=H * hd + r)
     rows = sorted({0, 23, int(np.argmin(mask.sum(1)))})
     _check_rollout_and_scores(gpu, cfg, w, queries, mask, seed=900 + r, T=0.7, N=3, rows=rows, expect_exact=False)
+
+
+def test_gelu_of_the_largest_negative_inputs_with_many_rows(gpu):
+    """FC1 biases of -3e38, for which the GELU of the large products is 0 as it is for -10000, to the bit."""
+    from synth.inputs import round_to_bf16
+    cfg = ModelConfig(n_layers=2, d_model=128, n_heads=2, head_dim=64, rotary_dims=16, d_ff=512, vocab=300, dtype="bf16",
+                      eos_id=0, pad_id=300)
+    w = make_weights(cfg, 41, variant="test")
+    g = np.random.default_rng(41)
+    tokens, mask = g.integers(1, 300, size=(3, 200)).astype(np.int32), np.ones((3, 200), np.uint8)
+    out = []
+    for low in (-1e4, -1e30, -3e38):
+        for layer in range(2):
+            w[f"layers.{layer}.b_fc1"][::2] = round_to_bf16(np.full(256, low, np.float32))
+        pol = gpu.Policy(cfg, w)
+        out.append([x.cpu().numpy() for x in pol.score_sequences(tokens, mask, 0.7)])
+        pol.close()
+    lp, val = _oracle().score_sequences(_oracle().OracleModel(w, cfg), tokens, mask, 0.7)
+    assert np.abs(out[0][0] - lp).max() <= TOL["bf16"] and np.abs(out[0][1] - val).max() <= TOL["bf16"]
+    for o in out[1:]:
+        assert (o[0] == out[0][0]).all() and (o[1] == out[0][1]).all()
