@@ -371,15 +371,18 @@ static int fr_form(int dtype, int n_a, int n_b, int rows, int steps, int ks, siz
     best = kEightWaves;
   return best;
 }
-// The split of a product left as slabs: the same for any number of rows, its consumer adds that many.  (At least seven
-// steps of 128 bytes to a block.)
+// The split of a product left as slabs: the same for any number of rows, its consumer adds that many.  At least seven
+// steps of 128 bytes to a block; and no step from one round to a second that is not full: out-projection + FC2 of widths 3136 to
+// 4032 with K in 4 / 8 (196 to 252 blocks / twice as many), us: 3328 1 row 21.1 / 22.1, 32 rows 24.6 / 26.1, 64 rows 30.5 / 32.1;
+// 3840 27.2 / 27.2, 30.5 / 32.9, 37.1 / 36.5; where both are full (4096), 30.8 / 30.0, 33.4 / 34.4, 40.0 / 38.2.
 int few_rows_splits(int N, int steps) {
-  int best = 1;
+  int best = 1, best_blocks = 0;
   double best_t = 0;
   for (int ks = 1; ks <= 8 && (ks == 1 || steps / ks >= 7); ks *= 2) {
     double t = 0;
-    fr_form(1, N, 0, 32, steps, ks, 0, &t);
-    if (ks == 1 || t < best_t * 0.95) best = ks, best_t = t;
+    const int c = 16 * kForms[fr_form(1, N, 0, 32, steps, ks, 0, &t)].ct, blocks = (N + c - 1) / c * ks;
+    const bool partial = best_blocks <= 256 && blocks > 256 && blocks < 512;
+    if (ks == 1 || (t < best_t * 0.95 && !partial)) best = ks, best_t = t, best_blocks = blocks;
   }
   return best;
 }

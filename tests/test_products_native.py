@@ -115,3 +115,11 @@ def test_eight_waves_for_the_lm_head_of_few_rows(products):
 def test_no_idle_row_tiles_in_fp32(products, d, rows):
     for _, row_tiles, column_tiles in _forms(products, 0, d, rows):
         assert row_tiles == min((rows + 15) // 16, 4) and (row_tiles, column_tiles) != (3, 5)
+
+
+@pytest.mark.parametrize("d,split", [(512, 4), (768, 8), (2560, 8), (3072, 8), (3136, 4), (3584, 4), (4032, 4), (4096, 8)])
+def test_split_of_the_residual_product(products, d, split):
+    """K in 8 but where that would be a second round of blocks that is not full, or fewer than seven steps to a block."""
+    for rows in (1, 32, 64):
+        r = subprocess.run([products, "forms", "1", str(d), str(4 * d), "515", str(rows)], capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0 and r.stdout.splitlines()[1].split()[1:3] == ["split", str(split)], r.stdout
