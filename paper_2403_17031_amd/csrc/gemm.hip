@@ -303,6 +303,9 @@ __global__ void __launch_bounds__(256)
 // FC1 180 / 132, out-projection + FC2 190 / 150, K-major 159 / 110; 3,456 rows 33 / 25, 35 / 30, 78 / 40; 83,373 rows of width
 // 2560 3381 / 3280, 4511 / 4240, 5203 / 5065; 21,504 of 4096 2041 / 1970, 2709 / 2572, 3410 / 3186 (FC1's with a fifth less
 // GELU arithmetic, and about 2 % of each between runs).
+// The quarter tiles' share of that, us without / with them: 22,200 rows of 768 QKV 108 / 98, FC1 145 / 139, out-projection +
+// FC2 184 / 149; 3,456 rows 29 / 25, 31 / 30, 77 / 40; 10,900 rows 55 / 56, 83 / 72, 90 / 89; 21,504 of 4096 1849 / 1836, 2434 /
+// 2421, 3233 / 3077; 83,373 of 2560 within 1 %.
 // =================================================================================================
 #define RLHF_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define RLHF_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -556,7 +559,7 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
   constexpr int NLD = 4;        // tile loads per wave, stage and operand
   constexpr int NMF = MT * NT;  // matrix instructions per wave per sub-step
   // stage s of the big tile: A rows in la<s>, W rows in lw<s> (separate variables, so that a read of one does not wait for
-  // the loads into another); the 128x128 tiles use the four as a ring of stages
+  // the loads into another); the 128x128 tiles use them as two stages of K depth 128, (la0, lw0) and (la1, lw1)
   __shared__ __attribute__((aligned(16))) uint16_t la0[DOP];
   __shared__ __attribute__((aligned(16))) uint16_t lw0[DOP];
   __shared__ __attribute__((aligned(16))) uint16_t la1[DOP];

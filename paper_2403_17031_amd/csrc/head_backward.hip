@@ -497,12 +497,11 @@ __global__ void __launch_bounds__(256)
   }
 }
 // The column-sum passes below: a block owns 64 columns of a row split.  Its 256 threads move a chunk of rows with 16-byte
-// accesses, four rows of each operand in flight per thread, and leave the values to be summed in LDS; one wave then adds
-// them, a lane per column, in increasing row order, while the others are at the next chunk (two buffers, one barrier per
-// chunk).  One row of part per split.
+// accesses, four loads in flight per thread (four rows; in the GELU pass, which has two operands, two), and leave the
+// values to be summed in LDS; one wave then adds them, a lane per column, in increasing row order, while the others are at
+// the next chunk (two buffers, one barrier per chunk).  One row of part per split.
 // (A thread that walks its columns alone, load after load, left 87 to 174 blocks of one load per lane: 258 us for the GELU
 // pass over 22 k x 3072, 54 and 50 us for the two others at width 768.)
-//
 template <typename T>
 __device__ __forceinline__ float add_rows(float s, const T (*buf)[64], int n) {  // first wave: s + column's n rows, in order
 #pragma unroll 16
@@ -575,7 +574,10 @@ __global__ void __launch_bounds__(256)
   for (int r = r0; r < r1; ++r) s += to_f32(a[(size_t)r * C + c]);
   part[(size_t)blockIdx.y * C + c] = s;
 }
-// The same with 16-byte accesses (C a multiple of 4 floats or 8 halfs).
+// The same with 16-byte accesses (C a multiple of 4 floats or 8 halfs).  The next chunk is requested before the barrier: with
+// the loads after it, wide matrices of many rows were slower than one thread per 16 bytes of columns.  fp16, us, thread by
+// thread / loads after the barrier / now: 22,000 x 7680 82 / 96 / 71, 97,000 x 7680 321 / 389 / 288, 22,000 x 12288 120 / 149 /
+// 109; 22,000 x 2304 58 / 34 / 26, 600 x 2304 21 / 8.0 / 6.4; fp32 22,000 x 768 50 / 27 / 21.
 template <typename T>
 __global__ void __launch_bounds__(256)
     colsum_part_vec_kernel(const T* __restrict__ a, int R, int C, int rows_per_split, float* __restrict__ part) {
@@ -586,13 +588,17 @@ __global__ void __launch_bounds__(256)
   const int c0 = blockIdx.x * 64 + V * tq;
   const int r0 = blockIdx.y * rows_per_split, r1 = min(R, r0 + rows_per_split);
   float s = 0.f;
-  for (int rc = r0, k = 0; rc < r1; rc += RC, k ^= 1) {
-    u32x4_t v[4];
+  u32x4_t v[4];
+  auto fetch = [&](int rc) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       if (c0 < C && rc + tr + RPP * i < r1) v[i] = *(const u32x4_t*)(a + (size_t)(rc + tr + RPP * i) * C + c0);
+  };
+  fetch(r0);
+  for (int rc = r0, k = 0; rc < r1; rc += RC, k ^= 1) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) *(u32x4_t*)&buf[k][tr + RPP * i][V * tq] = v[i];
+    if (rc + RC < r1) fetch(rc + RC);
     __syncthreads();
     if (threadIdx.x < 64) s = add_rows(s, buf[k], min(RC, r1 - rc));
   }
