@@ -633,7 +633,8 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
 //   turn and the K / V store as its prologue -> out-projection and FC2 as one product over K = d + d_ff, left as slabs.
 // At these sizes a layer is a chain of launches, each near its own latency: the seven to nine launches on two streams
 // that larger batches use (above) took 104 us per layer for one sequence at the 2.8B width and 92 us for 64 at the
-// 160M shape, of which the two stream joins alone are about 12; the launches of this pass take 51 and 36 us.
+// 160M shape, of which the two stream joins alone are about 12; the launches of this pass take 53 and 39 us in a kernel trace,
+// which lengthens each by a microsecond or two.
 struct FewDecode {
   FewRowsArgs in, outp;  // QKV | FC1, and the two halves of the residual update
 };

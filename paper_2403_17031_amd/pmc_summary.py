@@ -40,9 +40,9 @@ def main():
     print("|---|---|---|---|---|")
     total = []
     for k in sorted(f):
-        if "gemm_f16_dma_kernel" not in k:
+        if "gemm_f16_dma_kernel" not in k or "true" in k or "Lb1" in k:  # (the weight-gradient form is no layer product)
             continue
-        # the epilogue is the kernel's first template argument: "<5, 8>" demangled, "ILi5ELi8E" mangled
+        # the epilogue is the kernel's first template argument: "<5, false>" demangled, "ILi5ELb0E" mangled
         m = re.search(r"gemm_f16_dma_kernel(?:<|ILi)(\d+)", k)
         epi = m.group(1) if m else "?"
         rd, wr = f[k] * ff * 1024.0, w.get(k, 0.0) * fw * 1024.0
