@@ -104,3 +104,22 @@ def test_empty_and_bad_arguments(gpu):
         gpu.adamw_step(a, a.clone()[:4], a.clone(), a.clone(), 1)
     with pytest.raises(gpu.RlhfError):
         gpu.adamw_step(a, a.clone(), a.clone(), a.clone(), 1, eps=0.0)
+
+
+@pytest.mark.parametrize("n", [(1 << 25) + 3, (1 << 25) + 4 * 1024 + 5])
+def test_a_tensor_with_larger_blocks_is_the_step_of_its_parts(gpu, n):
+    """Beyond 2^25 elements (of a multiple of four) a block takes four times as many: bit for bit what the step leaves on
+    four parts of the tensor, which take the small blocks; the last one is ragged."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    whole = [torch.randn(n, generator=gen, device="cuda") for _ in range(4)]
+    whole[3].abs_()
+    parts = [t.clone() for t in whole]
+    bf = [torch.zeros(n, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    kw = dict(lr=1e-3, weight_decay=0.1, grad_scale=0.5)
+    gpu.adamw_step(*whole, 3, param_bf16=bf[0], **kw)
+    q = n // 16 * 4
+    for a, b in ((0, q), (q, 2 * q), (2 * q, 3 * q), (3 * q, n)):
+        gpu.adamw_step(*(t[a:b] for t in parts), 3, param_bf16=bf[1][a:b], **kw)
+    assert all(bool((x == y).all()) for x, y in zip(whole, parts)) and bool((bf[0] == bf[1]).all())
