@@ -538,18 +538,35 @@ class Policy:
 
 
 # ---------------------------------------------------------------------- PPO signals (stateless)
-def _dev_f32(torch, a, device):
+# These calls run for a few microseconds on the device, so the host's own work is what a caller waits for: what already is
+# where and as the kernels want it is passed on as it is, the current device is left alone where it is the right one, and
+# outputs are allocated after the shape of an input (four calls of 64 rows of 53 tokens: 67 -> 50 us, with the kernels' share hidden behind it).
+def _dev(torch, a, device, dtype):
+    if type(a) is torch.Tensor and a.dtype is dtype and a.device == device and a.is_contiguous():
+        return a
     t = a if isinstance(a, torch.Tensor) else torch.as_tensor(np.ascontiguousarray(a))
-    return t.to(device=device, dtype=torch.float32).contiguous()
+    return t.to(device=device, dtype=dtype).contiguous()
+
+
+def _dev_f32(torch, a, device):
+    return _dev(torch, a, device, torch.float32)
 
 
 def _dev_i32(torch, a, device):
-    t = a if isinstance(a, torch.Tensor) else torch.as_tensor(np.ascontiguousarray(a))
-    return t.to(device=device, dtype=torch.int32).contiguous()
+    return _dev(torch, a, device, torch.int32)
 
 
 def _cur_stream(torch, device):
     return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+
+
+def _on_device(torch, device, fn, *args):
+    """fn(*args, stream) with `device` current and its current stream."""
+    if device.type == "cuda" and device.index == torch.cuda.current_device():
+        _check(fn(*args, torch._C._cuda_getCurrentRawStream(device.index)))
+        return
+    with torch.cuda.device(device):
+        _check(fn(*args, _cur_stream(torch, device)))
 
 
 def ppo_assemble_rewards(logprobs, ref_logprobs, rm_values, tokens, query_len, eos_id, pad_id, beta=0.05,
@@ -568,15 +585,11 @@ def ppo_assemble_rewards(logprobs, ref_logprobs, rm_values, tokens, query_len, e
     Lq = int(query_len)
     if tuple(ref.shape) != (B, Lq + N) or tuple(rm.shape) != (B, Lq + N) or tuple(tok.shape) != (B, Lq + N):
         raise RlhfError("ppo_assemble_rewards: ref_logprobs, rm_values and tokens must be [B, query_len + N]")
-    rewards = torch.empty((B, N), dtype=torch.float32, device=dev)
-    scores = torch.empty((B,), dtype=torch.float32, device=dev)
-    kl = torch.empty((B,), dtype=torch.float32, device=dev)
-    kept = torch.empty((B,), dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib.rlhf_ppo_assemble_rewards(lp.data_ptr(), ref.data_ptr(), rm.data_ptr(), tok.data_ptr(), B, Lq, N,
-                                             int(eos_id), int(pad_id), float(beta), float(missing_eos_score),
-                                             rewards.data_ptr(), scores.data_ptr(), kl.data_ptr(), kept.data_ptr(),
-                                             _cur_stream(torch, dev)))
+    rewards = torch.empty_like(lp, memory_format=torch.contiguous_format)
+    scores, kl, kept = lp.new_empty(B), lp.new_empty(B), tok.new_empty(B)
+    _on_device(torch, dev, lib.rlhf_ppo_assemble_rewards, lp.data_ptr(), ref.data_ptr(), rm.data_ptr(), tok.data_ptr(), B,
+               Lq, N, int(eos_id), int(pad_id), float(beta), float(missing_eos_score), rewards.data_ptr(),
+               scores.data_ptr(), kl.data_ptr(), kept.data_ptr())
     return rewards, scores, kl, kept
 
 
@@ -593,11 +606,10 @@ def ppo_gae(rewards, values, kept, gamma=1.0, lam=0.95, value_offset=0, device="
     off = int(value_offset)
     if v.shape[0] != B or off < 0 or v.shape[1] < off + N or k.shape[0] != B:
         raise RlhfError("ppo_gae: values must be [B, >= value_offset + N] and kept [B]")
-    adv = torch.empty((B, N), dtype=torch.float32, device=dev)
-    ret = torch.empty((B, N), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib.rlhf_ppo_gae(r.data_ptr(), v.data_ptr() + 4 * off, v.shape[1], k.data_ptr(), B, N, float(gamma),
-                                float(lam), adv.data_ptr(), ret.data_ptr(), _cur_stream(torch, dev)))
+    adv = torch.empty_like(r, memory_format=torch.contiguous_format)
+    ret = torch.empty_like(r, memory_format=torch.contiguous_format)
+    _on_device(torch, dev, lib.rlhf_ppo_gae, r.data_ptr(), v.data_ptr() + 4 * off, v.shape[1], k.data_ptr(), B, N,
+               float(gamma), float(lam), adv.data_ptr(), ret.data_ptr())
     return adv, ret
 
 
@@ -611,10 +623,9 @@ def ppo_whiten(x, kept=None, shift_mean=True, device="cuda:0"):
     k = None if kept is None else _dev_i32(torch, kept, dev)
     if k is not None and k.shape[0] != B:
         raise RlhfError("ppo_whiten: kept must be [B]")
-    out = torch.empty((B, N), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib.rlhf_ppo_whiten(xv.data_ptr(), None if k is None else k.data_ptr(), B, N, 1 if shift_mean else 0,
-                                   out.data_ptr(), _cur_stream(torch, dev)))
+    out = torch.empty_like(xv, memory_format=torch.contiguous_format)
+    _on_device(torch, dev, lib.rlhf_ppo_whiten, xv.data_ptr(), None if k is None else k.data_ptr(), B, N,
+               1 if shift_mean else 0, out.data_ptr())
     return out
 
 
@@ -630,18 +641,18 @@ def ppo_loss(new_logprobs, old_logprobs, advantages, new_values, old_values, ret
     lib = load_library()
     dev = torch.device(device)
     arrs = [_dev_f32(torch, a, dev) for a in (new_logprobs, old_logprobs, advantages, new_values, old_values, returns)]
-    B, N = arrs[0].shape
-    if any(a.shape != (B, N) for a in arrs):
+    shape = arrs[0].shape
+    B, N = shape
+    if any(a.shape != shape for a in arrs):
         raise RlhfError("ppo_loss: all six arrays must be [B, N]")
     k = _dev_i32(torch, kept, dev)
     if k.shape[0] != B:
         raise RlhfError("ppo_loss: kept must be [B]")
-    d_lp = torch.empty((B, N), dtype=torch.float32, device=dev)
-    d_v = torch.empty((B, N), dtype=torch.float32, device=dev)
-    stats = torch.empty(8, dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        _check(lib.rlhf_ppo_loss(*[a.data_ptr() for a in arrs], k.data_ptr(), B, N, cliprange, cliprange_value, vf_coef,
-                                 d_lp.data_ptr(), d_v.data_ptr(), stats.data_ptr(), _cur_stream(torch, dev)))
+    d_lp = torch.empty_like(arrs[0], memory_format=torch.contiguous_format)
+    d_v = torch.empty_like(arrs[0], memory_format=torch.contiguous_format)
+    stats = arrs[0].new_empty(8)
+    _on_device(torch, dev, lib.rlhf_ppo_loss, *[a.data_ptr() for a in arrs], k.data_ptr(), B, N, cliprange,
+               cliprange_value, vf_coef, d_lp.data_ptr(), d_v.data_ptr(), stats.data_ptr())
     return stats, d_lp, d_v
 
 
