@@ -297,15 +297,20 @@ __global__ void __launch_bounds__(256)
 // loads of the next tile's first two, so that its start-up (index arithmetic, two cold loads) runs under the epilogue,
 // which has 32 KB of LDS of its own.  A round is 256 neighbouring tiles, 32 in a row on each XCD (they share panels in its
 // L2).  (One block per tile and an eighth of all tiles per XCD put 33 tiles on 32 CUs whenever the count was a little above
-// a multiple of 256, or 35 in the K-sliced form: a whole extra round.)  What is left over after the whole rounds is cut
-// into 128x128 tiles, four per tile, if that fills at most two half-length rounds; the sums of an output element are
-// formed in the same order either way.  gemm_driver, us, one block per tile / this: 22,200 rows of width 768 QKV 118 / 97,
-// FC1 180 / 132, out-projection + FC2 190 / 150, K-major 159 / 110; 3,456 rows 33 / 25, 35 / 30, 78 / 40; 83,373 rows of width
+// a multiple of 256, or 35 in the K-sliced form: a whole extra round.)  gemm_driver, us, one block per tile / this: 22,200
+// rows of width 768 QKV 118 / 97, FC1 180 / 132, out-projection + FC2 190 / 150, K-major 159 / 110; 83,373 rows of width
 // 2560 3381 / 3280, 4511 / 4240, 5203 / 5065; 21,504 of 4096 2041 / 1970, 2709 / 2572, 3410 / 3186 (FC1's with a fifth less
 // GELU arithmetic, and about 2 % of each between runs).
-// The quarter tiles' share of that, us without / with them: 22,200 rows of 768 QKV 108 / 98, FC1 145 / 139, out-projection +
-// FC2 184 / 149; 3,456 rows 29 / 25, 31 / 30, 77 / 40; 10,900 rows 55 / 56, 83 / 72, 90 / 89; 21,504 of 4096 1849 / 1836, 2434 /
-// 2421, 3233 / 3077; 83,373 of 2560 within 1 %.
+//
+// What is left over after the whole rounds is cut into 128x128 tiles if that fills at most two shorter rounds (K-major one:
+// its transposing reads make a quarter tile cost half of a whole one), and into 64x128 tiles where those are one round; the
+// sums of an output element are formed in the same order whatever the cut.  Such a tile has little matrix work per stage,
+// so its loads go through a ring of four stages with three under way: with two stages (of twice the depth, the second
+// requested when the first had landed) it waited for every one of them.  us, two stages and quarter tiles / the ring and
+// both sizes: 22,272 rows of 768 out-projection + FC2 148 / 137, the gradients' fp32 products 87 / 82 and 112 / 105; 3,456
+// rows 39 / 31, 23 / 20, 29 / 24; 1,000 rows 35 / 22, 19.5 / 12.4, 26 / 16; 600 rows of 2560 104 / 63, 64 / 41, 82 / 53; 2,200
+// rows 222 / 183, 134 / 111, 176 / 144; 2,500 of 2048 178 / 148; K-major 768 x 768 over 3,456 rows 31 / 15; where whole
+// rounds are most of the work 1 to 2 %.
 // =================================================================================================
 #define RLHF_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define RLHF_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -559,7 +564,7 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
   constexpr int NLD = 4;        // tile loads per wave, stage and operand
   constexpr int NMF = MT * NT;  // matrix instructions per wave per sub-step
   // stage s of the big tile: A rows in la<s>, W rows in lw<s> (separate variables, so that a read of one does not wait for
-  // the loads into another); the 128x128 tiles use them as two stages of K depth 128, (la0, lw0) and (la1, lw1)
+  // the loads into another); the smaller tiles use them as a ring of four stages
   __shared__ __attribute__((aligned(16))) uint16_t la0[DOP];
   __shared__ __attribute__((aligned(16))) uint16_t lw0[DOP];
   __shared__ __attribute__((aligned(16))) uint16_t la1[DOP];
@@ -572,7 +577,7 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
   const int G = gridDim.x, P = G >> 3;
   const int xcd = blockIdx.x & 7, slot_x = blockIdx.x >> 3;
   const int full = items / G, rem = items - full * G;
-  const bool cut = !KMAJ && g.slices == 1 && 2 * rem <= G;  // the rest as 128x128 tiles
+  const bool cut = (KMAJ ? 4 : 2) * rem <= G;  // the rest in smaller tiles
   // whole tiles of this block: `full` rounds, and one more if the rest is not cut and reaches it
   const int per_x = (rem + 7) >> 3;
   const int rest = full * G + xcd * per_x + slot_x;
@@ -707,18 +712,30 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
   __builtin_amdgcn_s_barrier();                  \
   asm volatile("" ::: "memory");                 \
   __builtin_amdgcn_sched_barrier(0);
+  // The same after an epilogue, which stored at least kStores times if the whole tile exists: memory operations complete in
+  // order, so the loads that are waited for, issued before it, have landed when at most that many are under way, and the
+  // stores need not have (1 to 2 % of products of several rounds)
+#define RLHF_WAIT_BARRIER_FIRST()                \
+  __builtin_amdgcn_sched_barrier(0);             \
+  asm volatile("" ::: "memory");                 \
+  if (pending) __builtin_amdgcn_s_waitcnt(kStores == 16 ? 0x4070 : 0x8070); /* vmcnt(16), (32) */ \
+  else __builtin_amdgcn_s_waitcnt(0x0070);       \
+  pending = false;                               \
+  __builtin_amdgcn_s_barrier();                  \
+  asm volatile("" ::: "memory");                 \
+  __builtin_amdgcn_sched_barrier(0);
   // One stage (K depth 64).  The first three sub-steps read their successors' fragments from the stage itself (CA, CW).
   // After the barrier it is free and (OA, OW) holds the next stage: the last sub-step reads the next
   // stage's first fragments from there and issues the loads at K offset KL into (CA, CW), so a
   // load has a whole stage of matrix work to land.
-#define RLHF_STAGE(CA, CW, OA, OW, KL)                                                            \
+#define RLHF_STAGE(CA, CW, OA, OW, KL, WAIT)                                                      \
   {                                                                                               \
     const char *pa, *pw;                                                                          \
     k_base(KL, pa, pw);                                                                           \
     RLHF_SUB(fa0, fw0, CA, CW, ch1, fa1, fw1, false, CA, CW)                                      \
     RLHF_SUB(fa1, fw1, CA, CW, ch2, fa0, fw0, false, CA, CW)                                      \
     RLHF_SUB(fa0, fw0, CA, CW, ch3, fa1, fw1, false, CA, CW)                                      \
-    RLHF_WAIT_BARRIER()                                                                           \
+    WAIT()                                                                                        \
     RLHF_SUB(fa1, fw1, OA, OW, ch0, fa0, fw0, true, CA, CW)                                       \
   }
     if (mine > 0) {
@@ -732,6 +749,8 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       for (int i = 0; i < 2 * NLD; ++i) load_one(la1, lw1, pa, pw, i);
       RLHF_WAIT_BARRIER()
     }
+    constexpr int kStores = EPI == EPI_F32 || EPI == EPI_BIAS_RESADD ? 32 : 16;
+    bool pending = false;
     for (int it = 0; it < mine; ++it) {
       // here stage 0 of this tile is in LDS for every wave, and its stage 1 has been requested
 #pragma unroll
@@ -744,8 +763,8 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       for (int q = 0; q < MT + NT; ++q) frag_one(la0, lw0, ch0, q, fa0, fw0);
       // K is a multiple of 2*DK here (the launcher routes other shapes to the staged kernel)
       for (int kt = 0; kt + 2 < nk; kt += 2) {
-        RLHF_STAGE(la0, lw0, la1, lw1, (kt + 2) * DK)
-        RLHF_STAGE(la1, lw1, la0, lw0, (kt + 3) * DK)
+        RLHF_STAGE(la0, lw0, la1, lw1, (kt + 2) * DK, RLHF_WAIT_BARRIER_FIRST)
+        RLHF_STAGE(la1, lw1, la0, lw0, (kt + 3) * DK, RLHF_WAIT_BARRIER)
       }
       // The last two stages request the first two of the block's next tile; after its last tile they re-issue a stage
       // that nobody reads.
@@ -765,58 +784,104 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
         for (int i = 0; i < MT; ++i)
           prow[i] = (qk.pos[g.M_sub + min(cm0 + wm + 32 * i + l32, M - 1)] + qk.pos_add) * (qk.r >> 1);
       }
-      RLHF_STAGE(la0, lw0, la1, lw1, kl0)
-      RLHF_STAGE(la1, lw1, la0, lw0, kl1)
+      RLHF_STAGE(la0, lw0, la1, lw1, kl0, RLHF_WAIT_BARRIER)
+      RLHF_STAGE(la1, lw1, la0, lw0, kl1, RLHF_WAIT_BARRIER)
       if (EPI == EPI_BIAS_RESADD) {  // (two biases do not fit the registers beside the main loop's)
         dma_load_bias(g.bias, cn0 + wn, N, hf, bv);
         dma_load_bias(g.bias2, cn0 + wn, N, hf, bv2);
       }
       dma_epilogue<EPI, MT>(g, lse, qk, cout, acc, cm0 + wm, cn0 + wn, M, ep, lane, bv, bv2, prow);
+      pending = !KMAJ && EPI != EPI_LSE && cm0 + TM <= M && cn0 + TN <= N;
     }
 #undef RLHF_STAGE
 #undef RLHF_SUB
   }
 
-  // ---- the rest: 128x128 tiles, 8 waves (4 x 2) of 32x64, two 64 KB stages of K depth 128 (k 0..63 of the A rows, then
-  //      of the W rows, in one array and k 64..127 in the other)
-  if (KMAJ || !cut || rem == 0) return;
-  if constexpr (!KMAJ) {
-    const int n_sub = 4 * rem, per_sx = (n_sub + 7) >> 3;
+  // ---- the rest: PM x 128 tiles, PM / 16 waves (PM / 32 x 2) of 32x64, a ring of four stages of K depth 64 (A rows, then W
+  //      rows; KMAJ: 64 k-rows of 2 PM and of 256 bytes).  A tile's matrix work is short against the way of its loads
+  //      (8 matrix instructions per wave and stage), so three stages are under way while one is used.  PM = 64 (half of the
+  //      waves only load) where that still is one round: half the matrix work per stage.
+  if (!cut || rem == 0) return;
+  auto run_rest = [&](auto pm) {
+    constexpr int PM = decltype(pm)::value, PER = 512 / PM;  // pieces per whole tile
+    constexpr int NLA = PM / 64, NL = NLA + 2;               // tile loads per wave and stage: A, then W
+    const int n_sub = PER * rem, per_sx = (n_sub + 7) >> 3;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
-    const int nk = g.K / (2 * DK);
+    constexpr int AOP = PM * DK;  // halfs of a stage's A part
+    const bool works = PM == 128 || wave < PM / 16;
+    uint16_t* const slots[4] = {la0, lw0, la1, lw1};
+    int koff[3] = {0, 0, 0};
+    if (KMAJ) {
+      const int r = lane & 15, gsel = (lane >> 4) & 1;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int colb = (q < 1 ? wm : wn + 32 * (q - 1)) + 16 * gsel;
+        const int chunk = ((colb >> 3) + ((r & 3) >> 1)) ^ (2 * ((r >> 2) & 3));
+        koff[q] = (q < 1 ? 0 : AOP) + (8 * hf + (r >> 2)) * (q < 1 ? PM : 128) + chunk * 8 + (r & 1) * 4;
+      }
+    }
     for (int j = slot_x; j < per_sx; j += P) {
       const int st = xcd * per_sx + j;
       if (st >= n_sub) break;
       int m0, n0;
-      tile_pos(full * G + (st >> 2), m0, n0);
-      m0 += 128 * ((st >> 1) & 1);
+      const int item = full * G + st / PER, z = KMAJ || g.slices > 1 ? item / tiles : 0;
+      tile_pos(item - z * tiles, m0, n0);
+      m0 += PM * ((st % PER) >> 1);
       n0 += 128 * (st & 1);
       if (m0 >= M || (EPI != EPI_LSE && n0 >= N)) continue;  // (EPI_LSE: columns past N leave empty parts)
-      const int nw = min(n0, N - 1);  // (first W row to read)
-      uint32_t goff[4];
+      const int nw = min(n0, KMAJ ? N - 8 : N - 1);  // (first W row, KMAJ: column, to read)
+      const int kb = z * g.k_slice, nk = (g.k_slice > 0 ? min(g.k_slice, g.K - kb) : g.K) / DK;
+      // wave-load i of an operand's `per` per wave: rows 8(per*wave + i) .. +7, 8 lanes per row; KMAJ: as many k-rows as 64
+      // chunks of 16 bytes are (see set_item for the chunks)
+      uint32_t goff[NL];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = 8 * (2 * wave + i) + (lane >> 3);
-        const int c = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
-        goff[i] = 2u * (uint32_t)(min(row, M - 1 - m0) * g.lda + c);
-        goff[2 + i] = 2u * (uint32_t)((min(n0 + row, N - 1) - nw) * g.ldw + c);
+      for (int q = 0; q < NL; ++q) {
+        const bool w = q >= NLA;
+        const int j = w ? 2 * wave + q - NLA : NLA * wave + q;
+        if (KMAJ) {
+          const int lanes = w ? 16 : PM / 8, krow = 64 / lanes * j + lane / lanes;
+          const int c = ((lane & (lanes - 1)) ^ (2 * (krow & 3))) * 8;
+          goff[q] = 2u * (uint32_t)(krow * (w ? g.ldw : g.lda) + (w ? min(c, N - 8 - nw) : min(c, M - 8 - m0)));
+        } else {
+          const int row = 8 * j + (lane >> 3);
+          const int c = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+          goff[q] = 2u * (uint32_t)((w ? (min(n0 + row, N - 1) - nw) * g.ldw : min(row, M - 1 - m0) * g.lda) + c);
+        }
       }
-      const char* const gA = (const char*)(g.A + (size_t)m0 * g.lda);
-      const char* const gW = (const char*)(g.W + (size_t)nw * g.ldw);
-      auto load_stage = [&](uint16_t* s0, uint16_t* s1, int kt) {
-        const size_t k0 = (size_t)min(kt, nk - 1) * (2 * DK);
+      const char* const gA = (const char*)(g.A + (KMAJ ? (size_t)kb * g.lda + m0 : (size_t)m0 * g.lda + kb));
+      const char* const gW = (const char*)(g.W + (KMAJ ? (size_t)kb * g.ldw + nw : (size_t)nw * g.ldw + kb));
+      void* const out = g.slices > 1 ? (void*)((float*)g.out + (size_t)z * g.slab) : g.out;
+      // The ring's loads are assembly (no destination registers: the data goes to LDS), because the compiler, which
+      // cannot tell the ring's stages apart, would wait for all of them at every fragment read.  What orders them is
+      // the counted wait before the barrier.  (m0 holds nothing else here: the compiler sets it before each direct load of
+      // its own, and none follows.)
+      auto load_one = [&](uint16_t* slot, int kt, int i) {
+        const size_t k0 = (size_t)min(kt, nk - 1) * DK;
+        const char* const p = i < NLA ? gA + 2 * (KMAJ ? k0 * g.lda : k0) : gW + 2 * (KMAJ ? k0 * g.ldw : k0);
+        const int at = i < NLA ? 8 * (NLA * wave + i) * DK : AOP + 8 * (2 * wave + i - NLA) * DK;
+        const uint32_t dst = (uint32_t)(uintptr_t)RLHF_LDS_PTR(slot + at);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(goff[i]), "s"(p)
+                     : "memory");
+      };
+      f16x8_t fa[2], fw[2][2];
+      auto frag = [&](const uint16_t* slot, int ks, int buf) {
+        if (KMAJ) {
+          typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+          typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+          typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const char *pa = gA + 2 * (k0 + h * DK), *pw = gW + 2 * (k0 + h * DK);
-          asm volatile("" : "+s"(pa), "+s"(pw));
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            uint32_t o = goff[i];
-            asm volatile("" : "+v"(o));
-            __builtin_amdgcn_global_load_lds(RLHF_GLOBAL_PTR((i < 2 ? pa : pw) + o),
-                                             RLHF_LDS_PTR((h ? s1 : s0) + ((i >> 1) * 128 + 8 * (2 * wave + (i & 1))) * DK),
-                                             16, 0, 0);
+          for (int q = 0; q < 3; ++q) {
+            const int row = q < 1 ? PM : 128;
+            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(slot + koff[q] + 16 * ks * row));
+            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(slot + koff[q] + (16 * ks + 4) * row));
+            const s16x8_t b = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            (q < 1 ? fa[buf] : fw[buf][q - 1]) = __builtin_bit_cast(f16x8_t, b);
           }
+        } else {
+          const int ch = ((2 * ks + hf) ^ key) << 3;
+          fa[buf] = *(const f16x8_t*)(slot + (wm + l32) * DK + ch);
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) fw[buf][jj] = *(const f16x8_t*)(slot + AOP + (wn + 32 * jj + l32) * DK + ch);
         }
       };
       f32x16_t acc[2][1];
@@ -824,47 +889,70 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[jj][0][e] = 0.f;
-      // one stage: once its loads have landed for every wave (and every wave has left the stage before), the next stage is
-      // requested into the one just left
-      auto stage = [&](const uint16_t* c0, const uint16_t* c1, uint16_t* n0, uint16_t* n1, int kt) {
-        RLHF_WAIT_BARRIER()
-        load_stage(n0, n1, kt + 1);
+      auto mul = [&](int buf) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint16_t* cur = h ? c1 : c0;
-          f16x8_t fa[4], fw[4][2];
+        for (int jj = 0; jj < 2; ++jj)
+          acc[jj][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[buf][jj], fa[buf], acc[jj][0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // at most N tile loads of the wave still under way (NL per stage), its fragment reads done, and every wave there
+#define RLHF_RING_BARRIER(N)                  \
+  __builtin_amdgcn_sched_barrier(0);          \
+  asm volatile("" ::: "memory");              \
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N));   \
+  __builtin_amdgcn_s_barrier();               \
+  asm volatile("" ::: "memory");              \
+  __builtin_amdgcn_sched_barrier(0);
+      RLHF_WAIT_BARRIER()  // every wave is done with the stages
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) {
-            const int ch = ((2 * ks + hf) ^ key) << 3;
-            fa[ks] = *(const f16x8_t*)(cur + (wm + l32) * DK + ch);
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj) fw[ks][jj] = *(const f16x8_t*)(cur + (128 + wn + 32 * jj + l32) * DK + ch);
+        for (int i = 0; i < NL; ++i) load_one(slots[u], u, i);
+      RLHF_RING_BARRIER(3 * NL)
+      auto stages = [&](auto multiplies) {
+        constexpr bool MUL = decltype(multiplies)::value;
+        if (MUL) frag(slots[0], 0, 0);
+        for (int kt = 0; kt < nk; kt += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (kt + u >= nk) break;
+            uint16_t *const cur = slots[u], *const nxt = slots[(u + 1) & 3];
+            if (MUL) {
+              frag(cur, 1, 1);
+              mul(0);
+              frag(cur, 2, 0);
+              mul(1);
+              frag(cur, 3, 1);
+              mul(0);
+            }
+            // the next stage is there for every wave, and every wave has read the last of this one: its place is free
+            RLHF_RING_BARRIER(2 * NL)
+#pragma unroll
+            for (int i = 0; i < NL; ++i) load_one(cur, kt + u + 4, i);
+            if (MUL) {
+              frag(nxt, 0, 0);
+              mul(1);
+            }
           }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-              acc[jj][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[ks][jj], fa[ks], acc[jj][0], 0, 0, 0);
         }
       };
-      RLHF_WAIT_BARRIER()  // every wave is done with the stages
-      load_stage(la0, lw0, 0);
-      for (int kt = 0; kt < nk; kt += 2) {
-        stage(la0, lw0, la1, lw1, kt);
-        if (kt + 1 >= nk) break;
-        stage(la1, lw1, la0, lw0, kt + 1);
-      }
+      if (works) stages(std::true_type{});
+      else stages(std::false_type{});
+#undef RLHF_RING_BARRIER
+      if (!works) continue;
       u32x2_t bv[2][4], bv2[2][4];
       int prow[1];
       if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESADD || EPI == EPI_QKV)
         dma_load_bias(g.bias, n0 + wn, N, hf, bv);
       if (EPI == EPI_BIAS_RESADD) dma_load_bias(g.bias2, n0 + wn, N, hf, bv2);
       if (EPI == EPI_QKV) prow[0] = (qk.pos[g.M_sub + min(m0 + wm + l32, M - 1)] + qk.pos_add) * (qk.r >> 1);
-      dma_epilogue<EPI, 1>(g, lse, qk, g.out, acc, m0 + wm, n0 + wn, M, ep, lane, bv, bv2, prow);
+      dma_epilogue<EPI, 1>(g, lse, qk, out, acc, m0 + wm, n0 + wn, M, ep, lane, bv, bv2, prow);
     }
-  }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the last tile's surplus loads)
+  };
+  if (8 * rem <= G) run_rest(std::integral_constant<int, 64>{});
+  else run_rest(std::integral_constant<int, 128>{});
 #undef RLHF_WAIT_BARRIER
 }
 #undef RLHF_WAVE_LDS_FENCE

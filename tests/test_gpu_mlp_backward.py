@@ -80,6 +80,13 @@ def test_rounds_of_the_large_product(gpu, T):
     _check(gpu, _cfg(256, 2048, "bf16"), T, seed=T, layer=0, scale=8.0)
 
 
+@pytest.mark.parametrize("T,d,F", [(600, 128, 1544), (1000, 256, 2048), (1025, 384, 2048), (1300, 640, 776)])
+def test_what_the_rounds_of_the_large_product_leave(gpu, T, d, F):
+    """FC1's product as 64 x 128 tiles (21 and 32 whole ones, the last that are cut so), as 128 x 128 (40) and, with the K-major
+    gradients, with remainders of rows and columns; K of 2, 4, 6 and 10 stages for a ring of four."""
+    _check(gpu, _cfg(d, F, "bf16"), T, seed=T, layer=0, scale=8.0)
+
+
 def test_linear_in_the_upstream_gradient_and_deterministic(gpu):
     cfg = _cfg(128, 512, "fp32")
     w = make_weights(cfg, 44, variant="test")
