@@ -3,6 +3,7 @@
 // sequence's keys occupying consecutive slots, so one (sequence, head) pair reads one contiguous
 // run of memory.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -118,43 +119,90 @@ __global__ void __launch_bounds__(256)
 // =================================================================================================
 // MFMA flash attention (fp16 operands, fp32 softmax and accumulation), head_dim HD a multiple of 16.
 //
-// Block = 4 waves; wave w owns 32 queries, all work is per wave except the shared K / V tile.
+// Block = 4 waves; wave w owns 32 queries, all work is per wave except the shared K / V tile of BK keys.
 // Scores are produced transposed, S^T[key][q] = K Q^T, so that a lane holds one query (lane % 32)
 // and 16 of each 32 keys: the running max / sum are per-lane scalars, shared with lane ^ 32 only.
 // The probabilities then feed O^T[d][q] = V^T P^T straight from registers: the accumulator layout
-// of S^T is the operand layout of P^T up to a fixed permutation of the 16 keys of a k-step, and
-// the V tile is stored in LDS transposed with that same permutation applied.
+// of S^T is the operand layout of P^T up to a fixed permutation of the 16 keys of a k-step (lane half
+// h holds keys 4h .. 4h+3 and 8+4h .. 8+4h+3), and a transposing LDS read (ds_read_b64_tr_b16: four
+// consecutive keys of one dim) delivers V in exactly that order from a row-major tile.
+//
+// Both tiles go global -> LDS directly, two of each, so that a tile is requested one iteration ahead and no register
+// holds it: one barrier per tile, and the registers that staging (and V's transposition) took are blocks per CU (four
+// instead of three at head size 64).  What bounds it at head sizes 64 and 80 is the vector arithmetic of the softmax (an
+// exponential per score, about 1050 of its cycles per tile and wave beside 512 and 704 of the matrix cores, which overlap
+// in part) and a block's start, 2 to 4 of its 10 to 13 us; at 256 the way of the tiles (without the loads 356 us of 560).
+// Staged through registers / this, us: 64 sequences of 155-539 tokens, 12 heads of 64 54 / 42; 256, 32 of 80 736 / 650; 61,
+// 32 of 128 263 / 230; 32 of 505-2021, 8 of 256 762 / 560; results the same bit for bit.  Tried: two or eight waves a block
+// (slower at every size), 32-key tiles (head size 128 3 % faster, 256 as fast with two blocks per CU, 15 % slower with short
+// sequences), loads dealt out between the matrix instructions (spills).
 // =================================================================================================
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
 
-constexpr int FA_BQ = 128, FA_BK = 64;
-constexpr int FA_VT_STRIDE = FA_BK + 8;  // halfs per V^T row: 144 B, odd multiple of 16 B
+constexpr int FA_BQ = 128;
 
+// Tile images.  A row of a tile is HD / 8 chunks of 16 bytes at a pitch of KP (K) or VP (V) chunks; chunk c of row r sits
+// at c ^ swizzle(r).  The fragment reads of K take the same chunk of 16 consecutive rows, which have to fall into the 16
+// groups of four banks; the transposing reads of V take four chunks of each of four consecutive rows.
 template <int HD>
-__global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
+struct FaTile {
+  static constexpr int CH = HD / 8;
+  static constexpr int KP = HD == 80 ? 11 : CH, VP = HD == 80 ? 12 : CH;  // (a pitch of 10 would be 160 bytes)
+  __device__ static int k_swizzle(int r) { return HD == 80 ? 0 : HD == 64 ? (r >> 1) & 7 : HD == 16 ? (r >> 3) & 1 : r & 15; }
+  __device__ static int v_swizzle(int r) { return HD == 64 ? 4 * ((r >> 1) & 1) : HD >= 128 ? 4 * (r & 3) : 0; }
+};
+
+template <int HD, int BK, int OCC>
+__global__ void __launch_bounds__(256, OCC)
     attn_prefill_mfma(const half_t* __restrict__ q, const half_t* __restrict__ kc, const half_t* __restrict__ vc,
                       long kv_extra, const int* __restrict__ len, const int* __restrict__ cu,
-                      const int* __restrict__ kvoff, int H, float scale_log2e, half_t* __restrict__ out, int out_ld) {
+                      const int* __restrict__ kvoff, int H, int B, int nqb, float scale_log2e, half_t* __restrict__ out,
+                      int out_ld) {
+  typedef FaTile<HD> TL;
   constexpr int NKS = HD / 16;         // k-steps of the Q K^T contraction
   constexpr int NDT = (HD + 31) / 32;  // 32-row tiles of O^T
-  constexpr int K_STRIDE = HD + 8;     // halfs per K row: odd multiple of 16 B for every HD used
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[FA_BK * K_STRIDE];
-  __shared__ __attribute__((aligned(16))) uint16_t Vt[NDT * 32 * FA_VT_STRIDE];
-  const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * FA_BQ;
+  constexpr int NKF = BK / 32;         // 32-key fragments of a tile
+  constexpr int K_HALFS = BK * TL::KP * 8, V_HALFS = BK * TL::VP * 8, BUF = K_HALFS + V_HALFS;
+  constexpr int NKL = (BK * TL::KP / 64 + 3) / 4, NVL = (BK * TL::VP / 64 + 3) / 4;  // tile loads per wave
+  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * BUF];
+  // the query blocks of a (sequence, head) pair run on one XCD, one after the other, the longest first: they share K and V
+  // in its L2 (all longest blocks first: 814 us instead of 650 at the 2.8B shape)
+  const int idx = blockIdx.x >> 3, pair = (blockIdx.x & 7) + 8 * (idx / nqb);
+  if (pair >= H * B) return;
+  const int b = pair / H, h = pair - b * H, q0 = (nqb - 1 - idx % nqb) * FA_BQ;
   const int n = len[b];
   if (q0 >= n) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: the per-tile branches below are scalar
   const int half = lane >> 5, l32 = lane & 31;
   const int d = H * HD;
-  const half_t* kb = kc + ((size_t)kvoff[b] * H + (size_t)h * (len[b] + kv_extra)) * HD;
-  const half_t* vb = vc + ((size_t)kvoff[b] * H + (size_t)h * (len[b] + kv_extra)) * HD;
+  const half_t* kb = kc + ((size_t)kvoff[b] * H + (size_t)h * (n + kv_extra)) * HD;
+  const half_t* vb = vc + ((size_t)kvoff[b] * H + (size_t)h * (n + kv_extra)) * HD;
 
-  // rows of V^T beyond HD are never loaded: zero them once
-  for (int c = tid; c < (NDT * 32 - HD) * FA_VT_STRIDE; c += 256) Vt[HD * FA_VT_STRIDE + c] = 0;
+  // Tile load i of the wave fills 64 chunks of the image: chunk index x = 64 * (NKL * wave + i) + lane, row x / pitch
+  // (past the image: the last 64 again, the same bytes).  Rows past the sequence repeat its last (their scores are masked).
+  // The loads are assembly (no destination registers: the data goes to LDS), because the compiler cannot tell the two
+  // buffers apart and would wait for the next tile at every fragment read of this one.  (m0 holds nothing else here.)
+  auto load_tile = [&](int k0, int buf, bool is_v) {
+    const int pitch = is_v ? TL::VP : TL::KP, nl = is_v ? NVL : NKL;
+    const half_t* const src = is_v ? vb : kb;
+#pragma unroll
+    for (int i = 0; i < (is_v ? NVL : NKL); ++i) {
+      const int j = min(nl * wave + i, BK * pitch / 64 - 1);
+      const int x = 64 * j + lane, r = x / pitch, pc = x - r * pitch;
+      const int c = min(pc ^ (is_v ? TL::v_swizzle(r) : TL::k_swizzle(r)), TL::CH - 1);
+      const uint32_t off = 2u * (uint32_t)(min(k0 + r, n - 1) * HD + c * 8);
+      const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(smem + buf * BUF + (is_v ? K_HALFS : 0) + j * 512);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(src) : "memory");
+    }
+  };
+  load_tile(0, 0, false);
+  load_tile(0, 0, true);
 
   // this lane's query and its Q fragments (kept in registers for the whole block)
   const int qi = q0 + wave * 32 + l32;
@@ -170,96 +218,55 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
     for (int e = 0; e < 16; ++e) o[t][e] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;  // l_run: sum over this lane's keys only
 
-  const int q_hi = min(q0 + FA_BQ, n) - 1;           // last query of the block
-  const int wq_lo = q0 + wave * 32;                  // first query of the wave
-  // The next K / V tile travels global -> registers while the current one is being multiplied.
-  //   K: row-major 16-byte chunks, keys past the sequence clamped (their scores are masked below).
-  //   V: stored transposed.  A thread takes 4 consecutive keys x 8 dims and writes 8 eight-byte
-  //      words, one per dim: keys 4g..4g+3 stay adjacent under the column permutation
-  //      (key kk of a 16-key group goes to column 8*((kk>>2)&1) + (kk&3) + 4*(kk>>3)).
-  constexpr int KCH = FA_BK * (HD / 8);             // 16-byte chunks of a K tile
-  constexpr int NKR = (KCH + 255) / 256;            // ... per thread
-  constexpr int VIT = (FA_BK / 4) * (HD / 8);       // V items (4 keys x 8 dims)
-  constexpr int NVR = (VIT + 255) / 256;            // ... per thread
-  u32x4_t kreg[NKR];
-  f16x8_t vreg[NVR][4];
-  auto load_tile = [&](int k0) {
+  const int q_hi = min(q0 + FA_BQ, n) - 1;  // last query of the block
+  const int wq_lo = q0 + wave * 32;         // first query of the wave
+  // fragment addresses (halfs): K row l32 of a fragment, chunk 2 ks + half; V: lane r of a group of 16 points at row r / 4
+  // of the four, columns 4 (r mod 4) .. of the group's 16
+  const int k_row = l32 * TL::KP * 8, k_key = TL::k_swizzle(l32);
+  int v_off[NDT];
+  {
+    const int r = lane & 15, gsel = (lane >> 4) & 1, row = 4 * half + (r >> 2);
 #pragma unroll
-    for (int i = 0; i < NKR; ++i) {
-      const int c = tid + 256 * i;
-      if (c < KCH) {
-        const int r = c / (HD / 8), ch = c - r * (HD / 8);
-        kreg[i] = *(const u32x4_t*)(kb + (size_t)min(k0 + r, n - 1) * HD + ch * 8);
-      }
+    for (int t = 0; t < NDT; ++t)
+      v_off[t] = row * TL::VP * 8 + (((4 * t + 2 * gsel + ((r & 3) >> 1)) ^ TL::v_swizzle(row)) % TL::VP) * 8 + (r & 1) * 4;
+  }
+  auto tile = [&](int k0, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    // this tile is in LDS for every wave, and every wave is done with the one before, whose place takes the next
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (k0 + BK <= q_hi) {
+      load_tile(k0 + BK, buf ^ 1, false);
+      load_tile(k0 + BK, buf ^ 1, true);
     }
-#pragma unroll
-    for (int i = 0; i < NVR; ++i) {
-      const int c = tid + 256 * i;
-      if (c < VIT) {
-        const int ch = c / (FA_BK / 4), g4 = c - ch * (FA_BK / 4);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          vreg[i][u] = *(const f16x8_t*)(vb + (size_t)min(k0 + 4 * g4 + u, n - 1) * HD + ch * 8);
-      }
-    }
-  };
-  auto store_tile = [&]() {
-#pragma unroll
-    for (int i = 0; i < NKR; ++i) {
-      const int c = tid + 256 * i;
-      if (c < KCH) {
-        const int r = c / (HD / 8), ch = c - r * (HD / 8);
-        *(u32x4_t*)(Ks + r * K_STRIDE + ch * 8) = kreg[i];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NVR; ++i) {
-      const int c = tid + 256 * i;
-      if (c < VIT) {
-        const int ch = c / (FA_BK / 4), g4 = c - ch * (FA_BK / 4);
-        const int kk = (4 * g4) & 15;
-        const int col = ((4 * g4) & ~15) + 8 * ((kk >> 2) & 1) + 4 * (kk >> 3);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          f16x4_t w = {vreg[i][0][e], vreg[i][1][e], vreg[i][2][e], vreg[i][3][e]};
-          *(f16x4_t*)((half_t*)Vt + (ch * 8 + e) * FA_VT_STRIDE + col) = w;
-        }
-      }
-    }
-  };
-  load_tile(0);
-  // Everything loaded so far (the Q fragments, tile 0) is waited for here, once: otherwise the compiler's wait
-  // bookkeeping carries the Q loads as possibly pending around the loop and, since loads retire in order, makes
-  // every iteration wait for the tile it has just prefetched before the first matrix instruction that reads Q.
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  for (int k0 = 0; k0 <= q_hi; k0 += FA_BK) {
-    __syncthreads();  // every wave is done with the previous tile
-    store_tile();
-    __syncthreads();
-    if (k0 + FA_BK <= q_hi) load_tile(k0 + FA_BK);
-    if (k0 > wq_lo + 31) continue;  // every key of this tile is in the future of this wave's queries
+    if (k0 > wq_lo + 31) return;  // every key of this tile is in the future of this wave's queries
+    const uint16_t* const Ks = smem + buf * BUF;
+    const uint16_t* const Vs = Ks + K_HALFS;
 
-    // ---- S^T = K Q^T for the two 32-key fragments.  The two accumulation chains alternate, and the fragment
-    //      reads run three ahead of the matrix instructions (scheduling groups: left to itself the compiler
-    //      waits for every read right before the instruction that uses it; four ahead costs the registers that
-    //      keep head sizes up to 80 from running three blocks per CU: 730 against 785 us at the 2.8B shape)
-    f32x16_t st[2];
+    // ---- S^T = K Q^T.  The accumulation chains alternate, and the fragment reads run three ahead of the matrix
+    //      instructions (scheduling groups: left to itself the compiler waits for every read right before the
+    //      instruction that uses it)
+    f32x16_t st[NKF];
 #pragma unroll
-    for (int kf = 0; kf < 2; ++kf)
+    for (int kf = 0; kf < NKF; ++kf)
 #pragma unroll
       for (int e = 0; e < 16; ++e) st[kf][e] = 0.f;
+    constexpr int AHEAD = NKF * NKS < 3 ? NKF * NKS : 3;
     {
-      f16x8_t kfr[2 * NKS];
+      f16x8_t kfr[NKF * NKS];
 #pragma unroll
-      for (int i = 0; i < 2 * NKS; ++i)
-        kfr[i] = *(const f16x8_t*)(Ks + ((i & 1) * 32 + l32) * K_STRIDE + 16 * (i >> 1) + 8 * half);
+      for (int i = 0; i < NKF * NKS; ++i)
+        kfr[i] = *(const f16x8_t*)(Ks + (i % NKF) * 32 * TL::KP * 8 + k_row + ((2 * (i / NKF) + half) ^ k_key) * 8);
 #pragma unroll
-      for (int i = 0; i < 2 * NKS; ++i)
-        st[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfr[i], qf[i >> 1], st[i & 1], 0, 0, 0);
-      constexpr int AHEAD = 2 * NKS < 3 ? 2 * NKS : 3;
+      for (int i = 0; i < NKF * NKS; ++i)
+        st[i % NKF] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfr[i], qf[i / NKF], st[i % NKF], 0, 0, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
 #pragma unroll
-      for (int i = 0; i < 2 * NKS - AHEAD; ++i) {
+      for (int i = 0; i < NKF * NKS - AHEAD; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
@@ -269,18 +276,18 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
     //      Key kj = k0 + 4*half + c of element (kf, e), c = 32*kf + 8*(e/4) + e%4 a constant, is visible iff
     //      kj <= min(qi, n - 1), i.e. c <= lim with lim formed once per tile: a compare and a select per element
     //      (the branch is wave-uniform).
-    const bool need_mask = (k0 + FA_BK - 1 > wq_lo) || (k0 + FA_BK > n);
+    const bool need_mask = (k0 + BK - 1 > wq_lo) || (k0 + BK > n);
     if (need_mask) {
       const int lim = min(qi, n - 1) - k0 - 4 * half;
 #pragma unroll
-      for (int kf = 0; kf < 2; ++kf)
+      for (int kf = 0; kf < NKF; ++kf)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
           if (kf * 32 + 8 * (e >> 2) + (e & 3) > lim) st[kf][e] = -INFINITY;
     }
     float mx = -INFINITY;  // raw dot products: the (positive) scale is applied inside the exponent's FMA
 #pragma unroll
-    for (int kf = 0; kf < 2; ++kf)
+    for (int kf = 0; kf < NKF; ++kf)
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[kf][e]);
     mx = half_max(mx);
@@ -288,9 +295,9 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // arguments <= 0: the bare instruction will do
     m_run = m_new;
     float psum = 0.f;
-    f16x8_t pf[4];  // P^T operand of each 16-key step
+    f16x8_t pf[2 * NKF];  // P^T operand of each 16-key step
 #pragma unroll
-    for (int kf = 0; kf < 2; ++kf)
+    for (int kf = 0; kf < NKF; ++kf)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const float p = __builtin_amdgcn_exp2f(fmaf(st[kf][e], scale_log2e, -m_new));
@@ -309,21 +316,34 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
     }
     //      (the NDT accumulation chains alternate; fragment reads three ahead as above)
     {
-      f16x8_t vfr[4 * NDT];
+      constexpr int NV = 2 * NKF * NDT;
+      f16x8_t vfr[NV];
 #pragma unroll
-      for (int i = 0; i < 4 * NDT; ++i)
-        vfr[i] = *(const f16x8_t*)(Vt + ((i % NDT) * 32 + l32) * FA_VT_STRIDE + 16 * (i / NDT) + 8 * half);
-#pragma unroll
-      for (int i = 0; i < 4 * NDT; ++i)
-        o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfr[i], pf[i / NDT], o[i % NDT], 0, 0, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-#pragma unroll
-      for (int i = 0; i < 4 * NDT - 3; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      for (int i = 0; i < NV; ++i) {
+        const uint16_t* const p = Vs + v_off[i % NDT] + 16 * (i / NDT) * TL::VP * 8;
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)p);
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + 8 * TL::VP * 8));
+        typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+        const s16x8_t w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        vfr[i] = __builtin_bit_cast(f16x8_t, w);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vfr[i], pf[i / NDT], o[i % NDT], 0, 0, 0);
+      constexpr int VA = NV < 3 ? NV : 3;
+      __builtin_amdgcn_sched_group_barrier(0x100, 2 * VA, 0);
+#pragma unroll
+      for (int i = 0; i < NV - VA; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, VA, 0);
     }
+  };
+  for (int k0 = 0; k0 <= q_hi; k0 += 2 * BK) {
+    tile(k0, std::integral_constant<int, 0>{});
+    if (k0 + BK > q_hi) break;
+    tile(k0 + BK, std::integral_constant<int, 1>{});
   }
   const float l_tot = half_sum(l_run);
   if (qi < n) {
@@ -344,13 +364,14 @@ __global__ void __launch_bounds__(256, (HD <= 80 ? 3 : HD <= 128 ? 2 : 1))
   }
 }
 
-template <int HD>
+template <int HD, int BK, int OCC>
 static void launch_fa(const void* q, const void* kc, const void* vc, long kv_extra, int B, int Lmax,
                       const int* len, const int* cu, const int* kvoff, int H, void* out, int out_ld, hipStream_t s) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)HD);
-  dim3 grid((Lmax + FA_BQ - 1) / FA_BQ, H, B);
-  hipLaunchKernelGGL(attn_prefill_mfma<HD>, grid, dim3(256), 0, s, (const half_t*)q, (const half_t*)kc,
-                     (const half_t*)vc, kv_extra, len, cu, kvoff, H, scale_log2e, (half_t*)out, out_ld);
+  const int nqb = (Lmax + FA_BQ - 1) / FA_BQ, pairs = (H * B + 7) / 8 * 8;
+  hipLaunchKernelGGL((attn_prefill_mfma<HD, BK, OCC>), dim3((unsigned)(nqb * pairs)), dim3(256), 0, s, (const half_t*)q,
+                     (const half_t*)kc, (const half_t*)vc, kv_extra, len, cu, kvoff, H, B, nqb, scale_log2e, (half_t*)out,
+                     out_ld);
 }
 
 hipError_t launch_attn_prefill(int dtype, const void* q, const void* kc, const void* vc, long kv_extra,
@@ -359,11 +380,11 @@ hipError_t launch_attn_prefill(int dtype, const void* q, const void* kc, const v
   if (hd > 256) return hipErrorInvalidValue;
   if (dtype == 1) {
     switch (hd) {
-      case 16: launch_fa<16>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
-      case 64: launch_fa<64>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
-      case 80: launch_fa<80>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
-      case 128: launch_fa<128>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
-      case 256: launch_fa<256>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
+      case 16: launch_fa<16, 64, 4>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
+      case 64: launch_fa<64, 64, 4>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
+      case 80: launch_fa<80, 64, 3>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
+      case 128: launch_fa<128, 64, 2>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
+      case 256: launch_fa<256, 64, 1>(q, kc, vc, kv_extra, B, Lmax, len, cu, kvoff, H, out, out_ld, s); return hipGetLastError();
       default: break;  // other head sizes: generic kernel below
     }
   }

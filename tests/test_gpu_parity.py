@@ -377,3 +377,20 @@ def test_gelu_of_the_largest_negative_inputs_with_many_rows(gpu):
     assert np.abs(out[0][0] - lp).max() <= TOL["bf16"] and np.abs(out[0][1] - val).max() <= TOL["bf16"]
     for o in out[1:]:
         assert (o[0] == out[0][0]).all() and (o[1] == out[0][1]).all()
+
+
+@pytest.mark.parametrize("H,hd", [(3, 16), (5, 64), (1, 80), (3, 128), (1, 256)])
+def test_packed_attention_at_the_edges_of_its_tiles(gpu, H, hd):
+    """Lengths on either side of a wave's 32 queries, of the 64-key tiles and of the 128-query blocks, in every head size of
+    the matrix-core kernel; numbers of (sequence, head) pairs that are no multiple of eight."""
+    O = _oracle()
+    cfg = ModelConfig(n_layers=1, d_model=H * hd, n_heads=H, head_dim=hd, rotary_dims=hd // 4, d_ff=2 * H * hd, vocab=517,
+                      dtype="bf16", pad_id=500)
+    w = make_weights(cfg, 33, variant="test")
+    lens = np.array([1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 192, 193, 257])
+    g = np.random.default_rng(hd)
+    tokens = g.integers(1, 500, size=(len(lens), 257)).astype(np.int32)
+    mask = (np.arange(257)[None, :] < lens[:, None]).astype(np.uint8)
+    lp, val = (x.cpu().numpy() for x in gpu.Policy(cfg, w).score_sequences(np.where(mask == 1, tokens, cfg.pad_id).astype(np.int32), mask, 0.7))
+    olp, oval = O.score_sequences(O.OracleModel(w, cfg), np.where(mask == 1, tokens, cfg.pad_id).astype(np.int32), mask, 0.7)
+    assert np.abs(lp - olp).max() <= TOL["bf16"] and np.abs(val - oval).max() <= TOL["bf16"]
