@@ -414,7 +414,7 @@ template <typename T>
 __global__ void __launch_bounds__(256)
     attn_decode_generic(const T* __restrict__ q, const T* __restrict__ kc, const T* __restrict__ vc,
                         long kv_extra, const int* __restrict__ len, int ctx_add,
-                        const int* __restrict__ kvoff, int H, int hd, float scale, T* __restrict__ out) {
+                        const int* __restrict__ kvoff, int H, int hd, float scale, T* __restrict__ out, int out_ld) {
   extern __shared__ float smem[];
   __shared__ float red[8];
   const int h = blockIdx.x, b = blockIdx.y;
@@ -461,7 +461,7 @@ __global__ void __launch_bounds__(256)
   if (tid < hd) {
     float o = 0.f;
     for (int gg = 0; gg < G; ++gg) o += part[gg * hd + tid];
-    out[(size_t)b * d + (size_t)h * hd + tid] = from_f32<T>(sum > 0.f ? o / sum : 0.f);  // empty context: zero row
+    out[(size_t)b * out_ld + (size_t)h * hd + tid] = from_f32<T>(sum > 0.f ? o / sum : 0.f);  // empty context: zero row
   }
 }
 
@@ -482,7 +482,7 @@ template <int HD>
 __global__ void __launch_bounds__(256)
     attn_decode_f16(const half_t* __restrict__ q, const half_t* __restrict__ kc, const half_t* __restrict__ vc,
                     long kv_extra, const int* __restrict__ len, int ctx_add, const int* __restrict__ kvoff,
-                    int H, float scale, half_t* __restrict__ out) {
+                    int H, float scale, half_t* __restrict__ out, int out_ld) {
   constexpr int CPR = HD / 8;             // 16-byte chunks per row
   constexpr int G = 64 / CPR;             // rows per wave instruction
   constexpr int ACTIVE = G * CPR;         // lanes that carry a chunk
@@ -602,13 +602,13 @@ __global__ void __launch_bounds__(256)
     float o = 0.f;
 #pragma unroll
     for (int r = 0; r < 4 * G; ++r) o += scratch[r * HD + e];
-    out[(size_t)b * d + (size_t)h * HD + e] = from_f32<half_t>(o * inv);
+    out[(size_t)b * out_ld + (size_t)h * HD + e] = from_f32<half_t>(o * inv);
   }
 }
 
 template <int HD>
 static hipError_t launch_dec(const void* q, const void* kc, const void* vc, long kv_extra, int B,
-                             const int* len, int ctx_add, int ctx_max, const int* kvoff, int H, void* out,
+                             const int* len, int ctx_add, int ctx_max, const int* kvoff, int H, void* out, int out_ld,
                              hipStream_t s) {
   constexpr int CPR = HD / 8, G = 64 / CPR;
   const size_t part = ((CPR & (CPR - 1)) == 0) ? 0 : (size_t)((ctx_max + G - 1) / G) * G * CPR;
@@ -618,21 +618,22 @@ static hipError_t launch_dec(const void* q, const void* kc, const void* vc, long
     (void)hipFuncSetAttribute((const void*)attn_decode_f16<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   hipLaunchKernelGGL(attn_decode_f16<HD>, dim3(H, B), dim3(256), sh, s, (const half_t*)q, (const half_t*)kc,
                      (const half_t*)vc, kv_extra, len, ctx_add, kvoff, H, 1.0f / sqrtf((float)HD),
-                     (half_t*)out);
+                     (half_t*)out, out_ld);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_decode(int dtype, const void* q, const void* kc, const void* vc, long kv_extra,
                               int B, const int* len, int ctx_add, int ctx_max, const int* kvoff, int H, int hd,
-                              void* out, hipStream_t s) {
+                              void* out, hipStream_t s, int out_ld) {
   if (hd > 256) return hipErrorInvalidValue;
+  if (!out_ld) out_ld = H * hd;
   if (dtype == 1) {
     switch (hd) {
-      case 16: return launch_dec<16>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, s);
-      case 64: return launch_dec<64>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, s);
-      case 80: return launch_dec<80>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, s);
-      case 128: return launch_dec<128>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, s);
-      case 256: return launch_dec<256>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, s);
+      case 16: return launch_dec<16>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, out_ld, s);
+      case 64: return launch_dec<64>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, out_ld, s);
+      case 80: return launch_dec<80>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, out_ld, s);
+      case 128: return launch_dec<128>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, out_ld, s);
+      case 256: return launch_dec<256>(q, kc, vc, kv_extra, B, len, ctx_add, ctx_max, kvoff, H, out, out_ld, s);
       default: break;  // other head sizes: generic kernel below
     }
   }
@@ -642,10 +643,10 @@ hipError_t launch_attn_decode(int dtype, const void* q, const void* kc, const vo
   dim3 grid(H, B);
   if (dtype == 0)
     hipLaunchKernelGGL(attn_decode_generic<float>, grid, dim3(256), sh, s, (const float*)q, (const float*)kc,
-                       (const float*)vc, kv_extra, len, ctx_add, kvoff, H, hd, scale, (float*)out);
+                       (const float*)vc, kv_extra, len, ctx_add, kvoff, H, hd, scale, (float*)out, out_ld);
   else
     hipLaunchKernelGGL(attn_decode_generic<half_t>, grid, dim3(256), sh, s, (const half_t*)q, (const half_t*)kc,
-                       (const half_t*)vc, kv_extra, len, ctx_add, kvoff, H, hd, scale, (half_t*)out);
+                       (const half_t*)vc, kv_extra, len, ctx_add, kvoff, H, hd, scale, (half_t*)out, out_ld);
   return hipGetLastError();
 }
 

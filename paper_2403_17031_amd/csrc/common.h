@@ -207,7 +207,7 @@ struct __align__(8) KvSlot {
 struct QkvArgs {
   const int* pos;      // [rows] position of a packed row (+ pos_add); rows are indexed from the start of the
                        // packed batch: a launch over a row chunk (GemmArgs::M_sub) adds its offset
-  const KvSlot* slots; // [rows] where a packed row's K and V go
+  const KvSlot* slots; // [rows] where a packed row's K and V go (+ pos_add slots)
   const float* cos_t;  // [positions][r/2]
   const float* sin_t;
   void* q;             // [rows, d] fp16
@@ -249,7 +249,12 @@ struct GemmArgs {
   bool small_footprint = false;  // few rows: stay on the staged tile kernel (24 KB of LDS, 4 blocks per CU), whose
                                  // blocks fit next to another kernel's on a CU; the weight-streaming kernel takes a
                                  // whole CU per block
+  bool large_tile = false;     // take the large-M kernel up to 512 rows too (its smaller tiles; the launch has the chip to
+                               // itself).  With EPI_F32 and splitk_ws: K cut into gemm_large_slices(a) slices, whose fp32
+                               // slabs [M_max, N] stay in splitk_ws for the consumer to add
 };
+int gemm_large_slices(const GemmArgs& a);
+bool gemm_takes_large(int dtype, const GemmArgs& a);
 // The few-rows (decode) kernel of gemm_skinny.hip: whether it takes these arguments, the K split it would use,
 // and the launch itself (ks > 1: fp32 partial slabs into a.splitk_ws; ks == 1: epilogue in the kernel).
 bool gemm_skinny_takes(int dtype, const GemmArgs& a);
@@ -310,6 +315,8 @@ hipError_t launch_row_spans(const uint8_t* mask, int B, int L, int kv_extra, int
 hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, const int* start, const int* len,
                              const int* cu, const void* embed, int d, int vocab, int* pos, int* rowid, int* tok,
                              float* x, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s);
+// Cache slots of the first token after every sequence (decode pass t stores t slots further).
+hipError_t launch_decode_slots(int B, const int* len, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s);
 hipError_t launch_gather_rows(const void* in, const int* src, int src_add, int rows, size_t row_bytes, void* out,
                               hipStream_t s);
 
@@ -319,6 +326,7 @@ hipError_t launch_layernorm(int dtype, const float* x, int rows_max, const int* 
                             void* out2, hipStream_t s);
 // Two split-K products (fp32 partial slabs of `slab` floats each, row-major [rows, d]) whose reduction
 // into the residual stream is still pending: x <- (x + (sum_z A_z + bias_a)) + (sum_z B_z + bias_b).
+// (ks_b == 0: one product, of both biases).
 struct PendingResidual {
   const float* part_a = nullptr;
   const float* part_b = nullptr;
@@ -365,7 +373,7 @@ hipError_t launch_attn_prefill(int dtype, const void* q, const void* kc, const v
 // Decode attention: one query row per sequence against ctx = len[b] + ctx_add cached keys.
 hipError_t launch_attn_decode(int dtype, const void* q, const void* kc, const void* vc, long kv_extra,
                               int B, const int* len, int ctx_add, int ctx_max, const int* kvoff, int H, int hd,
-                              void* out, hipStream_t s);
+                              void* out, hipStream_t s, int out_ld = 0);  // out_ld: row stride of out (0: H * hd)
 
 // The decode pass of few sequences (decode.hip).
 // x <- x + (sum of ks <= 8 slabs) + bias_a + bias_b (ks = 0: x as it is), then LayerNorm with one or two affine outputs

@@ -81,6 +81,18 @@ __global__ void pack_embed_kernel(const int32_t* __restrict__ tokens, int L, con
   for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = to_f32(e[c]);
 }
 
+__global__ void __launch_bounds__(64)
+    decode_slots_kernel(int B, const int* __restrict__ len, const int* __restrict__ kvoff, int H, int kv_extra,
+                        KvSlot* __restrict__ slots) {
+  const int b = blockIdx.x * 64 + threadIdx.x;
+  if (b < B) slots[b] = KvSlot{(uint32_t)kvoff[b] * (uint32_t)H + (uint32_t)len[b], (uint32_t)(len[b] + kv_extra)};
+}
+
+hipError_t launch_decode_slots(int B, const int* len, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s) {
+  hipLaunchKernelGGL(decode_slots_kernel, dim3((B + 63) / 64), dim3(64), 0, s, B, len, kvoff, H, kv_extra, slots);
+  return hipGetLastError();
+}
+
 hipError_t launch_pack_embed(int dtype, const int32_t* tokens, int B, int L, const int* start, const int* len,
                              const int* cu, const void* embed, int d, int vocab, int* pos, int* rowid, int* tok,
                              float* x, const int* kvoff, int H, int kv_extra, KvSlot* slots, hipStream_t s) {
@@ -192,6 +204,7 @@ __device__ __forceinline__ f32x4_t sum_slabs_n(const f32x4_t* __restrict__ p, si
 __device__ __forceinline__ f32x4_t sum_slabs(const f32x4_t* __restrict__ p, size_t slab4, int ks) {
   switch (ks) {
     case 2: return sum_slabs_n<2>(p, slab4);
+    case 3: return sum_slabs_n<3>(p, slab4);
     case 4: return sum_slabs_n<4>(p, slab4);
     case 8: return sum_slabs_n<8>(p, slab4);
     case 16: return sum_slabs_n<16>(p, slab4);
@@ -229,7 +242,8 @@ __global__ void __launch_bounds__(256)
         const size_t o = (size_t)r * nv + c;
         const size_t slab4 = pend.slab >> 2;
         const f32x4_t ta = sum_slabs((const f32x4_t*)pend.part_a + o, slab4, pend.ks_a);
-        const f32x4_t tb = sum_slabs((const f32x4_t*)pend.part_b + o, slab4, pend.ks_b);
+        f32x4_t tb = {0.f, 0.f, 0.f, 0.f};
+        if (pend.ks_b) tb = sum_slabs((const f32x4_t*)pend.part_b + o, slab4, pend.ks_b);
         v[i] += ta + bf16x4_to_f32(((const u32x2_t*)pend.bias_a)[c]);
         v[i] += tb + bf16x4_to_f32(((const u32x2_t*)pend.bias_b)[c]);
         ((f32x4_t*)(xw + (size_t)r * d))[c] = v[i];

@@ -486,7 +486,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
           const u32x4_t v = *(const u32x4_t*)(ep + row * 64 + ((rd_c ^ (row & 7)) << 3));
           if (grow < M && gcol < N) {
             if (EPI == EPI_QKV && sec != 0)
-              *(u32x4_t*)(cache + ((size_t)slot[it].x + (size_t)hh * slot[it].y) * qk.hd + e0) = v;
+              *(u32x4_t*)(cache + ((size_t)slot[it].x + qk.pos_add + (size_t)hh * slot[it].y) * qk.hd + e0) = v;
             else
               *(u32x4_t*)(ob + (size_t)(32 * i + 8 * it) * ld * 2 + lo) = v;
           }
@@ -1058,7 +1058,7 @@ static bool takes_dma(const GemmArgs& a) {
            (ldw % 8) == 0 && (size_t)a.K * std::max(lda, ldw) < (1ull << 32);
   }
   const size_t lda = a.lda ? a.lda : a.K, ldw = a.ldw ? a.ldw : a.K;
-  return RLHF_GEMM_DMA && a.M_max > 512 && (a.K % (2 * DK)) == 0 && (a.N % 8) == 0 && (a.ldo % 8) == 0 &&
+  return RLHF_GEMM_DMA && (a.M_max > 512 || a.large_tile) && (a.K % (2 * DK)) == 0 && (a.N % 8) == 0 && (a.ldo % 8) == 0 &&
          (lda % 8) == 0 && (ldw % 8) == 0 && std::max((size_t)a.M_max * lda, (size_t)a.N * ldw) < (1ull << 32);
 }
 // K slices of a large-M product with few output tiles and a long K (GemmArgs::long_k: the weight-gradient
@@ -1086,6 +1086,24 @@ static int dma_k_slices(const GemmArgs& a, int* k_slice) {
 bool gemm_takes_bias2(int dtype, const GemmArgs& a) {
   return dtype == 1 && a.epilogue == EPI_BIAS_RESADD && takes_dma(a);
 }
+bool gemm_takes_large(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
+// K slices of a large_tile product that leaves its slabs to the consumer: as many as minimise the length of a slice's stages
+// (about 0.24 us each in the 64x128 tiles, 0.36 in the 128x128, one round of them) plus what the slabs cost to write and to
+// read again.  us with 1 / 2 / 3 / 4 / 6 / 8 slices: 256 rows, out-projection and FC2 of width 2560 as one product (K = 12,800)
+// 55 / 31 / 25 / 25 / 22 / 29, of 2048 45 / 25 / 20 / 17 / 18 / 17, of 4096 83 / 52 / 48 / 46 / 52 / 49.
+int gemm_large_slices(const GemmArgs& a) {
+  const int tiles = ((a.M_max + 255) / 256) * ((a.N + 255) / 256), pairs = a.K / (2 * DK);
+  int best = 1;
+  double best_t = 1e30;
+  for (int n = 1; n <= 16 && n <= pairs; ++n) {
+    const int q = (pairs + n - 1) / n;
+    if ((pairs + q - 1) / q != n || (n > 1 && (size_t)n * a.M_max * a.N * sizeof(float) > a.splitk_ws_bytes)) continue;
+    const double stage = 8 * tiles * n <= kCUs ? 0.24 : 4 * tiles * n <= kCUs ? 0.36 : 1.5 * ((tiles * n + kCUs - 1) / kCUs);
+    const double t = 2 * q * stage + (double)n * a.M_max * a.N * 8 / 5e6;
+    if (t < best_t) { best_t = t; best = n; }
+  }
+  return best;
+}
 bool gemm_takes_k_major(int dtype, const GemmArgs& a) { return dtype == 1 && a.k_major && takes_dma(a); }
 bool gemm_takes_lse(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
 // EPI_QKV: 16-byte chunks must not straddle heads, a lane's 4-column group must be whole pairs, and the
@@ -1105,6 +1123,14 @@ static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, (const float*)a.A, (const float*)a.W,
                        (const float*)a.bias, a.out, a.M_max, a.M_dev, a.M_sub, a.N, a.K, a.ldo);
   } else {
+    if (a.large_tile && takes_dma(a)) {
+      const bool slabs = EPI == EPI_F32 && a.splitk_ws;
+      const int n = slabs ? gemm_large_slices(a) : 1, pairs = a.K / (2 * DK);
+      GemmArgs b = a;
+      if (slabs) { b.out = a.splitk_ws; b.ldo = a.N; }
+      launch_f16_dma<EPI>(b, s, n, (pairs + n - 1) / n * 2 * DK);
+      return;
+    }
     // Few rows (decode): the chip is filled by small N tiles and by splitting K, so that every CU
     // holds several short k-loops in flight; partial sums go through the caller's fp32 scratch.
     const int ksplit = gemm_splitk_factor(dtype, a);

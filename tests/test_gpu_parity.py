@@ -394,3 +394,20 @@ def test_packed_attention_at_the_edges_of_its_tiles(gpu, H, hd):
     lp, val = (x.cpu().numpy() for x in gpu.Policy(cfg, w).score_sequences(np.where(mask == 1, tokens, cfg.pad_id).astype(np.int32), mask, 0.7))
     olp, oval = O.score_sequences(O.OracleModel(w, cfg), np.where(mask == 1, tokens, cfg.pad_id).astype(np.int32), mask, 0.7)
     assert np.abs(lp - olp).max() <= TOL["bf16"] and np.abs(val - oval).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,H,hd,V", [(65, 4, 32, 520), (130, 4, 96, 517), (256, 4, 32, 517), (257, 2, 64, 520), (512, 4, 32, 520)])
+def test_decode_of_many_sequences_by_the_large_product(gpu, B, H, hd, V):
+    """Between the few-rows kernels' batches and 512 sequences: the smallest and the largest batch, either side of a row tile
+    of 256, a vocabulary that the large product does not take (no multiple of 8)."""
+    d = H * hd
+    cfg = ModelConfig(n_layers=2, d_model=d, n_heads=H, head_dim=hd, rotary_dims=hd // 4, d_ff=2 * d, vocab=V, dtype="bf16",
+                      pad_id=500)
+    w = make_weights(cfg, 34, variant="test")
+    queries, mask = _queries(cfg, B=B, Lq=6, lo=1, hi=6, seed=B)
+    p = gpu.Policy(cfg, w)
+    p.profile_enable()
+    p.rollout_generate(queries[:, -1:], mask[:, -1:], 5, 0.7, 2)
+    names = p.profile_read()
+    assert "gemm_decode_out_fc2" in names and "gemm_decode_qkv_fc1" not in names and "rope_kv_decode" not in names
+    _check_rollout_and_scores(gpu, cfg, w, queries, mask, seed=B, T=0.7, N=4, rows=[0, 63, 64, B // 2, B - 1], expect_exact=False)
