@@ -384,6 +384,11 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   GemmArgs base;
   base.M_max = p.rows_max;
   base.M_dev = p.rows_dev;
+  // Prefill and scoring of up to 512 rows: the large product's smaller tiles, with its fused epilogues and out-projection and
+  // FC2 as one, rather than the staged kernel (ms, staged / this: scoring 453 rows, six layers of 2.8B width 1.93 / 1.25, 150 at
+  // the 160M shape 1.31 / 0.79, 144 of two layers of 6.9B width 1.08 / 0.70; the prefill of one query of 320 tokens at 2.8B
+  // width 1.4 / 0.9).  Not a training forward: its sums stay in the order in which the backward pass forms them again.
+  base.large_tile = p.mode == 0 && p.rows_max > kFewRows && !p.keep;
   const bool split = p.mode == 1 && !few_rows_layer(c, p.rows_max);
   if (split) {
     base.splitk_ws = A.splitk;
@@ -429,6 +434,10 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   auto gcat = [&](int l) {
     GemmArgs g = gemm_args(A.att, h->w_o[l], h->b_o[l], A.x, d, d + c.d_ff, EPI_BIAS_RESADD);
     g.bias2 = h->b_fc2[l];
+    if (base.large_tile && p.rows_max <= 512) {  // a, m, qkv and q, which lie side by side, are done with by then
+      g.splitk_ws = A.a;
+      g.splitk_ws_bytes = (size_t)((char*)A.att - (char*)A.a);
+    }
     return g;
   };
   const bool cat = p.mode == 0 && h->ld_o2 != 0 && gemm_takes_bias2(dt, gcat(0));
@@ -1797,6 +1806,7 @@ static int score_tail(rlhf_handle* h, int B, int L, float temperature, ScoreWs& 
     lm.W = h->embed_out_mm; lm.bias = nullptr; lm.out = ws.logits;
     lm.M_max = rows; lm.M_dev = m.total; lm.M_sub = t0;  // rows past the device-side token count are skipped
     lm.N = c.vocab; lm.K = d; lm.ldo = c.vocab; lm.epilogue = EPI_F32;
+    lm.large_tile = rows > kFewRows;
     LAUNCH("gemm_lm_head", launch_gemm(dt, lm, s));
     LAUNCH("lse_gather", launch_lse_gather(ws.logits, rows, t0, m.total, c.vocab, temperature, m.tok, m.pos, ws.lp,
                                            s));

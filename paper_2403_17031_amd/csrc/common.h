@@ -250,8 +250,9 @@ struct GemmArgs {
                                  // blocks fit next to another kernel's on a CU; the weight-streaming kernel takes a
                                  // whole CU per block
   bool large_tile = false;     // take the large-M kernel up to 512 rows too (its smaller tiles; the launch has the chip to
-                               // itself).  With EPI_F32 and splitk_ws: K cut into gemm_large_slices(a) slices, whose fp32
-                               // slabs [M_max, N] stay in splitk_ws for the consumer to add
+                               // itself).  With splitk_ws K is cut into gemm_large_slices(a) slices, whose fp32 slabs
+                               // [M_max, N] stay there for the consumer to add (EPI_F32) or are added to out by a second
+                               // launch (EPI_BIAS_RESADD)
 };
 int gemm_large_slices(const GemmArgs& a);
 bool gemm_takes_large(int dtype, const GemmArgs& a);

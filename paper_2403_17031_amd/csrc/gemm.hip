@@ -1013,11 +1013,14 @@ static void launch_f16(const GemmArgs& a, hipStream_t s, void* out, int ksplit) 
                      a.N, a.K, a.ldo, nb_m, nb_n, ksplit, a.lda ? a.lda : a.K, a.ldw ? a.ldw : a.K);
 }
 
-// out = epilogue(sum_z partial[z] + bias), slabs added in index order: deterministic.
+// out = epilogue(sum_z partial[z] + bias (+ bias2)), slabs added in index order: deterministic.  M_dev: the device-side row
+// count, where the slabs' rows beyond it are not written.
 template <int EPI>
 __global__ void __launch_bounds__(256)
     splitk_reduce_kernel(const float* __restrict__ part, int ksplit, size_t slab, const bf16_t* __restrict__ bias,
-                         void* __restrict__ out, int M, int N, int ldo) {
+                         void* __restrict__ out, int M, int N, int ldo, const bf16_t* __restrict__ bias2 = nullptr,
+                         const int* __restrict__ M_dev = nullptr) {
+  if (M_dev) M = min(M, *M_dev);
   const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i4 >= (size_t)M * ldo) return;
   const int col = (int)(i4 % ldo);
@@ -1026,7 +1029,9 @@ __global__ void __launch_bounds__(256)
   for (int z = 1; z < ksplit; ++z) v += *(const f32x4_t*)(part + z * slab + i4);
 #pragma unroll
   for (int u = 0; u < 4; ++u)
-    if (col + u < N) epilogue_store<EPI, half_t>(out, i4 + u, v[u], (EPI != EPI_F32 && bias) ? to_f32(bias[col + u]) : 0.f);
+    if (col + u < N)
+      epilogue_store<EPI, half_t>(out, i4 + u, v[u], ((EPI != EPI_F32 && bias) ? to_f32(bias[col + u]) : 0.f) +
+                                                         ((EPI != EPI_F32 && bias2) ? to_f32(bias2[col + u]) : 0.f));
 }
 
 // Split factor of the few-rows path (1 = not split).  Few rows (decode): the chip is filled by small
@@ -1087,10 +1092,11 @@ bool gemm_takes_bias2(int dtype, const GemmArgs& a) {
   return dtype == 1 && a.epilogue == EPI_BIAS_RESADD && takes_dma(a);
 }
 bool gemm_takes_large(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
-// K slices of a large_tile product that leaves its slabs to the consumer: as many as minimise the length of a slice's stages
+// K slices of a large_tile product with scratch, as many as minimise the length of a slice's stages
 // (about 0.24 us each in the 64x128 tiles, 0.36 in the 128x128, one round of them) plus what the slabs cost to write and to
 // read again.  us with 1 / 2 / 3 / 4 / 6 / 8 slices: 256 rows, out-projection and FC2 of width 2560 as one product (K = 12,800)
-// 55 / 31 / 25 / 25 / 22 / 29, of 2048 45 / 25 / 20 / 17 / 18 / 17, of 4096 83 / 52 / 48 / 46 / 52 / 49.
+// 55 / 31 / 25 / 25 / 22 / 29, of 2048 45 / 25 / 20 / 17 / 18 / 17, of 4096 83 / 52 / 48 / 46 / 52 / 49.  The residual form adds
+// the launch that sums them.
 int gemm_large_slices(const GemmArgs& a) {
   const int tiles = ((a.M_max + 255) / 256) * ((a.N + 255) / 256), pairs = a.K / (2 * DK);
   int best = 1;
@@ -1099,7 +1105,7 @@ int gemm_large_slices(const GemmArgs& a) {
     const int q = (pairs + n - 1) / n;
     if ((pairs + q - 1) / q != n || (n > 1 && (size_t)n * a.M_max * a.N * sizeof(float) > a.splitk_ws_bytes)) continue;
     const double stage = 8 * tiles * n <= kCUs ? 0.24 : 4 * tiles * n <= kCUs ? 0.36 : 1.5 * ((tiles * n + kCUs - 1) / kCUs);
-    const double t = 2 * q * stage + (double)n * a.M_max * a.N * 8 / 5e6;
+    const double t = 2 * q * stage + (double)n * a.M_max * a.N * 8 / 5e6 + (a.epilogue == EPI_F32 || n == 1 ? 0.0 : 6.0);
     if (t < best_t) { best_t = t; best = n; }
   }
   return best;
@@ -1123,12 +1129,24 @@ static void launch_epi(int dtype, const GemmArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, (const float*)a.A, (const float*)a.W,
                        (const float*)a.bias, a.out, a.M_max, a.M_dev, a.M_sub, a.N, a.K, a.ldo);
   } else {
-    if (a.large_tile && takes_dma(a)) {
-      const bool slabs = EPI == EPI_F32 && a.splitk_ws;
-      const int n = slabs ? gemm_large_slices(a) : 1, pairs = a.K / (2 * DK);
-      GemmArgs b = a;
-      if (slabs) { b.out = a.splitk_ws; b.ldo = a.N; }
-      launch_f16_dma<EPI>(b, s, n, (pairs + n - 1) / n * 2 * DK);
+    if (a.large_tile && !a.long_k && takes_dma(a)) {
+      if constexpr (EPI == EPI_F32 || EPI == EPI_BIAS_RESADD) {
+        const int n = a.splitk_ws ? gemm_large_slices(a) : 1, pairs = a.K / (2 * DK);
+        if (a.splitk_ws && (EPI == EPI_F32 || (n > 1 && a.ldo == a.N && a.M_sub == 0))) {
+          GemmArgs b = a;
+          b.out = a.splitk_ws;
+          b.ldo = a.N;
+          launch_f16_dma<EPI_F32>(b, s, n, (pairs + n - 1) / n * 2 * DK);
+          if constexpr (EPI == EPI_BIAS_RESADD) {
+            const size_t quads = ((size_t)a.M_max * a.N + 3) / 4;
+            hipLaunchKernelGGL(splitk_reduce_kernel<EPI>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s,
+                               (const float*)a.splitk_ws, n, (size_t)a.M_max * a.N, (const bf16_t*)a.bias, a.out, a.M_max,
+                               a.N, a.ldo, (const bf16_t*)a.bias2, a.M_dev);
+          }
+          return;
+        }
+      }
+      launch_f16_dma<EPI>(a, s);
       return;
     }
     // Few rows (decode): the chip is filled by small N tiles and by splitting K, so that every CU

@@ -411,3 +411,20 @@ def test_decode_of_many_sequences_by_the_large_product(gpu, B, H, hd, V):
     names = p.profile_read()
     assert "gemm_decode_out_fc2" in names and "gemm_decode_qkv_fc1" not in names and "rope_kv_decode" not in names
     _check_rollout_and_scores(gpu, cfg, w, queries, mask, seed=B, T=0.7, N=4, rows=[0, 63, 64, B // 2, B - 1], expect_exact=False)
+
+
+@pytest.mark.parametrize("B,L,H", [(1, 64, 4), (1, 65, 4), (1, 257, 4), (2, 256, 4), (3, 171, 4), (2, 200, 3), (1, 400, 40)])
+def test_scoring_of_up_to_512_rows(gpu, B, L, H):
+    """Either side of 64 and of 512 rows, where the products change kernels; a width (192) that the large product does not take;
+    one (2560) whose out-projection and FC2 cut K into slabs."""
+    O = _oracle()
+    cfg = ModelConfig(n_layers=1, d_model=64 * H, n_heads=H, head_dim=64, rotary_dims=16, d_ff=256 if H == 4 else 64 * H, vocab=520,
+                      dtype="bf16", pad_id=519)
+    w = make_weights(cfg, 35, variant="test")
+    g = np.random.default_rng(L)
+    lens = np.array([L, L // 2, 1])[:B]
+    mask = (np.arange(L)[None, :] < lens[:, None]).astype(np.uint8)
+    tokens = np.where(mask == 1, g.integers(1, 500, size=(B, L)), cfg.pad_id).astype(np.int32)
+    lp, val = (x.cpu().numpy() for x in gpu.Policy(cfg, w).score_sequences(tokens, mask, 0.7))
+    olp, oval = O.score_sequences(O.OracleModel(w, cfg), tokens, mask, 0.7)
+    assert np.abs(lp - olp).max() <= TOL["bf16"] and np.abs(val - oval).max() <= TOL["bf16"]
