@@ -320,11 +320,14 @@ struct PassArgs {
   // for every row as usual, but attention, out-projection and MLP run on the B gathered last rows
   // only, into last->x ([B, d], row b = sequence b).
   const Acts* last = nullptr;
-  // Training forward: when set, the residual stream at the input of layer l is copied to
-  // keep + l * keep_stride (rows_max rows), and the stream after the last layer to slot n_layers.
+  // Training forward: when set, the residual stream at the input of layer l is left in
+  // keep + l * keep_stride, and the stream after the last layer in slot n_layers.  Either by copying keep_rows rows of the
+  // pass's own stream, or, with keep_chain (keep_chain_takes; the caller puts the embedding into slot 0), by having every
+  // layer's last product read one slot and write the next.
   float* keep = nullptr;
   size_t keep_stride = 0;
   size_t keep_rows = 0;
+  bool keep_chain = false;
   // Scoring from a first column on: when `sel` is set, the final layer computes K and V for every row as usual
   // and attention for every query, but the out-projection and the MLP run on the sel_rows selected rows only
   // (sel[j] = packed row, *n_sel of them), into selz->x.
@@ -441,11 +444,13 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
     return g;
   };
   const bool cat = p.mode == 0 && h->ld_o2 != 0 && gemm_takes_bias2(dt, gcat(0));
+  if (p.keep_chain && !cat) return fail(RLHF_EUNSUPPORTED, "chained residual stream: shape");
   const size_t slab = (size_t)p.rows_max * d;
   bool pending = false;  // out-projection and FC2 partial sums of the previous layer not yet in x
 
   for (int l = 0; l < c.n_layers; ++l) {
-    if (p.keep)
+    float* const x_l = p.keep_chain ? p.keep + (size_t)l * p.keep_stride : A.x;  // the stream at this layer's input
+    if (p.keep && !p.keep_chain)
       HIP_OK(hipMemcpyAsync(p.keep + (size_t)l * p.keep_stride, A.x, p.keep_rows * d * sizeof(float),
                             hipMemcpyDeviceToDevice, s));
     char* kc = p.kv + (p.kv_per_layer ? (size_t)l * 2 * plane : 0);
@@ -460,7 +465,7 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
                                                           A.a, h->ln2_g[l], h->ln2_b[l], A.m, pr, s));
       pending = false;
     } else {
-      LAUNCH(p.mode ? "layernorm_decode" : "layernorm", launch_layernorm(dt, A.x, p.rows_max, p.rows_dev, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l],
+      LAUNCH(p.mode ? "layernorm_decode" : "layernorm", launch_layernorm(dt, x_l, p.rows_max, p.rows_dev, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l],
                                            A.a, h->ln2_g[l], h->ln2_b[l], A.m, s));
     }
     GemmArgs g = gemm_args(A.a, h->w_qkv[l], h->b_qkv[l], A.qkv, 3 * d, d, EPI_BIAS);
@@ -606,7 +611,12 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
     if (cat) {
       // x += [att | ffn] [W_o | W_fc2]^T + b_o + b_fc2: one product, one pass over the residual stream
       if (!keep_u) LAUNCH("gemm", launch_gemm(dt, g1, s));
-      LAUNCH("gemm", launch_gemm(dt, gcat(l), s));
+      GemmArgs gc = gcat(l);
+      if (p.keep_chain) {
+        gc.res = x_l;
+        gc.out = x_l + p.keep_stride;
+      }
+      LAUNCH("gemm", launch_gemm(dt, gc, s));
       continue;
     }
     const bool defer = fold && l + 1 < c.n_layers;  // the next layer's LayerNorm adds both products
@@ -631,10 +641,19 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
       LAUNCH("gemm_decode_fc2", launch_gemm(dt, g2, s));
     }
   }
-  if (p.keep)
+  if (p.keep && !p.keep_chain)
     HIP_OK(hipMemcpyAsync(p.keep + (size_t)c.n_layers * p.keep_stride, A.x, p.keep_rows * d * sizeof(float),
                           hipMemcpyDeviceToDevice, s));
   return RLHF_OK;
+}
+// Whether a training forward over up to rows packed rows can chain its kept slots (PassArgs::keep_chain): every layer ends
+// with one product over out-projection and FC2, and rows of a slot are as aligned as those of the stream.
+bool keep_chain_takes(const rlhf_handle* h, const float* keep, size_t stride, int rows) {
+  const rlhf_model_config& c = h->cfg;
+  GemmArgs g;
+  g.A = g.W = g.bias = nullptr; g.out = nullptr; g.M_max = rows; g.M_dev = nullptr;
+  g.N = g.ldo = c.d_model; g.K = c.d_model + c.d_ff; g.epilogue = EPI_BIAS_RESADD;
+  return c.n_layers > 0 && h->ld_o2 != 0 && gemm_takes_bias2(c.dtype, g) && ((uintptr_t)keep & 15) == 0 && (stride & 3) == 0;
 }
 
 // Decode pass of few sequences (few_decode_size): four launches per layer, all on one stream.
@@ -1693,6 +1712,9 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
                          int keep_u_layers = 0) {
   const rlhf_model_config& c = h->cfg;
   const Meta& m = ws.meta;
+  const size_t kept_rows = keep_rows ? keep_rows : (size_t)B * L;  // rows copied per layer = row stride of the kept slices
+  const bool chain = keep && keep_chain_takes(h, keep, kept_rows * c.d_model, B * L);
+  if (chain) ws.acts.x = keep;
   LAUNCH("row_spans", launch_row_spans(mask, B, L, 0, m.start, m.len, m.cu, m.kvoff, m.total, s));
   LAUNCH("pack_embed", launch_pack_embed(c.dtype, tokens, B, L, m.start, m.len, m.cu, h->w.embed_in, c.d_model,
                                          c.vocab, m.pos, m.rowid, m.tok, ws.acts.x, m.cu, c.n_heads, 0, m.slots, s));
@@ -1716,7 +1738,8 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
   p.kv_slots = ws.Tmax;
   p.kv_per_layer = false;
   p.keep = keep;
-  p.keep_rows = keep_rows ? keep_rows : (size_t)B * L;  // rows copied per layer = row stride of the kept slices
+  p.keep_rows = kept_rows;
+  p.keep_chain = chain;
   p.keep_stride = p.keep_rows * c.d_model;
   if (keep && keep_q && keep_kv) {
     p.kv = keep_kv;
@@ -1742,7 +1765,9 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
       ws.sel_layers = true;
     }
   }
-  return run_layers(h, ws.acts, p, s);
+  const int rc = run_layers(h, ws.acts, p, s);
+  if (chain) ws.acts.x = keep + (size_t)c.n_layers * p.keep_stride;  // where the stream is now
+  return rc;
 }
 
 // After score_forward: final LayerNorm + value head, LM head + log-softmax of the next token, and the packed ->

@@ -239,6 +239,8 @@ struct GemmArgs {
   const struct QkvArgs* qkv = nullptr;  // EPI_QKV only
   int lda = 0, ldw = 0;        // row strides of A and W in elements (0: K); fp16 kernels and the few-rows kernel
   const void* bias2 = nullptr; // second bias added like the first; EPI_BIAS_RESADD of the large-M fp16 kernel only
+  const float* res = nullptr;  // EPI_BIAS_RESADD of the large-M fp16 kernel (gemm_takes_bias2): what the product is added to,
+                               // rows of ldo (null: out itself)
   int max_split = 0;           // few-rows kernel: cap on the K split (0: as many as cover the chip)
   bool k_major = false;        // operands given K-major: A is [K, M_max], W is [K, N], row-major, lda / ldw their row
                                // strides (0: M_max / N); out = A^T W, fp32 (EPI_F32), large-M fp16 kernel only: ask

@@ -323,6 +323,7 @@ struct DmaArgs {
   const half_t *A, *W;
   const bf16_t *bias, *bias2;
   void* out;
+  const float* res;     // EPI_BIAS_RESADD: what the product is added to
   const int* M_dev;
   int M_max, M_sub, N, K, ldo, lda, ldw;
   int slices, k_slice;  // K cut into `slices` ranges of k_slice; slice z writes its fp32 result to slab z of out
@@ -498,6 +499,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
       // registers beside the accumulators)
       float* const epf = (float*)ep;
       char* const ob = (char*)((float*)out + (size_t)row0 * ldo + col0);
+      const char* const rb = EPI == EPI_BIAS_RESADD ? (const char*)(g.res + (size_t)row0 * ldo + col0) : nullptr;
       const uint32_t lo = 4u * (uint32_t)(rd_row * ldo + rd_c * 4);
       f32x4_t xv[3][4];
       auto fetch = [&](int p) {
@@ -505,7 +507,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
 #pragma unroll
         for (int it = 0; it < 4; ++it)
           if (row0 + 32 * i + 8 * it + rd_row < M && col0 + 32 * j + 4 * rd_c < N)
-            xv[p % 3][it] = *(const f32x4_t*)(ob + ((size_t)(32 * i + 8 * it) * ldo + 32 * j) * 4 + lo);
+            xv[p % 3][it] = *(const f32x4_t*)(rb + ((size_t)(32 * i + 8 * it) * ldo + 32 * j) * 4 + lo);
       };
       if (EPI == EPI_BIAS_RESADD) {
         fetch(0);
@@ -966,6 +968,7 @@ static void launch_f16_dma(const GemmArgs& a, hipStream_t s, int k_slices = 1, i
   g.bias = (const bf16_t*)a.bias;
   g.bias2 = (const bf16_t*)a.bias2;
   g.out = split ? a.splitk_ws : a.out;
+  g.res = a.res ? a.res : (const float*)a.out;
   g.M_dev = a.M_dev;
   g.M_max = a.M_max; g.M_sub = a.M_sub; g.N = a.N; g.K = a.K;
   g.ldo = split ? a.N : a.ldo;
@@ -1196,7 +1199,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   if (a.M_max <= 0) return hipSuccess;
   if (dtype == 1 && (a.K % 8) != 0) return hipErrorInvalidValue;
   if (dtype != 1 && (a.bias2 || ((a.lda || a.ldw) && !few_rows_takes(dtype, a)))) return hipErrorInvalidValue;
-  if (a.bias2 && !gemm_takes_bias2(dtype, a)) return hipErrorInvalidValue;
+  if ((a.bias2 || a.res) && !gemm_takes_bias2(dtype, a)) return hipErrorInvalidValue;
+  if (a.res && (a.splitk_ws || a.long_k)) return hipErrorInvalidValue;
   if (a.k_major && !gemm_takes_k_major(dtype, a)) return hipErrorInvalidValue;
   if (few_rows_takes(dtype, a)) return launch_few_rows_gemm(dtype, a, s);
   switch (a.epilogue) {
