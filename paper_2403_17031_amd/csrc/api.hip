@@ -1202,6 +1202,10 @@ struct BranchShare {
   const void* go16 = nullptr;
   const float* base = nullptr;
   const void* kept_u = nullptr;  // MLP branch: FC1's output before the GELU as the forward pass left it, [T, d_ff]
+  // Both LayerNorms' backward in one pass, the attention branch's: the MLP branch leaves the gradient of LN2's output here
+  // ([T, d]) and ends, the attention branch takes it and writes LN2's gradients too.
+  float* d_ln2_out = nullptr;
+  float *d_ln2_g = nullptr, *d_ln2_b = nullptr;  // (attention branch)
 };
 static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, const float* d_out, int32_t T, float* d_x,
                              float* d_ln2_g, float* d_ln2_b, float* d_w_fc1, float* d_b_fc1, float* d_w_fc2,
@@ -1302,7 +1306,8 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_gemm(ws.fT, ws.mT, d_w_fc1, F, d), s));
   }
   LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, h->w_fc1[l], (size_t)d, ws.w1T, (size_t)F, F, d, F, s));
-  LAUNCH("gemm_mlp_dx", launch_gemm(dt, gemm(ws.df, ws.w1T, nullptr, ws.dm, T, d, F, EPI_F32), s));
+  LAUNCH("gemm_mlp_dx", launch_gemm(dt, gemm(ws.df, ws.w1T, nullptr, sh.d_ln2_out ? sh.d_ln2_out : ws.dm, T, d, F, EPI_F32), s));
+  if (sh.d_ln2_out) return RLHF_OK;
   // ---- LN2: the branch's term of dL/dx, and the gradients of its gain and bias
   if (sh.base && !(ln_backward_rows_supported(dt, d) && (((uintptr_t)x_in | (uintptr_t)d_x | (uintptr_t)sh.base) & 15) == 0))
     return fail(RLHF_EUNSUPPORTED, "accumulating LayerNorm backward: shape");
@@ -1352,7 +1357,7 @@ AttnBwdWs carve_attn_bwd(Carver& c, const rlhf_model_config& cfg, int T, size_t 
   w.delta = c.take<float>((size_t)T * cfg.n_heads);
   w.slabs_bytes = 8 * 3 * d * d * sizeof(float);
   w.slabs = c.take_bytes(w.slabs_bytes);
-  w.lnpart = c.take<float>(ln_backward_rows_scratch_floats(T, (int)d));
+  w.lnpart = c.take<float>((ln_backward_pair_supported(1, (int)d) ? 2 : 1) * ln_backward_rows_scratch_floats(T, (int)d));  // (both LayerNorms')
   return w;
 }
 }  // namespace
@@ -1504,7 +1509,11 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
   // ---- LN1: the branch's term of dL/dx, and the gradients of its gain and bias
   if (sh.base && !(ln_backward_rows_supported(dt, d) && (((uintptr_t)x_in | (uintptr_t)d_x | (uintptr_t)sh.base) & 15) == 0))
     return fail(RLHF_EUNSUPPORTED, "accumulating LayerNorm backward: shape");
-  if (ln_backward_rows_supported(dt, d) && (((uintptr_t)x_in | (uintptr_t)d_x) & 15) == 0)
+  if (sh.d_ln2_out)
+    LAUNCH("ln_backward", launch_ln_backward_pair(x_in, LnTerm{sh.d_ln2_out, h->ln2_g[l], sh.d_ln2_g, sh.d_ln2_b},
+                                                  LnTerm{ws.da, h->ln1_g[l], d_ln1_g, d_ln1_b}, T, d, c.ln_eps, d_x, ws.lnpart,
+                                                  s, sh.base));
+  else if (ln_backward_rows_supported(dt, d) && (((uintptr_t)x_in | (uintptr_t)d_x) & 15) == 0)
     LAUNCH("ln_backward", launch_ln_backward_rows(x_in, ws.da, h->ln1_g[l], T, d, c.ln_eps, d_x, ws.lnpart, d_ln1_g,
                                                   d_ln1_b, s, sh.base));
   else
@@ -1987,8 +1996,8 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
   float* go_part = (float*)(go16 + go_bytes);
   char* sub = go16 + go_bytes + part_bytes;
   const size_t sub_bytes = workspace_bytes - (size_t)(sub - (char*)workspace);
-  // one conversion and one set of column sums of dx per layer for both branches, and each branch's LayerNorm
-  // backward adding onto the running sum (dx + MLP term, then + attention term) -- where the one-pass kernel runs
+  // one conversion and one set of column sums of dx per layer for both branches, and one LayerNorm backward that adds both
+  // branches' terms onto dx, or each branch's adding onto the running sum -- where the one-pass kernel runs
   const bool share = c.dtype == 1 && c.n_layers > 0 && ln_backward_rows_supported(c.dtype, c.d_model) && (c.d_model & 3) == 0;
   const int go_splits = std::max(1, std::min(256, (T + 255) / 256));
   if (share && Tp > (size_t)T)
@@ -2023,8 +2032,15 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
     BranchShare sm, sa;
     if (share) {
       sm.go16 = sa.go16 = go16;
-      sm.base = dx;    // dx_m = dx + MLP term
-      sa.base = dx_m;  // dx_n = dx_m + attention term
+      if (ln_backward_pair_supported(c.dtype, c.d_model)) {
+        sa.base = dx;  // dx_n = (dx + MLP term) + attention term, both formed by the attention branch's last kernel
+        sm.d_ln2_out = sa.d_ln2_out = dx_m;
+        sa.d_ln2_g = g->ln2_g[l];
+        sa.d_ln2_b = g->ln2_b[l];
+      } else {
+        sm.base = dx;    // dx_m = dx + MLP term
+        sa.base = dx_m;  // dx_n = dx_m + attention term
+      }
     }
     if (kept_u && l < kept_u_layers) sm.kept_u = kept_u + (size_t)l * kept_u_stride;
     rc = mlp_backward_impl(h, l, xl, dx, T, dx_m, g->ln2_g[l], g->ln2_b[l], g->w_fc1[l], g->b_fc1[l], g->w_fc2[l],

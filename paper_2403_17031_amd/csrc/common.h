@@ -495,6 +495,16 @@ size_t ln_backward_rows_scratch_floats(int T, int d);
 // base (optional): dx = base + the LayerNorm input gradient (rows of d floats like dx).
 hipError_t launch_ln_backward_rows(const float* x, const float* dy, const void* g, int T, int d, float eps, float* dx,
                                    float* part, float* d_g, float* d_b, hipStream_t s, const float* base = nullptr);
+// The two LayerNorms of one input together: dx = (base + the gradient of a.dy) + that of b.dy; twice the scratch; widths up
+// to 1536 (a row of four arrays and four rows of sums in a wave's registers).
+bool ln_backward_pair_supported(int dtype, int d);
+struct LnTerm {
+  const float* dy;
+  const void* g;
+  float *d_g, *d_b;
+};
+hipError_t launch_ln_backward_pair(const float* x, const LnTerm& a, const LnTerm& b, int T, int d, float eps, float* dx,
+                                   float* part, hipStream_t s, const float* base);
 // sums[c] = sum_r a[r][c] of a float [R, C] matrix (C a multiple of 4) and out_f16 = its fp16 copy, in one pass;
 // part: [splits][C] floats of scratch.
 hipError_t launch_convert_colsum(const float* a, int R, int C, float* part, int splits, float* sums, void* out_f16,

@@ -264,29 +264,39 @@ __global__ void __launch_bounds__(256)
 // and of dy in registers (NV float4 per lane, d = 256 * NV), forms the row's statistics and dx, and keeps the column
 // sums sum dy * xh and sum dy of its rows in registers; they go to part [waves][2][d], which
 // ln_backward_rows_final_kernel adds in wave order.  x, dy read once, dx written once.
-template <int NV>
+// NG = 2: the two LayerNorms of a layer, which have their input and so their statistics in common: dx = (base + the term of
+// dy[0]) + the term of dy[1], their column sums in part[0] and part[1].  22 k rows of 768: two launches 110 us (544 MB) and 21
+// for their sums, one 74 (340 MB) and 11.
+struct LnBwdArgs {
+  const float* dy[2];
+  const bf16_t* g[2];
+  float* part[2];
+};
+template <int NV, int NG>
 __global__ void __launch_bounds__(256)
-    ln_backward_rows_kernel(const float* __restrict__ x, const float* __restrict__ dyp, const bf16_t* __restrict__ g,
-                            int T, float eps, float* __restrict__ dx, float* __restrict__ part, int rows_per_wave,
-                            const float* __restrict__ base) {
+    ln_backward_rows_kernel(const float* __restrict__ x, LnBwdArgs in, int T, float eps, float* __restrict__ dx,
+                            int rows_per_wave, const float* __restrict__ base) {
   constexpr int d = 256 * NV;
   const int lane = threadIdx.x & 63;
   const int gw = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int t0 = gw * rows_per_wave, t1 = min(T, t0 + rows_per_wave);
-  f32x4_t sg[NV], sb[NV];
+  f32x4_t sg[NG][NV], sb[NG][NV];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    sg[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    sb[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int k = 0; k < NG; ++k)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      sg[k][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      sb[k][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
   for (int t = t0; t < t1; ++t) {
     const f32x4_t* xr = (const f32x4_t*)(x + (size_t)t * d);
-    const f32x4_t* dr = (const f32x4_t*)(dyp + (size_t)t * d);
-    f32x4_t xv[NV], dv[NV];
+    f32x4_t xv[NV], dv[NG][NV], bv[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       xv[j] = xr[lane + 64 * j];
-      dv[j] = dr[lane + 64 * j];
+#pragma unroll
+      for (int k = 0; k < NG; ++k) dv[k][j] = ((const f32x4_t*)(in.dy[k] + (size_t)t * d))[lane + 64 * j];
+      if (NG == 2) bv[j] = ((const f32x4_t*)(base + (size_t)t * d))[lane + 64 * j];
     }
     float a = 0.f;
 #pragma unroll
@@ -301,39 +311,60 @@ __global__ void __launch_bounds__(256)
         q += xv[j][e] * xv[j][e];
       }
     const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
-    float su = 0.f, sux = 0.f;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const u32x2_t gb = *(const u32x2_t*)(g + 4 * (lane + 64 * j));
-      const float gf[4] = {__uint_as_float(gb[0] << 16), __uint_as_float(gb[0] & 0xFFFF0000u),
-                           __uint_as_float(gb[1] << 16), __uint_as_float(gb[1] & 0xFFFF0000u)};
+    for (int j = 0; j < NV; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        xv[j][e] *= rstd;  // xh
-        sg[j][e] += dv[j][e] * xv[j][e];
-        sb[j][e] += dv[j][e];
-        dv[j][e] *= gf[e];  // u = dy * g, in place: dy itself is not needed again
-        su += dv[j][e];
-        sux += dv[j][e] * xv[j][e];
+      for (int e = 0; e < 4; ++e) xv[j][e] *= rstd;  // xh
+    float mu[NG], mux[NG];
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      float su = 0.f, sux = 0.f;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const u32x2_t gb = *(const u32x2_t*)(in.g[k] + 4 * (lane + 64 * j));
+        const float gf[4] = {__uint_as_float(gb[0] << 16), __uint_as_float(gb[0] & 0xFFFF0000u),
+                             __uint_as_float(gb[1] << 16), __uint_as_float(gb[1] & 0xFFFF0000u)};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sg[k][j][e] += dv[k][j][e] * xv[j][e];
+          sb[k][j][e] += dv[k][j][e];
+          dv[k][j][e] *= gf[e];  // u = dy * g, in place: dy itself is not needed again
+          su += dv[k][j][e];
+          sux += dv[k][j][e] * xv[j][e];
+        }
       }
+      mu[k] = wave_sum(su) / (float)d;
+      mux[k] = wave_sum(sux) / (float)d;
     }
-    const float mu = wave_sum(su) / (float)d, mux = wave_sum(sux) / (float)d;
     f32x4_t* o = (f32x4_t*)(dx + (size_t)t * d);
     const f32x4_t* bs = base ? (const f32x4_t*)(base + (size_t)t * d) : nullptr;  // dx = base + this term
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       f32x4_t r;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) r[e] = rstd * (dv[j][e] - mu - xv[j][e] * mux);
-      if (bs) r += bs[lane + 64 * j];
+      for (int e = 0; e < 4; ++e) r[e] = rstd * (dv[0][j][e] - mu[0] - xv[j][e] * mux[0]);
+      if constexpr (NG == 2) {
+        f32x4_t r1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r1[e] = rstd * (dv[NG - 1][j][e] - mu[NG - 1] - xv[j][e] * mux[NG - 1]);
+        // (terms and sums rounded on their own, as two launches leave them: no FMA across)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(r[e]), "+v"(r1[e]));
+        r = r1 + (r + bv[j]);
+      } else if (bs) {
+        r += bs[lane + 64 * j];
+      }
       o[lane + 64 * j] = r;
     }
   }
-  f32x4_t* p = (f32x4_t*)(part + (size_t)gw * 2 * d);
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    p[lane + 64 * j] = sg[j];
-    p[d / 4 + lane + 64 * j] = sb[j];
+  for (int k = 0; k < NG; ++k) {
+    f32x4_t* p = (f32x4_t*)(in.part[k] + (size_t)gw * 2 * d);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      p[lane + 64 * j] = sg[k][j];
+      p[d / 4 + lane + 64 * j] = sb[k][j];
+    }
   }
 }
 
@@ -342,9 +373,13 @@ __global__ void __launch_bounds__(256)
 // chunks ahead of the 128 threads that add up one chain of one column each.  With one thread per column, six blocks
 // waited for 512 loads one after the other: 160 us at width 768 (2048 waves), now 11.
 constexpr int kSumChunk = 256;
+struct LnBwdSums {
+  float *d_g[2], *d_b[2];
+};
 __global__ void __launch_bounds__(1024)
-    ln_backward_rows_final_kernel(const float* __restrict__ part, int waves, int d, float* __restrict__ d_g,
-                                  float* __restrict__ d_b) {
+    ln_backward_rows_final_kernel(LnBwdArgs in, int waves, int d, LnBwdSums sums) {
+  const float* const part = in.part[blockIdx.y];
+  float *const d_g = sums.d_g[blockIdx.y], *const d_b = sums.d_b[blockIdx.y];
   __shared__ float buf[2][kSumChunk][32];
   __shared__ float chain[4][32];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -911,23 +946,43 @@ size_t ln_backward_rows_scratch_floats(int T, int d) {
   const int rpw = std::max(1, (T + 2047) / 2048), waves = ((T + rpw - 1) / rpw + 3) & ~3;
   return (size_t)waves * 2 * d;
 }
-hipError_t launch_ln_backward_rows(const float* x, const float* dy, const void* g, int T, int d, float eps, float* dx,
-                                   float* part, float* d_g, float* d_b, hipStream_t s, const float* base) {
+template <int NG>
+static hipError_t ln_backward_launch(const float* x, const LnBwdArgs& in, int T, int d, float eps, float* dx,
+                                     const LnBwdSums& sums, hipStream_t s, const float* base) {
   if (T <= 0) return hipSuccess;
   const int rpw = std::max(1, (T + 2047) / 2048), waves = ((T + rpw - 1) / rpw + 3) & ~3;
-#define RLHF_LNB(NV)                                                                                             \
-  case NV:                                                                                                       \
-    hipLaunchKernelGGL(ln_backward_rows_kernel<NV>, dim3(waves / 4), dim3(256), 0, s, x, dy, (const bf16_t*)g, T, \
-                       eps, dx, part, rpw, base);                                                                \
+#define RLHF_LNB(NV)                                                                                                 \
+  case NV:                                                                                                           \
+    hipLaunchKernelGGL((ln_backward_rows_kernel<NV, NG>), dim3(waves / 4), dim3(256), 0, s, x, in, T, eps, dx, rpw, base); \
     break;
   switch (d / 256) {
-    RLHF_LNB(1) RLHF_LNB(2) RLHF_LNB(3) RLHF_LNB(4) RLHF_LNB(5) RLHF_LNB(6) RLHF_LNB(7) RLHF_LNB(8)
-    RLHF_LNB(9) RLHF_LNB(10) RLHF_LNB(11) RLHF_LNB(12) RLHF_LNB(13) RLHF_LNB(14) RLHF_LNB(15) RLHF_LNB(16)
-    default: return hipErrorInvalidValue;
+    RLHF_LNB(1) RLHF_LNB(2) RLHF_LNB(3) RLHF_LNB(4) RLHF_LNB(5) RLHF_LNB(6)
+    default:
+      if constexpr (NG == 1) {
+        switch (d / 256) {
+          RLHF_LNB(7) RLHF_LNB(8) RLHF_LNB(9) RLHF_LNB(10) RLHF_LNB(11) RLHF_LNB(12) RLHF_LNB(13) RLHF_LNB(14)
+          RLHF_LNB(15) RLHF_LNB(16)
+          default: return hipErrorInvalidValue;
+        }
+      } else {
+        return hipErrorInvalidValue;
+      }
   }
 #undef RLHF_LNB
-  hipLaunchKernelGGL(ln_backward_rows_final_kernel, dim3((2 * d + 31) / 32), dim3(1024), 0, s, part, waves, d, d_g, d_b);
+  hipLaunchKernelGGL(ln_backward_rows_final_kernel, dim3((2 * d + 31) / 32, NG), dim3(1024), 0, s, in, waves, d, sums);
   return hipGetLastError();
+}
+hipError_t launch_ln_backward_rows(const float* x, const float* dy, const void* g, int T, int d, float eps, float* dx,
+                                   float* part, float* d_g, float* d_b, hipStream_t s, const float* base) {
+  return ln_backward_launch<1>(x, LnBwdArgs{{dy, nullptr}, {(const bf16_t*)g, nullptr}, {part, nullptr}}, T, d, eps, dx,
+                               LnBwdSums{{d_g, nullptr}, {d_b, nullptr}}, s, base);
+}
+bool ln_backward_pair_supported(int dtype, int d) { return ln_backward_rows_supported(dtype, d) && d <= 1536; }
+hipError_t launch_ln_backward_pair(const float* x, const LnTerm& a, const LnTerm& b, int T, int d, float eps, float* dx,
+                                   float* part, hipStream_t s, const float* base) {
+  return ln_backward_launch<2>(x, LnBwdArgs{{a.dy, b.dy}, {(const bf16_t*)a.g, (const bf16_t*)b.g},
+                                            {part, part + ln_backward_rows_scratch_floats(T, d)}},
+                               T, d, eps, dx, LnBwdSums{{a.d_g, b.d_g}, {a.d_b, b.d_b}}, s, base);
 }
 
 hipError_t launch_head_ln_backward(int dtype, const float* x, const float* dhl, const float* gv, float scale,
