@@ -375,7 +375,8 @@ int rlhf_policy_backward(rlhf_handle *h, const float *x_keep, int64_t x_keep_lay
  * (B_minibatch = B / n_minibatches, L = Lq + N, T_max = the largest entry of minibatch_tokens): that is the minimum.
  * A bf16 model uses whatever the caller passes beyond it to keep FC1's output (before the GELU) of the forward pass
  * instead of recomputing it in the backward pass: T_max * d_ff * 2 bytes (rounded up to 256) per layer, for as many
- * of the first layers as fit; results are the same up to the rounding of the GELU's two forms.  Everything is
+ * of the first layers as fit; results are the same up to the rounding of the GELU's two forms.  What is left once every
+ * layer's is kept (T_max rounded up to 128, * d_model * 4 bytes per layer) keeps the LayerNorms' outputs.  Everything is
  * enqueued on `stream`; no host synchronisation. */
 typedef struct {
   int32_t epochs, n_minibatches;            /* the paper: 4, 1 */

@@ -479,14 +479,19 @@ class Policy:
         need = C.c_size_t()
         _check(self.lib.rlhf_ppo_update_workspace_bytes(self._h, Bm, L, N, int(counts.max()), C.byref(need)))
         # Workspace beyond the minimum lets the loop keep FC1's pre-activations instead of recomputing them (one
-        # [T_max, d_ff] fp16 slice per layer): as many layers as leave 16 GB of the device free.
+        # [T_max, d_ff] fp16 slice per layer), then the LayerNorms' outputs (two of [T_max padded to 128, d_model]): as many
+        # layers as leave 16 GB of the device free.
         want = need.value
         if keep_preactivations and self.cfg.dtype != "fp32":
             per_layer = (int(counts.max()) * self.cfg.d_ff * 2 + 255) // 256 * 256
             free_b, _ = torch.cuda.mem_get_info()
             have = self._ws.numel() if self._ws is not None else 0
             room = free_b + have - need.value - (16 << 30)
-            want += max(0, min(self.cfg.n_layers, room // per_layer)) * per_layer + 256
+            n_u = max(0, min(self.cfg.n_layers, room // per_layer))
+            want += n_u * per_layer + 256
+            if n_u == self.cfg.n_layers:
+                ln_layer = (int(counts.max()) + 127) // 128 * 128 * self.cfg.d_model * 4
+                want += max(0, min(n_u, (room - n_u * per_layer) // ln_layer)) * ln_layer
         ws = self._workspace(want)
         stats = self._out((epochs * n_minibatches, 8), torch.float32)
         with torch.cuda.device(self.device):

@@ -344,6 +344,11 @@ struct PassArgs {
   char* u_keep = nullptr;
   size_t u_keep_stride = 0;
   int u_keep_layers = 0;
+  // ... and, for the first ln_keep_layers layers, its two LayerNorms' outputs: LN1's at ln_keep + l * ln_keep_stride bytes,
+  // LN2's half a stride further, instead of the pass's own buffers.
+  char* ln_keep = nullptr;
+  size_t ln_keep_stride = 0;
+  int ln_keep_layers = 0;
 };
 
 // Whether the few-rows kernel takes the four products of a layer over this many rows (of its tiles' rows at least).
@@ -455,6 +460,11 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
                             hipMemcpyDeviceToDevice, s));
     char* kc = p.kv + (p.kv_per_layer ? (size_t)l * 2 * plane : 0);
     char* vc = kc + plane;
+    void *a_l = A.a, *m_l = A.m;  // this layer's LayerNorm outputs
+    if (p.ln_keep && l < p.ln_keep_layers) {
+      a_l = p.ln_keep + (size_t)l * p.ln_keep_stride;
+      m_l = (char*)a_l + p.ln_keep_stride / 2;
+    }
     void* const q_l = p.q_keep ? (void*)(p.q_keep + (size_t)l * p.q_keep_stride) : A.q;  // this layer's rotated q rows
     if (pending) {
       PendingResidual pr;
@@ -466,9 +476,9 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
       pending = false;
     } else {
       LAUNCH(p.mode ? "layernorm_decode" : "layernorm", launch_layernorm(dt, x_l, p.rows_max, p.rows_dev, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l],
-                                           A.a, h->ln2_g[l], h->ln2_b[l], A.m, s));
+                                           a_l, h->ln2_g[l], h->ln2_b[l], m_l, s));
     }
-    GemmArgs g = gemm_args(A.a, h->w_qkv[l], h->b_qkv[l], A.qkv, 3 * d, d, EPI_BIAS);
+    GemmArgs g = gemm_args(a_l, h->w_qkv[l], h->b_qkv[l], A.qkv, 3 * d, d, EPI_BIAS);
     if (p.mode == 1) g.max_split = cap_qkv;
     if (fold) {
       g.phase = 1;
@@ -561,7 +571,7 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
       break;
     }
     GemmArgs go = gemm_args(A.att, h->w_o[l], h->b_o[l], A.x, d, d, EPI_BIAS_RESADD);
-    GemmArgs g1 = gemm_args(A.m, h->w_fc1[l], h->b_fc1[l], A.ffn, c.d_ff, d, EPI_BIAS_GELU);
+    GemmArgs g1 = gemm_args(m_l, h->w_fc1[l], h->b_fc1[l], A.ffn, c.d_ff, d, EPI_BIAS_GELU);
     GemmArgs g2 = gemm_args(A.ffn, h->w_fc2[l], h->b_fc2[l], A.x, d, c.d_ff, EPI_BIAS_RESADD);
     go.ldw = g2.ldw = h->ld_o2;
     if (p.mode == 1) {
@@ -1202,6 +1212,8 @@ struct BranchShare {
   const void* go16 = nullptr;
   const float* base = nullptr;
   const void* kept_u = nullptr;  // MLP branch: FC1's output before the GELU as the forward pass left it, [T, d_ff]
+  // The branch's LayerNorm output as the forward pass left it, [T padded to 128 rows, d] (the padding rows are zeroed here).
+  void* kept_ln = nullptr;
   // Both LayerNorms' backward in one pass, the attention branch's: the MLP branch leaves the gradient of LN2's output here
   // ([T, d]) and ends, the attention branch takes it and writes LN2's gradients too.
   float* d_ln2_out = nullptr;
@@ -1244,11 +1256,13 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
     return g;
   };
   // ---- the branch's forward, recomputed from the layer input: m = LN2(x), u = m W1^T + b1, f = gelu(u)
-  LAUNCH("final_ln", launch_final_ln(dt, x_in, nullptr, 0, T, nullptr, d, c.ln_eps, h->ln2_g[l], h->ln2_b[l], ws.m,
-                                     nullptr, 0.f, nullptr, s));
+  void* const ln_out = sh.kept_ln ? sh.kept_ln : ws.m;
+  if (!sh.kept_ln)
+    LAUNCH("final_ln", launch_final_ln(dt, x_in, nullptr, 0, T, nullptr, d, c.ln_eps, h->ln2_g[l], h->ln2_b[l], ws.m,
+                                       nullptr, 0.f, nullptr, s));
   const void* u = sh.kept_u ? sh.kept_u : ws.u;
   if (!sh.kept_u)
-    LAUNCH("gemm_mlp_fwd", launch_gemm(dt, gemm(ws.m, h->w_fc1[l], h->b_fc1[l], ws.u, T, F, d, EPI_BIAS), s));
+    LAUNCH("gemm_mlp_fwd", launch_gemm(dt, gemm(ln_out, h->w_fc1[l], h->b_fc1[l], ws.u, T, F, d, EPI_BIAS), s));
   // ---- FC2: db2 = sum_t G, df = G W2, dW2 = G^T f
   const void* go = sh.go16 ? sh.go16 : ws.go;
   if (!sh.go16) {
@@ -1280,7 +1294,7 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
     return g;
   };
   const bool kmaj = gemm_takes_k_major(dt, dw_kmajor(go, ws.f, d_w_fc2, d, F)) &&
-                    gemm_takes_k_major(dt, dw_kmajor(ws.df, ws.m, d_w_fc1, F, d));
+                    gemm_takes_k_major(dt, dw_kmajor(ws.df, ln_out, d_w_fc1, F, d));
   if (kmaj) {
     ZeroSpans tails;
     auto tail = [&](void* buf, int width) {
@@ -1289,7 +1303,7 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
     if (!sh.go16) tail(ws.go, d);
     tail(ws.f, F);
     tail(ws.df, F);
-    tail(ws.m, d);
+    tail(ln_out, d);
     LAUNCH("mlp_bwd_zero", launch_fill_zero_spans(tails, s));
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_kmajor(go, ws.f, d_w_fc2, d, F), s));
   } else {
@@ -1299,10 +1313,10 @@ static int mlp_backward_impl(rlhf_handle* h, int32_t layer, const float* x_in, c
   }
   // ---- FC1: dW1 = du^T m, dm = du W1
   if (kmaj) {
-    LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_kmajor(ws.df, ws.m, d_w_fc1, F, d), s));
+    LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_kmajor(ws.df, ln_out, d_w_fc1, F, d), s));
   } else {
     LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, ws.df, (size_t)F, ws.fT, (size_t)Tp, T, F, Tp, s));
-    LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, ws.m, (size_t)d, ws.mT, (size_t)Tp, T, d, Tp, s));
+    LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, ln_out, (size_t)d, ws.mT, (size_t)Tp, T, d, Tp, s));
     LAUNCH("gemm_mlp_dw", launch_gemm(dt, dw_gemm(ws.fT, ws.mT, d_w_fc1, F, d), s));
   }
   LAUNCH("mlp_bwd_transpose", launch_transpose_pad(dt, h->w_fc1[l], (size_t)d, ws.w1T, (size_t)F, F, d, F, s));
@@ -1425,12 +1439,14 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
     return g;
   };
   // ---- the branch's forward, recomputed from the layer input: a = LN1(x), qkv = a Wqkv^T + b, rotary turn
-  LAUNCH("final_ln", launch_final_ln(dt, x_in, nullptr, 0, T, nullptr, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l], ws.a,
-                                     nullptr, 0.f, nullptr, s));
+  void* const ln_out = sh.kept_ln ? sh.kept_ln : ws.a;
+  if (!sh.kept_ln)
+    LAUNCH("final_ln", launch_final_ln(dt, x_in, nullptr, 0, T, nullptr, d, c.ln_eps, h->ln1_g[l], h->ln1_b[l], ws.a,
+                                       nullptr, 0.f, nullptr, s));
   const bool kept = kept_q && kept_k && kept_v;
   if (kept && !attention_backward_takes_cache(dt, hd)) return fail(RLHF_EUNSUPPORTED, "kept K/V cache: head size");
   if (!kept) {
-    LAUNCH("gemm_attn_fwd", launch_gemm(dt, gemm(ws.a, h->w_qkv[l], h->b_qkv[l], ws.qkv, T, 3 * d, d, EPI_BIAS), s));
+    LAUNCH("gemm_attn_fwd", launch_gemm(dt, gemm(ln_out, h->w_qkv[l], h->b_qkv[l], ws.qkv, T, 3 * d, d, EPI_BIAS), s));
     LAUNCH("rope_inplace", launch_rope_inplace(dt, ws.qkv, (size_t)3 * d, cu_seqlens, B, T, H, hd, c.rotary_dims,
                                                h->rope_cos, h->rope_sin, 0, s));
   }
@@ -1472,7 +1488,7 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
     return g;
   };
   const bool kmaj = gemm_takes_k_major(dt, dw_kmajor(go, ws.att, d_w_o, d, d)) &&
-                    gemm_takes_k_major(dt, dw_kmajor(ws.dqkv, ws.a, d_w_qkv, 3 * d, d));
+                    gemm_takes_k_major(dt, dw_kmajor(ws.dqkv, ln_out, d_w_qkv, 3 * d, d));
   if (kmaj) {
     ZeroSpans tails;
     auto tail = [&](void* buf, int width) {
@@ -1481,7 +1497,7 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
     if (!sh.go16) tail(ws.go, d);
     tail(ws.att, d);
     tail(ws.dqkv, 3 * d);
-    tail(ws.a, d);
+    tail(ln_out, d);
     LAUNCH("attn_bwd_zero", launch_fill_zero_spans(tails, s));
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(go, ws.att, d_w_o, d, d), s));
   } else {
@@ -1494,10 +1510,10 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
                                              h->rope_cos, h->rope_sin, 1, s));
   LAUNCH("colsum", launch_colsum(dt, ws.dqkv, T, 3 * d, ws.part, ws.splits, reordered ? ws.dbq : d_b_qkv, s));
   if (kmaj) {
-    LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(ws.dqkv, ws.a, reordered ? ws.dwq : d_w_qkv, 3 * d, d), s));
+    LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(ws.dqkv, ln_out, reordered ? ws.dwq : d_w_qkv, 3 * d, d), s));
   } else {
     LAUNCH("attn_bwd_transpose", launch_transpose_pad(dt, ws.dqkv, (size_t)3 * d, ws.dqkvT, (size_t)Tp, T, 3 * d, Tp, s));
-    LAUNCH("attn_bwd_transpose", launch_transpose_pad(dt, ws.a, (size_t)d, ws.aT, (size_t)Tp, T, d, Tp, s));
+    LAUNCH("attn_bwd_transpose", launch_transpose_pad(dt, ln_out, (size_t)d, ws.aT, (size_t)Tp, T, d, Tp, s));
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_gemm(ws.dqkvT, ws.aT, reordered ? ws.dwq : d_w_qkv, 3 * d, d), s));
   }
   if (reordered) {
@@ -1718,7 +1734,7 @@ int rollout_generate(rlhf_handle* h, const int32_t* queries, const uint8_t* pad_
 static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* mask, int B, int L, ScoreWs& ws,
                          hipStream_t s, float* keep = nullptr, size_t keep_rows = 0, char* keep_q = nullptr,
                          char* keep_kv = nullptr, char* keep_u = nullptr, size_t keep_u_stride = 0,
-                         int keep_u_layers = 0) {
+                         int keep_u_layers = 0, char* keep_ln = nullptr, size_t keep_ln_stride = 0, int keep_ln_layers = 0) {
   const rlhf_model_config& c = h->cfg;
   const Meta& m = ws.meta;
   const size_t kept_rows = keep_rows ? keep_rows : (size_t)B * L;  // rows copied per layer = row stride of the kept slices
@@ -1761,6 +1777,11 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
     p.u_keep = keep_u;
     p.u_keep_stride = keep_u_stride;
     p.u_keep_layers = keep_u_layers;
+  }
+  if (keep && keep_ln && keep_ln_layers > 0) {
+    p.ln_keep = keep_ln;
+    p.ln_keep_stride = keep_ln_stride;
+    p.ln_keep_layers = keep_ln_layers;
   }
   ws.sel_layers = false;
   if (ws.sel_rows) {
@@ -1943,7 +1964,8 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
                                 float temperature, float grad_scale, const rlhf_grads* g, void* workspace,
                                 size_t workspace_bytes, void* stream, const int* sel, int sel_rows, const int* n_sel,
                                 const char* kept_q = nullptr, const char* kept_kv = nullptr,
-                                const char* kept_u = nullptr, size_t kept_u_stride = 0, int kept_u_layers = 0);
+                                const char* kept_u = nullptr, size_t kept_u_stride = 0, int kept_u_layers = 0,
+                                char* kept_ln = nullptr, size_t kept_ln_stride = 0, int kept_ln_layers = 0);
 
 int rlhf_policy_backward(rlhf_handle* h, const float* x_keep, int64_t x_keep_layer_stride, const int32_t* cu_seqlens,
                          const int32_t* packed_tokens, int32_t B, int32_t T, int32_t max_len, const int32_t* targets,
@@ -1960,7 +1982,7 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
                                 float temperature, float grad_scale, const rlhf_grads* g, void* workspace,
                                 size_t workspace_bytes, void* stream, const int* sel, int sel_rows, const int* n_sel,
                                 const char* kept_q, const char* kept_kv, const char* kept_u, size_t kept_u_stride,
-                                int kept_u_layers) {
+                                int kept_u_layers, char* kept_ln, size_t kept_ln_stride, int kept_ln_layers) {
   // kept_q / kept_kv: what score_forward's keep_q / keep_kv received, with keep_rows = x_keep_layer_stride / d_model
   if (!h || !g) return fail(RLHF_EINVAL, "null argument");
   const rlhf_model_config& c = h->cfg;
@@ -2042,6 +2064,10 @@ static int policy_backward_impl(rlhf_handle* h, const float* x_keep, int64_t x_k
         sa.base = dx_m;  // dx_n = dx_m + attention term
       }
     }
+    if (kept_ln && l < kept_ln_layers) {
+      sa.kept_ln = kept_ln + (size_t)l * kept_ln_stride;
+      sm.kept_ln = (char*)sa.kept_ln + kept_ln_stride / 2;
+    }
     if (kept_u && l < kept_u_layers) sm.kept_u = kept_u + (size_t)l * kept_u_stride;
     rc = mlp_backward_impl(h, l, xl, dx, T, dx_m, g->ln2_g[l], g->ln2_b[l], g->w_fc1[l], g->b_fc1[l], g->w_fc2[l],
                            g->b_fc2[l], sub, sub_bytes, stream, sm);
@@ -2070,6 +2096,9 @@ struct UpdateWs {
   char* u_keep = nullptr;      // FC1 pre-activations of the first u_layers layers: whatever workspace the caller
   size_t u_stride = 0;         // gave beyond the minimum
   int u_layers = 0;
+  char* ln_keep = nullptr;     // both LayerNorms' outputs of the first ln_layers layers: what is left of that
+  size_t ln_stride = 0;
+  int ln_layers = 0;
   float *x_keep, *lp_full, *val_full, *new_lp, *new_v, *d_lp, *d_v, *gl, *gv;
   int32_t* targets;
   void* bwd;
@@ -2179,6 +2208,10 @@ int rlhf_ppo_update(rlhf_handle* h, const rlhf_ppo_update_config* cfg, const rlh
     ws.u_stride = (((size_t)T_max * c.d_ff * h->esz) + 255) & ~(size_t)255;
     ws.u_layers = (int)std::min<size_t>((size_t)c.n_layers, (workspace_bytes - used) / ws.u_stride);
     ws.u_keep = ws.u_layers > 0 ? (char*)workspace + used : nullptr;
+    const size_t rest = workspace_bytes - used - (size_t)ws.u_layers * ws.u_stride;
+    ws.ln_stride = 2 * (((size_t)T_max + 127) & ~(size_t)127) * c.d_model * h->esz;
+    ws.ln_layers = ws.u_layers == c.n_layers ? (int)std::min<size_t>((size_t)c.n_layers, rest / ws.ln_stride) : 0;
+    ws.ln_keep = ws.ln_layers > 0 ? (char*)workspace + used + (size_t)ws.u_layers * ws.u_stride : nullptr;
   }
   hipStream_t s = (hipStream_t)stream;
   // from here on the value head's bias is the device scalar the optimizer updates
@@ -2190,9 +2223,11 @@ int rlhf_ppo_update(rlhf_handle* h, const rlhf_ppo_update_config* cfg, const rlh
       const int32_t* tok_j = tokens + r0 * L;
       const uint8_t* mask_j = mask + r0 * L;
       const int T = minibatch_tokens[j];
+      // (up to 2048 rows the backward pass forms the LayerNorms with another kernel than the padded forward pass may)
+      char* const ln_keep = T > 2048 ? ws.ln_keep : nullptr;
       // forward with the current weights, keeping the layer inputs (packed rows: slices of T rows)
       rc = score_forward(h, tok_j, mask_j, Bm, L, ws.score, s, ws.x_keep, (size_t)T, ws.q_keep, ws.kv_keep, ws.u_keep,
-                         ws.u_stride, ws.u_layers);
+                         ws.u_stride, ws.u_layers, ln_keep, ws.ln_stride, ws.ln_layers);
       if (rc) return rc;
       rc = score_tail(h, Bm, L, cfg->temperature, ws.score, ws.lp_full, ws.val_full, s);
       if (rc) return rc;
@@ -2207,7 +2242,8 @@ int rlhf_ppo_update(rlhf_handle* h, const rlhf_ppo_update_config* cfg, const rlh
       rc = policy_backward_impl(h, ws.x_keep, (int64_t)T * c.d_model, m.cu, m.tok, Bm, T, max_len, ws.targets, ws.gl,
                                 ws.gv, cfg->temperature, cfg->grad_scale, &G, ws.bwd, ws.bwd_bytes, stream,
                                 ws.score.sel_rows ? ws.score.sel : nullptr, ws.score.sel_rows, ws.score.n_sel,
-                                ws.q_keep, ws.kv_keep, ws.u_keep, ws.u_stride, ws.u_layers);
+                                ws.q_keep, ws.kv_keep, ws.u_keep, ws.u_stride, ws.u_layers, ln_keep, ws.ln_stride,
+                                ws.ln_layers);
       if (rc) return rc;
       // AdamW on every tensor; a bf16 model keeps fp32 masters and gets its storage arrays rewritten
       std::vector<AdamwTensor> adam;

@@ -254,3 +254,35 @@ def test_the_optimizer_step_over_all_tensors_is_the_step_of_each(gpu, layers):
         if name != "value_b":
             assert bool((pol._dev[name] == bf).all()), name
     pol.close()
+
+
+def test_kept_layer_norms_change_nothing(gpu, monkeypatch):
+    """An update whose workspace has room for both LayerNorms' outputs of every layer, of one layer, and of none (they are
+    formed again from the layer inputs): 2,400-odd rows, no multiple of 128; the same bits."""
+    import ctypes as C
+    import torch
+    cfg = ModelConfig(n_layers=2, d_model=256, n_heads=4, head_dim=64, rotary_dims=16, d_ff=640, vocab=200, dtype="bf16",
+                      pad_id=199, eos_id=1)
+    w = make_weights(cfg, 94, variant="test")
+    g = np.random.default_rng(17)
+    B, Lq, N = 50, 40, 13
+    L = Lq + N
+    tokens = g.integers(2, 190, (B, L)).astype(np.int32)
+    mask = (np.arange(L)[None, :] >= g.integers(0, 8, B)[:, None]).astype(np.uint8)
+    tokens[mask == 0] = cfg.pad_id
+    T = int(mask.sum())
+    assert T > 2048 and T % 128
+    old_lp, adv, old_v, ret = (g.normal(0, 1, (4, B, N)) - np.array([4, 0, 0, 0])[:, None, None]).astype(np.float32)
+    u, ln = (T * cfg.d_ff * 2 + 255) // 256 * 256, (T + 127) // 128 * 128 * cfg.d_model * 4
+    results = []
+    for layers in (2, 1, 0):
+        pol = gpu.Policy(cfg, w)
+        need = C.c_size_t()
+        assert pol.lib.rlhf_ppo_update_workspace_bytes(pol._h, B, L, N, T, C.byref(need)) == 0
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda *a: (need.value + (16 << 30) + 2 * u + layers * ln, 0))
+        stats = pol.ppo_update(tokens, mask, Lq, old_lp, adv, old_v, ret, np.full(B, N, np.int32), 0.7, epochs=2, lr=1e-3, eps=1e-3)
+        assert pol._ws.numel() == need.value + 256 + 2 * u + layers * ln
+        results.append([stats, *pol.train_state()["grads"].values(), *pol.train_state()["master"].values()])
+        results[-1] = [x.clone() for x in results[-1]]
+    for other in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(results[0], other))
