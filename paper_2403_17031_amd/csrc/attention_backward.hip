@@ -267,40 +267,122 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Matrix-core form of the dK / dV kernel (fp16).  A block owns 128 keys of one (sequence, head), a wave 32 of them,
-// one per lane pair; their K and V rows stay in registers as MFMA operands.  Tiles of 64 queries (rows i0 .. i0+63
-// of the sequence, from the key tile's own position to the end) go through LDS twice over: row-major (Q, dO) as
-// the first operand of S = Q K^T and dP = dO V^T, whose accumulators hold, for the lane's key, the tile's queries
-// as rows; and transposed (Q^T, dO^T, columns in the order the accumulator rows map to operand slots) as the first
-// operand of dK^T += Q^T dS and dV^T += dO^T P.  P = exp(S scale - lse_i) needs no running maximum: lse_i and
-// delta_i come from the query-side kernel.
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+typedef __attribute__((address_space(3))) s16x4_t* lds4_t;
 
-// Two blocks per CU where the registers allow it without spilling (head sizes up to 80 here, up to 128 for the
-// query-side kernel): a second wave per SIMD covers the first one's waits (3.45 against 4.9 ms per layer at the
-// 2.8B shape for the two kernels together).
+// The matrix-core kernels' LDS image of 64 rows of one head's matrix, which goes global -> LDS directly and which both
+// kinds of read take: whole chunks of 16 bytes of consecutive rows (an operand whose contraction runs over the head's dims)
+// and the transposing read ds_read_b64_tr_b16 (one whose contraction runs over the rows; it delivers rows 4 half .. + 3 and
+// 8 + 4 half .. + 3 of 16, the order in which the accumulators hold them).  Row r is P chunks, chunk c of it at c ^ swizzle(r):
+// 16 consecutive rows of one chunk fall into the 16 groups of four banks, and so do four chunks of four rows; eight rows on
+// the swizzle differs by 2, sixteen on it is the same.
+template <int HD>
+struct BwdTile {
+  static constexpr int CH = HD / 8, P = HD == 80 ? 12 : CH, ROW = P * 8, HALFS = 64 * ROW, NL = P / 4;
+  __device__ static int swizzle(int r) {
+    if (HD == 64) return 4 * ((r >> 1) & 1) | ((r >> 2) & 3);
+    if (HD == 80) return (r >> 2) & 3;
+    return 4 * (r & 3) | ((r >> 2) & 3);
+  }
+  // Rows row0 .. row0 + 63 (past the last: the last again) of src, rows ld apart, into img.  One of the block's four waves
+  // fills NL * 64 chunks.  Assembly without destination registers, for the compiler would wait for the next tile at every
+  // read of this one; the tile's start waits for all of them.  (m0 holds nothing else here.)
+  __device__ static void load(const half_t* src, size_t ld, int row0, int last, const uint16_t* img, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int x = 64 * (NL * wave + i) + lane, r = x / P;
+      const int c = min((x - r * P) ^ swizzle(r), CH - 1);
+      const uint32_t off = 2u * ((uint32_t)min(row0 + r, last) * (uint32_t)ld + c * 8);
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(
+          (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(img + 512 * (NL * wave + i)));
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(src) : "memory");
+    }
+  }
+  __device__ static f16x8_t rows(const uint16_t* img, int f, int l32, int chunk) {  // row 32 f + l32
+    return *(const f16x8_t*)(img + (32 * f + l32) * ROW + (chunk ^ swizzle(l32)) * 8);
+  }
+  // column 32 t + lane % 32 of the rows 16 step .. + 15 (the lane's half of them)
+  __device__ static f16x8_t cols(const uint16_t* img, int t, int step, int lane) {
+    const int r = lane & 15, row = 4 * (lane >> 5) + (r >> 2), c = (4 * t + 2 * ((lane >> 4) & 1) + ((r & 3) >> 1)) ^ swizzle(row);
+    const uint16_t* const p = img + 16 * step * ROW + row * ROW + (r & 1) * 4;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + c * 8));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + 8 * ROW + (c ^ 2) * 8));
+    const s16x8_t w = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(f16x8_t, w);
+  }
+};
+
+// The start of a tile: what this wave has loaded is in LDS and what it has read it holds; then the same for every wave.
+__device__ __forceinline__ void tile_start() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The block's (sequence, head) pair and its 128 rows' number in it: the blocks of a pair run on one XCD, one after the
+// other, and share the pair's matrices in its L2.
+__device__ __forceinline__ bool bwd_block(int H, int B, int nblk, int& b, int& h, int& blk) {
+  const int idx = blockIdx.x >> 3, pair = (blockIdx.x & 7) + 8 * (idx / nblk);
+  if (pair >= H * B) return false;
+  b = pair / H;
+  h = pair - b * H;
+  blk = idx % nblk;
+  return true;
+}
+
+// Matrix-core form of the dK / dV kernel (fp16).  A block owns 128 keys of one (sequence, head), a wave 32 of them,
+// one per lane pair; their K and V rows stay in registers as MFMA operands.  Tiles of 64 queries (rows i0 .. i0+63
+// of the sequence, from the key tile's own position to the end) go through LDS: read by rows (Q, dO) as
+// the first operand of S = Q K^T and dP = dO V^T, whose accumulators hold, for the lane's key, the tile's queries
+// as rows; and by columns (Q^T, dO^T) as the first
+// operand of dK^T += Q^T dS and dV^T += dO^T P.  P = exp(S scale - lse_i) needs no running maximum: lse_i and
+// delta_i come from the query-side kernel.  The block with the most queries runs first.
+//
+// Bound by the vector arithmetic between the products (an exponential, a difference and two conversions per score) and the
+// LDS reads, 16 operands of 16 bytes per 4 products; so what a tile needs besides goes straight to LDS, one tile ahead, from
+// matrices that the pair's blocks find in their L2, and no register holds it.  As many blocks per CU as the registers give
+// without spilling to speak of (two up to head size 80 here; three at 64, two at 80 and 128 for the query-side kernel;
+// one more block would spill 38 to 113 registers).  Both kernels, tiles staged and transposed through registers / this, us:
+// 64 sequences of 155-539 rows, 12 heads of 64 239 / 176, 32 of 80 737 / 632, 32 of 128 926 / 820; 32 of 505-2021, 8 of
+// 256 6580 / 2990 (there the old order of blocks gave eight XCDs each their own copy of every pair); results the same bit
+// for bit.
 template <int HD>
 __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
     attn_bwd_kv_mfma(const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v,
-                     const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, float scale,
+                     const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, int B, int nblk, float scale,
                      const float* __restrict__ lse, const float* __restrict__ delta, half_t* __restrict__ dk,
                      half_t* __restrict__ dv, size_t ldq, size_t ldg, size_t ldo, int kv_cache) {
   // kv_cache: k and v are the forward pass's K / V cache of the layer (sequence b owns the slots from cu[b] * H on,
   // head h of it len_b consecutive rows of HD) instead of [T, .] matrices with row stride ldq
-  constexpr int NKS = HD / 16, NDT = (HD + 31) / 32, RS = HD + 8, TS = 64 + 8;
-  __shared__ __attribute__((aligned(16))) uint16_t Qs[64 * RS];
-  __shared__ __attribute__((aligned(16))) uint16_t Gs[64 * RS];
-  __shared__ __attribute__((aligned(16))) uint16_t Qt[NDT * 32 * TS];
-  __shared__ __attribute__((aligned(16))) uint16_t Gt[NDT * 32 * TS];
-  __shared__ __attribute__((aligned(16))) float lse_s[64], del_s[64];
-  const int b = blockIdx.z, h = blockIdx.y, k0 = blockIdx.x * 128;
+  typedef BwdTile<HD> TL;
+  constexpr int NKS = HD / 16, NDT = (HD + 31) / 32;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TL::HALFS];  // two of (Q, dO)
+  __shared__ __attribute__((aligned(16))) float lse_s[2][64], del_s[2][64];
+  int b, h, blk;
+  if (!bwd_block(H, B, nblk, b, h, blk)) return;
+  const int k0 = blk * 128;
   const int s0 = min(max(cu[b], 0), Tn), n = min(cu[b + 1], Tn) - s0;  // clamped: a malformed cu must not lead out of bounds
   if (k0 >= n) return;
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: the per-tile tests become scalar branches
   const size_t col = (size_t)h * HD;
+  const half_t* const qb = q + (size_t)s0 * ldq + col;
+  const half_t* const gb = g + (size_t)s0 * ldg + col;
+  float lse_r, del_r;
+  auto load_tile = [&](int i0, int buf) {
+    TL::load(qb, ldq, i0, n - 1, smem + buf * 2 * TL::HALFS, wave, lane);
+    TL::load(gb, ldg, i0, n - 1, smem + buf * 2 * TL::HALFS + TL::HALFS, wave, lane);
+    const size_t row = (size_t)(s0 + min(i0 + lane, n - 1));
+    lse_r = lse[row * H + h];
+    del_r = delta[row * H + h];
+  };
+  load_tile(k0, 0);
   const int kj = k0 + wave * 32 + l32;  // this lane's key
   const int kjc = min(kj, n - 1);
   f16x8_t kf[NKS], vf[NKS];
@@ -313,10 +395,6 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
       vf[ks] = *(const f16x8_t*)(v + kvb + 16 * ks + 8 * half);
     }
   }
-  for (int c = tid; c < (NDT * 32 - HD) * TS; c += 256) {  // rows of the transposed tiles past HD stay zero
-    Qt[HD * TS + c] = 0;
-    Gt[HD * TS + c] = 0;
-  }
   f32x16_t dvT[NDT], dkT[NDT];
 #pragma unroll
   for (int t = 0; t < NDT; ++t)
@@ -327,66 +405,16 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
     }
   const float scale_log2e = scale * 1.4426950408889634f;
   const int kw0 = k0 + wave * 32;  // first key of the wave
-  constexpr int CPR = HD / 8;
-  // A tile travels global -> registers one iteration ahead of its use, once: a thread's item is 4 queries x 8 dims
-  // of Q and of dO, which it writes to LDS both row-major (4 x 16 bytes) and transposed (8 x 8 bytes, the 4 queries
-  // adjacent under the column permutation of the accumulator layout).  Threads past the tile's 16 * CPR items
-  // re-read the last item instead of branching around the loads (the wait counting stays static).
-  constexpr int ITEMS = 16 * CPR, NIT = (ITEMS + 255) / 256;  // items of the tile, items per thread
-  f16x8_t qv[NIT][4], gv[NIT][4];
-  float lse_r = 0.f, del_r = 0.f;
-  auto load_tile = [&](int i0) {
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int item = min(tid + 256 * it, ITEMS - 1), ich = item / 16, ig4 = item - ich * 16;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const size_t row = (size_t)(s0 + min(i0 + 4 * ig4 + u, n - 1));
-        qv[it][u] = *(const f16x8_t*)(q + row * ldq + col + ich * 8);
-        gv[it][u] = *(const f16x8_t*)(g + row * ldg + col + ich * 8);
-      }
+  for (int i0 = k0, buf = 0; i0 < n; i0 += 64, buf ^= 1) {
+    if (wave == 0) {  // (read last two tiles ago, before the barrier of the tile between)
+      lse_s[buf][lane] = lse_r * 1.4426950408889634f;
+      del_s[buf][lane] = del_r;
     }
-    const size_t row = (size_t)(s0 + min(i0 + (tid & 63), n - 1));
-    lse_r = lse[row * H + h];
-    del_r = delta[row * H + h];
-  };
-  auto store_tile = [&]() {
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int item = tid + 256 * it, ich = item / 16, ig4 = item - ich * 16;
-      if (item < ITEMS) {
-        const int kk = (4 * ig4) & 15;
-        const int colp = ((4 * ig4) & ~15) + 8 * ((kk >> 2) & 1) + 4 * (kk >> 3);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          *(f16x8_t*)((half_t*)Qs + (4 * ig4 + u) * RS + ich * 8) = qv[it][u];
-          *(f16x8_t*)((half_t*)Gs + (4 * ig4 + u) * RS + ich * 8) = gv[it][u];
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const f16x4_t wq = {qv[it][0][e], qv[it][1][e], qv[it][2][e], qv[it][3][e]};
-          const f16x4_t wg = {gv[it][0][e], gv[it][1][e], gv[it][2][e], gv[it][3][e]};
-          *(f16x4_t*)((half_t*)Qt + (ich * 8 + e) * TS + colp) = wq;
-          *(f16x4_t*)((half_t*)Gt + (ich * 8 + e) * TS + colp) = wg;
-        }
-      }
-    }
-    if (tid < 64) {
-      lse_s[tid] = lse_r * 1.4426950408889634f;
-      del_s[tid] = del_r;
-    }
-  };
-  const int i_first = k0 & ~63;
-  const int i_last = ((n - 1) / 64) * 64;  // first query of the sequence's last tile
-  load_tile(i_first);
-  // (the loads issued so far are waited for here, once: see the note in attn_prefill_mfma)
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  for (int i0 = i_first; i0 < n; i0 += 64) {
-    __syncthreads();  // every wave is done with the previous tile
-    store_tile();
-    __syncthreads();
-    load_tile(min(i0 + 64, i_last));
+    tile_start();
+    if (i0 + 64 < n) load_tile(i0 + 64, buf ^ 1);
     if (i0 + 63 < kw0) continue;  // every query of this tile comes before every key of this wave
+    const uint16_t* const Qs = smem + buf * 2 * TL::HALFS;
+    const uint16_t* const Gs = Qs + TL::HALFS;
     // lse and delta of this lane's 32 queries of the tile: rows 32*qf2 + 8*g + 4*half + (0..3), as 4-vectors
     f16x8_t pf[4], df[4];  // P and dS of the tile for this lane's key, as second operands of the 16-query steps
     // a query i sees key kj iff i >= kj; rows past the sequence's end and keys past it contribute nothing
@@ -399,8 +427,8 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
         f16x8_t qa[NKS], ga[NKS];
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
-          qa[ks] = *(const f16x8_t*)(Qs + (qf2 * 32 + l32) * RS + 16 * ks + 8 * half);
-          ga[ks] = *(const f16x8_t*)(Gs + (qf2 * 32 + l32) * RS + 16 * ks + 8 * half);
+          qa[ks] = TL::rows(Qs, qf2, l32, 2 * ks + half);
+          ga[ks] = TL::rows(Gs, qf2, l32, 2 * ks + half);
         }
         const f32x16_t z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         st = z;
@@ -423,8 +451,8 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
       f32x4_t ls[4], dl[4];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
-        ls[g4] = *(const f32x4_t*)(lse_s + qf2 * 32 + 8 * g4 + 4 * half);
-        dl[g4] = *(const f32x4_t*)(del_s + qf2 * 32 + 8 * g4 + 4 * half);
+        ls[g4] = *(const f32x4_t*)(lse_s[buf] + qf2 * 32 + 8 * g4 + 4 * half);
+        dl[g4] = *(const f32x4_t*)(del_s[buf] + qf2 * 32 + 8 * g4 + 4 * half);
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -441,19 +469,19 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
       f16x8_t ga[4 * NDT], qa[4 * NDT];
 #pragma unroll
       for (int i = 0; i < 4 * NDT; ++i) {
-        ga[i] = *(const f16x8_t*)(Gt + ((i % NDT) * 32 + l32) * TS + 16 * (i / NDT) + 8 * half);
-        qa[i] = *(const f16x8_t*)(Qt + ((i % NDT) * 32 + l32) * TS + 16 * (i / NDT) + 8 * half);
+        ga[i] = TL::cols(Gs, i % NDT, i / NDT, lane);
+        qa[i] = TL::cols(Qs, i % NDT, i / NDT, lane);
       }
 #pragma unroll
       for (int i = 0; i < 4 * NDT; ++i) {
         dvT[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ga[i], pf[i / NDT], dvT[i % NDT], 0, 0, 0);
         dkT[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(qa[i], df[i / NDT], dkT[i % NDT], 0, 0, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
       for (int i = 0; i < 8 * NDT - 4; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     }
@@ -481,28 +509,35 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
 }
 
 // Matrix-core form of the query-side kernel (fp16).  A block owns 128 queries of one (sequence, head), a wave 32,
-// whose Q and dO rows stay in registers as second operands; tiles of 64 keys go through LDS row-major (K, V) and
-// transposed (K^T, V^T).  Pass 1 is the forward pass (S^T = K Q^T, running maximum and sum, O^T += V^T P^T): it
+// whose Q and dO rows stay in registers as second operands; tiles of 64 keys go through LDS, read by rows (K, V) and
+// by columns (K^T, V^T).  Pass 1 is the forward pass (S^T = K Q^T, running maximum and sum, O^T += V^T P^T): it
 // yields O, lse_i and delta_i = dO_i . O_i.  Pass 2 walks the key tiles again: P^T = exp(S^T scale - lse_i),
-// dP^T = V dO^T, dS^T = P^T (dP^T - delta_i), dQ^T += K^T dS^T.
+// dP^T = V dO^T, dS^T = P^T (dP^T - delta_i), dQ^T += K^T dS^T.  The block with the most keys runs first.
 template <int HD>
-__global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
+__global__ void __launch_bounds__(256, HD <= 64 ? 3 : HD <= 128 ? 2 : 1)
     attn_bwd_q_mfma(const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v,
-                    const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, float scale,
+                    const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, int B, int nblk, float scale,
                     float* __restrict__ lse, float* __restrict__ delta, half_t* __restrict__ dq, size_t ldq, size_t ldg,
                     size_t ldo, half_t* __restrict__ o_out, size_t ldoo, int kv_cache) {
   // kv_cache: k and v are the forward pass's K / V cache of the layer (see attn_bwd_kv_mfma); q stays [T, .]
-  constexpr int NKS = HD / 16, NDT = (HD + 31) / 32, RS = HD + 8, TS = 64 + 8, CPR = HD / 8;
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[64 * RS];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[64 * RS];
-  __shared__ __attribute__((aligned(16))) uint16_t Kt[NDT * 32 * TS];
-  __shared__ __attribute__((aligned(16))) uint16_t Vt[NDT * 32 * TS];
-  const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 128;
+  typedef BwdTile<HD> TL;
+  constexpr int NKS = HD / 16, NDT = (HD + 31) / 32;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TL::HALFS];  // two of (K, V)
+  int b, h, blk;
+  if (!bwd_block(H, B, nblk, b, h, blk)) return;
+  const int q0 = (nblk - 1 - blk) * 128;
   const int s0 = min(max(cu[b], 0), Tn), n = min(cu[b + 1], Tn) - s0;
   if (q0 >= n) return;
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: the per-tile tests become scalar branches
   const size_t col = (size_t)h * HD;
+  const size_t kvb = kv_cache ? ((size_t)s0 * H + (size_t)h * (cu[b + 1] - cu[b])) * HD : (size_t)s0 * ldq + col;
+  const size_t kvld = kv_cache ? (size_t)HD : ldq;
+  auto load_tile = [&](int k0, int buf) {
+    TL::load(k + kvb, kvld, k0, n - 1, smem + buf * 2 * TL::HALFS, wave, lane);
+    TL::load(v + kvb, kvld, k0, n - 1, smem + buf * 2 * TL::HALFS + TL::HALFS, wave, lane);
+  };
+  load_tile(0, 0);
   const int qi = q0 + wave * 32 + l32;  // this lane's query (two lanes per query: half 0 / 1)
   const int qic = min(qi, n - 1);
   f16x8_t qf[NKS], gf[NKS];
@@ -511,112 +546,60 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
     qf[ks] = *(const f16x8_t*)(q + (size_t)(s0 + qic) * ldq + col + 16 * ks + 8 * half);
     gf[ks] = *(const f16x8_t*)(g + (size_t)(s0 + qic) * ldg + col + 16 * ks + 8 * half);
   }
-  for (int c = tid; c < (NDT * 32 - HD) * TS; c += 256) {
-    Kt[HD * TS + c] = 0;
-    Vt[HD * TS + c] = 0;
-  }
   const int q_hi = min(q0 + 128, n) - 1, wq_lo = q0 + wave * 32;
-  const int k_last = (q_hi / 64) * 64;  // first key of the block's last tile
   const float scale_log2e = scale * 1.4426950408889634f;
-  // A tile travels global -> registers one iteration ahead of its use, once: a thread's item is 4 keys x 8 dims of K
-  // and of V, which it writes to LDS row-major (4 x 16 bytes) and / or transposed (8 x 8 bytes, the 4 keys adjacent
-  // under the column permutation of the accumulator layout), whichever images the pass reads.  Threads past the
-  // tile's 16 * CPR items re-read the last item instead of branching around the loads (static wait counts).
-  constexpr int ITEMS = 16 * CPR, NIT = (ITEMS + 255) / 256;  // items of the tile, items per thread
-  f16x8_t kv[NIT][4], vv[NIT][4];
-  const size_t kvb = kv_cache ? ((size_t)s0 * H + (size_t)h * (cu[b + 1] - cu[b])) * HD : (size_t)s0 * ldq + col;
-  const size_t kvld = kv_cache ? (size_t)HD : ldq;
-  auto load_tile = [&](int k0) {
-    k0 = min(k0, k_last);
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int item = min(tid + 256 * it, ITEMS - 1), ich = item / 16, ig4 = item - ich * 16;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const size_t off = kvb + (size_t)min(k0 + 4 * ig4 + u, n - 1) * kvld + ich * 8;
-        kv[it][u] = *(const f16x8_t*)(k + off);
-        vv[it][u] = *(const f16x8_t*)(v + off);
-      }
-    }
-  };
-  auto store_tile = [&](bool second_pass) {
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int item = tid + 256 * it, ich = item / 16, ig4 = item - ich * 16;
-      if (item < ITEMS) {
-        const int kk = (4 * ig4) & 15;
-        const int colp = ((4 * ig4) & ~15) + 8 * ((kk >> 2) & 1) + 4 * (kk >> 3);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          *(f16x8_t*)((half_t*)Ks + (4 * ig4 + u) * RS + ich * 8) = kv[it][u];
-          if (second_pass) *(f16x8_t*)((half_t*)Vs + (4 * ig4 + u) * RS + ich * 8) = vv[it][u];
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (second_pass) {
-            const f16x4_t wk = {kv[it][0][e], kv[it][1][e], kv[it][2][e], kv[it][3][e]};
-            *(f16x4_t*)((half_t*)Kt + (ich * 8 + e) * TS + colp) = wk;
-          } else {
-            const f16x4_t wv = {vv[it][0][e], vv[it][1][e], vv[it][2][e], vv[it][3][e]};
-            *(f16x4_t*)((half_t*)Vt + (ich * 8 + e) * TS + colp) = wv;
-          }
-        }
-      }
-    }
-  };
   // S^T of the tile for this lane's query: two fragments of 32 keys, their accumulation chains alternating, the
   // fragment reads four ahead of the matrix instructions
-#define BWD_SCORES(ST)                                                                                      \
-  {                                                                                                         \
-    f16x8_t kfr[2 * NKS];                                                                                   \
-    _Pragma("unroll") for (int i = 0; i < 2 * NKS; ++i)                                                     \
-        kfr[i] = *(const f16x8_t*)(Ks + ((i & 1) * 32 + l32) * RS + 16 * (i >> 1) + 8 * half);            \
-    const f32x16_t z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};    \
-    ST[0] = z;                                                                                              \
-    ST[1] = z;                                                                                              \
-    _Pragma("unroll") for (int i = 0; i < 2 * NKS; ++i)                                                     \
-        ST[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfr[i], qf[i >> 1], ST[i & 1], 0, 0, 0);       \
-    constexpr int AH = 2 * NKS < 4 ? 2 * NKS : 4;                                                           \
-    __builtin_amdgcn_sched_group_barrier(0x100, AH, 0);                                                     \
-    _Pragma("unroll") for (int i = 0; i < 2 * NKS - AH; ++i) {                                              \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                    \
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                    \
-    }                                                                                                       \
-    __builtin_amdgcn_sched_group_barrier(0x008, AH, 0);                                                     \
-  }
-  // NDT accumulation chains over the four 16-key steps of a transposed image, reads four ahead
-#define BWD_OUT(IMG, OPS, ACC)                                                                              \
-  {                                                                                                         \
-    f16x8_t fr[4 * NDT];                                                                                    \
-    _Pragma("unroll") for (int i = 0; i < 4 * NDT; ++i)                                                     \
-        fr[i] = *(const f16x8_t*)(IMG + ((i % NDT) * 32 + l32) * TS + 16 * (i / NDT) + 8 * half);         \
-    _Pragma("unroll") for (int i = 0; i < 4 * NDT; ++i)                                                     \
-        ACC[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[i], OPS[i / NDT], ACC[i % NDT], 0, 0, 0); \
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);                                                      \
-    _Pragma("unroll") for (int i = 0; i < 4 * NDT - 4; ++i) {                                               \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                    \
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                    \
-    }                                                                                                       \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);                                                      \
-  }
-  // ---- pass 1: the forward pass
+  auto scores = [&](const uint16_t* Ks, f32x16_t (&st)[2]) {
+    f16x8_t kfr[2 * NKS];
+#pragma unroll
+    for (int i = 0; i < 2 * NKS; ++i) kfr[i] = TL::rows(Ks, i & 1, l32, 2 * (i >> 1) + half);
+    const f32x16_t z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    st[0] = z;
+    st[1] = z;
+#pragma unroll
+    for (int i = 0; i < 2 * NKS; ++i)
+      st[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kfr[i], qf[i >> 1], st[i & 1], 0, 0, 0);
+    constexpr int AH = 2 * NKS < 4 ? 2 * NKS : 4;
+    __builtin_amdgcn_sched_group_barrier(0x100, AH, 0);
+#pragma unroll
+    for (int i = 0; i < 2 * NKS - AH; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, AH, 0);
+  };
   f32x16_t acc[NDT];
+  // NDT accumulation chains over the four 16-key steps of an image's columns, reads four ahead
+  auto accumulate = [&](const uint16_t* img, const f16x8_t (&ops)[4]) {
+    f16x8_t fr[4 * NDT];
+#pragma unroll
+    for (int i = 0; i < 4 * NDT; ++i) fr[i] = TL::cols(img, i % NDT, i / NDT, lane);
+#pragma unroll
+    for (int i = 0; i < 4 * NDT; ++i)
+      acc[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[i], ops[i / NDT], acc[i % NDT], 0, 0, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+    for (int i = 0; i < 4 * NDT - 4; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+  };
+  // ---- pass 1: the forward pass
 #pragma unroll
   for (int t = 0; t < NDT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  load_tile(0);
-  // (the loads issued so far are waited for here, once: see the note in attn_prefill_mfma)
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  for (int k0 = 0; k0 <= q_hi; k0 += 64) {
-    __syncthreads();  // every wave is done with the previous tile
-    store_tile(false);
-    __syncthreads();
-    load_tile(k0 + 64 <= q_hi ? k0 + 64 : 0);  // after the last tile: tile 0, which the second pass starts with
+  int buf = 0;
+  for (int k0 = 0; k0 <= q_hi; k0 += 64, buf ^= 1) {
+    tile_start();
+    load_tile(k0 + 64 <= q_hi ? k0 + 64 : 0, buf ^ 1);  // after the last tile: tile 0, which the second pass starts with
     if (k0 > wq_lo + 31) continue;  // every key of this tile is in the future of this wave's queries
+    const uint16_t* const Ks = smem + buf * 2 * TL::HALFS;
     f32x16_t st[2];
-    BWD_SCORES(st)
+    scores(Ks, st);
     // key kj = k0 + 4*half + c of element (kf, e), c = 32*kf + 8*(e/4) + e%4, is visible iff kj <= min(qi, n - 1)
     if ((k0 + 63 > wq_lo) || (k0 + 64 > n)) {
       const int lim = min(qi, n - 1) - k0 - 4 * half;
@@ -652,7 +635,7 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] *= alpha;
     }
-    BWD_OUT(Vt, pf, acc)
+    accumulate(Ks + TL::HALFS, pf);
   }
   const float l_tot = half_sum(l_run);
   const float inv = 1.0f / l_tot;
@@ -689,14 +672,13 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
   for (int t = 0; t < NDT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  for (int k0 = 0; k0 <= q_hi; k0 += 64) {  // (tile 0 is in the registers: the first pass's last load)
-    __syncthreads();
-    store_tile(true);
-    __syncthreads();
-    load_tile(k0 + 64);
+  for (int k0 = 0; k0 <= q_hi; k0 += 64, buf ^= 1) {
+    tile_start();
+    if (k0 + 64 <= q_hi) load_tile(k0 + 64, buf ^ 1);
     if (k0 > wq_lo + 31) continue;
+    const uint16_t* const Ks = smem + buf * 2 * TL::HALFS;
     f32x16_t st[2];
-    BWD_SCORES(st)
+    scores(Ks, st);
     f16x8_t df[4];
     const bool need_mask = (k0 + 63 > wq_lo) || (k0 + 64 > n);
     const int lim = min(qi, n - 1) - k0 - 4 * half;
@@ -706,7 +688,7 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
       {
         f16x8_t va[NKS];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) va[ks] = *(const f16x8_t*)(Vs + (kf * 32 + l32) * RS + 16 * ks + 8 * half);
+        for (int ks = 0; ks < NKS; ++ks) va[ks] = TL::rows(Ks + TL::HALFS, kf, l32, 2 * ks + half);
         const f32x16_t z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         dp = z;
 #pragma unroll
@@ -719,10 +701,8 @@ __global__ void __launch_bounds__(256, HD <= 128 ? 2 : 1)
         df[kf * 2 + (e >> 3)][e & 7] = (half_t)(pr * (dp[e] - dl));
       }
     }
-    BWD_OUT(Kt, df, acc)
+    accumulate(Ks, df);
   }
-#undef BWD_SCORES
-#undef BWD_OUT
   if (qi < n) {
     half_t* drow = dq + (size_t)(s0 + qi) * ldo + col;
 #pragma unroll
@@ -832,14 +812,15 @@ hipError_t launch_attention_backward(int dtype, const void* q, const void* k, co
       (void)hipFuncSetAttribute((const void*)attn_bwd_kv_kernel<half_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
     }
     if (hd == 64 || hd == 80 || hd == 128 || hd == 256) {  // the model family's head sizes: matrix-core forms of both kernels
-      dim3 mgrid((max_len + 127) / 128, H, B);
+      const int nblk = (max_len + 127) / 128;
+      const dim3 mgrid((unsigned)nblk * (((unsigned)H * B + 7) / 8 * 8));
 #define RLHF_BWD_MFMA(HD_)                                                                                      \
   hipLaunchKernelGGL(attn_bwd_q_mfma<HD_>, mgrid, dim3(256), 0, s, (const half_t*)q, (const half_t*)k,          \
-                     (const half_t*)v, (const half_t*)g, cu, Tn, H, scale, lse, delta, (half_t*)dq, ld_qkv,     \
-                     ld_g, ld_out, (half_t*)o, ld_o, kv_cache ? 1 : 0);                                         \
+                     (const half_t*)v, (const half_t*)g, cu, Tn, H, B, nblk, scale, lse, delta, (half_t*)dq,   \
+                     ld_qkv, ld_g, ld_out, (half_t*)o, ld_o, kv_cache ? 1 : 0);                                 \
   hipLaunchKernelGGL(attn_bwd_kv_mfma<HD_>, mgrid, dim3(256), 0, s, (const half_t*)q, (const half_t*)k,         \
-                     (const half_t*)v, (const half_t*)g, cu, Tn, H, scale, lse, delta, (half_t*)dk, (half_t*)dv, \
-                     ld_qkv, ld_g, ld_out, kv_cache ? 1 : 0)
+                     (const half_t*)v, (const half_t*)g, cu, Tn, H, B, nblk, scale, lse, delta, (half_t*)dk,   \
+                     (half_t*)dv, ld_qkv, ld_g, ld_out, kv_cache ? 1 : 0)
       if (hd == 64) { RLHF_BWD_MFMA(64); }
       else if (hd == 80) { RLHF_BWD_MFMA(80); }
       else if (hd == 128) { RLHF_BWD_MFMA(128); }

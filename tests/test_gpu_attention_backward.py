@@ -55,6 +55,13 @@ def test_fp16(gpu, lens, H, hd):
     _run(gpu, lens, H, hd, "fp16", seed=sum(lens) + hd)
 
 
+@pytest.mark.parametrize("hd", [64, 80, 128, 256])
+def test_fp16_at_the_edges_of_the_tiles(gpu, hd):
+    """Lengths one below, at and above a tile of 64 rows and a block of 128, where the last tile is loaded short and
+    the waves of a block stop at different tiles; 27 pairs of sequence and head, no multiple of the 8 XCDs."""
+    _run(gpu, (63, 64, 65, 127, 128, 129, 191, 193, 257), 3, hd, "fp16", seed=hd)
+
+
 def test_long_sequences_need_the_large_scratch(gpu):
     _run(gpu, (2021, 638), 1, 80, "fp16", seed=9)
 
