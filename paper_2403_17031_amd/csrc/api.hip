@@ -1461,17 +1461,20 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
   // ---- attention core: (dq | dk | dv) into the sections of dqkv, and the forward output o
   char* qkv = (char*)ws.qkv;
   char* dqkv = (char*)ws.dqkv;
+  // (its matrix-core form also takes the rotary turn back from dq and dk: 27 us a layer at 22 k rows of 12 heads of 64)
+  const bool turns = attention_backward_takes_cache(dt, hd);
+  const int rot = turns ? c.rotary_dims : 0;
   if (kept)
     LAUNCH("attention_backward",
            launch_attention_backward(dt, kept_q, kept_k, kept_v, ws.dO, cu_seqlens, B, T, H, hd, max_len, ws.lse, ws.delta,
                                      dqkv, dqkv + (size_t)d * esz, dqkv + (size_t)2 * d * esz, s, (size_t)d, (size_t)d,
-                                     (size_t)3 * d, ws.att, (size_t)d, true));
+                                     (size_t)3 * d, ws.att, (size_t)d, true, rot, h->rope_cos, h->rope_sin));
   else
     LAUNCH("attention_backward",
            launch_attention_backward(dt, qkv, qkv + (size_t)d * esz, qkv + (size_t)2 * d * esz, ws.dO, cu_seqlens, B, T, H,
                                      hd, max_len, ws.lse, ws.delta, dqkv, dqkv + (size_t)d * esz,
                                      dqkv + (size_t)2 * d * esz, s, (size_t)3 * d, (size_t)d, (size_t)3 * d, ws.att,
-                                     (size_t)d));
+                                     (size_t)d, false, rot, h->rope_cos, h->rope_sin));
   // ---- dWo = G^T o
   auto dw_gemm = [&](const void* A, const void* W, void* out, int M, int N) {  // K = the rows: sliced
     GemmArgs g = gemm(A, W, nullptr, out, M, N, Tp, EPI_F32);
@@ -1506,8 +1509,9 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_gemm(ws.goT, ws.attT, d_w_o, d, d), s));
   }
   // ---- back through the rotary turn, then the QKV product: dbqkv, dWqkv, da
-  LAUNCH("rope_inplace", launch_rope_inplace(dt, ws.dqkv, (size_t)3 * d, cu_seqlens, B, T, H, hd, c.rotary_dims,
-                                             h->rope_cos, h->rope_sin, 1, s));
+  if (!turns)
+    LAUNCH("rope_inplace", launch_rope_inplace(dt, ws.dqkv, (size_t)3 * d, cu_seqlens, B, T, H, hd, c.rotary_dims,
+                                               h->rope_cos, h->rope_sin, 1, s));
   LAUNCH("colsum", launch_colsum(dt, ws.dqkv, T, 3 * d, ws.part, ws.splits, reordered ? ws.dbq : d_b_qkv, s));
   if (kmaj) {
     LAUNCH("gemm_attn_dw", launch_gemm(dt, dw_kmajor(ws.dqkv, ln_out, reordered ? ws.dwq : d_w_qkv, 3 * d, d), s));

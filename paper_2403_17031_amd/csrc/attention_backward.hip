@@ -315,6 +315,28 @@ struct BwdTile {
   }
 };
 
+// One pair's rotary turn; the fused steps are written out so that every kernel rounds alike.
+__device__ __forceinline__ void turn(float lo, float hi, float co, float si, float& lo_out, float& hi_out) {
+  const float a = hi * si, b = hi * co;
+  lo_out = fmaf(lo, co, -a);
+  hi_out = fmaf(lo, si, b);
+}
+
+// Four neighbouring dims dd .. dd + 3 of a gradient row, which the rotary turn of the row's position takes back if the table is
+// given (cs and sn at the position's r / 2 angles, pairs (2i, 2i + 1)): what the pass of rope_inplace_kernel over the stored
+// row would make of it.
+__device__ __forceinline__ f16x4_t turned_back(f16x4_t a, int dd, int r, const float* cs, const float* sn) {
+#pragma unroll
+  for (int u = 0; u < 4; u += 2)
+    if (dd + u + 1 < r) {
+      float lo, hi;
+      turn((float)a[u], (float)a[u + 1], cs[(dd + u) >> 1], -sn[(dd + u) >> 1], lo, hi);
+      a[u] = from_f32<half_t>(lo);
+      a[u + 1] = from_f32<half_t>(hi);
+    }
+  return a;
+}
+
 // The start of a tile: what this wave has loaded is in LDS and what it has read it holds; then the same for every wave.
 __device__ __forceinline__ void tile_start() {
   __builtin_amdgcn_sched_barrier(0);
@@ -357,7 +379,8 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
     attn_bwd_kv_mfma(const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v,
                      const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, int B, int nblk, float scale,
                      const float* __restrict__ lse, const float* __restrict__ delta, half_t* __restrict__ dk,
-                     half_t* __restrict__ dv, size_t ldq, size_t ldg, size_t ldo, int kv_cache) {
+                     half_t* __restrict__ dv, size_t ldq, size_t ldg, size_t ldo, int kv_cache, int rot,
+                     const float* __restrict__ cos_t, const float* __restrict__ sin_t) {
   // kv_cache: k and v are the forward pass's K / V cache of the layer (sequence b owns the slots from cu[b] * H on,
   // head h of it len_b consecutive rows of HD) instead of [T, .] matrices with row stride ldq
   typedef BwdTile<HD> TL;
@@ -487,6 +510,8 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
     }
   }
   if (kj < n) {
+    const float* const cs = cos_t + (size_t)kj * (rot >> 1);
+    const float* const sn = sin_t + (size_t)kj * (rot >> 1);
     half_t* dvr = dv + (size_t)(s0 + kj) * ldo + col;
     half_t* dkr = dk + (size_t)(s0 + kj) * ldo + col;
 #pragma unroll
@@ -502,7 +527,7 @@ __global__ void __launch_bounds__(256, HD <= 80 ? 2 : 1)
             c2[u] = from_f32<half_t>(dkT[t][4 * g4 + u] * scale);
           }
           *(f16x4_t*)(dvr + dd) = a;
-          *(f16x4_t*)(dkr + dd) = c2;
+          *(f16x4_t*)(dkr + dd) = turned_back(c2, dd, rot, cs, sn);
         }
       }
   }
@@ -518,7 +543,8 @@ __global__ void __launch_bounds__(256, HD <= 64 ? 3 : HD <= 128 ? 2 : 1)
     attn_bwd_q_mfma(const half_t* __restrict__ q, const half_t* __restrict__ k, const half_t* __restrict__ v,
                     const half_t* __restrict__ g, const int* __restrict__ cu, int Tn, int H, int B, int nblk, float scale,
                     float* __restrict__ lse, float* __restrict__ delta, half_t* __restrict__ dq, size_t ldq, size_t ldg,
-                    size_t ldo, half_t* __restrict__ o_out, size_t ldoo, int kv_cache) {
+                    size_t ldo, half_t* __restrict__ o_out, size_t ldoo, int kv_cache, int rot, const float* __restrict__ cos_t,
+                    const float* __restrict__ sin_t) {
   // kv_cache: k and v are the forward pass's K / V cache of the layer (see attn_bwd_kv_mfma); q stays [T, .]
   typedef BwdTile<HD> TL;
   constexpr int NKS = HD / 16, NDT = (HD + 31) / 32;
@@ -704,6 +730,8 @@ __global__ void __launch_bounds__(256, HD <= 64 ? 3 : HD <= 128 ? 2 : 1)
     accumulate(Ks, df);
   }
   if (qi < n) {
+    const float* const cs = cos_t + (size_t)qi * (rot >> 1);
+    const float* const sn = sin_t + (size_t)qi * (rot >> 1);
     half_t* drow = dq + (size_t)(s0 + qi) * ldo + col;
 #pragma unroll
     for (int t = 0; t < NDT; ++t)
@@ -714,7 +742,7 @@ __global__ void __launch_bounds__(256, HD <= 64 ? 3 : HD <= 128 ? 2 : 1)
           f16x4_t a;
 #pragma unroll
           for (int u = 0; u < 4; ++u) a[u] = from_f32<half_t>(acc[t][4 * g4 + u] * scale);
-          *(f16x4_t*)(drow + dd) = a;
+          *(f16x4_t*)(drow + dd) = turned_back(a, dd, rot, cs, sn);
         }
       }
   }
@@ -737,10 +765,10 @@ __global__ void __launch_bounds__(256)
     const int u = c / half, i = c - u * half;  // u = section * H + head
     T* hb = qkv + (size_t)t * ld + (size_t)u * hd;  // sections are d = H*hd apart, so (section, head) is u heads in
     const int lo_i = ADJ ? 2 * i : i, hi_i = ADJ ? 2 * i + 1 : i + half;
-    const float co = cs[i], si = sn[i] * dir;
-    const float lo = to_f32(hb[lo_i]), hi = to_f32(hb[hi_i]);
-    hb[lo_i] = from_f32<T>(lo * co - hi * si);
-    hb[hi_i] = from_f32<T>(hi * co + lo * si);
+    float lo, hi;
+    turn(to_f32(hb[lo_i]), to_f32(hb[hi_i]), cs[i], sn[i] * dir, lo, hi);
+    hb[lo_i] = from_f32<T>(lo);
+    hb[hi_i] = from_f32<T>(hi);
   }
 }
 
@@ -782,9 +810,10 @@ bool attention_backward_takes_cache(int dtype, int hd) { return dtype == 1 && (h
 hipError_t launch_attention_backward(int dtype, const void* q, const void* k, const void* v, const void* g,
                                      const int* cu, int B, int Tn, int H, int hd, int max_len, float* lse,
                                      float* delta, void* dq, void* dk, void* dv, hipStream_t s, size_t ld_qkv,
-                                     size_t ld_g, size_t ld_out, void* o, size_t ld_o, bool kv_cache) {
+                                     size_t ld_g, size_t ld_out, void* o, size_t ld_o, bool kv_cache, int rot,
+                                     const float* cos_t, const float* sin_t) {
   const size_t dm = (size_t)H * hd;
-  if (kv_cache && !attention_backward_takes_cache(dtype, hd)) return hipErrorInvalidValue;
+  if ((kv_cache || rot) && !attention_backward_takes_cache(dtype, hd)) return hipErrorInvalidValue;
   if (!ld_qkv) ld_qkv = dm;
   if (!ld_g) ld_g = dm;
   if (!ld_out) ld_out = dm;
@@ -817,10 +846,10 @@ hipError_t launch_attention_backward(int dtype, const void* q, const void* k, co
 #define RLHF_BWD_MFMA(HD_)                                                                                      \
   hipLaunchKernelGGL(attn_bwd_q_mfma<HD_>, mgrid, dim3(256), 0, s, (const half_t*)q, (const half_t*)k,          \
                      (const half_t*)v, (const half_t*)g, cu, Tn, H, B, nblk, scale, lse, delta, (half_t*)dq,   \
-                     ld_qkv, ld_g, ld_out, (half_t*)o, ld_o, kv_cache ? 1 : 0);                                 \
+                     ld_qkv, ld_g, ld_out, (half_t*)o, ld_o, kv_cache ? 1 : 0, rot, cos_t, sin_t);              \
   hipLaunchKernelGGL(attn_bwd_kv_mfma<HD_>, mgrid, dim3(256), 0, s, (const half_t*)q, (const half_t*)k,         \
                      (const half_t*)v, (const half_t*)g, cu, Tn, H, B, nblk, scale, lse, delta, (half_t*)dk,   \
-                     (half_t*)dv, ld_qkv, ld_g, ld_out, kv_cache ? 1 : 0)
+                     (half_t*)dv, ld_qkv, ld_g, ld_out, kv_cache ? 1 : 0, rot, cos_t, sin_t)
       if (hd == 64) { RLHF_BWD_MFMA(64); }
       else if (hd == 80) { RLHF_BWD_MFMA(80); }
       else if (hd == 128) { RLHF_BWD_MFMA(128); }

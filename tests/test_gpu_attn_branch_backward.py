@@ -74,6 +74,13 @@ def test_bf16_mode(gpu, lens, H, hd, r):
     _check(gpu, _cfg(H, hd, r, "bf16"), lens, seed=sum(lens) + hd, layer=0, scale=8.0)
 
 
+@pytest.mark.parametrize("lens,H,hd,r", [((130, 63), 2, 256, 64), ((129, 5), 3, 64, 0), ((65,), 1, 80, 6), ((127, 2), 3, 128, 128)])
+def test_the_rotary_turn_of_the_attention_kernels(gpu, lens, H, hd, r):
+    """Head sizes whose attention kernels take the rotary turn back themselves: none of the head rotary, a count that ends
+    inside a group of four dims, all of it."""
+    _check(gpu, _cfg(H, hd, r, "bf16"), lens, seed=sum(lens) + r, layer=0, scale=8.0)
+
+
 def test_bad_arguments_are_rejected(gpu):
     cfg = _cfg(2, 16, 4, "bf16")
     pol = gpu.Policy(cfg, make_weights(cfg, 65, variant="test"))
