@@ -168,16 +168,20 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
   return a;
 }
 
-// Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256 while
-// the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such tile, its
-// launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of 64-512 tokens, 53
-// sampled; this pass against the other, ms): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9,
-// 192 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 130 78.6 / 81.4, 192 100.4 / 103.5, 256 127.9 / 127.0; 2.8B width (79 M)
-// 65 65.9 / 68.1, 96 80.5 / 84.6, 128 95.9 / 99.8, 160 121.0 / 118.9, 256 173.6 / 161.8; 6.9B width (201 M, two layers) 65
-// 46.2 / 42.9, 128 63.5 / 60.4.  It gains 3-5 % at 150 to 157 M and loses 1 % at 201 M; the line is at 168 M, and at 256
-// sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width, two layers): 1 15.3 / 28.6, 17 18.7 / 30.3,
-// 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the gap (1900 tokens, 20 sampled: 160M 256
-// sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
+// Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256
+// while the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such
+// tile, its launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of
+// 64-512 tokens, 53 sampled; this pass against run_decode_many on the same day, ms): 160M shape 65 sequences 31.0 /
+// 39.6, 128 44.5 / 54.2, 192 59.4 / 66.7, 256 74.8 / 79.0; 1B width 65 32.6 / 33.4, 96 40.0 / 40.5, 130 52.9 / 48.3,
+// 192 67.5 / 63.8; 2.8B width (four layers) 65 45.2 / 44.4, 96 and 128 even.  Against the pass that run_decode_many
+// does not take (staged tiles): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9, 192
+// 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 130 78.6 / 81.4, 192 100.4 / 103.5, 256 127.9 / 127.0; 2.8B width (79
+// M) 65 65.9 / 68.1, 96 80.5 / 84.6, 128 95.9 / 99.8, 160 121.0 / 118.9, 256 173.6 / 161.8; 6.9B width (201 M, two
+// layers) 65 46.2 / 42.9, 128 63.5 / 60.4.  Against that pass it gains 3-5 % at 150 to 157 M and loses 1 % at 201 M;
+// the line is at 168 M (three row tiles at 1B width would be 6-9 % faster with run_decode_many; the 160M shape up to
+// 10-20 % slower), and at 256 sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width, two
+// layers): 1 15.3 / 28.6, 17 18.7 / 30.3, 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the
+// gap (1900 tokens, 20 sampled: 160M 256 sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
 bool few_decode_size(const rlhf_model_config& c, int B) {
   if (B <= kFewRows) return true;
   const size_t per_layer = (size_t)c.d_model * (4 * (size_t)c.d_model + 2 * (size_t)c.d_ff);
