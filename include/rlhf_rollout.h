@@ -369,8 +369,9 @@ int rlhf_policy_backward(rlhf_handle *h, const float *x_keep, int64_t x_keep_lay
  * the weight arrays themselves are updated).  THE CALL WRITES THE CALLER'S WEIGHT ARRAYS.  value_b: a device float in
  * each set; master.value_b must hold the model's value bias on entry, and from the first call on the handle reads the
  * bias from there (it must outlive the handle) instead of rlhf_weights.value_b.
- * minibatch_tokens: HOST int32 [n_minibatches], the number of real tokens (mask == 1) of each mini-batch; max_len
- * (host): at least the longest row.  grad_scale: see rlhf_head_backward (64 x the kept response tokens of a
+ * minibatch_tokens: HOST int32 [n_minibatches], the number of real tokens (mask == 1) of each mini-batch (with a smaller
+ * number the tokens past it, in row order, are left out as if the mask ended there); max_len (host): at least the
+ * longest row.  grad_scale: see rlhf_head_backward (64 x the kept response tokens of a
  * mini-batch is a good value in bf16 mode; 1 in fp32 mode).  Workspace size from rlhf_ppo_update_workspace_bytes
  * (B_minibatch = B / n_minibatches, L = Lq + N, T_max = the largest entry of minibatch_tokens): that is the minimum.
  * A bf16 model uses whatever the caller passes beyond it to keep FC1's output (before the GELU) of the forward pass

@@ -1748,7 +1748,9 @@ static int score_forward(rlhf_handle* h, const int32_t* tokens, const uint8_t* m
   const size_t kept_rows = keep_rows ? keep_rows : (size_t)B * L;  // rows copied per layer = row stride of the kept slices
   const bool chain = keep && keep_chain_takes(h, keep, kept_rows * c.d_model, B * L);
   if (chain) ws.acts.x = keep;
-  LAUNCH("row_spans", launch_row_spans(mask, B, L, 0, m.start, m.len, m.cu, m.kvoff, m.total, s));
+  // (every kept slice holds kept_rows rows by the caller's count: a count below the mask's shortens the batch, so that what
+  // each kernel writes into them ends there)
+  LAUNCH("row_spans", launch_row_spans(mask, B, L, 0, m.start, m.len, m.cu, m.kvoff, m.total, s, (int)kept_rows));
   LAUNCH("pack_embed", launch_pack_embed(c.dtype, tokens, B, L, m.start, m.len, m.cu, h->w.embed_in, c.d_model,
                                          c.vocab, m.pos, m.rowid, m.tok, ws.acts.x, m.cu, c.n_heads, 0, m.slots, s));
   PassArgs p;

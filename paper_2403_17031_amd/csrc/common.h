@@ -1,6 +1,7 @@
 // Shared device helpers and the launcher declarations of the gfx950 kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 namespace rlhf {
@@ -309,9 +310,10 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 
 // Row metadata of a packed batch -------------------------------------------------------------------
 // mask [B, L] (1 = real) -> start[b], len[b]; then cu[b] = sum_{b'<b} len, kvoff[b] = sum_{b'<b}
-// (len + kv_extra), total[0] = cu[B], total[1] = kvoff[B].
+// (len + kv_extra), total[0] = cu[B], total[1] = kvoff[B].  cap: the rows that the caller's buffers hold; tokens past it are
+// left out as if the mask ended there.
 hipError_t launch_row_spans(const uint8_t* mask, int B, int L, int kv_extra, int* start, int* len, int* cu,
-                            int* kvoff, int* total, hipStream_t s);
+                            int* kvoff, int* total, hipStream_t s, int cap = INT_MAX);
 // Packed row t = cu[b] + i for i < len[b]: pos[t] = i, rowid[t] = b, tok[t] = tokens[b, start[b]+i],
 // x[t, :] = embed[tok[t], :]; slots[t] = the row's place in a K/V cache whose sequence b starts at slot kvoff[b] * H and
 // holds len[b] + kv_extra rows per head.

@@ -32,16 +32,19 @@ __global__ void row_span_kernel(const uint8_t* __restrict__ mask, int L, int* __
   }
 }
 
-// Exclusive prefix sums over B rows (B is at most a few thousand: one thread walks them).
-__global__ void row_scan_kernel(const int* __restrict__ len, int B, int kv_extra, int* __restrict__ cu,
+// Exclusive prefix sums over B rows (B is at most a few thousand: one thread walks them).  Tokens past the first cap are cut
+// off the rows that hold them.
+__global__ void row_scan_kernel(int* __restrict__ len, int B, int kv_extra, int cap, int* __restrict__ cu,
                                 int* __restrict__ kvoff, int* __restrict__ total) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   int a = 0, k = 0;
   for (int b = 0; b < B; ++b) {
     cu[b] = a;
     kvoff[b] = k;
-    a += len[b];
-    k += len[b] + kv_extra;
+    int n = len[b];
+    if (n > cap - a) len[b] = n = cap - a;
+    a += n;
+    k += n + kv_extra;
   }
   cu[B] = a;
   kvoff[B] = k;
@@ -50,9 +53,9 @@ __global__ void row_scan_kernel(const int* __restrict__ len, int B, int kv_extra
 }
 
 hipError_t launch_row_spans(const uint8_t* mask, int B, int L, int kv_extra, int* start, int* len, int* cu,
-                            int* kvoff, int* total, hipStream_t s) {
+                            int* kvoff, int* total, hipStream_t s, int cap) {
   hipLaunchKernelGGL(row_span_kernel, dim3(B), dim3(64), 0, s, mask, L, start, len);
-  hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(64), 0, s, len, B, kv_extra, cu, kvoff, total);
+  hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(64), 0, s, len, B, kv_extra, cap, cu, kvoff, total);
   return hipGetLastError();
 }
 

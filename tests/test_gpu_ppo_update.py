@@ -286,3 +286,42 @@ def test_kept_layer_norms_change_nothing(gpu, monkeypatch):
         results[-1] = [x.clone() for x in results[-1]]
     for other in results[1:]:
         assert all(torch.equal(a, b) for a, b in zip(results[0], other))
+
+
+@pytest.mark.parametrize("dtype,B,short", [("bf16", 50, 77), ("bf16", 50, 53), ("bf16", 7, 60), ("fp32", 7, 60)])
+def test_a_token_count_below_the_masks_ends_the_batch_there(gpu, monkeypatch, dtype, B, short):
+    """minibatch_tokens is the caller's: every kept slice holds that many rows, so a smaller count than the mask's has to give
+    the update of the batch whose mask ends there, bit for bit.  Slots chained from layer to layer (2,400 rows), copied ones
+    (bf16 and fp32, 350 rows); the cut inside a row and at a row's end."""
+    import ctypes as C
+    import torch
+    cfg = ModelConfig(n_layers=2, d_model=256, n_heads=4, head_dim=64, rotary_dims=16, d_ff=640, vocab=200, dtype=dtype,
+                      pad_id=199, eos_id=1)
+    w = make_weights(cfg, 95, variant="test")
+    g = np.random.default_rng(18)
+    Lq, N = 40, 13
+    L = Lq + N
+    tokens = g.integers(2, 190, (B, L)).astype(np.int32)
+    mask = (np.arange(L)[None, :] >= g.integers(0, 8, B)[:, None]).astype(np.uint8)
+    mask[-1] = 1
+    T = int(mask.sum()) - short
+    ended = (np.cumsum(mask.ravel()) <= T).reshape(B, L) * mask
+    old_lp, adv, old_v, ret = (g.normal(0, 1, (4, B, N)) - np.array([4, 0, 0, 0])[:, None, None]).astype(np.float32)
+    results = []
+    for m, low in ((ended, False), (mask, True)):
+        pol = gpu.Policy(cfg, w)
+        if low:
+            lib, count = pol.lib, (C.c_int32 * 1)(T)
+
+            class Short:
+                def __getattr__(self, name):
+                    return getattr(lib, name)
+
+                def rlhf_ppo_update(self, *a):
+                    return lib.rlhf_ppo_update(*a[:13], count, *a[14:])
+            monkeypatch.setattr(pol, "lib", Short())
+        stats = pol.ppo_update(tokens, m, Lq, old_lp, adv, old_v, ret, np.full(B, N, np.int32), 0.7, epochs=2, lr=1e-3, eps=1e-3)
+        state = pol.train_state()
+        results.append([x.clone() for x in [stats, *state["grads"].values(), *state["master"].values()]])
+        pol.close()
+    assert all(torch.equal(a, b) for a, b in zip(*results))
