@@ -186,8 +186,8 @@ __global__ void __launch_bounds__(256, OCC)
 
   // Tile load i of the wave fills 64 chunks of the image: chunk index x = 64 * (NKL * wave + i) + lane, row x / pitch
   // (past the image: the last 64 again, the same bytes).  Rows past the sequence repeat its last (their scores are masked).
-  // The loads are assembly (no destination registers: the data goes to LDS), because the compiler cannot tell the two
-  // buffers apart and would wait for the next tile at every fragment read of this one.  (m0 holds nothing else here.)
+  // The loads are load_to_lds, because the compiler cannot tell the two buffers apart and would wait for the next tile at
+  // every fragment read of this one.
   auto load_tile = [&](int k0, int buf, bool is_v) {
     const int pitch = is_v ? TL::VP : TL::KP, nl = is_v ? NVL : NKL;
     const half_t* const src = is_v ? vb : kb;
@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(256, OCC)
       const int c = min(pc ^ (is_v ? TL::v_swizzle(r) : TL::k_swizzle(r)), TL::CH - 1);
       const uint32_t off = 2u * (uint32_t)(min(k0 + r, n - 1) * HD + c * 8);
       const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(smem + buf * BUF + (is_v ? K_HALFS : 0) + j * 512);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(src) : "memory");
+      load_to_lds(src, off, dst);
     }
   };
   load_tile(0, 0, false);

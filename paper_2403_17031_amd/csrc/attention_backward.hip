@@ -288,8 +288,8 @@ struct BwdTile {
     return 4 * (r & 3) | ((r >> 2) & 3);
   }
   // Rows row0 .. row0 + 63 (past the last: the last again) of src, rows ld apart, into img.  One of the block's four waves
-  // fills NL * 64 chunks.  Assembly without destination registers, for the compiler would wait for the next tile at every
-  // read of this one; the tile's start waits for all of them.  (m0 holds nothing else here.)
+  // fills NL * 64 chunks.  load_to_lds, for the compiler would wait for the next tile at every read of this one; the tile's
+  // start waits for all of them.
   __device__ static void load(const half_t* src, size_t ld, int row0, int last, const uint16_t* img, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -298,7 +298,7 @@ struct BwdTile {
       const uint32_t off = 2u * ((uint32_t)min(row0 + r, last) * (uint32_t)ld + c * 8);
       const uint32_t dst = __builtin_amdgcn_readfirstlane(
           (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(img + 512 * (NL * wave + i)));
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(src) : "memory");
+      load_to_lds(src, off, dst);
     }
   }
   __device__ static f16x8_t rows(const uint16_t* img, int f, int l32, int chunk) {  // row 32 f + l32

@@ -115,6 +115,19 @@ __device__ __forceinline__ float half_max(float v) {
   return half_fold(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
+// One tile load of a wave, global memory straight to LDS: lane i's 16 bytes at base + off go to the LDS address lds + 16 i
+// (base and lds the same in all lanes).  Assembly without destination registers, for kernels that count their own waits: the
+// compiler does not know that such a load is under way, so whoever reads what it brings waits for it (s_waitcnt vmcnt) first.
+// The address travels in m0, which no clobber list may name (the register is reserved) and which the compiler sets for direct
+// loads of its own, once for several where the address is the same: it is put back.
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0)
+               : "s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 // 1 / (1 + 2^t), the division correctly rounded.  The compiler's division is eleven instructions, half of the GELU below,

@@ -853,17 +853,14 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       const char* const gA = (const char*)(g.A + (KMAJ ? (size_t)kb * g.lda + m0 : (size_t)m0 * g.lda + kb));
       const char* const gW = (const char*)(g.W + (KMAJ ? (size_t)kb * g.ldw + nw : (size_t)nw * g.ldw + kb));
       void* const out = g.slices > 1 ? (void*)((float*)g.out + (size_t)z * g.slab) : g.out;
-      // The ring's loads are assembly (no destination registers: the data goes to LDS), because the compiler, which
-      // cannot tell the ring's stages apart, would wait for all of them at every fragment read.  What orders them is
-      // the counted wait before the barrier.  (m0 holds nothing else here: the compiler sets it before each direct load of
-      // its own, and none follows.)
+      // The ring's loads are load_to_lds, because the compiler, which cannot tell the ring's stages apart, would wait for
+      // all of them at every fragment read.  What orders them is the counted wait before the barrier.
       auto load_one = [&](uint16_t* slot, int kt, int i) {
         const size_t k0 = (size_t)min(kt, nk - 1) * DK;
         const char* const p = i < NLA ? gA + 2 * (KMAJ ? k0 * g.lda : k0) : gW + 2 * (KMAJ ? k0 * g.ldw : k0);
         const int at = i < NLA ? 8 * (NLA * wave + i) * DK : AOP + 8 * (2 * wave + i - NLA) * DK;
         const uint32_t dst = (uint32_t)(uintptr_t)RLHF_LDS_PTR(slot + at);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(goff[i]), "s"(p)
-                     : "memory");
+        load_to_lds(p, goff[i], dst);
       };
       f16x8_t fa[2], fw[2][2];
       auto frag = [&](const uint16_t* slot, int ks, int buf) {
