@@ -1586,6 +1586,12 @@ int run_decode_many(rlhf_handle* h, const Acts& A, const PassArgs& p, void* hl, 
   PendingResidual pr;
   pr.part_a = (const float*)A.splitk;
   pr.slab = (size_t)B * d;
+  // FC1's GELU in the erf form, as in the few-sequence pass (gelu_f16out is up to 65 fp16 steps off between -4 and -3), where
+  // its arithmetic is a small part of the product: K of 2048 or more and output tiles that do not fill the chip.  Rollouts of
+  // 12 tokens, two layers, erf against gelu_f16out: width 2048 65 to 128 sequences +1.1 to 1.8 %, 2688 +1.1 and 2.1, 3072 +0.3
+  // to 1.8; beyond the line 512 and 1024 256 to 512 sequences +1.4 to 5.1, 2560 130 to 512 +1.8 to 2.6, and the headline
+  // rollout of 256 sequences at width 2560 +0.7.
+  const int gelu = d >= 2048 && ((B + 127) / 128) * ((F + 63) / 64) < 256 ? EPI_BIAS_GELU_ERF : EPI_BIAS_GELU;
   for (int l = 0; l < c.n_layers; ++l) {
     char* kc = p.kv + (size_t)l * 2 * plane;
     char* vc = kc + plane;
@@ -1607,7 +1613,7 @@ int run_decode_many(rlhf_handle* h, const Acts& A, const PassArgs& p, void* hl, 
     LAUNCH("gemm_decode_qkv", launch_gemm(1, g, s));
     LAUNCH("attn_decode", launch_attn_decode(1, A.q, kc, vc, (long)p.kv_extra, B, p.len, p.ctx_add, p.ctx_max, p.kvoff,
                                              c.n_heads, c.head_dim, A.att, s, d + F));
-    GemmArgs g1 = gemm_args(A.m, h->w_fc1[l], h->b_fc1[l], (char*)A.att + (size_t)d * h->esz, F, d, EPI_BIAS_GELU);
+    GemmArgs g1 = gemm_args(A.m, h->w_fc1[l], h->b_fc1[l], (char*)A.att + (size_t)d * h->esz, F, d, gelu);
     g1.ldo = d + F;
     LAUNCH("gemm_decode_fc1", launch_gemm(1, g1, s));
     GemmArgs g2 = gemm_args(A.att, h->w_o[l], nullptr, nullptr, d, d + F, EPI_F32);

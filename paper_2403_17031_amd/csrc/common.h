@@ -160,11 +160,12 @@ __device__ __forceinline__ float gelu_f16out(float x) {
 // ------------------------------------------------------------------------------------------------
 enum Epilogue {
   EPI_BIAS = 0,         // out[T]   = acc + bias
-  EPI_BIAS_GELU = 1,    // out[T]   = gelu_erf(acc + bias)
+  EPI_BIAS_GELU = 1,    // out[T]   = GELU(acc + bias): gelu_erf, in the fp16 products of many rows gelu_f16out
   EPI_BIAS_RESADD = 2,  // out[f32] += acc + bias      (residual stream update, in place)
   EPI_F32 = 3,          // out[f32] = acc              (logits)
   EPI_LSE = 4,          // nothing stored but per-row softmax statistics of acc/T (scoring LM head)
-  EPI_QKV = 5           // acc + bias with the rotary turn applied, q stored as rows, K and V into the cache
+  EPI_QKV = 5,          // acc + bias with the rotary turn applied, q stored as rows, K and V into the cache
+  EPI_BIAS_GELU_ERF = 6 // out[T]   = gelu_erf(acc + bias); large-M fp16 kernel only (decode)
 };
 
 // EPI_LSE: the product is a [rows, vocab] logits matrix that is never stored.  Each part p (the columns of

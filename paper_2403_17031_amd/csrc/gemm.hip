@@ -423,7 +423,7 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
         }
       }
     const int rd_row = lane >> 3, rd_c = lane & 7;  // on the way out: row within a group of 8, 16-byte chunk of the row
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_QKV) {
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_ERF || EPI == EPI_QKV) {
       // EPI_QKV: for each of the lane's eight 4-column groups the index of its first rotary angle (-1: the group is not
       // rotary).  A group is two whole pairs.
       const int qd = qk.H * qk.hd;
@@ -477,7 +477,8 @@ __device__ __forceinline__ void dma_epilogue(const DmaArgs& g, const LseArgs& ls
               }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) h[u] = from_f32<half_t>(EPI == EPI_BIAS_GELU ? gelu_f16out(v[u]) : v[u]);
+            for (int u = 0; u < 4; ++u)
+              h[u] = from_f32<half_t>(EPI == EPI_BIAS_GELU ? gelu_f16out(v[u]) : EPI == EPI_BIAS_GELU_ERF ? gelu_erf(v[u]) : v[u]);
             *(f16x4_t*)(ep + l32 * 64 + (((4 * j + q) ^ (l32 & 7)) << 3) + 4 * hf) = h;
           }
         RLHF_WAVE_LDS_FENCE();
@@ -780,7 +781,8 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       }
       u32x2_t bv[2][4], bv2[2][4];
       int prow[MT];
-      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_QKV) dma_load_bias(g.bias, cn0 + wn, N, hf, bv);
+      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_ERF || EPI == EPI_QKV)
+        dma_load_bias(g.bias, cn0 + wn, N, hf, bv);
       if (EPI == EPI_QKV) {
 #pragma unroll
         for (int i = 0; i < MT; ++i)
@@ -942,7 +944,7 @@ __global__ void __launch_bounds__(512, 1) gemm_f16_dma_kernel(DmaArgs g, LseArgs
       if (!works) continue;
       u32x2_t bv[2][4], bv2[2][4];
       int prow[1];
-      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_RESADD || EPI == EPI_QKV)
+      if (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU || EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_RESADD || EPI == EPI_QKV)
         dma_load_bias(g.bias, n0 + wn, N, hf, bv);
       if (EPI == EPI_BIAS_RESADD) dma_load_bias(g.bias2, n0 + wn, N, hf, bv2);
       if (EPI == EPI_QKV) prow[0] = (qk.pos[g.M_sub + min(m0 + wm + l32, M - 1)] + qk.pos_add) * (qk.r >> 1);
@@ -1208,6 +1210,10 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     case EPI_LSE:
       if (!a.lse || !gemm_takes_lse(dtype, a)) return hipErrorInvalidValue;
       launch_f16_dma<EPI_LSE>(a, s);
+      break;
+    case EPI_BIAS_GELU_ERF:
+      if (!gemm_takes_large(dtype, a)) return hipErrorInvalidValue;
+      launch_f16_dma<EPI_BIAS_GELU_ERF>(a, s);
       break;
     case EPI_QKV:
       if (!a.qkv || !gemm_takes_qkv(dtype, a, a.qkv->H, a.qkv->hd, a.qkv->r)) return hipErrorInvalidValue;

@@ -184,27 +184,28 @@ def test_weights_at_any_float_address(monkeypatch):
             assert rep["deficit"] <= 0.0 and abs(lps[rep["row"], rep["step"]] - rep["logprob"]) <= TOL["fp32"], rep
 
 
-@pytest.mark.parametrize("B", [1, 17, 64])
-def test_gelu_of_negative_inputs(B):
+@pytest.mark.parametrize("B,d,hd", [(1, 128, 64), (17, 128, 64), (64, 128, 64), (65, 2048, 32), (256, 2048, 32)])
+def test_gelu_of_negative_inputs(B, d, hd):
     """FC1 outputs in [-4, -3], where GELU is x * Phi(x) with Phi down to 3e-5: an absolute error that fp16 would hide
     at 1 is a few per cent there.  Hidden values depend on b_fc1 alone and are all the residual stream holds, so their
     relative error is the logits'.  Bound: fp16 rounding of the hidden values and of the final LayerNorm's output, each
     2^-10 / sqrt(12) of a value (rms, worst case), on logits / T of standard deviation S: 4e-4 S, times three.  A GELU
-    that is 2.6e-5 off (the form the large products use) gives 5e-3 S."""
+    that is 2.6e-5 off (the form the large products use) gives 5e-3 S.  Beyond 64 sequences the decode passes are the large
+    kernel's, which takes the erf form at wide models; the first draw, the prefill's, is left out."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import paper_2403_17031_amd as P
     from oracle import neox_oracle as O
     from synth.inputs import round_to_bf16
-    d, F, V, N = 128, 512, 300, 8
-    cfg = ModelConfig(1, d, 2, 64, 16, F, vocab=V, dtype="bf16", pad_id=V)
+    F, V, N = 512, 300, 8
+    cfg = ModelConfig(1, d, d // hd, hd, hd // 4, F, vocab=V, dtype="bf16", pad_id=V)
     w = make_weights(cfg, 77, variant="test")
     g = np.random.default_rng(B)
     w["layers.0.w_o"][:], w["layers.0.b_o"][:], w["layers.0.w_fc1"][:], w["layers.0.b_fc2"][:] = 0, 0, 0, 0
     w["layers.0.b_fc1"] = round_to_bf16(g.uniform(-4, -3, F).astype(np.float32))
     w["layers.0.w_fc2"] = round_to_bf16(60 * g.standard_normal((d, F), dtype=np.float32))
-    w["embed_out"] = round_to_bf16(0.3 * g.standard_normal((V, d), dtype=np.float32))
+    w["embed_out"] = round_to_bf16(np.float32(0.3 * (128 / d) ** 0.5) * g.standard_normal((V, d), dtype=np.float32))
     queries = g.integers(1, V, size=(B, 3)).astype(np.int32)
     mask = np.ones((B, 3), np.uint8)
     toks, lps, _ = (x.cpu().numpy() for x in P.Policy(cfg, w).rollout_generate(queries, mask, 3, 0.7, N))
@@ -214,6 +215,8 @@ def test_gelu_of_negative_inputs(B):
         x, _ = O.forward_sequence(m, toks[b], np.arange(3 + N))
         logits, _ = O.heads(m, x[2:-1])
         for t in range(N):
+            if t == 0 and B > 64:
+                continue
             err.append(lps[b, t] - O.log_softmax_at(logits[t], 0.7, int(toks[b, 3 + t])))
             spread.append(logits[t].std() / 0.7)
             if toks[b, 3 + t] == cfg.eos_id:
