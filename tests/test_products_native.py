@@ -123,3 +123,20 @@ def test_split_of_the_residual_product(products, d, split):
     for rows in (1, 32, 64):
         r = subprocess.run([products, "forms", "1", str(d), str(4 * d), "515", str(rows)], capture_output=True, text=True, timeout=100)
         assert r.returncode == 0 and r.stdout.splitlines()[1].split()[1:3] == ["split", str(split)], r.stdout
+
+
+def test_assembly_that_writes_m0_puts_it_back():
+    """The register that holds a direct load's LDS address is the compiler's, and no clobber list may name it: assembly that
+    sets it saves it first and restores it last."""
+    from paper_2403_17031_amd import build
+    seen = 0
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            for text in re.findall(r"\basm\b(?:\s+volatile)?\s*\(((?:\s*\"(?:[^\"\\]|\\.)*\")+)", f.read()):
+                lines = "".join(re.findall(r"\"((?:[^\"\\]|\\.)*)\"", text)).replace("\\n\\t", "\\n").split("\\n")
+                if not any(re.match(r"\s*s_\w+ m0\b", line) for line in lines):
+                    continue
+                seen += 1
+                saved = re.fullmatch(r"s_mov_b32 (%\d+), m0", lines[0])
+                assert saved and lines[-1] == f"s_mov_b32 m0, {saved[1]}", (name, lines)
+    assert seen == 1
