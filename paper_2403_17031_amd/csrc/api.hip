@@ -168,20 +168,18 @@ Acts carve_acts(Carver& c, const rlhf_model_config& cfg, size_t rows, size_t esz
   return a;
 }
 
-// Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256
-// while the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such
-// tile, its launches are half as many: what decides is row tiles times weights per layer.  Measured (queries of
-// 64-512 tokens, 53 sampled; this pass against run_decode_many on the same day, ms): 160M shape 65 sequences 31.0 /
-// 39.6, 128 44.5 / 54.2, 192 59.4 / 66.7, 256 74.8 / 79.0; 1B width 65 32.6 / 33.4, 96 40.0 / 40.5, 130 52.9 / 48.3,
-// 192 67.5 / 63.8; 2.8B width (four layers) 65 45.2 / 44.4, 96 and 128 even.  Against the pass that run_decode_many
-// does not take (staged tiles): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9, 192
-// 44.9 / 71.2, 256 54.9 / 77.4; 1B width (50 M) 130 78.6 / 81.4, 192 100.4 / 103.5, 256 127.9 / 127.0; 2.8B width (79
-// M) 65 65.9 / 68.1, 96 80.5 / 84.6, 128 95.9 / 99.8, 160 121.0 / 118.9, 256 173.6 / 161.8; 6.9B width (201 M, two
-// layers) 65 46.2 / 42.9, 128 63.5 / 60.4.  Against that pass it gains 3-5 % at 150 to 157 M and loses 1 % at 201 M;
-// the line is at 168 M (three row tiles at 1B width would be 6-9 % faster with run_decode_many; the 160M shape up to
-// 10-20 % slower), and at 256 sequences, beyond which nothing was measured.  Up to 64 sequences (6.9B width, two
-// layers): 1 15.3 / 28.6, 17 18.7 / 30.3, 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the
-// gap (1900 tokens, 20 sampled: 160M 256 sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
+// Whether a rollout's decode passes are run_decode_few's by their size: up to kFewRows sequences always, up to 256 while
+// the weights are few.  Its products take 64 rows at a time and read a layer's weights again for each such tile: what
+// decides is row tiles times weights per layer.  The line, 168 M of them, was drawn against the pass of staged tiles, which
+// is what a shape that decode_many_takes refuses still has beyond it (queries of 64-512 tokens, 53 sampled, ms, this pass /
+// that): 160M shape (7 M weights per layer) 80 sequences 29.0 / 57.9, 128 35.0 / 63.9, 192 44.9 / 71.2, 256 54.9 / 77.4; 1B
+// width (50 M) 130 78.6 / 81.4, 192 100.4 / 103.5, 256 127.9 / 127.0; 2.8B width (79 M) 65 65.9 / 68.1, 96 80.5 / 84.6, 128 95.9 /
+// 99.8, 160 121.0 / 118.9, 256 173.6 / 161.8; 6.9B width (201 M, two layers) 65 46.2 / 42.9, 128 63.5 / 60.4: 3-5 % gained at 150
+// to 157 M, 1 % lost at 201 M.  Against run_decode_many, which most shapes have beyond it, it lies too high at 1B
+// width: 130 sequences 52.9 / 48.3 and 192 67.5 / 63.8 (taken although 6-9 % slower), 65 32.6 / 33.4, 96 40.0 / 40.5; 2.8B width (four layers) 65 45.2 / 44.4, 96 and 128 even; 160M shape 65 31.0 / 39.6, 128 44.5 /
+// 54.2, 192 59.4 / 66.7, 256 74.8 / 79.0.  Nothing was measured beyond 256 sequences.  Up to 64 (6.9B width, two layers,
+// staged): 1 15.3 / 28.6, 17 18.7 / 30.3, 32 21.5 / 32.3, 48 25.2 / 34.7, 64 28.9 / 37.5.  Longer contexts narrow the gap (1900
+// tokens, 20 sampled, staged: 160M 256 sequences 86 / 89, 1B 128 111 / 113, 6.9B 64 70 / 73).
 bool few_decode_size(const rlhf_model_config& c, int B) {
   if (B <= kFewRows) return true;
   const size_t per_layer = (size_t)c.d_model * (4 * (size_t)c.d_model + 2 * (size_t)c.d_ff);
@@ -399,7 +397,9 @@ int run_layers(rlhf_handle* h, const Acts& A, const PassArgs& p, hipStream_t s) 
   // Prefill and scoring of up to 512 rows: the large product's smaller tiles, with its fused epilogues and out-projection and
   // FC2 as one, rather than the staged kernel (ms, staged / this: scoring 453 rows, six layers of 2.8B width 1.93 / 1.25, 150 at
   // the 160M shape 1.31 / 0.79, 144 of two layers of 6.9B width 1.08 / 0.70; the prefill of one query of 320 tokens at 2.8B
-  // width 1.4 / 0.9).  Not a training forward: its sums stay in the order in which the backward pass forms them again.
+  // width 1.4 / 0.9; scoring 65 and 512 rows, four layers of width 128 0.22 / 0.18 and 0.26 / 0.22, 512 0.40 / 0.27 and 0.49 /
+  // 0.35, 1024 0.47 / 0.25 and 0.52 / 0.29, 2048 1.09 / 0.50 and 1.32 / 0.78, two of 5120 1.21 / 0.65 and 1.60 / 1.17).  Not a
+  // training forward: its sums stay in the order in which the backward pass forms them again.
   base.large_tile = p.mode == 0 && p.rows_max > kFewRows && !p.keep;
   const bool split = p.mode == 1 && !few_rows_layer(c, p.rows_max);
   if (split) {
@@ -1554,7 +1554,11 @@ static int attention_branch_backward_impl(rlhf_handle* h, int32_t layer, const f
 // attention and two products' slabs for the LayerNorm, the form that run_layers still has for what this one does not take:
 // 256 sequences of 2.8B width 290 us a layer against 250; beside each other the two kernels take as long as in turn, and an
 // event recorded or waited for costs 6 us.  Rollouts of 53 tokens, ms, that form / this: 256 sequences, six layers of 2.8B
-// width 162.0 / 152.5, 160 117.3 / 107.5; 100, two of 6.9B 51.7 / 49.5; 230, six of 1B 116.5 / 108.)
+// width 162.0 / 152.5, 160 117.3 / 107.5; 100, two of 6.9B 51.7 / 49.5; 230, six of 1B 116.5 / 108.  To 512 sequences, 12 tokens of
+// short queries, two layers: 257 and 512 of width 512 2.46 / 1.68 and 2.93 / 2.28, 1024 3.22 / 2.47 and 4.47 / 3.85, 2048 5.91 / 5.01
+// and 8.75 / 8.00, 2560 6.97 / 5.62 and 10.1 / 8.7, 4096 13.4 / 10.5 and 20.2 / 16.3.)  What bounds its products is the way of
+// the weights, which they find cold: QKV 27, FC1 35, out-projection and FC2 31 us at 256 rows of width 2560 (1.5 to 2.1 TB/s),
+// the matrix pipe busy 12 to 18 % of the cycles, the vector pipe 6.
 bool decode_many_takes(const rlhf_handle* h, const Acts& A, int B) {
   const rlhf_model_config& c = h->cfg;
   if (c.dtype != 1 || c.n_layers == 0 || B <= kFewRows || B > 512 || !h->ld_o2 || !h->vec_params ||

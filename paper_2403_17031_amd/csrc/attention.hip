@@ -131,7 +131,8 @@ __global__ void __launch_bounds__(256)
 // holds it: one barrier per tile, and the registers that staging (and V's transposition) took are blocks per CU (four
 // instead of three at head size 64).  What bounds it at head sizes 64 and 80 is the vector arithmetic of the softmax (an
 // exponential per score, about 1050 of its cycles per tile and wave beside 512 and 704 of the matrix cores, which overlap
-// in part) and a block's start, 2 to 4 of its 10 to 13 us; at 256 the way of the tiles (without the loads 356 us of 560).
+// in part; counters at 256 sequences of 32 heads of 80: vector pipe busy 50 %, matrix pipe 26, no bank conflicts) and a block's
+// start, 2 to 4 of its 10 to 13 us; at 256 the way of the tiles (without the loads 356 us of 560).
 // Staged through registers / this, us: 64 sequences of 155-539 tokens, 12 heads of 64 54 / 42; 256, 32 of 80 736 / 650; 61,
 // 32 of 128 263 / 230; 32 of 505-2021, 8 of 256 762 / 560; results the same bit for bit.  Tried: two or eight waves a block
 // (slower at every size), 32-key tiles (head size 128 3 % faster, 256 as fast with two blocks per CU, 15 % slower with short

@@ -366,8 +366,10 @@ __device__ __forceinline__ bool bwd_block(int H, int B, int nblk, int& b, int& h
 // operand of dK^T += Q^T dS and dV^T += dO^T P.  P = exp(S scale - lse_i) needs no running maximum: lse_i and
 // delta_i come from the query-side kernel.  The block with the most queries runs first.
 //
-// Bound by the vector arithmetic between the products (an exponential, a difference and two conversions per score) and the
-// LDS reads, 16 operands of 16 bytes per 4 products; so what a tile needs besides goes straight to LDS, one tile ahead, from
+// Bound by the chain of a tile, products, the vector arithmetic between them (an exponential, a difference and two
+// conversions per score) and products again, which two or three waves per SIMD cover in part: at head size 64 the vector pipe
+// is busy 45 % (query side) and 29 % (this one), the matrix pipe 21 and 15, and 36 and 44 % of the waves' cycles are waits; 36, 25,
+// 21 and 16 % at head size 80; no LDS bank conflicts.  So what a tile needs besides goes straight to LDS, one tile ahead, from
 // matrices that the pair's blocks find in their L2, and no register holds it.  As many blocks per CU as the registers give
 // without spilling to speak of (two up to head size 80 here; three at 64, two at 80 and 128 for the query-side kernel;
 // one more block would spill 38 to 113 registers).  Both kernels, tiles staged and transposed through registers / this, us:

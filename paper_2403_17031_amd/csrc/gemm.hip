@@ -7,7 +7,9 @@
 //    filled directly from global memory, XOR-swizzled 16-byte chunks (conflict-free ds_read_b128).
 //    One block per CU takes tile after tile, in rounds in which the 32 tiles of an XCD are neighbours
 //    and share A and W panels in its L2; what is left for a last round is cut smaller.
-//    Few rows (decode): 128x64 tiles staged through registers, split over K.
+//    Up to 512 rows where the caller says so (GemmArgs::large_tile: prefill, scoring, decode of many sequences) its smaller
+//    tiles alone; other products of few rows: 128x64 tiles staged through registers, split over K (weights streamed in
+//    gemm_skinny.hip and few_rows.hip).
 //  * fp32: plain FMA tile kernel (check mode only; not tuned).
 #include <algorithm>
 #include <type_traits>
@@ -1070,7 +1072,9 @@ static bool takes_dma(const GemmArgs& a) {
 }
 // K slices of a large-M product with few output tiles and a long K (GemmArgs::long_k: the weight-gradient
 // products of a backward pass, K = the batch's rows): the slice count (at most 8, each slice a whole number of
-// stage pairs, the fp32 slabs fitting the caller's scratch) that minimises rounds of 256 tiles times slice length.
+// stage pairs, the fp32 slabs fitting the caller's scratch) that minimises rounds of 256 whole tiles times slice length.  It
+// knows nothing of the smaller tiles that the kernel cuts a K-major rest of up to a quarter round into (768 x 768 over 22,272
+// rows: eight slices, 72 whole tiles, where seven would be 252 quarter tiles); another count is another order of sums.
 static int dma_k_slices(const GemmArgs& a, int* k_slice) {
   *k_slice = 0;
   if (!a.long_k || !a.splitk_ws || a.M_dev || a.bias || a.bias2 || a.ldo != a.N ||
@@ -1095,10 +1099,14 @@ bool gemm_takes_bias2(int dtype, const GemmArgs& a) {
 }
 bool gemm_takes_large(int dtype, const GemmArgs& a) { return dtype == 1 && takes_dma(a); }
 // K slices of a large_tile product with scratch, as many as minimise the length of a slice's stages
-// (about 0.24 us each in the 64x128 tiles, 0.36 in the 128x128, one round of them) plus what the slabs cost to write and to
-// read again.  us with 1 / 2 / 3 / 4 / 6 / 8 slices: 256 rows, out-projection and FC2 of width 2560 as one product (K = 12,800)
-// 55 / 31 / 25 / 25 / 22 / 29, of 2048 45 / 25 / 20 / 17 / 18 / 17, of 4096 83 / 52 / 48 / 46 / 52 / 49.  The residual form adds
-// the launch that sums them.
+// (about 0.24 us each in the 64x128 tiles, 0.36 in the 128x128, one round of them; two rounds of 128x128 are charged as one of
+// whole tiles) plus what the slabs cost to write and to read again.  Fitted at 256 rows with the weights in the caches, us
+// with 1 / 2 / 3 / 4 / 6 / 8 slices: out-projection and FC2 of width 2560 as one product (K = 12,800) 55 / 31 / 25 / 25 / 22 / 29,
+// of 2048 45 / 25 / 20 / 17 / 18 / 17, of 4096 83 / 52 / 48 / 46 / 52 / 49.  A decode pass finds the weights cold, and the count
+// taken (the last) still is the fastest of those the rule weighs: width 768 256 rows 1 / 2 / 3 / 4 / 6 slices 31 / 18 / 14 / 12 /
+// 10, 512 rows 1 / 2 / 5 30 / 18 / 11; 1024 65 rows 1 / 4 / 8 33 / 12 / 9; 2048 256 rows 1 / 2 / 4 74 / 40 / 25; 2560 128 rows 1 /
+// 3 / 6 92 / 37 / 29, 256 90 / 39 / 32, 512 1 / 2 / 3 89 / 65 / 51; 4096 256 rows 1 / 2 / 4 141 / 82 / 63, 512 1 / 2 145 / 108.
+// The residual form adds the launch that sums them.
 int gemm_large_slices(const GemmArgs& a) {
   const int tiles = ((a.M_max + 255) / 256) * ((a.N + 255) / 256), pairs = a.K / (2 * DK);
   int best = 1;
